@@ -159,7 +159,7 @@ int qa_local_grad_batched(int format, const float* A_or_vals, const int64_t* ind
  * With QA_THRESH_EXACT each bucket's threshold is the largest magnitude NOT kept by the k that
  * maximises (sum of the k largest |v|)^2 / k (equal magnitudes are never split), so that the
  * strict comparisons keep exactly the optimal set; scale and codes follow as usual.  Buckets of
- * up to 4096 components are ranked inside one work-group; longer buckets, and one threshold for
+ * up to 4096 components are searched inside one wave or work-group; longer buckets, and one threshold for
  * a vector of more than 4096 components (Section 3.4's optimum over the whole gradient), are
  * ranked by a device-wide sort, worker after worker, in 17 bytes of workspace per component
  * (d < 2^32, else QA_ERR_TOO_LARGE); that form calls a library sort, which may enqueue memset

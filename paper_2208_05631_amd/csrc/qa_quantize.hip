@@ -181,12 +181,10 @@ __device__ __forceinline__ void bucket_sums(double s[4], uint32_t c[4], double* 
 }
 
 template <int LOG2B>
-__global__ __launch_bounds__(kThreads) void quantize_bucket_kernel(QuantArgs a) {
+__device__ __forceinline__ void quantize_buckets_of_tile(const QuantArgs& a, int64_t tile, int m) {
   __shared__ double lds_s[4 * kWaves];
   __shared__ uint32_t lds_c[4 * kWaves];
   constexpr int b = 1 << LOG2B;
-  const int64_t tile = blockIdx.x;
-  const int m = blockIdx.y;
   const float* g = a.g + (int64_t)m * a.g_stride;
   const int t = threadIdx.x;
   const bool whole = (tile + 1) * kTile <= a.d;          // the vector does not end inside the tile
@@ -295,6 +293,11 @@ __global__ __launch_bounds__(kThreads) void quantize_bucket_kernel(QuantArgs a) 
   }
 }
 
+template <int LOG2B>
+__global__ __launch_bounds__(kThreads) void quantize_bucket_kernel(QuantArgs a) {
+  quantize_buckets_of_tile<LOG2B>(a, blockIdx.x, blockIdx.y);
+}
+
 // ---- bucket == 4096 == the tile : single pass, two work-group reductions ---------------------
 
 // Kept-magnitude sum, kept count (wave-wide, from the compare masks on the scalar unit) and the
@@ -321,12 +324,10 @@ __device__ __forceinline__ uint32_t quantize4(const float v[4], float Delta, boo
   return b;
 }
 
-__global__ __launch_bounds__(kThreads) void quantize_tile_kernel(QuantArgs a) {
+__device__ __forceinline__ void quantize_tile(const QuantArgs& a, int64_t tile, int m) {
   __shared__ double lds_s1[kWaves];
   __shared__ double lds_s2[kWaves];
   __shared__ uint32_t lds_c[kWaves];
-  const int64_t tile = blockIdx.x;
-  const int m = blockIdx.y;
   const int t = threadIdx.x;
   const int64_t lo = tile * kTile;
   const float* g = a.g + (int64_t)m * a.g_stride;
@@ -384,6 +385,10 @@ __global__ __launch_bounds__(kThreads) void quantize_tile_kernel(QuantArgs a) {
     a.scales[(int64_t)m * a.scale_stride + tile] = scale_from_sum(S2, C);
     if (a.thresholds && !a.thresh_given) a.thresholds[(int64_t)m * a.scale_stride + tile] = Delta;
   }
+}
+
+__global__ __launch_bounds__(kThreads) void quantize_tile_kernel(QuantArgs a) {
+  quantize_tile(a, blockIdx.x, blockIdx.y);
 }
 
 // ---- exact optimal threshold by ranking (Section 3.4: the magnitudes are sorted and each one
@@ -485,7 +490,7 @@ __device__ __forceinline__ void sort_phase(uint32_t (&e)[16], int t, uint32_t (*
 // bucket of the tile sorted on its own; the prefix sums and the search then run per bucket, over
 // the 2^(LOG2B-4) consecutive threads that hold it.
 template <int LOG2B>
-__global__ __launch_bounds__(kThreads) void exact_threshold_kernel(QuantArgs a) {
+__device__ __forceinline__ void rank_tile(const QuantArgs& a, int64_t tile, int m) {
   static_assert(LOG2B >= 6 && LOG2B <= 12, "bucket of 64 .. 4096 components");
   constexpr int kSeg = 1 << (LOG2B - 4);                 // threads per bucket
   constexpr int kSegLanes = kSeg < kWave ? kSeg : kWave; // ... of them inside one wave
@@ -497,8 +502,6 @@ __global__ __launch_bounds__(kThreads) void exact_threshold_kernel(QuantArgs a) 
   __shared__ int lds_k[kWaves];
   __shared__ float lds_next[kWaves];
   const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
-  const int64_t tile = blockIdx.x;
-  const int m = blockIdx.y;
   uint32_t e[16];                 // which 16 of the tile a thread starts with does not matter
   {
     float v[4][4];
@@ -595,6 +598,404 @@ __global__ __launch_bounds__(kThreads) void exact_threshold_kernel(QuantArgs a) 
   if (ts == 0) {
     const int64_t k = tile * (kTile >> LOG2B) + (t >> (LOG2B - 4));   // bucket index
     if (k < a.nb) a.thresholds[(int64_t)m * a.scale_stride + k] = best_k > 0 ? best_next : 0.0f;
+  }
+}
+
+template <int LOG2B>
+__global__ __launch_bounds__(kThreads) void exact_threshold_kernel(QuantArgs a) {
+  rank_tile<LOG2B>(a, blockIdx.x, blockIdx.y);
+}
+
+// ---- the same optimum without ranking everything: buckets of 512 .. 4096 ------------------------
+//
+// With s_k the mean of the k largest magnitudes, the objective k s_k^2 does not grow when the next
+// magnitude a is added iff a <= s_k (sqrt(k^2 + k) - k) < s_k / 2, and does not grow when the last
+// one is taken away iff that one is >= s_k / 2.  So the optimum keeps nothing below half the mean,
+// and only a few positions around the best one have to be looked at:
+//
+//   1. magnitudes in [mean/2, max] are counted in a histogram whose bins are equal ranges of the bit
+//      pattern; a bin holds its count and the sum of its members' offsets from the bin's lower end in
+//      units of the last place, so the bin's sum is exact;
+//   2. every lane sums its run of bins; per run the objective at its lower edge, and a bound for every
+//      cut inside it: the j largest of c members with sum o + c L in [L, H] sum to at most
+//      min(j H, o + j L), largest objective where the two meet, at j = o / (H - L); towards the
+//      run's ends the bound falls to the edges' values because (A + B j)^2 / (K + j) is convex in j;
+//   3. the same bin by bin (a lane per bin) within the runs that reach the best edge;
+//   4. the members of the bins that still reach it, and of the next one below -- some 20 magnitudes of
+//      a smooth distribution -- are collected, ranked by counting and evaluated in binary64 exactly
+//      like the ranking network does.
+//
+// One wave per bucket, 64 to 8 components per lane: no work-group barrier.  A bucket where more than 64
+// magnitudes survive (ties, objectives flat over a long stretch), with non-finite members, with
+// subnormal ones above mean/2 or with more than 64 binades between mean/2 and max gets the mark
+// -1 for a threshold and is left to the ranking network (exact_rank_marked_kernel, launched behind
+// this one).
+//
+// Bound by vector instructions (2300 per wave and bucket of 4096; the network took 78 stages for the same
+// and left the codes to a second pass over the gradient).  2^26 x 4 Gaussian components, thresholds and
+// codes, ranking + quantizing before -> this: buckets of 4096 1366 -> 265 us, 2048 1300 -> 299,
+// 1024 1189 -> 385, 512 1094 -> 603.  Steps 2 to 4 cost the same for every bucket size, so halving
+// the bucket nearly doubles the time: at 256 the network (889 us) stays ahead.
+constexpr float kRankMark = -1.0f;
+constexpr int kExactList = 64;            // survivors that one wave ranks by counting
+constexpr float kBelowBest = 1.0f - 2e-6f;   // objectives in binary32 are good to a few 2^-24
+
+// Inclusive prefix sums over the 64 lanes (shifts within rows of 16, then row broadcasts).
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t lanes_or_zero_u32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xF, false);
+}
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double lanes_or_zero_f64(double v) {
+  return __hiloint2double((int)lanes_or_zero_u32<CTRL, ROW_MASK>((uint32_t)__double2hiint(v)),
+                          (int)lanes_or_zero_u32<CTRL, ROW_MASK>((uint32_t)__double2loint(v)));
+}
+__device__ __forceinline__ double wave_scan_f64(double v) {
+  v += lanes_or_zero_f64<0x111, 0xF>(v);
+  v += lanes_or_zero_f64<0x112, 0xF>(v);
+  v += lanes_or_zero_f64<0x114, 0xF>(v);
+  v += lanes_or_zero_f64<0x118, 0xF>(v);
+  v += lanes_or_zero_f64<0x142, 0xA>(v);
+  v += lanes_or_zero_f64<0x143, 0xC>(v);
+  return v;
+}
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
+  v += lanes_or_zero_u32<0x111, 0xF>(v);
+  v += lanes_or_zero_u32<0x112, 0xF>(v);
+  v += lanes_or_zero_u32<0x114, 0xF>(v);
+  v += lanes_or_zero_u32<0x118, 0xF>(v);
+  v += lanes_or_zero_u32<0x142, 0xA>(v);
+  v += lanes_or_zero_u32<0x143, 0xC>(v);
+  return v;
+}
+__device__ __forceinline__ float wave_sum_f32(float v) {
+  v += __int_as_float(dpp_i32<kDppQuadXor1>(__float_as_int(v)));
+  v += __int_as_float(dpp_i32<kDppQuadXor2>(__float_as_int(v)));
+  v += __int_as_float(dpp_i32<kDppRowHalfMirror>(__float_as_int(v)));
+  v += __int_as_float(dpp_i32<kDppRowMirror>(__float_as_int(v)));
+  const int i = __float_as_int(v);
+  return (__int_as_float(__builtin_amdgcn_readlane(i, 0)) + __int_as_float(__builtin_amdgcn_readlane(i, 16))) +
+         (__int_as_float(__builtin_amdgcn_readlane(i, 32)) + __int_as_float(__builtin_amdgcn_readlane(i, 48)));
+}
+// maximum of non-negative floats, by their bit patterns
+__device__ __forceinline__ float wave_max_positive(float v) {
+  return __int_as_float(wave_reduce_i32(__float_as_int(v), [](int p, int q) { return p > q ? p : q; }));
+}
+// LDS of one wave only: order between its own accesses, no barrier
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+// Bits of |x|, formed anew at every use: kept from one pass over the registers to the next, the 64
+// masked copies would not fit beside the components (the empty statement makes x opaque).
+__device__ __forceinline__ uint32_t magnitude_bits(float& x) {
+  asm volatile("" : "+v"(x));
+  return __float_as_uint(x) & 0x7fffffffu;
+}
+// A run of c magnitudes with sum `sum` = c * low + excess in [low, high) below k0 others with sum s0:
+// the objective with all of them kept, or the bound for keeping some if that is larger (0 without any).
+__device__ __forceinline__ float run_score(float s0, float k0, float sum, float c, float excess, float low,
+                                           float high, float* edge) {
+  const float s1 = s0 + sum, j = excess * __builtin_amdgcn_rcpf(high - low);
+  const float s_in = fmaf(j, high, s0);
+  *edge = c > 0.0f ? s1 * s1 * __builtin_amdgcn_rcpf(k0 + c) : 0.0f;
+  const float inside = c > 1.0f ? s_in * s_in * __builtin_amdgcn_rcpf(k0 + j) : 0.0f;
+  return inside > *edge ? inside : *edge;
+}
+
+template <int LOG2B>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void exact_histogram_kernel(QuantArgs a) {
+  static_assert(LOG2B >= 9 && LOG2B <= 12, "64 lanes x 8 .. 64 components");
+  constexpr int b = 1 << LOG2B;
+  constexpr int kGroups = b / (4 * kWave);               // float4 groups per lane
+  constexpr int kLogBins = LOG2B - 2, kBins = 1 << kLogBins;
+  constexpr int kLogPer = kLogBins - 6, kPer = 1 << kLogPer;       // bins per lane
+  // a bin lies within a binade, and its members' offsets sum to less than 2^32
+  constexpr int kMaxShift = 32 - LOG2B;
+  __shared__ uint64_t hist_of[kWaves][kBins];
+  __shared__ uint32_t list_of[kWaves][kExactList];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int64_t k = (int64_t)blockIdx.x * kWaves + wave;           // bucket
+  const int m = blockIdx.y;
+  if (k >= a.nb) return;                                 // the whole wave
+  uint64_t* hist = hist_of[wave];
+  uint32_t* list = list_of[wave];
+  const float* g = a.g + (int64_t)m * a.g_stride;
+  const int64_t lo = k << LOG2B;
+
+  float v[kGroups][4];                                   // group j * 64 + lane of the bucket
+  if (lo + b <= a.d) {
+#pragma unroll
+    for (int j = 0; j < kGroups; ++j) {
+      typedef float floatx4 __attribute__((ext_vector_type(4)));
+      const floatx4 q = __builtin_nontemporal_load(
+          reinterpret_cast<const floatx4*>(g + lo + (j * kWave + lane) * 4));
+      v[j][0] = q.x; v[j][1] = q.y; v[j][2] = q.z; v[j][3] = q.w;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < kGroups; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t i = lo + (j * kWave + lane) * 4 + e;
+        v[j][e] = i < a.d ? g[i] : 0.0f;
+      }
+  }
+#pragma unroll
+  for (int r = 0; r < kPer; ++r) hist[r * kWave + lane] = 0;
+
+  float s32[4] = {0.0f, 0.0f, 0.0f, 0.0f}, top_f = 0.0f;
+#pragma unroll
+  for (int j = 0; j < kGroups; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      s32[e] += fabsf(v[j][e]);
+      top_f = fmaxf(top_f, fabsf(v[j][e]));
+    }
+  const uint32_t top = __float_as_uint(wave_max_positive(top_f));
+  const float total = wave_sum_f32((s32[0] + s32[1]) + (s32[2] + s32[3]));       // NaN if any member is
+
+  float* thr_out = a.thresholds + (int64_t)m * a.scale_stride + k;
+  float delta = 0.0f, scale = 0.0f;
+  if (top != 0 || !(total == total)) {
+    // half the mean, less more than the binary32 sum's error
+    const uint32_t low = __float_as_uint(total * (0.499f / (float)b));
+    int shift = 32 - __clz((int)((top - low) | 1u)) - kLogBins;
+    shift = shift < 0 ? 0 : shift;
+    uint32_t base = low & ~((1u << shift) - 1u);
+    if (((top - base) >> shift) >= (uint32_t)kBins) { ++shift; base = low & ~((1u << shift) - 1u); }
+    // (a total that overflowed makes low larger than top, a NaN larger than anything)
+    bool leave = top >= 0x7f800000u || low >= top || low < 0x00800000u || (top >> 23) - (base >> 23) > 64u ||
+                 shift > kMaxShift;
+    uint32_t count = 0, k_above = 0;
+    double s_above = 0.0;
+    float env_lo = 0.0f;
+    // sums are formed on magnitudes scaled by a power of two that puts max into [1, 2)
+    const uint32_t rescale = ((top >> 23) - 127u) << 23;
+    if (!leave) {
+      const uint32_t mask = (1u << shift) - 1u, limit = (uint32_t)kBins << shift;
+      wave_lds_fence();
+#pragma unroll
+      for (int j = 0; j < kGroups; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t rel = magnitude_bits(v[j][e]) - base;
+          if (rel < limit)
+            atomicAdd(reinterpret_cast<unsigned long long*>(hist + (rel >> shift)),
+                      (1ull << 32) | (unsigned long long)(rel & mask));
+        }
+      wave_lds_fence();
+      // sum of a bin's members in binary64: count * lower end + offsets in units of the last place
+      const auto scaled_end = [&](uint32_t bin) { return base + (bin << shift) - rescale; };
+      const auto bin_sum = [&](uint64_t h, uint32_t bits) {
+        const double ulp = __hiloint2double((int)(((bits >> 23) + (1023 - 150)) << 20), 0);
+        return fma((double)(uint32_t)h, ulp, (double)(uint32_t)(h >> 32) * (double)__uint_as_float(bits));
+      };
+      // lane 0 holds the run of the kPer topmost bins, lane 63 the lowest; a lane starts reading at a
+      // place of its own in its run so that the lanes' reads fall into different LDS banks
+      const uint32_t bin0 = (uint32_t)((kWave - 1 - lane) << kLogPer);
+      double lane_sum = 0.0;
+      uint32_t lane_cnt = 0;
+#pragma unroll 4
+      for (int r = 0; r < kPer; ++r) {
+        const uint32_t bin = bin0 + (uint32_t)((r + lane) & (kPer - 1));
+        const uint64_t h = hist[bin];
+        lane_sum += bin_sum(h, scaled_end(bin));
+        lane_cnt += (uint32_t)(h >> 32);
+      }
+      const double run_before = wave_scan_f64(lane_sum) - lane_sum;
+      const uint32_t run_cnt_before = wave_scan_u32(lane_cnt) - lane_cnt;
+      float edge;
+      const float run_low = __uint_as_float(scaled_end(bin0));
+      const float excess = (float)fma(-(double)lane_cnt, (double)run_low, lane_sum);
+      const float score = run_score((float)run_before, (float)run_cnt_before, (float)lane_sum, (float)lane_cnt,
+                                    excess, run_low, __uint_as_float(scaled_end(bin0 + kPer)), &edge);
+      const float bar = wave_max_positive(edge) * kBelowBest;
+      const uint64_t runs = __ballot(lane_cnt != 0u && score >= bar), filled_runs = __ballot(lane_cnt != 0u);
+      const int first = __ffsll((unsigned long long)runs) - 1;
+      int last = 63 - __clzll((long long)runs);
+      const uint64_t after = last < kWave - 1 ? filled_runs >> (last + 1) : 0ull;
+      if (after) last += __ffsll((unsigned long long)after);        // the next magnitude below lies there
+      // the bins of runs first .. last from the top, a row of 64 at a time
+      const uint32_t bin_top = (uint32_t)(((kWave - first) << kLogPer) - 1);
+      const int n_bins = (last - first + 1) << kLogPer;
+      const double row_sum0 = readlane_f64(run_before, first);
+      const uint32_t row_cnt0 = (uint32_t)__builtin_amdgcn_readlane((int)run_cnt_before, first);
+      float best = 0.0f;
+      double row_sum = row_sum0;
+      uint32_t row_cnt = row_cnt0;
+      uint32_t c = 0;
+      double before = 0.0;
+      uint32_t cnt_before = 0;
+      const auto next_row = [&](int i0) {                // this lane's bin i0 + lane from the top
+        const bool live = i0 + lane < n_bins;
+        const uint32_t bin = live ? bin_top - (uint32_t)(i0 + lane) : 0u;
+        const uint64_t h = live ? hist[bin] : 0ull;
+        const uint32_t bits = scaled_end(bin);
+        const double sum = bin_sum(h, bits);
+        c = (uint32_t)(h >> 32);
+        const double incl = wave_scan_f64(sum);
+        const uint32_t cnt_incl = wave_scan_u32(c);
+        before = row_sum + (incl - sum);
+        cnt_before = row_cnt + (cnt_incl - c);
+        row_sum += readlane_f64(incl, kWave - 1);
+        row_cnt += (uint32_t)__builtin_amdgcn_readlane((int)cnt_incl, kWave - 1);
+        const float ulp = __uint_as_float((bits & 0x7f800000u) - (23u << 23));
+        return run_score((float)before, (float)cnt_before, (float)sum, (float)c, (float)(uint32_t)h * ulp,
+                         __uint_as_float(bits), __uint_as_float(bits + mask + 1u), &edge);
+      };
+#pragma unroll 1
+      for (int i0 = 0; i0 < n_bins; i0 += kWave) {
+        next_row(i0);
+        best = edge > best ? edge : best;
+      }
+      const float bin_bar = wave_max_positive(best) * kBelowBest;
+      // envelope: from the topmost surviving bin down to the next filled bin below the lowest one
+      uint32_t bin_t = 0, bin_b = 0;
+      bool found = false, open = false;
+      row_sum = row_sum0;
+      row_cnt = row_cnt0;
+#pragma unroll 1
+      for (int i0 = 0; i0 < n_bins; i0 += kWave) {
+        const float bin_score = next_row(i0);
+        const uint64_t with = __ballot(c != 0u && bin_score >= bin_bar), any = __ballot(c != 0u);
+        const uint32_t row_top = bin_top - (uint32_t)i0;
+        if (with) {
+          const int lt = __ffsll((unsigned long long)with) - 1, lb = 63 - __clzll((long long)with);
+          if (!found) {
+            bin_t = row_top - (uint32_t)lt;
+            s_above = readlane_f64(before, lt);
+            k_above = (uint32_t)__builtin_amdgcn_readlane((int)cnt_before, lt);
+            found = true;
+          }
+          const uint64_t lower = lb < kWave - 1 ? any >> (lb + 1) : 0ull;
+          open = lower == 0ull;
+          bin_b = row_top - (uint32_t)(open ? lb : lb + __ffsll((unsigned long long)lower));
+        } else if (open && any) {
+          open = false;
+          bin_b = row_top - (uint32_t)(__ffsll((unsigned long long)any) - 1);
+        }
+      }
+      const uint32_t lo_bits = base + (bin_b << shift);
+      env_lo = __uint_as_float(lo_bits);
+      const float env_hi = __uint_as_float(base + ((bin_t + 1u) << shift));
+#pragma unroll
+      for (int j = 0; j < kGroups; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x = __uint_as_float(magnitude_bits(v[j][e]));
+          const uint64_t who = __ballot(x >= env_lo && x < env_hi);
+          if (who) {
+            const uint32_t at = count + __builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32),
+                                            __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u));
+            if (((who >> lane) & 1ull) && at < (uint32_t)kExactList) list[at] = __float_as_uint(x);
+            count += (uint32_t)__popcll(who);
+          }
+        }
+      leave = count > (uint32_t)kExactList;
+    }
+    if (leave) {                                           // the ranking network takes this bucket
+      if (lane == 0) *thr_out = kRankMark;
+      return;
+    }
+    wave_lds_fence();
+    uint32_t key = lane < (int)count ? list[lane] : 0u;
+    uint32_t rank = 0;
+    for (int j = 0; j < (int)count; ++j) {
+      const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)key, j);
+      rank += (o > key || (o == key && j < lane)) ? 1u : 0u;
+    }
+    wave_lds_fence();
+    if (lane < (int)count) list[rank] = key;
+    wave_lds_fence();
+    key = lane < (int)count ? list[lane] : 0u;
+    const uint32_t next = lane + 1 < (int)count ? list[lane + 1] : 0u;
+    const double value = lane < (int)count ? (double)__uint_as_float(key - rescale) : 0.0;
+    const double sum = s_above + wave_scan_f64(value);
+    const double kept = (double)(k_above + (uint32_t)lane + 1u);
+    const double obj = lane < (int)count && key > next ? sum * sum / kept : -1.0;
+    double top_obj = obj;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+      const double o = shfl_xor_f64(top_obj, off);
+      top_obj = o > top_obj ? o : top_obj;
+    }
+    const int w = __ffsll((unsigned long long)__ballot(obj == top_obj)) - 1;       // smallest k
+    // the scale in the magnitudes' own units: the power of two comes back exactly
+    const double back = __hiloint2double((int)((top >> 23) - 127u + 1023u) << 20, 0);
+    scale = scale_from_sum(readlane_f64(sum, w) * back, (uint64_t)(k_above + (uint32_t)w + 1u));
+    if (w + 1 < (int)count) {
+      delta = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)key, w + 1));
+    } else {                                             // everything collected is kept: look below
+      float below = 0.0f;
+#pragma unroll
+      for (int j = 0; j < kGroups; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x = fabsf(v[j][e]);
+          below = x < env_lo && x > below ? x : below;
+        }
+      delta = wave_max_positive(below);
+    }
+  }
+  if (lane == 0) {
+    *thr_out = delta;
+    a.scales[(int64_t)m * a.scale_stride + k] = scale;
+  }
+  // group j * 64 + lane gives byte lane & 3 of code word j * 16 + lane / 4; four groups at a time,
+  // lane l of a quad stores group l & 3's word
+  uint32_t* codes = a.codes + (int64_t)m * a.code_stride;
+  const int64_t w0 = lo / 16;
+#pragma unroll
+  for (int j4 = 0; j4 < kGroups; j4 += 4) {
+    constexpr int kQuads = kGroups < 4 ? kGroups : 4;
+    uint32_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < kQuads; ++j) {
+      uint32_t bits = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float x = v[j4 + j][e];
+        const uint32_t pat = 1u | ((__float_as_uint(x) >> 30) & 2u);
+        bits |= (fabsf(x) > delta ? pat : 0u) << (2 * e);
+      }
+      uint32_t w = bits << (8 * (lane & 3));
+      w |= (uint32_t)dpp_i32<kDppQuadXor1>((int)w);
+      w |= (uint32_t)dpp_i32<kDppQuadXor2>((int)w);
+      if ((lane & 3) == j) mine = w;
+    }
+    const int64_t widx = w0 + (j4 + (lane & 3)) * 16 + (lane >> 2);
+    if ((lane & 3) < kQuads && widx < a.W) codes[widx] = mine;
+  }
+}
+
+// The buckets that exact_histogram_kernel marked: ranked by the network, then quantized with the
+// thresholds it found.  A work-group looks at kRankSpan tiles; a tile without a mark costs it one load.
+constexpr int kRankSpan = 8;
+template <int LOG2B>
+__global__ __launch_bounds__(kThreads) void exact_rank_marked_kernel(QuantArgs a) {
+  constexpr int kPerTile = kTile >> LOG2B;
+  const int m = blockIdx.y;
+  const int64_t tile0 = (int64_t)blockIdx.x * kRankSpan;
+  const float* thr = a.thresholds + (int64_t)m * a.scale_stride;
+  const int64_t mine = tile0 * kPerTile + threadIdx.x;
+  const bool marked = threadIdx.x < kRankSpan * kPerTile && mine < a.nb && thr[mine] == kRankMark;
+  __shared__ uint64_t lds_marks;
+  if (threadIdx.x < kWave) {
+    const uint64_t w = __ballot(marked);
+    if (threadIdx.x == 0) lds_marks = w;
+  }
+  __syncthreads();
+  uint64_t marks = lds_marks;
+  while (marks) {
+    const int64_t tile = tile0 + (__ffsll((unsigned long long)marks) - 1) / kPerTile;
+    marks &= ~(((1ull << kPerTile) - 1ull) << ((tile - tile0) * kPerTile));
+    rank_tile<LOG2B>(a, tile, m);
+    __syncthreads();                                     // its thresholds are read next
+    if constexpr (LOG2B == 12) quantize_tile(a, tile, m);
+    else quantize_buckets_of_tile<LOG2B>(a, tile, m);
+    __syncthreads();                                     // LDS is free for the next tile
   }
 }
 
@@ -930,15 +1331,34 @@ int quantize_launch(const qa_layout* L, const float* g, int64_t g_stride, uint32
     if (rc != QA_OK) return rc;
     a.thresh_given = 1;                                  // the passes below read what it wrote
   } else if (flags & QA_THRESH_EXACT) {
-    // one ranking network per tile: buckets that fit a tile
-    switch (L->bucket ? ilog2(L->bucket) : 12) {
+    const int log2b = L->bucket ? ilog2(L->bucket) : 12;
+    if (log2b >= 9) {                                    // threshold, scale and codes in one pass
+      QuantArgs q = a;
+      q.thresh_given = 1;                                // for the buckets that are ranked behind it
+      q.bucket_len = 1 << log2b;
+      q.log2b = log2b;
+      const dim3 grid_waves((unsigned)((a.nb + kWaves - 1) / kWaves), (unsigned)L->M);
+      const dim3 grid_spans((unsigned)((a.ntiles + kRankSpan - 1) / kRankSpan), (unsigned)L->M);
+      if (log2b == 9) {
+        hipLaunchKernelGGL(exact_histogram_kernel<9>, grid_waves, block, 0, stream, q);
+        hipLaunchKernelGGL(exact_rank_marked_kernel<9>, grid_spans, block, 0, stream, q);
+      } else if (log2b == 10) {
+        hipLaunchKernelGGL(exact_histogram_kernel<10>, grid_waves, block, 0, stream, q);
+        hipLaunchKernelGGL(exact_rank_marked_kernel<10>, grid_spans, block, 0, stream, q);
+      } else if (log2b == 11) {
+        hipLaunchKernelGGL(exact_histogram_kernel<11>, grid_waves, block, 0, stream, q);
+        hipLaunchKernelGGL(exact_rank_marked_kernel<11>, grid_spans, block, 0, stream, q);
+      } else {
+        hipLaunchKernelGGL(exact_histogram_kernel<12>, grid_waves, block, 0, stream, q);
+        hipLaunchKernelGGL(exact_rank_marked_kernel<12>, grid_spans, block, 0, stream, q);
+      }
+      return launch_status();
+    }
+    // one ranking network per tile for the smaller buckets
+    switch (log2b) {
       case 6: hipLaunchKernelGGL(exact_threshold_kernel<6>, grid_tiles, block, 0, stream, a); break;
       case 7: hipLaunchKernelGGL(exact_threshold_kernel<7>, grid_tiles, block, 0, stream, a); break;
-      case 8: hipLaunchKernelGGL(exact_threshold_kernel<8>, grid_tiles, block, 0, stream, a); break;
-      case 9: hipLaunchKernelGGL(exact_threshold_kernel<9>, grid_tiles, block, 0, stream, a); break;
-      case 10: hipLaunchKernelGGL(exact_threshold_kernel<10>, grid_tiles, block, 0, stream, a); break;
-      case 11: hipLaunchKernelGGL(exact_threshold_kernel<11>, grid_tiles, block, 0, stream, a); break;
-      default: hipLaunchKernelGGL(exact_threshold_kernel<12>, grid_tiles, block, 0, stream, a); break;
+      default: hipLaunchKernelGGL(exact_threshold_kernel<8>, grid_tiles, block, 0, stream, a); break;
     }
     a.thresh_given = 1;                                  // the passes below read what it wrote
   }

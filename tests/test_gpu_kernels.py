@@ -645,6 +645,61 @@ def test_exact_threshold_never_splits_equal_magnitudes_and_handles_zeros(bucket)
     assert th[2, first_empty] == 0 and s[2, first_empty] == 0 and not c[2, 256:].any()
 
 
+def hard_bucket(kind, n, rng):
+    """Magnitudes on which the search for the optimum has little to go by, or much to rank."""
+    if kind == "one":                                   # a single non-zero component
+        v = np.zeros(n); v[n // 3] = -2.5
+    elif kind == "equal":
+        v = np.full(n, 0.37)
+    elif kind == "two values":                          # equal objectives for one value and for both
+        v = np.where(np.arange(n) % 4 == 0, 3.0, 1.0)
+    elif kind == "flat":                                # a_k ~ k^-1/2: the objective hardly changes with k
+        v = 1.0 / np.sqrt(np.arange(1, n + 1))
+    elif kind == "crowded":                             # all magnitudes within one bin's width of each other
+        v = 1.0 + rng.random(n) * 1e-5
+    elif kind == "two clusters":
+        v = np.where(rng.random(n) < 0.5, 1.0 + 0.01 * rng.random(n), 0.2 + 0.01 * rng.random(n))
+    elif kind == "outlier":
+        v = rng.standard_normal(n) * 1e-3; v[5] = 1e4
+    elif kind == "wide":                                # 60 binades
+        v = np.exp2(rng.uniform(-40, 20, n))
+    elif kind == "tiny":                                # subnormal members
+        v = rng.standard_normal(n) * 1e-38
+    elif kind == "huge":                                # their binary32 sum overflows
+        v = rng.uniform(0.5, 1.0, n) * 3e38
+    else:                                               # integers: ties everywhere
+        v = rng.integers(-9, 10, n).astype(float)
+    return (v * np.where(rng.random(n) < 0.5, -1.0, 1.0)).astype(np.float32)
+
+
+HARD = ["one", "equal", "two values", "flat", "crowded", "two clusters", "outlier", "wide", "tiny", "huge",
+        "integers"]
+
+
+@pytest.mark.parametrize("bucket,tail", [(4096, 0), (4096, 1), (2048, 4095), (1024, 1023), (1024, 0),
+                                         (512, 300)])
+def test_exact_threshold_on_hard_buckets(bucket, tail):
+    """One kind of bucket after the other in one vector, every kind also in the incomplete last bucket
+    (one worker per kind).  Where sums of the kept magnitudes round differently the scale may differ by
+    an ulp; the kept set may not."""
+    rng = np.random.default_rng(bucket + tail)
+    rows = []
+    for k in range(len(HARD)):
+        kinds = HARD[k:] + HARD[:k]
+        parts = [hard_bucket(q, bucket, rng) for q in kinds]
+        if tail:
+            parts.append(hard_bucket(kinds[-1], tail, rng) if tail > 5 else parts[0][:tail])
+        rows.append(np.concatenate(parts))
+    g = np.stack(rows)
+    th_ref = np.stack([oracle.exact_thresholds(r, bucket) for r in g])
+    c_ref, s_ref, _ = oracle.quantize_pack(g, bucket, thresholds=th_ref)
+    c, s, th, L = gpu_quantize_pack(g, bucket, exact=True)
+    nb = L.n_buckets
+    assert np.array_equal(th[:, :nb].view(np.uint32), th_ref.view(np.uint32))
+    assert np.array_equal(c[:, :L.words], c_ref)
+    assert int(ulp_distance(s[:, :nb], s_ref).max()) <= 1
+
+
 # buckets longer than one tile, and one threshold for a long vector: device-wide ranking
 @pytest.mark.parametrize("d,M,bucket", [(70001, 2, 0), (70001, 2, 8192), (4096 * 5 + 1, 3, 16384),
                                         (4097, 1, 0), (300001, 1, 0), (8192 * 3, 2, 8192),
