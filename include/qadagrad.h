@@ -161,9 +161,9 @@ int qa_local_grad_batched(int format, const float* A_or_vals, const int64_t* ind
  * strict comparisons keep exactly the optimal set; scale and codes follow as usual.  Buckets of
  * up to 4096 components are searched inside one wave or work-group; longer buckets, and one threshold for
  * a vector of more than 4096 components (Section 3.4's optimum over the whole gradient), are
- * ranked by a device-wide sort, worker after worker, in 17 bytes of workspace per component
- * (d < 2^32, else QA_ERR_TOO_LARGE); that form calls a library sort, which may enqueue memset
- * operations: do not record it into a HIP graph.  Candidates whose objectives agree to binary64 rounding
+ * found by refining histograms of the magnitudes, in 17 bytes of workspace per component
+ * (d < 2^32, else QA_ERR_TOO_LARGE); the call only enqueues kernels.  A bucket with non-finite
+ * components gets the threshold 0 there.  Candidates whose objectives agree to binary64 rounding
  * (likely only beyond some 1e7 components per bucket) may be resolved differently from a
  * strictly sequential summation.
  * g_stride >= d and a multiple of 4.  ws: qa_workspace_bytes(layout, QA_OP_QUANTIZE), or

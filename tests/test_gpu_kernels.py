@@ -655,6 +655,8 @@ def hard_bucket(kind, n, rng):
         v = np.where(np.arange(n) % 4 == 0, 3.0, 1.0)
     elif kind == "flat":                                # a_k ~ k^-1/2: the objective hardly changes with k
         v = 1.0 / np.sqrt(np.arange(1, n + 1))
+    elif kind == "level":                               # S_k = sqrt(k): every cut is as good as any other
+        v = np.sqrt(np.arange(1, n + 1)) - np.sqrt(np.arange(n)); v = rng.permutation(v)
     elif kind == "crowded":                             # all magnitudes within one bin's width of each other
         v = 1.0 + rng.random(n) * 1e-5
     elif kind == "two clusters":
@@ -672,7 +674,7 @@ def hard_bucket(kind, n, rng):
     return (v * np.where(rng.random(n) < 0.5, -1.0, 1.0)).astype(np.float32)
 
 
-HARD = ["one", "equal", "two values", "flat", "crowded", "two clusters", "outlier", "wide", "tiny", "huge",
+HARD = ["one", "equal", "two values", "flat", "level", "crowded", "two clusters", "outlier", "wide", "tiny", "huge",
         "integers"]
 
 
@@ -739,6 +741,29 @@ def test_exact_threshold_over_several_tiles_with_ties_zeros_and_a_ramp(bucket):
     assert np.array_equal(s.view(np.uint32), s_ref.view(np.uint32))
     if bucket:
         assert th[2, 1] == 0 and s[2, 1] == 0 and not c[2, 512:].any()
+
+
+@pytest.mark.parametrize("bucket,n,tail", [(8192, 8192, 0), (8192, 8192, 4099), (65536, 65536, 3), (0, 9001, 0),
+                                           (0, 65537, 0), (131072, 131072, 70001), (0, 300001, 0)])
+def test_exact_threshold_over_several_tiles_on_hard_buckets(bucket, n, tail):
+    """The same for buckets inside one work-group's reach (up to 65536) and beyond; "level" is what the
+    levels of the search cannot narrow down.  Scales within an ulp, the kept sets the oracle's."""
+    rng = np.random.default_rng(n + tail)
+    kinds = HARD if n < 100000 else ["two values", "level", "wide", "tiny", "integers"]
+    rows = []
+    for k in range(len(kinds) if bucket == 0 else 2):
+        parts = [hard_bucket(q, n, rng) for q in (kinds[k:k + 1] if bucket == 0 else kinds)]
+        if tail:
+            parts.append(hard_bucket(kinds[k], tail, rng) if tail > 5 else parts[0][:tail])
+        rows.append(np.concatenate(parts))
+    g = np.stack(rows)
+    th_ref = np.stack([oracle.exact_thresholds(r, bucket) for r in g])
+    c_ref, s_ref, _ = oracle.quantize_pack(g, bucket, thresholds=th_ref)
+    c, s, th, L = gpu_quantize_pack(g, bucket, exact=True)
+    nb = L.n_buckets
+    assert np.array_equal(th[:, :nb].view(np.uint32), th_ref.view(np.uint32))
+    assert np.array_equal(c[:, :L.words], c_ref)
+    assert int(ulp_distance(s[:, :nb], s_ref).max()) <= 1
 
 
 def test_exact_threshold_of_a_long_vector_is_optimal_to_binary64_resolution():
