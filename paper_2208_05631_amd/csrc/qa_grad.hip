@@ -4,9 +4,8 @@
 //
 //   margins  : p_b = a_{r_b}.x in binary64 (work-group per row for dense, wave per row for CSR),
 //              then coef_b = -y/(1+exp(y p_b))/B and the row's loss, in binary64.
-//   gradient : dense -- one thread per 4 columns (one column when d is not a multiple of 4 or the
-//                       operands are not 16-byte aligned) walks the batch in order, binary64
-//                       accumulator;
+//   gradient : dense -- one thread per 4 columns walks the batch (or a quarter of it), binary64
+//                       accumulators;
 //              CSR   -- hardware binary64 atomic adds into a d-long accumulator that is cleared
 //                       only at the batch's columns, then rounded into the zero-filled g.
 //   Every product coef*a is exact in binary64, so only the order of the binary64 additions can
@@ -16,6 +15,15 @@
 namespace qa {
 
 constexpr int kMaxBatch = 65536;
+
+// Dense rows: up to this many columns a wave takes a row, beyond it a work-group (4 workers x 64 rows of
+// 1000 columns, both kernels: 6.9 us with a work-group per row, 7.7 with a wave; 16 x 384 rows of
+// 64 columns: 19.3 and 10.8).
+constexpr int kShortRow = 512;
+// Column sums take the 16-way split of the batch below this many work-groups of the 4-way split (the chip has
+// 256 compute units) if the batch has rows for all sixteen parts: 8 x 256 rows of 4000 columns (128
+// work-groups) 16.6 us against 19.0; 2 x 256 rows of 30000 (236) 27.3 against 25.9.
+constexpr int kFewGroups = 192;
 
 struct GradArgs {
   const float* A;            // dense matrix or CSR values
@@ -49,12 +57,15 @@ __device__ __forceinline__ GradArgs for_worker(GradArgs a) {
   return a;
 }
 
-// The matrix rows of a batch are read once per pass: streaming (non-temporal) 16-byte load.
+// Four consecutive floats at any address that is a multiple of 4: the memory system takes a 16-byte
+// load on a 4-byte boundary (rows of an odd length start on those).  Streaming (non-temporal): the
+// matrix rows of a batch are read once per pass.
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ float4 stream_load4(const float4* p) {
-  const floatx4 t = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(p));
-  return make_float4(t.x, t.y, t.z, t.w);
+typedef floatx4 floatx4_any __attribute__((aligned(4)));
+__device__ __forceinline__ floatx4 stream_load4(const float* p) {
+  return __builtin_nontemporal_load(reinterpret_cast<const floatx4_any*>(p));
 }
+__device__ __forceinline__ floatx4 load4(const float* p) { return *reinterpret_cast<const floatx4_any*>(p); }
 
 // coef and loss of one sample from its binary32 margin term p = a.x
 __device__ __forceinline__ void logistic_terms(float p, float y, int B, float* coef, double* loss) {
@@ -65,127 +76,158 @@ __device__ __forceinline__ void logistic_terms(float p, float y, int B, float* c
   *coef = (float)((-(double)y * sig) / (double)B);
 }
 
-// Work-group per batch row.  VEC: d is a multiple of 4 and A, x are 16-byte aligned, so a row is
-// read as float4 with four loads in flight per thread.
-template <bool VEC>
+// sum of the losses of a worker's batch rows -> loss_out, by one work-group
+__device__ __forceinline__ void reduce_loss(const GradArgs& a, double* lds_d) {
+  double s = 0.0;
+  for (int b = threadIdx.x; b < a.B; b += kThreads) s += a.loss_part[b];
+  s = segment_sum(s, kThreads, lds_d);
+  if (threadIdx.x == 0) *a.loss_out = (float)(s / (double)a.B);
+}
+
+// LANES threads per batch row (the work-group, or a wave for short rows), which is read as 16-byte
+// pieces with four loads in flight per thread.
+template <int LANES>
 __global__ __launch_bounds__(kThreads) void dense_margin_kernel(GradArgs a_all) {
+  static_assert(LANES == kThreads || LANES == kWave, "a work-group or a wave per row");
   const GradArgs a = for_worker(a_all);
   __shared__ double lds_d[kWaves];
-  const int b = blockIdx.x;
+  const int b = LANES == kWave ? (int)(blockIdx.x * kWaves + threadIdx.x / kWave) : (int)blockIdx.x;
+  if (LANES == kWave && b >= a.B) return;
+  const int lane = threadIdx.x % LANES;
   const int64_t r = a.rows[b];
   const bool ok = r >= 0 && r < a.n_rows;
   double s = 0.0;
   if (ok) {
     const float* row = a.A + r * a.d;
-    if (VEC) {
-      const float4* row4 = reinterpret_cast<const float4*>(row);
-      const float4* x4 = reinterpret_cast<const float4*>(a.x);
-      const int64_t n4 = a.d / 4;
-      double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-      int64_t j = threadIdx.x;
-      for (; j + 3 * kThreads < n4; j += 4 * kThreads) {
-        float4 v[4], w[4];
+    const int64_t whole = a.d & ~int64_t(3);
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    int64_t j = 4 * lane;
+    for (; j + 4 * 3 * LANES < whole; j += 4 * 4 * LANES) {
+      floatx4 v[4], w[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = stream_load4(row4 + j + u * kThreads);
+      for (int u = 0; u < 4; ++u) v[u] = stream_load4(row + j + u * 4 * LANES);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) w[u] = x4[j + u * kThreads];
+      for (int u = 0; u < 4; ++u) w[u] = load4(a.x + j + u * 4 * LANES);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          s0 = fma((double)v[u].x, (double)w[u].x, s0);
-          s1 = fma((double)v[u].y, (double)w[u].y, s1);
-          s2 = fma((double)v[u].z, (double)w[u].z, s2);
-          s3 = fma((double)v[u].w, (double)w[u].w, s3);
-        }
+      for (int u = 0; u < 4; ++u) {
+        s0 = fma((double)v[u].x, (double)w[u].x, s0);
+        s1 = fma((double)v[u].y, (double)w[u].y, s1);
+        s2 = fma((double)v[u].z, (double)w[u].z, s2);
+        s3 = fma((double)v[u].w, (double)w[u].w, s3);
       }
-      for (; j < n4; j += kThreads) {
-        const float4 v = stream_load4(row4 + j), w = x4[j];
-        s0 = fma((double)v.x, (double)w.x, s0);
-        s1 = fma((double)v.y, (double)w.y, s1);
-        s2 = fma((double)v.z, (double)w.z, s2);
-        s3 = fma((double)v.w, (double)w.w, s3);
-      }
-      s = (s0 + s1) + (s2 + s3);
-    } else {
-      for (int64_t j = threadIdx.x; j < a.d; j += kThreads)
-        s = fma((double)row[j], (double)a.x[j], s);
     }
+    for (; j < whole; j += 4 * LANES) {
+      const floatx4 v = stream_load4(row + j), w = load4(a.x + j);
+      s0 = fma((double)v.x, (double)w.x, s0);
+      s1 = fma((double)v.y, (double)w.y, s1);
+      s2 = fma((double)v.z, (double)w.z, s2);
+      s3 = fma((double)v.w, (double)w.w, s3);
+    }
+    if (whole + lane < a.d)
+      s0 = fma((double)row[whole + lane], (double)a.x[whole + lane], s0);
+    s = (s0 + s1) + (s2 + s3);
   }
-  s = segment_sum(s, kThreads, lds_d);
-  if (threadIdx.x == 0) {
+  s = LANES == kWave ? wave_sum_f64(s) : segment_sum(s, kThreads, lds_d);
+  if (lane == 0) {
     float c = 0.0f; double l = 0.0;
     if (ok) logistic_terms((float)s, a.y[r], a.B, &c, &l);
     a.coef[b] = c; a.loss_part[b] = l;
   }
 }
 
-// g_j = sum over the batch, in batch order, of coef_b * A[r_b][j].  VEC: thread per 4 columns,
-// sixteen rows' loads in flight.  The batch's row ids and coefficients pass through LDS, 1024 at
-// a time, so that the matrix loads of a thread depend on nothing but an LDS read (read one by one
-// from memory they made a chain of dependent scalar loads: 13.7 us for 64 rows of 1000 columns).
-template <bool VEC>
+// g_j = sum over the batch of coef_b * A[r_b][j]: thread per 4 columns, sixteen rows' loads in
+// flight.  The batch's row ids and coefficients pass through LDS, 1024 at a time, so that the matrix
+// loads of a thread depend on nothing but an LDS read (read one by one from memory they made a
+// chain of dependent scalar loads).
+// SPLIT parts of the work-group share out the rows, sixteen at a time, for 256 / SPLIT threads' columns:
+// narrow matrices would leave the chip idle with a thread walking the whole batch, where the time
+// is the number of dependent rounds of loads (8 x 256 rows of 4000 columns: 35.9 us without a split),
+// and wide ones lose nothing (8 x 128 rows of 100003 columns, both kernels: 147 us against 155; 318
+// with a column per thread, as rows that do not start on 16 bytes were read before.  Both kernels
+// are bound by the two reads of the batch, 5.6-6.4 TB/s; a second read that could come from the
+// last-level cache -- workers taken in groups of 60-220 MB -- was no faster).
+// The last work-group of a worker adds up the losses instead, if they are asked for.
+template <int SPLIT>
 __global__ __launch_bounds__(kThreads) void dense_colsum_kernel(GradArgs a_all) {
+  constexpr int kRows = 16, kStage = 1024, kCols = kThreads / SPLIT;
   const GradArgs a = for_worker(a_all);
-  if (VEC) {
-    constexpr int kRows = 16, kStage = 1024;
-    __shared__ int4 s_row[kStage / 4];                    // -1: no row or id out of range, adds nothing
-    __shared__ float4 s_coef[kStage / 4];
-    int32_t* s_row1 = reinterpret_cast<int32_t*>(s_row);
-    float* s_coef1 = reinterpret_cast<float*>(s_coef);
-    const int64_t j4 = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const bool live = j4 < a.d / 4;
-    const float4* A4 = reinterpret_cast<const float4*>(a.A);
-    const int64_t pitch4 = a.d / 4;
-    double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0, acc3 = 0.0;
-    for (int c0 = 0; c0 < a.B; c0 += kStage) {
-      const int nb = a.B - c0 < kStage ? a.B - c0 : kStage;
-      const int nb_pad = (nb + kRows - 1) / kRows * kRows;
-      if (c0 > 0) __syncthreads();                        // the previous ids have been used
-      for (int i = threadIdx.x; i < nb_pad; i += kThreads) {
-        const int32_t r = i < nb ? a.rows[c0 + i] : -1;
-        const bool ok = r >= 0 && r < a.n_rows;
-        s_row1[i] = ok ? r : -1;
-        s_coef1[i] = ok ? a.coef[c0 + i] : 0.0f;
-      }
-      __syncthreads();
-      if (!live) continue;
-      for (int b0 = 0; b0 < nb_pad; b0 += kRows) {
-        int32_t r[kRows];
-        float cf32[kRows];
+  __shared__ int4 s_row[kStage / 4];                      // -1: no row or id out of range, adds nothing
+  __shared__ float4 s_coef[kStage / 4];
+  __shared__ double s_part[(SPLIT - 1) * 4 * kCols];
+  const int64_t n4 = (a.d + 3) / 4;
+  if ((int64_t)blockIdx.x * kCols >= n4) {
+    reduce_loss(a, s_part);
+    return;
+  }
+  int32_t* s_row1 = reinterpret_cast<int32_t*>(s_row);
+  float* s_coef1 = reinterpret_cast<float*>(s_coef);
+  const int part = (int)threadIdx.x / kCols, col = (int)threadIdx.x % kCols;
+  const int64_t j = ((int64_t)blockIdx.x * kCols + col) * 4;
+  const bool live = j < a.d, whole = j + 3 < a.d;
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int c0 = 0; c0 < a.B; c0 += kStage) {
+    const int nb = a.B - c0 < kStage ? a.B - c0 : kStage;
+    const int nb_pad = (nb + kRows - 1) / kRows * kRows;
+    if (c0 > 0) __syncthreads();                          // the previous ids have been used
+    for (int i = threadIdx.x; i < nb_pad; i += kThreads) {
+      const int32_t r = i < nb ? a.rows[c0 + i] : -1;
+      const bool ok = r >= 0 && r < a.n_rows;
+      s_row1[i] = ok ? r : -1;
+      s_coef1[i] = ok ? a.coef[c0 + i] : 0.0f;
+    }
+    __syncthreads();
+    if (!live) continue;
+    for (int b0 = part * kRows; b0 < nb_pad; b0 += SPLIT * kRows) {
+      int32_t r[kRows];
+      float cf32[kRows];
 #pragma unroll
-        for (int u = 0; u < kRows / 4; ++u) {
-          const int4 rr = s_row[b0 / 4 + u];
-          const float4 cc = s_coef[b0 / 4 + u];
-          r[4 * u] = rr.x; r[4 * u + 1] = rr.y; r[4 * u + 2] = rr.z; r[4 * u + 3] = rr.w;
-          cf32[4 * u] = cc.x; cf32[4 * u + 1] = cc.y; cf32[4 * u + 2] = cc.z; cf32[4 * u + 3] = cc.w;
-        }
-        float4 v[kRows];
+      for (int u = 0; u < kRows / 4; ++u) {
+        const int4 rr = s_row[b0 / 4 + u];
+        const float4 cc = s_coef[b0 / 4 + u];
+        r[4 * u] = rr.x; r[4 * u + 1] = rr.y; r[4 * u + 2] = rr.z; r[4 * u + 3] = rr.w;
+        cf32[4 * u] = cc.x; cf32[4 * u + 1] = cc.y; cf32[4 * u + 2] = cc.z; cf32[4 * u + 3] = cc.w;
+      }
+      floatx4 v[kRows];
+      if (whole) {
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) v[u] = stream_load4(a.A + (int64_t)(r[u] >= 0 ? r[u] : 0) * a.d + j);
+      } else {                                            // the last columns of a row of odd length
 #pragma unroll
         for (int u = 0; u < kRows; ++u) {
-          v[u] = stream_load4(A4 + (int64_t)(r[u] >= 0 ? r[u] : 0) * pitch4 + j4);
-          if (r[u] < 0) v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-#pragma unroll
-        for (int u = 0; u < kRows; ++u) {
-          const double cf = (double)cf32[u];
-          acc0 = fma(cf, (double)v[u].x, acc0);
-          acc1 = fma(cf, (double)v[u].y, acc1);
-          acc2 = fma(cf, (double)v[u].z, acc2);
-          acc3 = fma(cf, (double)v[u].w, acc3);
+          const float* p = a.A + (int64_t)(r[u] >= 0 ? r[u] : 0) * a.d + j;
+          v[u].x = p[0];
+          v[u].y = j + 1 < a.d ? p[1] : 0.0f;
+          v[u].z = j + 2 < a.d ? p[2] : 0.0f;
+          v[u].w = 0.0f;
         }
       }
+#pragma unroll
+      for (int u = 0; u < kRows; ++u) {
+        const double cf = (double)cf32[u];
+        if (r[u] < 0) v[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+        acc[0] = fma(cf, (double)v[u].x, acc[0]);
+        acc[1] = fma(cf, (double)v[u].y, acc[1]);
+        acc[2] = fma(cf, (double)v[u].z, acc[2]);
+        acc[3] = fma(cf, (double)v[u].w, acc[3]);
+      }
     }
-    if (live)
-      reinterpret_cast<float4*>(a.g)[j4] = make_float4((float)acc0, (float)acc1, (float)acc2, (float)acc3);
-  } else {
-    const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (j >= a.d) return;
-    double acc = 0.0;
-    for (int b = 0; b < a.B; ++b) {
-      const int64_t r = a.rows[b];
-      if (r < 0 || r >= a.n_rows) continue;
-      acc = fma((double)a.coef[b], (double)a.A[r * a.d + j], acc);
-    }
-    a.g[j] = (float)acc;
+  }
+  if (part > 0) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s_part[((part - 1) * 4 + e) * kCols + col] = acc[e];
+  }
+  __syncthreads();
+  if (part > 0) return;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int q = 0; q < SPLIT - 1; ++q) acc[e] += s_part[(q * 4 + e) * kCols + col];
+  if (whole) {
+    *reinterpret_cast<float4*>(a.g + j) = make_float4((float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]);
+  } else if (live) {
+    a.g[j] = (float)acc[0];
+    if (j + 1 < a.d) a.g[j + 1] = (float)acc[1];
+    if (j + 2 < a.d) a.g[j + 2] = (float)acc[2];
   }
 }
 
@@ -256,10 +298,7 @@ __global__ __launch_bounds__(kThreads) void csr_scatter_kernel(GradArgs a_all) {
 __global__ __launch_bounds__(kThreads) void loss_finalize_kernel(GradArgs a_all) {
   const GradArgs a = for_worker(a_all);
   __shared__ double lds_d[kWaves];
-  double s = 0.0;
-  for (int b = threadIdx.x; b < a.B; b += kThreads) s += a.loss_part[b];
-  s = segment_sum(s, kThreads, lds_d);
-  if (threadIdx.x == 0) *a.loss_out = (float)(s / (double)a.B);
+  reduce_loss(a, lds_d);
 }
 
 static inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
@@ -300,15 +339,18 @@ static int grad_launch(int format, const float* A_or_vals, const int64_t* indptr
   const dim3 block(kThreads);
   const unsigned Mu = (unsigned)M;
   if (!csr) {
-    if ((d % 4) == 0 && aligned(A_or_vals, 16) && aligned(x, 16)) {
-      hipLaunchKernelGGL((dense_margin_kernel<true>), dim3(B, Mu), block, 0, stream, a);
-      hipLaunchKernelGGL((dense_colsum_kernel<true>),
-                         dim3((unsigned)((d / 4 + kThreads - 1) / kThreads), Mu), block, 0, stream, a);
-    } else {
-      hipLaunchKernelGGL((dense_margin_kernel<false>), dim3(B, Mu), block, 0, stream, a);
-      hipLaunchKernelGGL((dense_colsum_kernel<false>),
-                         dim3((unsigned)((d + kThreads - 1) / kThreads), Mu), block, 0, stream, a);
-    }
+    const int64_t n4 = (d + 3) / 4;
+    const unsigned extra = loss_out ? 1u : 0u;            // a work-group per worker for the loss
+    if (d <= kShortRow)
+      hipLaunchKernelGGL(dense_margin_kernel<kWave>, dim3((B + kWaves - 1) / kWaves, Mu), block, 0, stream, a);
+    else
+      hipLaunchKernelGGL(dense_margin_kernel<kThreads>, dim3(B, Mu), block, 0, stream, a);
+    const int64_t groups = (n4 + kWave - 1) / kWave;
+    if (groups * M < kFewGroups && B > 64)
+      hipLaunchKernelGGL(dense_colsum_kernel<16>, dim3((unsigned)((n4 + 15) / 16) + extra, Mu), block, 0, stream, a);
+    else
+      hipLaunchKernelGGL(dense_colsum_kernel<4>, dim3((unsigned)groups + extra, Mu), block, 0, stream, a);
+    return launch_status();
   } else {
     const dim3 grid_rows((B + kWaves - 1) / kWaves, Mu);
     // few rows for a long vector: the zero-fill gets a launch of its own

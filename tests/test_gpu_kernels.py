@@ -372,6 +372,44 @@ def test_local_grad_dense_matches_oracle(d, B):
     assert (gg == og).mean() > 0.999
 
 
+@pytest.mark.parametrize("d,B,M", [(1, 1, 1), (3, 65, 2), (5, 16, 3), (511, 64, 2), (513, 80, 2), (63, 1025, 1),
+                                   (1023, 1040, 2), (257, 2049, 1), (12290, 64, 5)])
+@pytest.mark.parametrize("shift", [0, 1, 3])
+def test_local_grad_dense_at_any_alignment_and_batch_split(d, B, M, shift):
+    """Matrix and x starting `shift` floats past a 16-byte boundary (and rows of odd length anywhere), batches
+    around the shares of sixteen rows and the 1024 row ids staged at a time, ids outside the
+    matrix (which add nothing), short and long rows."""
+    rng = np.random.default_rng(d + B)
+    n = 200
+    A = rng.standard_normal((n, d)).astype(np.float32)
+    y = np.where(rng.random(n) < 0.5, -1.0, 1.0).astype(np.float32)
+    x = (rng.standard_normal(d) * 0.1).astype(np.float32)
+    rows = rng.integers(0, n, (M, B)).astype(np.int32)
+    gs = (d + 3) // 4 * 4 + 4
+    A_d = dev(np.concatenate([np.full(shift, np.nan, np.float32), A.reshape(-1)]))[shift:]
+    x_d = dev(np.concatenate([np.full(shift, np.nan, np.float32), x]))[shift:]
+    ws = workspace(qa.qa_workspace_bytes(qa.Layout.make(d, M, 0), qa.QA_OP_GRAD_DENSE))
+    g = torch.full((M, gs), 5.0, dtype=torch.float32, device=DEV)
+    loss = torch.zeros(M, dtype=torch.float32, device=DEV)
+    ref = [oracle.local_grad_dense(A, y, rows[m], x) for m in range(M)]
+    for with_bad in (False, True):
+        ids = rows.copy()
+        if with_bad and B > 16:                          # a row replaced by one outside: its term is missing
+            ids[:, 7], ids[:, B - 1] = -1, n
+            gone = [oracle.local_grad_dense(A, y, np.repeat(rows[m, [7, B - 1]], 1), x)[0] * (2.0 / B) for m in range(M)]
+        qa.qa_local_grad_batched(qa.QA_DENSE, A_d, None, None, n, d, dev(y), dev(ids), B, M, x_d, g, gs, loss, ws)
+        torch.cuda.synchronize()
+        gg = host(g)
+        R = np.stack([r[0] for r in ref])
+        assert np.all(gg[:, d:] == 5.0)
+        if with_bad and B > 16:
+            # the reference less two terms, each rounded to binary32: 2^-23 of the larger operand
+            assert np.allclose(gg[:, :d], R - np.stack(gone), rtol=1e-6, atol=4e-7 * np.abs(R).max())
+        else:
+            assert np.allclose(gg[:, :d], R, rtol=1e-6, atol=1e-30)
+            assert np.allclose(host(loss), [r[1] for r in ref], rtol=1e-6)
+
+
 def _random_csr(rng, n, d, k):
     idx = np.stack([np.sort(rng.choice(d, k, replace=False)) for _ in range(n)]).astype(np.int32)
     vals = rng.standard_normal((n, k)).astype(np.float32)
