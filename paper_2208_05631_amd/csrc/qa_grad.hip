@@ -6,8 +6,11 @@
 //              then coef_b = -y/(1+exp(y p_b))/B and the row's loss, in binary64.
 //   gradient : dense -- one thread per 4 columns walks the batch (or a quarter of it), binary64
 //                       accumulators;
-//              CSR   -- hardware binary64 atomic adds into a d-long accumulator that is cleared
-//                       only at the batch's columns, then rounded into the zero-filled g.
+//              CSR   -- the batch's entries are sorted into ranges of columns while the margins are
+//                       formed, and a work-group per range adds them up in LDS and writes its part
+//                       of g; vectors of more than 2^22 columns take hardware binary64 atomic adds
+//                       into a d-long accumulator that is cleared only at the batch's columns, then
+//                       rounded into the zero-filled g.
 //   Every product coef*a is exact in binary64, so only the order of the binary64 additions can
 //   differ from a sequential evaluation.
 #include "qa_common.h"
@@ -295,6 +298,300 @@ __global__ __launch_bounds__(kThreads) void csr_scatter_kernel(GradArgs a_all) {
   }
 }
 
+// ---- CSR rows, up to 2^22 columns: two launches, no global atomics -------------------------------
+//
+// A batch touches few of the d columns, at random.  An accumulator in memory costs three or four cache
+// lines per entry (clear, atomic addition, read back, g) beside a zero-filled g.  Here instead
+//
+//   csr_bin     a work-group per group of rows (a multiple of 16, 16 lanes per row) forms their margins,
+//               coefficients and losses, counts the entries per range of 2^LOGW columns, and writes the
+//               entries -- value, batch row, column in its range -- to the group's part of the
+//               workspace, ordered by range, with a table of where each range begins;
+//   csr_gather  a work-group per range of a worker collects the groups' entries of its range, adds
+//               coefficient * value into 2^LOGW binary64 accumulators in LDS and writes its part of g
+//               in one piece, zeros included.
+//
+// A group whose entries do not fit its part of the workspace (their number is known on the device
+// only; all groups of a worker together have room for some 98 000 + d entries) leaves a mark, and
+// csr_gather reads the group's rows themselves and takes what lies in its range.
+//
+// Ranges are as narrow as 256 of them allow (a counter per thread of csr_bin's work-group), at least 256
+// columns, at most 16384 (128 KiB of LDS): narrow ones are more work-groups on short vectors (4 x 300
+// rows of 150 entries, 5003 columns: 13.9 us with 256, 24 with 1024).  Beyond 2^22 columns the atomic form
+// stays; at 2^22 (8 x 256 rows x 100) it takes 48 us, this one 39.
+// Bound by the write of g (4 d bytes per worker) and, for few rows, by the chains of dependent loads (row
+// id, row bounds, columns, x; table, entry, coefficient).  Atomic form -> this, batched calls: 16 x 256
+// rows x 100 entries, d = 2^20 52.9 -> 26.4 us (csr_bin 10, csr_gather 16; 64 MiB of g alone take 11);
+// 4 workers 21.0 -> 14.3; 16 x 384 x 200, d = 2^18 108 -> 32; 4 x 64 x 50, d = 4096 9.7 -> 9.4.
+constexpr int kBinThreads = 256, kMaxRanges = 256, kMaxGroups = 64, kRowLanes = 16;
+constexpr int kMinLogWidth = 8, kMaxLogWidth = 14;
+constexpr uint32_t kOverflow = 0xffffffffu;
+
+struct BinArgs {
+  uint32_t* table;           // [groups][ranges + 1], first range's entry kOverflow if the group did not fit
+  uint2* entries;            // [groups][capacity]: value bits, batch row << 14 | column in range
+  int64_t ws_stride_bytes;
+  int groups, rows_per_group, ranges, log_width;
+  uint32_t capacity;
+};
+
+__device__ __forceinline__ BinArgs for_worker(BinArgs b) {
+  const int64_t m = blockIdx.y;
+  b.table = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(b.table) + m * b.ws_stride_bytes);
+  b.entries = reinterpret_cast<uint2*>(reinterpret_cast<char*>(b.entries) + m * b.ws_stride_bytes);
+  return b;
+}
+
+__device__ __forceinline__ double row16_sum_f64(double v) {
+  v += dpp_f64<kDppQuadXor1>(v);
+  v += dpp_f64<kDppQuadXor2>(v);
+  v += dpp_f64<kDppRowHalfMirror>(v);
+  v += dpp_f64<kDppRowMirror>(v);
+  return v;
+}
+
+// Up to 128 entries of a row, eight per lane of its team: column ids (0xffffffff: none), values.
+constexpr int kAhead = 8;
+struct RowChunk {
+  uint32_t c[kAhead];
+  float v[kAhead];
+};
+__device__ __forceinline__ void load_columns(const GradArgs& a, int64_t k, int64_t k1, uint32_t (&c)[kAhead]) {
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u)
+    c[u] = k + kRowLanes * u < k1 ? (uint32_t)a.indices[k + kRowLanes * u] : 0xffffffffu;
+}
+__device__ __forceinline__ void load_chunk(const GradArgs& a, int64_t k, int64_t k1, RowChunk& q) {
+  load_columns(a, k, k1, q.c);
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) q.v[u] = k + kRowLanes * u < k1 ? a.A[k + kRowLanes * u] : 0.0f;
+}
+
+// ONE_ROW: a team has one row, whose row bounds and first 128 entries stay in registers between the
+// counting and the writing (the time of small batches is the chain of dependent loads).
+template <bool ONE_ROW>
+__global__ __launch_bounds__(kBinThreads) void csr_bin_kernel(GradArgs a_all, BinArgs b_all) {
+  const GradArgs a = for_worker(a_all);
+  const BinArgs b = for_worker(b_all);
+  __shared__ uint32_t count[kMaxRanges];
+  __shared__ uint32_t place[kMaxRanges];                 // where the range's entries without a rank go
+  __shared__ uint32_t wave_total[kBinThreads / kWave];
+  constexpr int kTeams = kBinThreads / kRowLanes, kStep = kRowLanes * kAhead;
+  const int t = threadIdx.x, lane = t % kRowLanes, team = t / kRowLanes;
+  const int group = blockIdx.x;
+  const int first = group * b.rows_per_group;
+  const int last = first + b.rows_per_group < a.B ? first + b.rows_per_group : a.B;
+  const uint32_t d = (uint32_t)a.d;
+  count[t] = 0u;
+  place[t] = 0u;
+  __syncthreads();
+  RowChunk q;
+  uint32_t rank[kAhead];                                 // of the chunk in registers, among the range's
+  int64_t k0 = 0, k1 = 0;
+  double s = 0.0;
+  bool ok = false;
+  float label = 0.0f;
+  const auto row_bounds = [&](int i) {
+    const int64_t r = i < last ? a.rows[i] : -1;
+    ok = r >= 0 && r < a.n_rows;
+    k0 = ok ? a.indptr[r] : 0;
+    k1 = ok ? a.indptr[r + 1] : 0;
+    label = ok ? a.y[r] : 0.0f;
+  };
+  const auto count_chunk = [&](bool ranked) {
+    float x[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) x[u] = q.c[u] < d ? a.x[q.c[u]] : 0.0f;
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      if (q.c[u] < d) {
+        if (ranked) rank[u] = atomicAdd(&count[q.c[u] >> b.log_width], 1u);
+        else atomicAdd(&place[q.c[u] >> b.log_width], 1u);
+      }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      if (q.c[u] < d) s = fma((double)q.v[u], (double)x[u], s);
+  };
+  // coefficient and loss of row i from the team's margin, by two lanes
+  const auto finish_row = [&](int i) {
+    if (i < last && lane < 2) {
+      float coef = 0.0f; double loss = 0.0;
+      if (ok) logistic_terms((float)s, label, a.B, &coef, &loss);
+      if (lane == 0) a.coef[i] = coef;
+      else a.loss_part[i] = loss;
+    }
+  };
+  if (ONE_ROW) {
+    row_bounds(first + team);
+    for (int64_t k = k1 - k0 > kStep ? k0 + kStep + lane : k1; k < k1; k += kStep) {       // beyond the first chunk
+      load_chunk(a, k, k1, q);
+      count_chunk(false);
+    }
+    load_chunk(a, k0 + lane, k1, q);
+    count_chunk(true);
+    s = row16_sum_f64(s);
+  } else {
+    for (int i = first + team; i < last; i += kTeams) {
+      row_bounds(i);
+      s = 0.0;
+      for (int64_t k = k0 + lane; k < k1; k += kStep) {
+        load_chunk(a, k, k1, q);
+        count_chunk(false);
+      }
+      s = row16_sum_f64(s);
+      finish_row(i);
+    }
+  }
+  __syncthreads();
+  // where each range begins in the group's part
+  const uint32_t ranked = count[t], mine = ranked + place[t];
+  uint32_t incl = mine;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const uint32_t o = __shfl_up(incl, off, kWave);
+    if (t % kWave >= off) incl += o;
+  }
+  if (t % kWave == kWave - 1) wave_total[t / kWave] = incl;
+  __syncthreads();
+  uint32_t before = incl - mine, total = 0;
+#pragma unroll
+  for (int w = 0; w < kBinThreads / kWave; ++w) {
+    if (w < t / kWave) before += wave_total[w];
+    total += wave_total[w];
+  }
+  uint32_t* table = b.table + (int64_t)group * (b.ranges + 1);
+  const bool fits = total <= b.capacity;                 // the same for the whole work-group
+  if (t < b.ranges) table[t] = !fits && t == 0 ? kOverflow : before;
+  if (t == 0) table[b.ranges] = total;
+  count[t] = before;
+  place[t] = before + ranked;
+  __syncthreads();
+  uint2* entries = b.entries + (int64_t)group * b.capacity;
+  const uint32_t in_range = (1u << b.log_width) - 1u;
+  const auto write_chunk = [&](int i, bool is_ranked) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      if (q.c[u] < d) {
+        const uint32_t of = q.c[u] >> b.log_width;
+        const uint32_t at = is_ranked ? count[of] + rank[u] : atomicAdd(&place[of], 1u);
+        entries[at] = make_uint2(__float_as_uint(q.v[u]), ((uint32_t)i << 14) | (q.c[u] & in_range));
+      }
+  };
+  if (ONE_ROW) {
+    if (fits) {
+      write_chunk(first + team, true);
+      for (int64_t k = k1 - k0 > kStep ? k0 + kStep + lane : k1; k < k1; k += kStep) {
+        load_chunk(a, k, k1, q);
+        write_chunk(first + team, false);
+      }
+    }
+    finish_row(first + team);
+  } else if (fits) {
+    for (int i = first + team; i < last; i += kTeams) {
+      row_bounds(i);
+      for (int64_t k = k0 + lane; k < k1; k += kStep) {
+        load_chunk(a, k, k1, q);
+        write_chunk(i, false);
+      }
+    }
+  }
+}
+
+template <int LOGW> constexpr int gather_threads() { return LOGW >= 14 ? 1024 : 512; }
+
+template <int LOGW>
+__global__ __launch_bounds__(gather_threads<LOGW>()) void csr_gather_kernel(GradArgs a_all, BinArgs b_all) {
+  constexpr int kWidth = 1 << LOGW, kThr = gather_threads<LOGW>(), kTeams = kThr / kRowLanes;
+  const GradArgs a = for_worker(a_all);
+  const BinArgs b = for_worker(b_all);
+  __shared__ double acc[kWidth];
+  __shared__ int overflow;
+  static_assert(kThr / kWave <= kWidth, "room for the waves' sums");
+  const int t = threadIdx.x, lane = t % kRowLanes, team = t / kRowLanes;
+  const uint32_t range = blockIdx.x;
+  if ((int)range >= b.ranges) {                            // a worker's extra work-group: the loss
+    double s = 0.0;
+    for (int i = t; i < a.B; i += kThr) s += a.loss_part[i];
+    s = wave_sum_f64(s);
+    if (t % kWave == 0) acc[t / kWave] = s;
+    __syncthreads();
+    if (t == 0) {
+      double all = 0.0;
+      for (int w = 0; w < kThr / kWave; ++w) all += acc[w];
+      *a.loss_out = (float)(all / (double)a.B);
+    }
+    return;
+  }
+  // a team's first 64 entries of one group are on their way while the accumulators are cleared
+  uint2 e[4];
+  float coef[4];
+  uint32_t lo = 0, hi = 0;
+  bool marked = false;
+  const uint2* entries = b.entries;
+  const auto load_entries = [&](uint32_t i) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) e[u] = i + kRowLanes * u < hi ? entries[i + kRowLanes * u] : make_uint2(0u, 0u);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) coef[u] = i + kRowLanes * u < hi ? a.coef[e[u].y >> 14] : 0.0f;
+  };
+  const auto open_group = [&](int g) {
+    const uint32_t* table = b.table + (int64_t)g * (b.ranges + 1);
+    const bool live = g < b.groups;
+    const uint32_t first = live ? table[0] : 0u;
+    lo = live ? table[range] : 0u;
+    hi = live ? table[range + 1] : 0u;
+    marked = first == kOverflow;
+    if (marked) lo = hi = 0u;
+    entries = b.entries + (int64_t)g * b.capacity;
+    load_entries(lo + lane);
+  };
+  open_group(team);
+  for (int i = t; i < kWidth / 2; i += kThr) reinterpret_cast<double2*>(acc)[i] = make_double2(0.0, 0.0);
+  if (t == 0) overflow = 0;
+  __syncthreads();
+  for (int g = team; g < b.groups;) {
+    if (marked && lane == 0) overflow = 1;
+    for (uint32_t i = lo + lane; i < hi;) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (i + kRowLanes * u < hi)
+          unsafeAtomicAdd(&acc[e[u].y & (kWidth - 1)], (double)coef[u] * (double)__uint_as_float(e[u].x));
+      i += kRowLanes * 4;
+      if (i < hi) load_entries(i);
+    }
+    g += kTeams;
+    if (g < b.groups) open_group(g);
+  }
+  __syncthreads();
+  if (overflow) {
+    for (int i = team; i < a.B; i += kTeams) {
+      const int64_t r = a.rows[i];
+      if (r < 0 || r >= a.n_rows || b.table[(int64_t)(i / b.rows_per_group) * (b.ranges + 1)] != kOverflow) continue;
+      const double coef = (double)a.coef[i];
+      const int64_t k1 = a.indptr[r + 1];
+      for (int64_t k = a.indptr[r] + lane; k < k1; k += kRowLanes * kAhead) {
+        uint32_t c[kAhead];
+        load_columns(a, k, k1, c);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+          if (c[u] < (uint32_t)a.d && c[u] >> LOGW == range)
+            unsafeAtomicAdd(&acc[c[u] & (kWidth - 1)], coef * (double)a.A[k + kRowLanes * u]);
+      }
+    }
+    __syncthreads();
+  }
+  const int64_t c0 = (int64_t)range << LOGW;
+  const int n = a.d - c0 < kWidth ? (int)(a.d - c0) : kWidth;
+  float* g = a.g + c0;
+  for (int i = 4 * t; i < n; i += 4 * kThr) {
+    if (i + 3 < n) {
+      *reinterpret_cast<float4*>(g + i) = make_float4((float)acc[i], (float)acc[i + 1], (float)acc[i + 2], (float)acc[i + 3]);
+    } else {
+      for (int e = 0; i + e < n; ++e) g[i + e] = (float)acc[i + e];
+    }
+  }
+}
+
 __global__ __launch_bounds__(kThreads) void loss_finalize_kernel(GradArgs a_all) {
   const GradArgs a = for_worker(a_all);
   __shared__ double lds_d[kWaves];
@@ -306,6 +603,43 @@ static inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 size_t grad_workspace_bytes(int64_t d, bool csr) {
   return align256((size_t)kMaxBatch * sizeof(float)) + align256((size_t)kMaxBatch * sizeof(double)) +
          (csr ? align256((size_t)d * sizeof(double)) : 0);
+}
+
+// The two-launch form for CSR rows; false if the vector is too long for its ranges.  A worker's part of
+// the workspace holds [coefficients][losses][table][entries]: grad_workspace_bytes counts the first two
+// for the largest batch, so some 98 000 entries fit beside the d of the accumulator.
+static bool csr_launch(GradArgs a, int M, hipStream_t stream) {
+  int log_width = kMinLogWidth;
+  while (((a.d + (int64_t(1) << log_width) - 1) >> log_width) > kMaxRanges) ++log_width;
+  if (log_width > kMaxLogWidth) return false;
+  BinArgs b{};
+  b.log_width = log_width;
+  b.ranges = (int)((a.d + (int64_t(1) << log_width) - 1) >> log_width);
+  const int teams = kBinThreads / kRowLanes;
+  b.rows_per_group = teams * ((a.B + teams * kMaxGroups - 1) / (teams * kMaxGroups));
+  b.groups = (a.B + b.rows_per_group - 1) / b.rows_per_group;
+  char* const base = reinterpret_cast<char*>(a.coef);
+  size_t at = align256((size_t)a.B * sizeof(float));
+  a.loss_part = reinterpret_cast<double*>(base + at);
+  at += align256((size_t)a.B * sizeof(double));
+  b.table = reinterpret_cast<uint32_t*>(base + at);
+  at += align256((size_t)b.groups * (b.ranges + 1) * sizeof(uint32_t));
+  if (at > (size_t)a.ws_stride_bytes) return false;
+  b.entries = reinterpret_cast<uint2*>(base + at);
+  const size_t room = ((size_t)a.ws_stride_bytes - at) / sizeof(uint2) / (size_t)b.groups;
+  b.capacity = room < (size_t)kOverflow ? (uint32_t)room : kOverflow - 1u;
+  b.ws_stride_bytes = a.ws_stride_bytes;
+  const dim3 grid((unsigned)b.ranges + (a.loss_out ? 1u : 0u), (unsigned)M), groups((unsigned)b.groups, (unsigned)M);
+  if (b.rows_per_group == teams) hipLaunchKernelGGL(csr_bin_kernel<true>, groups, dim3(kBinThreads), 0, stream, a, b);
+  else hipLaunchKernelGGL(csr_bin_kernel<false>, groups, dim3(kBinThreads), 0, stream, a, b);
+  switch (log_width) {
+#define QA_GATHER(w) \
+    case w: hipLaunchKernelGGL(csr_gather_kernel<w>, grid, dim3(gather_threads<w>()), 0, stream, a, b); break
+    QA_GATHER(8); QA_GATHER(9); QA_GATHER(10); QA_GATHER(11); QA_GATHER(12); QA_GATHER(13); QA_GATHER(14);
+#undef QA_GATHER
+    default: return false;
+  }
+  return true;
 }
 
 static int grad_launch(int format, const float* A_or_vals, const int64_t* indptr,
@@ -350,6 +684,8 @@ static int grad_launch(int format, const float* A_or_vals, const int64_t* indptr
       hipLaunchKernelGGL(dense_colsum_kernel<16>, dim3((unsigned)((n4 + 15) / 16) + extra, Mu), block, 0, stream, a);
     else
       hipLaunchKernelGGL(dense_colsum_kernel<4>, dim3((unsigned)groups + extra, Mu), block, 0, stream, a);
+    return launch_status();
+  } else if (csr_launch(a, M, stream)) {
     return launch_status();
   } else {
     const dim3 grid_rows((B + kWaves - 1) / kWaves, Mu);

@@ -442,6 +442,63 @@ def test_local_grad_csr_matches_oracle():
     assert (gg == og).mean() > 0.999
 
 
+@pytest.mark.parametrize("d,n,B,M,nnz", [(1, 9, 5, 1, 2), (40, 50, 384, 3, 30), (1024, 300, 70, 2, 40),
+                                         (1025, 300, 17, 2, 40), (5003, 400, 300, 4, 150), (262145, 600, 130, 2, 70),
+                                         (1 << 19, 300, 16, 3, 300), ((1 << 20) + 3, 500, 1100, 1, 60),
+                                         ((1 << 21) + 1, 100, 33, 1, 50), (1 << 22, 64, 64, 1, 20),
+                                         ((1 << 22) + 1, 64, 64, 1, 20),
+                                         # no group, and about half of the groups, without room
+                                         (1025, 300, 400, 2, 600), (900, 200, 300, 1, 330)])
+def test_local_grad_csr_across_the_column_ranges(d, n, B, M, nnz):
+    """Lengths around every width of the column ranges and the last one that takes them, batches with more
+    entries than the workspace has room for (read again from the rows), rows of different lengths (also
+    empty ones), duplicate columns, columns outside the vector and row ids outside the matrix."""
+    rng = np.random.default_rng(d + B)
+    lens = rng.integers(0, 2 * nnz, n)
+    lens[0] = 0
+    indptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    total = int(indptr[-1])
+    idx = np.where(rng.random(total) < 0.5, rng.integers(0, d, total), rng.integers(0, max(1, d // 64), total))
+    if total > 4:
+        idx[:2] = [d - 1, 0]
+    idx = idx.astype(np.int32)
+    vals = rng.standard_normal(max(total, 1)).astype(np.float32)
+    y = np.where(rng.random(n) < 0.5, -1.0, 1.0).astype(np.float32)
+    x = (rng.standard_normal(d) * 0.1).astype(np.float32)
+    rows = rng.integers(0, n, (M, B)).astype(np.int32)
+    rows[:, 0] = 0
+    gs = (d + 3) // 4 * 4 + 8
+    ws = workspace(qa.qa_workspace_bytes(qa.Layout.make(d, M, 0), qa.QA_OP_GRAD_CSR))
+    ws.fill_(0xFF)
+    g = torch.full((M, gs), 5.0, dtype=torch.float32, device=DEV)
+    loss = torch.zeros(M, dtype=torch.float32, device=DEV)
+    ip_d, y_d, x_d, v_d = dev(indptr), dev(y), dev(x), dev(vals)
+    for bad in (False, True):
+        ix, ids = idx.copy(), rows.copy()
+        if bad and total > 4:                            # entries of row 0.. moved outside: they add nothing
+            ix[::97] = np.where(np.arange(len(ix[::97])) % 2, -1, d).astype(np.int32)
+        if bad:
+            ids[:, -1] = n + 3
+        qa.qa_local_grad_batched(qa.QA_CSR, v_d, ip_d, dev(ix), n, d, y_d, dev(ids), B, M, x_d, g, gs, loss, ws)
+        torch.cuda.synchronize()
+        gg, ll = host(g), host(loss)
+        v2 = np.where((ix < 0) | (ix >= d), np.float32(0), vals[:total])
+        i2 = np.where((ix < 0) | (ix >= d), 0, ix).astype(np.int32)
+        assert np.all(gg[:, d:] == 5.0)
+        for m in range(M):
+            keep = ids[m] < n
+            if not keep.any():
+                continue
+            og, ol = oracle.local_grad_csr(v2, indptr, i2, d, y, ids[m][keep], x)
+            if keep.all():
+                assert np.array_equal(gg[m, :d] != 0, og != 0)
+                assert np.allclose(gg[m, :d], og, rtol=1e-6, atol=1e-30)
+                assert ll[m] == pytest.approx(ol, rel=1e-6)
+            else:                                        # the oracle divides by the rows kept: coefficients
+                # rounded to binary32 after another division, 2^-23 each
+                assert np.allclose(gg[m, :d], og * (keep.sum() / B), rtol=1e-5, atol=1e-6 * np.abs(og).max())
+
+
 @pytest.mark.parametrize("csr,shape", [(False, (400, 3000, 30, 48, 5)), (True, (400, 3000, 30, 48, 5)),
                                        # large batches, heavy collisions on a few columns, a ragged last row group
                                        (True, (600, 5000, 30, 301, 7)), (True, (600, 1500, 20, 256, 8))])
