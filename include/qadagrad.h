@@ -168,7 +168,10 @@ int qa_local_grad_batched(int format, const float* A_or_vals, const int64_t* ind
  * strictly sequential summation.
  * g_stride >= d and a multiple of 4.  ws: qa_workspace_bytes(layout, QA_OP_QUANTIZE), or
  * qa_workspace_bytes(layout, QA_OP_QUANTIZE_EXACT) with QA_THRESH_EXACT (the two agree for
- * buckets of up to 4096 components). */
+ * buckets of up to 4096 components).  Buckets of 2^24 components and more are read once instead of
+ * twice if the workspace has the 8 bytes per worker and 4096 coordinates that this takes, which
+ * QA_OP_QUANTIZE counts; 12 bytes per worker and 4096 coordinates plus 4 per bucket, each array rounded
+ * up to 256, are enough for the call to be accepted. */
 int qa_quantize_pack(const qa_layout* layout, const float* g, int64_t g_stride, uint32_t* codes,
                      float* scales, float* thresholds, uint32_t flags, void* ws, size_t ws_bytes,
                      void* stream);
@@ -179,8 +182,8 @@ int qa_quantize_pack(const qa_layout* layout, const float* g, int64_t g_stride, 
  * counts and thresholds that the multi-pass layouts need (one scale per vector, or buckets above
  * 4096) live in a 4 MiB array in the library's own device image instead.  The call allocates
  * nothing and frees nothing.
- *   - Limit: qa_workspace_bytes(layout, QA_OP_QUANTIZE) <= 4 MiB (QA_STATIC_SCRATCH_BYTES), about
- *     12 bytes per worker and 4096 coordinates: e.g. M * ceil(d/4096) <= 349 000.  Larger
+ *   - Limit: the partial sums fit 4 MiB (QA_STATIC_SCRATCH_BYTES), 12 bytes per worker and 4096
+ *     coordinates: e.g. M * ceil(d/4096) <= 349 000.  Larger
  *     problems return QA_ERR_TOO_LARGE and launch nothing.  Layouts that need no workspace
  *     (bucket <= 4096, or a vector of at most 4096 coordinates) have no limit.  QA_THRESH_EXACT
  *     for buckets longer than 4096 components needs a sort's worth of scratch and is refused

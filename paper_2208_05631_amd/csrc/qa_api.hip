@@ -3,6 +3,7 @@
 
 namespace qa {
 size_t quantize_workspace_bytes(const qa_layout* L);
+size_t one_read_bytes(const qa_layout* L);
 size_t exact_wide_workspace_bytes(const qa_layout* L);
 size_t step_workspace_bytes(const qa_layout* L);
 size_t select_workspace_bytes(const qa_layout* L);
@@ -33,7 +34,7 @@ extern "C" size_t qa_workspace_bytes(const qa_layout* layout, int op) {
     return (size_t)layout->M * grad_workspace_bytes(layout->d, op == QA_OP_GRAD_CSR);
   }
   if (check_layout(layout) != QA_OK) return 0;
-  if (op == QA_OP_QUANTIZE) return quantize_workspace_bytes(layout);
+  if (op == QA_OP_QUANTIZE) return quantize_workspace_bytes(layout) + one_read_bytes(layout);
   if (op == QA_OP_QUANTIZE_EXACT)
     return quantize_workspace_bytes(layout) + exact_wide_workspace_bytes(layout);
   if (op == QA_OP_STEP) return step_workspace_bytes(layout);

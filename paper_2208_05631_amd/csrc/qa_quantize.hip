@@ -7,7 +7,8 @@
 //   bucket <= 4096 : one kernel; sums, threshold, scale and codes of a tile's buckets are
 //                    formed in registers/LDS; the gradient is read once (4 B/elem + 0.25 B out).
 //   bucket  > 4096 or 0 (whole vector): tile partial sums -> finalize threshold -> codes and
-//                    tile partial (count, sum) -> finalize scale; the gradient is read twice.
+//                    tile partial (count, sum) -> finalize scale; the gradient is read twice, or,
+//                    for long buckets, once: a sample brackets the threshold beforehand.
 #include <mutex>
 
 #include "qa_common.h"
@@ -35,6 +36,11 @@ struct QuantArgs {
   int64_t tiles_per_bucket;  // ntiles when bucket == 0
   int64_t nb;
   int64_t bucket_len;        // elements per bucket (d when bucket == 0)
+  // one-read form of the two-pass path
+  double* kept_sum;          // [M][ntiles]; before that the samples' sums
+  float2* band;              // [M][nb]
+  int64_t samples;           // sampled tiles per bucket (at most)
+  int64_t settle_groups;     // work-groups per bucket of the settling pass
 };
 
 // Load the thread's 4 float4 groups of tile `tile`; elements at or beyond d read as +0.
@@ -1084,6 +1090,240 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void quantize_scale_finalize
     a.scales[(int64_t)m * a.scale_stride + k] = scale_from_sum(s, (uint64_t)c);
 }
 
+// ---- long buckets in one read -------------------------------------------------------------------
+//
+// The threshold of a long bucket is known only after all of it has been read, but a sample of its tiles
+// brackets it closely: [lo, hi] from the mean of every 64th tile and the spread between neighbouring
+// samples, five standard errors to either side (0.2 % for 10^8 Gaussian components).  The one pass over
+// the gradient then sums |v| and writes final codes for every component outside the bracket; the few
+// inside (some 6 per 4096) get the bit pattern 10, which no message holds.  When the threshold is known
+// the settling pass reads the codes, looks those components up in the gradient and replaces the
+// pattern.  Exactly the same threshold and codes as the two-read passes; the kept magnitudes are added
+// in another order.
+//
+// Where the sample says nothing (few tiles, a spread above 5 %, non-finite values) or the threshold falls
+// outside its bracket, the settling pass does the second read for that bucket after all; the cost is
+// then the two-read passes' plus the sample (1/64 of a read).
+//
+// Bound by the read of the gradient (6.2 TB/s in the one pass; the settling pass, 0.25 bytes per component and a
+// cache line per open one, takes a seventh of it).  One scale per vector, Gaussian / 10 %-dense
+// Student-t / 5 %-dense Laplace components, two reads -> one: 10^8 x 8 1039 -> 708 / 649 / 635 us;
+// 10^8 x 1 150 -> 111 / 103 / 101; 2^24 x 4 91 -> 76 / 68 / 66; 2^24 x 2 47.5 -> 47.5 / 42 / 41.
+// Below that the two further launches cost more than the second read (2^24 x 1 27.4 -> 31), and buckets
+// of fewer than 4096 tiles give too few samples (2^22: 343 -> 376 at 2^26 x 4 sparse components).
+constexpr int kSampleEvery = 64, kSettleTiles = 8;
+constexpr float kWidestBand = 0.08f;
+
+// Full tiles of bucket k.
+__device__ __forceinline__ int64_t whole_tiles(const QuantArgs& a, int64_t k) {
+  const int64_t t0 = k * a.tiles_per_bucket, all = a.d / kTile - t0;
+  return all < a.tiles_per_bucket ? (all > 0 ? all : 0) : a.tiles_per_bucket;
+}
+
+__global__ __launch_bounds__(kThreads) void quantize_sample_kernel(QuantArgs a) {
+  __shared__ double lds_d[kWaves];
+  const int64_t k = blockIdx.x / a.samples, i = blockIdx.x % a.samples;
+  const int m = blockIdx.y;
+  if (i >= whole_tiles(a, k) / kSampleEvery) return;
+  // one tile of every 64, not always the same one of them
+  const int64_t tile = k * a.tiles_per_bucket + i * kSampleEvery + (i * 29) % kSampleEvery;
+  float v[4][4];
+  load_tile(a.g + (int64_t)m * a.g_stride, a.d, tile, v);
+  double s = 0.0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s += (double)fabsf(v[j][e]);
+  s = block_sum_f64(s, lds_d);
+  if (threadIdx.x == 0) a.kept_sum[((int64_t)m * a.nb + k) * a.samples + i] = s;
+}
+
+__global__ __launch_bounds__(kThreads) QA_FEW_WAVES void quantize_band_kernel(QuantArgs a) {
+  __shared__ double lds_d[kWaves];
+  const int64_t k = blockIdx.x;
+  const int m = blockIdx.y;
+  const double* part = a.kept_sum + ((int64_t)m * a.nb + k) * a.samples;
+  const int64_t n = whole_tiles(a, k) / kSampleEvery;
+  double sum = 0.0, diff = 0.0;
+  for (int64_t i = threadIdx.x; i < n; i += kThreads) {
+    const double v = part[i], w = i + 1 < n ? part[i + 1] : v;
+    sum += v;
+    diff += (w - v) * (w - v);
+  }
+  sum = segment_sum(sum, kThreads, lds_d);
+  diff = segment_sum(diff, kThreads, lds_d);
+  if (threadIdx.x == 0) {
+    float2 band = make_float2(-1.0f, -1.0f);               // no bracket
+    if (n >= 16) {
+      // neighbouring samples differ by two independent deviations; trends along the vector drop out
+      const double mean = sum / (double)n, rel = 5.0 * sqrt(diff / (2.0 * (double)(n - 1)) / (double)n) / mean + 1e-6;
+      const double mid = (double)a.thr_coef * mean / (double)kTile;
+      if (mean > 0.0 && rel < (double)kWidestBand && mid < 1e38)
+        band = make_float2((float)(mid * (1.0 - rel)), (float)(mid * (1.0 + rel)));
+    }
+    a.band[(int64_t)m * a.nb + k] = band;
+  }
+}
+
+// The one pass: tile sums of |v|; with a bracket also codes, sums and counts of what is certainly kept.
+__global__ __launch_bounds__(kThreads) void quantize_bracketed_kernel(QuantArgs a) {
+  __shared__ double lds_s1[kWaves];
+  __shared__ double lds_s2[kWaves];
+  __shared__ uint32_t lds_c[kWaves];
+  const int64_t tile = blockIdx.x;
+  const int m = blockIdx.y;
+  const int t = threadIdx.x;
+  const float2 band = a.band[(int64_t)m * a.nb + tile / a.tiles_per_bucket];
+  float v[4][4];
+  load_tile_stream(a.g + (int64_t)m * a.g_stride, a.d, tile, v);
+  double s1[4], s2[4] = {0.0, 0.0, 0.0, 0.0};
+  uint32_t wave_cnt = 0, mine = 0;
+  const bool bracket = band.x >= 0.0f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    s1[j] = (double)fabsf(v[j][0]);
+#pragma unroll
+    for (int e = 1; e < 4; ++e) s1[j] += (double)fabsf(v[j][e]);
+  }
+  if (bracket) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      uint32_t b = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float av = fabsf(v[j][e]);
+        const bool keep = av > band.y;
+        wave_cnt += (uint32_t)__popcll(__ballot(keep));
+        s2[j] += (double)(keep ? av : 0.0f);
+        const uint32_t pat = 1u | ((__float_as_uint(v[j][e]) >> 30) & 2u);
+        b |= (keep ? pat : (av > band.x ? 2u : 0u)) << (2 * e);
+      }
+      uint32_t w = b << (8 * (t & 3));
+      w |= (uint32_t)dpp_i32<kDppQuadXor1>((int)w);
+      w |= (uint32_t)dpp_i32<kDppQuadXor2>((int)w);
+      if ((t & 3) == j) mine = w;
+    }
+    const int64_t widx = tile * kTileWords + (t & 3) * 64 + (t >> 2);
+    if (widx < a.W) (a.codes + (int64_t)m * a.code_stride)[widx] = mine;
+  }
+  const double S1 = wave_sum_f64((s1[0] + s1[1]) + (s1[2] + s1[3]));
+  const double S2 = wave_sum_f64((s2[0] + s2[1]) + (s2[2] + s2[3]));
+  if (t % kWave == 0) { lds_s1[t / kWave] = S1; lds_s2[t / kWave] = S2; lds_c[t / kWave] = wave_cnt; }
+  __syncthreads();
+  if (t == 0) {
+    const int64_t at = (int64_t)m * a.ntiles + tile;
+    a.part_sum[at] = (lds_s1[0] + lds_s1[1]) + (lds_s1[2] + lds_s1[3]);
+    a.kept_sum[at] = (lds_s2[0] + lds_s2[1]) + (lds_s2[2] + lds_s2[3]);
+    a.part_cnt[at] = lds_c[0] + lds_c[1] + lds_c[2] + lds_c[3];
+  }
+}
+
+// The settling pass: eight tiles per work-group, thread t holds word t of each.  Its sums and counts of all
+// that these tiles keep take the place of the tile sums of |v|, which the threshold has been made of: [M][nb * settle_groups]
+// sums, then as many counts.
+__global__ __launch_bounds__(kThreads) void quantize_settle_kernel(QuantArgs a) {
+  __shared__ double lds_d[kWaves];
+  __shared__ uint32_t lds_u[kWaves];
+  const int64_t k = blockIdx.x / a.settle_groups, part = blockIdx.x % a.settle_groups;
+  const int m = blockIdx.y;
+  const int t = threadIdx.x;
+  const int64_t tile0 = k * a.tiles_per_bucket + part * kSettleTiles;
+  const int64_t bucket_end = (k + 1) * a.tiles_per_bucket < a.ntiles ? (k + 1) * a.tiles_per_bucket : a.ntiles;
+  const int64_t tile1 = tile0 + kSettleTiles < bucket_end ? tile0 + kSettleTiles : bucket_end;
+  const float D = a.thr_ws[(int64_t)m * a.nb + k];
+  const float2 band = a.band[(int64_t)m * a.nb + k];
+  const float* g = a.g + (int64_t)m * a.g_stride;
+  uint32_t* codes = a.codes + (int64_t)m * a.code_stride;
+  double s = 0.0;
+  uint32_t c = 0;
+  if (band.x >= 0.0f && D >= band.x && D <= band.y) {
+    if (t < kSettleTiles && tile0 + t < tile1) {         // what the one pass has kept for certain
+      s = a.kept_sum[(int64_t)m * a.ntiles + tile0 + t];
+      c = a.part_cnt[(int64_t)m * a.ntiles + tile0 + t];
+    }
+    uint32_t w[kSettleTiles], open[kSettleTiles], any = 0;
+#pragma unroll
+    for (int u = 0; u < kSettleTiles; ++u) {
+      const int64_t widx = (tile0 + u) * kTileWords + t;
+      w[u] = tile0 + u < tile1 && widx < a.W ? codes[widx] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < kSettleTiles; ++u) {
+      open[u] = (w[u] >> 1) & ~w[u] & 0x55555555u;       // low bit of every field 10
+      any |= open[u];
+    }
+    const bool touched = any != 0;
+    while (__any(any != 0)) {                            // one field of every word at a time
+      float x[kSettleTiles];
+      int at[kSettleTiles];
+      any = 0;
+#pragma unroll
+      for (int u = 0; u < kSettleTiles; ++u) {
+        at[u] = open[u] ? __ffs((int)open[u]) - 1 : -1;
+        x[u] = at[u] >= 0 ? g[(tile0 + u) * kTile + 16 * t + (at[u] >> 1)] : 0.0f;
+      }
+#pragma unroll
+      for (int u = 0; u < kSettleTiles; ++u)
+        if (at[u] >= 0) {
+          const float av = fabsf(x[u]);
+          const bool keep = av > D;
+          s += keep ? (double)av : 0.0;
+          c += keep ? 1u : 0u;
+          w[u] = (w[u] & ~(3u << at[u])) | (ternary_field(x[u], D) << at[u]);
+          open[u] &= open[u] - 1u;
+          any |= open[u];
+        }
+    }
+    if (touched) {
+#pragma unroll
+      for (int u = 0; u < kSettleTiles; ++u) {
+        const int64_t widx = (tile0 + u) * kTileWords + t;
+        if (tile0 + u < tile1 && widx < a.W) codes[widx] = w[u];
+      }
+    }
+  } else {
+    for (int64_t tile = tile0; tile < tile1; ++tile) {
+      float v[4][4];
+      load_tile_stream(g, a.d, tile, v);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        double sj; uint32_t cj;
+        kept_sums(v[j], D, &sj, &cj);
+        s += sj; c += cj;
+      }
+      const float Delta[4] = {D, D, D, D};
+      pack_and_store(v, Delta, codes, tile, a.W);
+    }
+  }
+  s = wave_sum_f64(s);
+  c = wave_sum_u32(c);
+  if (t % kWave == 0) { lds_d[t / kWave] = s; lds_u[t / kWave] = c; }
+  __syncthreads();
+  if (t == 0) {
+    const int64_t groups = a.nb * a.settle_groups, at = (int64_t)m * groups + blockIdx.x;
+    a.part_sum[at] = (lds_d[0] + lds_d[1]) + (lds_d[2] + lds_d[3]);
+    reinterpret_cast<uint32_t*>(a.part_sum + gridDim.y * groups)[at] = lds_u[0] + lds_u[1] + lds_u[2] + lds_u[3];
+  }
+}
+
+__global__ __launch_bounds__(kThreads) QA_FEW_WAVES void quantize_settled_scale_kernel(QuantArgs a) {
+  __shared__ double lds_d[kWaves];
+  __shared__ double lds_c[kWaves];
+  const int64_t k = blockIdx.x;
+  const int m = blockIdx.y;
+  const int64_t t0 = k * a.tiles_per_bucket;
+  const int64_t t1 = (t0 + a.tiles_per_bucket) < a.ntiles ? (t0 + a.tiles_per_bucket) : a.ntiles;
+  const int64_t groups = a.nb * a.settle_groups, g0 = k * a.settle_groups;
+  const int64_t g1 = g0 + (t1 - t0 + kSettleTiles - 1) / kSettleTiles;
+  const uint32_t* settled_cnt = reinterpret_cast<const uint32_t*>(a.part_sum + gridDim.y * groups);
+  double s, c;
+  strided_partial_sums(a.part_sum + (int64_t)m * groups, settled_cnt + (int64_t)m * groups, g0, g1, &s, &c);
+  s = segment_sum(s, kThreads, lds_d);
+  c = segment_sum(c, kThreads, lds_c);
+  if (threadIdx.x == 0)
+    a.scales[(int64_t)m * a.scale_stride + k] = scale_from_sum(s, (uint64_t)c);
+}
+
 // ---- stochastic ternary quantizer (TernGrad: max-norm scale, keep probability |v|/s) ----------
 //
 // Uniform numbers: Philox4x32-10 keyed by the 64-bit seed, counter (j low, j high, worker, step)
@@ -1292,6 +1532,16 @@ size_t quantize_workspace_bytes(const qa_layout* L) {
          align256((size_t)L->M * nb * sizeof(float));
 }
 
+// What the one-read form needs on top of it, 0 where it is not taken: buckets of fewer than 4096 tiles
+// (64 samples), or less than 2^25 components in all.
+constexpr int64_t kOneReadBucketTiles = 4096, kOneReadTiles = 8192;
+size_t one_read_bytes(const qa_layout* L) {
+  const int64_t nt = tiles_of(L->d), nb = buckets_of(L->d, L->bucket);
+  const int64_t per = L->bucket ? L->bucket / kTile : nt;
+  if (per < kOneReadBucketTiles || nt < kOneReadBucketTiles || nt * L->M < kOneReadTiles) return 0;
+  return align256((size_t)L->M * nt * sizeof(double)) + align256((size_t)L->M * nb * sizeof(float2));
+}
+
 // Where the multi-pass quantizer keeps its per-tile sums, counts and per-bucket thresholds inside
 // its workspace (all worker-major).
 void quantize_workspace_parts(const qa_layout* L, void* ws, double** part_sum, uint32_t** part_cnt,
@@ -1393,6 +1643,25 @@ int quantize_launch(const qa_layout* L, const float* g, int64_t g_stride, uint32
   a.log2b = L->bucket ? ilog2(L->bucket) : 0;
   const dim3 grid_buckets((unsigned)a.nb, (unsigned)L->M);
 
+  if (!a.thresh_given && !(flags & kQuantAbsPartialsGiven) && one_read_bytes(L) != 0 &&
+      ws_bytes >= need + one_read_bytes(L)) {
+    char* p = static_cast<char*>(ws) + need;
+    a.kept_sum = reinterpret_cast<double*>(p);
+    a.band = reinterpret_cast<float2*>(p + align256((size_t)L->M * a.ntiles * sizeof(double)));
+    a.samples = a.tiles_per_bucket / kSampleEvery;
+    a.settle_groups = (a.tiles_per_bucket + kSettleTiles - 1) / kSettleTiles;
+    if (a.nb * a.samples <= 0x7fffffffLL && a.nb * a.settle_groups <= 0x7fffffffLL) {
+      const dim3 grid_samples((unsigned)(a.nb * a.samples), (unsigned)L->M);
+      const dim3 grid_settle((unsigned)(a.nb * a.settle_groups), (unsigned)L->M);
+      hipLaunchKernelGGL(quantize_sample_kernel, grid_samples, block, 0, stream, a);
+      hipLaunchKernelGGL(quantize_band_kernel, grid_buckets, block, 0, stream, a);
+      hipLaunchKernelGGL(quantize_bracketed_kernel, grid_tiles, block, 0, stream, a);
+      hipLaunchKernelGGL(quantize_threshold_finalize_kernel, grid_buckets, block, 0, stream, a);
+      hipLaunchKernelGGL(quantize_settle_kernel, grid_settle, block, 0, stream, a);
+      hipLaunchKernelGGL(quantize_settled_scale_kernel, grid_buckets, block, 0, stream, a);
+      return launch_status();
+    }
+  }
   if (!a.thresh_given) {
     if (!(flags & kQuantAbsPartialsGiven))
       hipLaunchKernelGGL(quantize_abs_partial_kernel, grid_tiles, block, 0, stream, a);

@@ -703,6 +703,67 @@ def test_aggregate_quantize_checks_its_arguments():
     assert e.value.code == -1
 
 
+def one_read_gradient(kind, d, rng):
+    g = (rng.standard_normal(d) * 1e-2).astype(np.float32)
+    tile = np.arange(d) // 4096
+    if kind == "sparse":
+        g *= rng.random(d) < 0.05
+    elif kind == "trend":                               # magnitudes grow along the vector
+        g *= (1.0 + 3.0 * np.arange(d, dtype=np.float32) / d)
+    elif kind == "sample misleads":                     # the tiles that are sampled are ten times smaller
+        at = (tile // 64 * 64 + (tile // 64 * 29) % 64 == tile)
+        g[at] *= np.float32(0.1)
+    elif kind == "sample empty":
+        g[(tile // 64 * 64 + (tile // 64 * 29) % 64 == tile)] = 0
+    elif kind == "crowd at the threshold":              # a third of the components within 1e-3 of it
+        near = rng.random(d) < 0.33
+        mean = np.abs(g[~near]).mean(dtype=np.float64)
+        # mean of the mixture m = 0.67 mean + 0.33 * 0.75 m
+        delta = 0.75 * 0.67 * mean / (1 - 0.33 * 0.75)
+        g[near] = (delta * (1 + 1e-3 * rng.uniform(-1, 1, int(near.sum())))).astype(np.float32)
+        g *= np.where(rng.random(d) < 0.5, -1, 1).astype(np.float32)
+    elif kind == "zero":
+        g[:] = 0
+    elif kind == "nan":
+        g[d // 2] = np.nan
+    return g
+
+
+@pytest.mark.parametrize("kinds,d,bucket", [(("gauss", "sparse"), (1 << 24) + 12345, 0),
+                                            (("trend", "sample misleads"), 1 << 24, 0),
+                                            (("sample empty", "crowd at the threshold"), (1 << 24) + 1, 0),
+                                            (("zero", "nan", "gauss"), (1 << 24) + 4095, 0),
+                                            (("gauss",), (1 << 25) + (1 << 23) + 77, 1 << 24)])
+def test_quantizer_of_long_buckets_matches_oracle(kinds, d, bucket):
+    """Buckets long enough for the form that reads the gradient once (2^24 components, 2^25 in all): where the
+    sample brackets the threshold, where it does not, and in an incomplete last bucket; with the smaller
+    workspace of the two-read form the message is the same."""
+    rng = np.random.default_rng(d % 1000 + len(kinds))
+    g = np.stack([one_read_gradient(k, d, rng) for k in kinds])
+    M = len(kinds)
+    c_ref, s_ref, t_ref = oracle.quantize_pack(g, bucket=bucket)
+    c, s, th, L = gpu_quantize_pack(g, bucket)
+    nb = L.n_buckets
+    same = np.isnan(t_ref) | (ulp_distance(np.nan_to_num(th[:, :nb]), np.nan_to_num(t_ref)) <= 1)
+    assert same.all()
+    assert np.array_equal(np.isnan(th[:, :nb]), np.isnan(t_ref))
+    assert int(ulp_distance(s[:, :nb], s_ref).max()) <= 1
+    if np.array_equal(np.nan_to_num(th[:, :nb]), np.nan_to_num(t_ref)):
+        assert np.array_equal(c[:, :L.words], c_ref)
+    else:                                               # a threshold's last bit (2^-29 each): codes for the GPU's own
+        assert np.array_equal(c[:, :L.words], oracle.quantize_pack(g, bucket=bucket, thresholds=th[:, :nb])[0])
+    gs = (d + 3) // 4 * 4
+    gp = np.zeros((M, gs), np.float32); gp[:, :d] = g
+    small = workspace(M * ((d + 4095) // 4096) * 12 + M * nb * 4 + 768)
+    assert small.numel() < qa.qa_workspace_bytes(L, qa.QA_OP_QUANTIZE)
+    codes = torch.full((M, L.code_stride), -1, dtype=torch.int32, device=DEV)
+    scales = torch.zeros((M, L.scale_stride), dtype=torch.float32, device=DEV)
+    qa.qa_quantize_pack(L, dev(gp), gs, codes, scales, None, 0, small)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(codes).view(np.uint32)[:, :L.words], c[:, :L.words])
+    assert int(ulp_distance(host(scales)[:, :nb], s[:, :nb]).max()) <= 1
+
+
 # ---- exact least-squares threshold by ranking (Section 3.4) ------------------------------------
 
 @pytest.mark.parametrize("d,M,bucket", [(4096, 1, 0), (1000, 2, 0), (3, 1, 0), (4096 * 5, 3, 4096),
