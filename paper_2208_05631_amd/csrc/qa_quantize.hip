@@ -114,78 +114,103 @@ __device__ __forceinline__ void kept_sums(const float v[4], float Delta, double*
 //
 // Slice j of the tile (elements j*1024 .. j*1024+1023) is held four elements per thread, so a
 // bucket of b <= 1024 elements is SEG = b/4 consecutive threads of one slice, and a bucket of 2048
-// is two whole slices.  Sums over 16 lanes use DPP, 32 and 64 lanes one more cross-row step, and
-// larger segments one LDS exchange for all four slices at once: no barrier for b <= 256, one per
-// phase otherwise.  Every thread receives the sums of its own buckets.
-template <int SEG>
-__device__ __forceinline__ double lanes_sum_f64(double v) {
-  v += dpp_f64<kDppQuadXor1>(v);
-  v += dpp_f64<kDppQuadXor2>(v);
-  v += dpp_f64<kDppRowHalfMirror>(v);
-  v += dpp_f64<kDppRowMirror>(v);                        // sum of the row of 16
-  if (SEG == 32) v += shfl_xor_f64(v, 16);
-  if (SEG >= 64)
-    v = (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
+// is two whole slices.  The four slices are summed together: the first two exchanges (lanes l^1,
+// l^2) leave lane l with the part of slice l & 3, the others run on one value instead of four.
+// Every exchange adds the same two operands in both lanes, so all lanes of a bucket hold the same
+// sum.  Threshold, scale and their divisions are likewise formed once, slice l & 3's in lane l.
+__device__ __forceinline__ double lanes_xor4_f64(double v) {
+  return dpp_f64<0x1B>(dpp_f64<kDppRowHalfMirror>(v));   // l^7, then l^3
+}
+__device__ __forceinline__ uint32_t lanes_xor4_u32(uint32_t v) {
+  return (uint32_t)dpp_i32<0x1B>(dpp_i32<kDppRowHalfMirror>((int)v));
+}
+constexpr int kDppRowRor8 = 0x128;                       // l^8 within the row of 16
+// v of the even row plus v of the odd row (ROWS = 16), of the lower half plus of the upper (32)
+template <int ROWS>
+__device__ __forceinline__ void swap_rows(uint32_t v, uint32_t* a, uint32_t* b) {
+  const auto r = ROWS == 16 ? __builtin_amdgcn_permlane16_swap(v, v, false, false)
+                            : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  *a = r[0]; *b = r[1];
+}
+template <int ROWS> __device__ __forceinline__ double add_rows_f64(double v) {
+  uint32_t al, bl, ah, bh;
+  swap_rows<ROWS>((uint32_t)__double2loint(v), &al, &bl);
+  swap_rows<ROWS>((uint32_t)__double2hiint(v), &ah, &bh);
+  return __hiloint2double((int)ah, (int)al) + __hiloint2double((int)bh, (int)bl);
+}
+template <int ROWS> __device__ __forceinline__ uint32_t add_rows_u32(uint32_t v) {
+  uint32_t a, b;
+  swap_rows<ROWS>(v, &a, &b);
+  return a + b;
+}
+
+// s[j]: this thread's part of slice j -> for slice l & 3, the sum over LANES lanes of the wave
+template <int LANES>
+__device__ __forceinline__ double slices_sum_f64(const double s[4]) {
+  const bool odd = threadIdx.x & 1, high = threadIdx.x & 2;
+  const double a = (odd ? s[1] : s[0]) + dpp_f64<kDppQuadXor1>(odd ? s[0] : s[1]);
+  const double b = (odd ? s[3] : s[2]) + dpp_f64<kDppQuadXor1>(odd ? s[2] : s[3]);
+  double v = (high ? b : a) + dpp_f64<kDppQuadXor2>(high ? a : b);
+  v += lanes_xor4_f64(v);
+  v += dpp_f64<kDppRowRor8>(v);
+  if (LANES >= 32) v = add_rows_f64<16>(v);
+  if (LANES >= 64) v = add_rows_f64<32>(v);
   return v;
 }
-template <int SEG>
-__device__ __forceinline__ uint32_t lanes_sum_u32(uint32_t v) {
-  v += (uint32_t)dpp_i32<kDppQuadXor1>((int)v);
-  v += (uint32_t)dpp_i32<kDppQuadXor2>((int)v);
-  v += (uint32_t)dpp_i32<kDppRowHalfMirror>((int)v);
-  v += (uint32_t)dpp_i32<kDppRowMirror>((int)v);
-  if (SEG == 32) v += (uint32_t)__shfl_xor((int)v, 16, kWave);
-  if (SEG >= 64)
-    v = (uint32_t)__builtin_amdgcn_readlane((int)v, 0) + (uint32_t)__builtin_amdgcn_readlane((int)v, 16) +
-        (uint32_t)__builtin_amdgcn_readlane((int)v, 32) + (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
+template <int LANES>
+__device__ __forceinline__ uint32_t slices_sum_u32(const uint32_t c[4]) {
+  const bool odd = threadIdx.x & 1, high = threadIdx.x & 2;
+  const uint32_t a = (odd ? c[1] : c[0]) + (uint32_t)dpp_i32<kDppQuadXor1>((int)(odd ? c[0] : c[1]));
+  const uint32_t b = (odd ? c[3] : c[2]) + (uint32_t)dpp_i32<kDppQuadXor1>((int)(odd ? c[2] : c[3]));
+  uint32_t v = (high ? b : a) + (uint32_t)dpp_i32<kDppQuadXor2>((int)(high ? a : b));
+  v += lanes_xor4_u32(v);
+  v += (uint32_t)dpp_i32<kDppRowRor8>((int)v);
+  if (LANES >= 32) v = add_rows_u32<16>(v);
+  if (LANES >= 64) v = add_rows_u32<32>(v);
   return v;
 }
 
-// s[j], c[j]: this thread's part of slice j -> the sums over its bucket.  LOG2B = log2(bucket).
-// lds: 16 doubles and 16 words nobody else uses; the caller's threads all take part.
+// The sums over the buckets that hold this thread's part of slice l & 3.  lds_*: 16 entries each that
+// nobody else uses; the work-group's threads all take part (barriers for buckets above 256).
 template <int LOG2B, bool WITH_COUNT>
-__device__ __forceinline__ void bucket_sums(double s[4], uint32_t c[4], double* lds_s, uint32_t* lds_c) {
+__device__ __forceinline__ void bucket_sums(const double s[4], const uint32_t c[4], double* lds_s, uint32_t* lds_c,
+                                            double* sum, uint32_t* count) {
   constexpr int SEG = LOG2B >= 10 ? 256 : (1 << LOG2B) / 4;     // threads per bucket within a slice
   constexpr int LANES = SEG < 64 ? SEG : 64;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    s[j] = lanes_sum_f64<LANES>(s[j]);
-    if (WITH_COUNT) c[j] = lanes_sum_u32<LANES>(c[j]);
-  }
-  if (SEG > 64) {
-    const int wave = threadIdx.x / kWave;
+  *sum = slices_sum_f64<LANES>(s);
+  if (WITH_COUNT) *count = slices_sum_u32<LANES>(c);
+  if constexpr (SEG > 64) {
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, j = lane & 3;
     __syncthreads();                                     // earlier readers of lds are done
-    if ((threadIdx.x % kWave) == 0) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        lds_s[j * kWaves + wave] = s[j];
-        if (WITH_COUNT) lds_c[j * kWaves + wave] = c[j];
-      }
+    if (lane < 4) {
+      lds_s[j * kWaves + wave] = *sum;
+      if (WITH_COUNT) lds_c[j * kWaves + wave] = *count;
     }
     __syncthreads();
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (SEG == 128) {                                  // waves {0,1} and {2,3}
-        const int w0 = wave & ~1;
-        s[j] = lds_s[j * kWaves + w0] + lds_s[j * kWaves + w0 + 1];
-        if (WITH_COUNT) c[j] = lds_c[j * kWaves + w0] + lds_c[j * kWaves + w0 + 1];
-      } else {
-        s[j] = (lds_s[j * kWaves] + lds_s[j * kWaves + 1]) + (lds_s[j * kWaves + 2] + lds_s[j * kWaves + 3]);
-        if (WITH_COUNT)
-          c[j] = lds_c[j * kWaves] + lds_c[j * kWaves + 1] + lds_c[j * kWaves + 2] + lds_c[j * kWaves + 3];
-      }
-    }
+    const auto waves_of = [&](int q) {                   // slice q over the waves of the bucket
+      const int w0 = SEG == 128 ? wave & ~1 : 0;
+      const double pair = lds_s[q * kWaves + w0] + lds_s[q * kWaves + w0 + 1];
+      return SEG == 128 ? pair : pair + (lds_s[q * kWaves + 2] + lds_s[q * kWaves + 3]);
+    };
+    const auto counts_of = [&](int q) {
+      const int w0 = SEG == 128 ? wave & ~1 : 0;
+      const uint32_t pair = lds_c[q * kWaves + w0] + lds_c[q * kWaves + w0 + 1];
+      return SEG == 128 ? pair : pair + lds_c[q * kWaves + 2] + lds_c[q * kWaves + 3];
+    };
     if (LOG2B == 11) {                                   // a bucket is two slices
-      const double s01 = s[0] + s[1], s23 = s[2] + s[3];
-      s[0] = s[1] = s01; s[2] = s[3] = s23;
-      if (WITH_COUNT) {
-        const uint32_t c01 = c[0] + c[1], c23 = c[2] + c[3];
-        c[0] = c[1] = c01; c[2] = c[3] = c23;
-      }
+      *sum = waves_of(j & ~1) + waves_of(j | 1);
+      if (WITH_COUNT) *count = counts_of(j & ~1) + counts_of(j | 1);
+    } else {
+      *sum = waves_of(j);
+      if (WITH_COUNT) *count = counts_of(j);
     }
   }
 }
 
+// Bound by the read of the gradient; with four sums per slice, four thresholds and a division per slice
+// and barrier it was bound by vector instructions (693 per wave and tile).  2^26 x 4 Gaussian components:
+// buckets of 64 269 -> 216 us, 128 256 -> 195, 256 264 -> 192, 512 262 -> 193, 1024 265 -> 190, 2048 274 -> 191
+// (4096, its own kernel: 180); 50 000 017 x 5, 256: 292 -> 217.
 template <int LOG2B>
 __device__ __forceinline__ void quantize_buckets_of_tile(const QuantArgs& a, int64_t tile, int m) {
   __shared__ double lds_s[4 * kWaves];
@@ -196,61 +221,48 @@ __device__ __forceinline__ void quantize_buckets_of_tile(const QuantArgs& a, int
   const bool whole = (tile + 1) * kTile <= a.d;          // the vector does not end inside the tile
 
   float v[4][4];
-  if (whole) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      typedef float floatx4 __attribute__((ext_vector_type(4)));
-      const floatx4 q = __builtin_nontemporal_load(
-          reinterpret_cast<const floatx4*>(g + tile * kTile + (j * kThreads + t) * 4));
-      v[j][0] = q.x; v[j][1] = q.y; v[j][2] = q.z; v[j][3] = q.w;
-    }
-  } else {
-    load_tile(g, a.d, tile, v);
-  }
-  float Delta[4];
-  const int64_t k0 = tile * (kTile >> LOG2B);            // first bucket of the tile
-  int kb[4];                                             // bucket of slice j within the tile
-#pragma unroll
-  for (int j = 0; j < 4; ++j) kb[j] = ((j * kThreads + t) * 4) >> LOG2B;
-
+  load_tile_stream(g, a.d, tile, v);
+  // this lane's bucket among the tile's: the one with its elements of slice l & 3
+  const int kb = (((t & 3) * kThreads + t) * 4) >> LOG2B;
+  const int64_t k = tile * (kTile >> LOG2B) + kb;
+  float mine_delta;                                      // of that bucket
   if (!a.thresh_given) {
-    double S1[4];
-    uint32_t unused[4] = {0u, 0u, 0u, 0u};
+    double S1[4], sum;
+    const uint32_t none[4] = {0u, 0u, 0u, 0u};
+    uint32_t unused;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       S1[j] = (double)fabsf(v[j][0]);
 #pragma unroll
       for (int e = 1; e < 4; ++e) S1[j] += (double)fabsf(v[j][e]);
     }
-    bucket_sums<LOG2B, false>(S1, unused, lds_s, lds_c);
+    bucket_sums<LOG2B, false>(S1, none, lds_s, lds_c, &sum, &unused);
     // Every bucket of the tile is complete unless the vector ends inside the tile; dividing by
     // the power of two b is then an exact scaling, the same value as the division.
     if (whole) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        Delta[j] = (float)(((double)a.thr_coef * S1[j]) * (1.0 / (double)b));
+      mine_delta = (float)(((double)a.thr_coef * sum) * (1.0 / (double)b));
     } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int64_t lo = (k0 + kb[j]) << LOG2B;
-        const int64_t n = (a.d - lo) < (int64_t)b ? (a.d - lo) : (int64_t)b;   // true length
-        Delta[j] = n > 0 ? threshold_from_sum(S1[j], a.thr_coef, n) : 0.0f;
-      }
+      const int64_t lo = k << LOG2B;
+      const int64_t n = (a.d - lo) < (int64_t)b ? (a.d - lo) : (int64_t)b;   // true length
+      mine_delta = n > 0 ? threshold_from_sum(sum, a.thr_coef, n) : 0.0f;
     }
   } else {
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      Delta[j] = k0 + kb[j] < a.nb ? a.thresholds[(int64_t)m * a.scale_stride + k0 + kb[j]] : 0.0f;
+    mine_delta = k < a.nb ? a.thresholds[(int64_t)m * a.scale_stride + k] : 0.0f;
   }
+  float Delta[4];                                        // lane j of every quad has slice j's
+  Delta[0] = __int_as_float(dpp_i32<0x00>(__float_as_int(mine_delta)));
+  Delta[1] = __int_as_float(dpp_i32<0x55>(__float_as_int(mine_delta)));
+  Delta[2] = __int_as_float(dpp_i32<0xAA>(__float_as_int(mine_delta)));
+  Delta[3] = __int_as_float(dpp_i32<0xFF>(__float_as_int(mine_delta)));
 
   // kept sums, counts and 2-bit fields; for Delta >= 0 the field of a kept element is
   // 01 | sign << 1, a negative (given) threshold takes the two plain comparisons
+  const bool plain = __any(mine_delta < 0.0f);
   double S2[4];
   uint32_t C[4];
   uint32_t mine = 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const bool plain = Delta[j] < 0.0f;
     double s2 = 0.0;
     uint32_t c = 0, bits = 0;
 #pragma unroll
@@ -260,8 +272,12 @@ __device__ __forceinline__ void quantize_buckets_of_tile(const QuantArgs& a, int
       s2 += (double)(keep ? av : 0.0f);
       c += keep ? 1u : 0u;
       const uint32_t pat = 1u | ((__float_as_uint(v[j][e]) >> 30) & 2u);
-      const uint32_t f = plain ? ternary_field(v[j][e], Delta[j]) : (keep ? pat : 0u);
-      bits |= f << (2 * e);
+      bits |= (keep ? pat : 0u) << (2 * e);
+    }
+    if (plain) {
+      bits = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bits |= ternary_field(v[j][e], Delta[j]) << (2 * e);
     }
     S2[j] = s2; C[j] = c;
     uint32_t w = bits << (8 * (t & 3));
@@ -273,29 +289,15 @@ __device__ __forceinline__ void quantize_buckets_of_tile(const QuantArgs& a, int
     const int64_t widx = tile * kTileWords + (t & 3) * 64 + (t >> 2);
     if (widx < a.W) (a.codes + (int64_t)m * a.code_stride)[widx] = mine;
   }
-  bucket_sums<LOG2B, true>(S2, C, lds_s, lds_c);
-
-  // The thread holding a bucket's first element hands (sum, count, threshold) of the bucket to
-  // LDS; thread k of the work-group then divides for bucket k of the tile, so that a wave runs
-  // the binary64 division once instead of once per slice.
-  constexpr int kBucketsPerTile = kTile >> LOG2B;
-  __shared__ double out_s[kBucketsPerTile];
-  __shared__ uint32_t out_c[kBucketsPerTile];
-  __shared__ float out_d[kBucketsPerTile];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int e0 = (j * kThreads + t) * 4;               // first element of this thread in slice j
-    if ((e0 & (b - 1)) == 0) {
-      out_s[e0 >> LOG2B] = S2[j]; out_c[e0 >> LOG2B] = C[j]; out_d[e0 >> LOG2B] = Delta[j];
-    }
-  }
-  __syncthreads();
-  if (t < kBucketsPerTile) {
-    const int64_t k = tile * kBucketsPerTile + t;
-    if (k < a.nb) {
-      a.scales[(int64_t)m * a.scale_stride + k] = scale_from_sum(out_s[t], out_c[t]);
-      if (a.thresholds && !a.thresh_given) a.thresholds[(int64_t)m * a.scale_stride + k] = out_d[t];
-    }
+  double sum;
+  uint32_t count;
+  bucket_sums<LOG2B, true>(S2, C, lds_s, lds_c, &sum, &count);
+  // the quad with the bucket's first element writes (of a bucket of two slices, the first one's lane)
+  constexpr int SEG = LOG2B >= 10 ? 256 : b / 4;
+  const bool writes = (t & (SEG - 1)) < 4 && (LOG2B < 11 || (t & 1) == 0);
+  if (writes && k < a.nb) {
+    a.scales[(int64_t)m * a.scale_stride + k] = scale_from_sum(sum, count);
+    if (a.thresholds && !a.thresh_given) a.thresholds[(int64_t)m * a.scale_stride + k] = mine_delta;
   }
 }
 
