@@ -12,6 +12,7 @@
 #include <mutex>
 
 #include "qa_common.h"
+#include "qa_settle.h"
 
 namespace qa {
 
@@ -1113,7 +1114,7 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void quantize_scale_finalize
 // 10^8 x 1 150 -> 111 / 103 / 101; 2^24 x 4 91 -> 76 / 68 / 66; 2^24 x 2 47.5 -> 47.5 / 42 / 41.
 // Below that the two further launches cost more than the second read (2^24 x 1 27.4 -> 31), and buckets
 // of fewer than 4096 tiles give too few samples (2^22: 343 -> 376 at 2^26 x 4 sparse components).
-constexpr int kSampleEvery = 64, kSettleTiles = 8;
+constexpr int kSampleEvery = 64;
 constexpr float kWidestBand = 0.08f;
 
 // Full tiles of bucket k.
@@ -1224,6 +1225,7 @@ __global__ __launch_bounds__(kThreads) void quantize_bracketed_kernel(QuantArgs 
 // that these tiles keep take the place of the tile sums of |v|, which the threshold has been made of: [M][nb * settle_groups]
 // sums, then as many counts.
 __global__ __launch_bounds__(kThreads) void quantize_settle_kernel(QuantArgs a) {
+  __shared__ SettleLds lds;
   __shared__ double lds_d[kWaves];
   __shared__ uint32_t lds_u[kWaves];
   const int64_t k = blockIdx.x / a.settle_groups, part = blockIdx.x % a.settle_groups;
@@ -1243,40 +1245,13 @@ __global__ __launch_bounds__(kThreads) void quantize_settle_kernel(QuantArgs a) 
       s = a.kept_sum[(int64_t)m * a.ntiles + tile0 + t];
       c = a.part_cnt[(int64_t)m * a.ntiles + tile0 + t];
     }
-    uint32_t w[kSettleTiles], open[kSettleTiles], any = 0;
+    uint32_t w[kSettleTiles];
 #pragma unroll
     for (int u = 0; u < kSettleTiles; ++u) {
       const int64_t widx = (tile0 + u) * kTileWords + t;
       w[u] = tile0 + u < tile1 && widx < a.W ? codes[widx] : 0u;
     }
-#pragma unroll
-    for (int u = 0; u < kSettleTiles; ++u) {
-      open[u] = (w[u] >> 1) & ~w[u] & 0x55555555u;       // low bit of every field 10
-      any |= open[u];
-    }
-    const bool touched = any != 0;
-    while (__any(any != 0)) {                            // one field of every word at a time
-      float x[kSettleTiles];
-      int at[kSettleTiles];
-      any = 0;
-#pragma unroll
-      for (int u = 0; u < kSettleTiles; ++u) {
-        at[u] = open[u] ? __ffs((int)open[u]) - 1 : -1;
-        x[u] = at[u] >= 0 ? g[(tile0 + u) * kTile + 16 * t + (at[u] >> 1)] : 0.0f;
-      }
-#pragma unroll
-      for (int u = 0; u < kSettleTiles; ++u)
-        if (at[u] >= 0) {
-          const float av = fabsf(x[u]);
-          const bool keep = av > D;
-          s += keep ? (double)av : 0.0;
-          c += keep ? 1u : 0u;
-          w[u] = (w[u] & ~(3u << at[u])) | (ternary_field(x[u], D) << at[u]);
-          open[u] &= open[u] - 1u;
-          any |= open[u];
-        }
-    }
-    if (touched) {
+    if (settle_words(g, tile0, D, w, lds, s, c)) {
 #pragma unroll
       for (int u = 0; u < kSettleTiles; ++u) {
         const int64_t widx = (tile0 + u) * kTileWords + t;

@@ -83,5 +83,10 @@ size_t quantize_segments_workspace_bytes(const qa_segment_plan* P, int M);
 int quantize_segments_launch(const qa_layout* L, const qa_segment_plan* P, const float* g,
                              int64_t g_stride, uint32_t* codes, float* scales, float* thresholds,
                              void* ws, size_t ws_bytes, hipStream_t stream);
+size_t segments_one_read_bytes(const qa_segment_plan* P, int M);
+void segments_workspace_parts(const qa_layout* L, const qa_segment_plan* P, void* ws, double** part_sum,
+                              uint32_t** part_cnt, float** thr);
+void segments_finalize_launch(const qa_layout* L, const qa_segment_plan* P, int which, float* scales, void* ws,
+                              hipStream_t stream);
 
 }  // namespace qa

@@ -4,10 +4,12 @@
 // Work-group = one piece (tile x tensor intersection) of one worker.  Four passes, as for a
 // bucket larger than a tile: piece sums of |v| -> threshold per tensor -> codes and piece
 // (sum, count) of the kept magnitudes -> scale per tensor.  Partial results are combined in a
-// fixed order in binary64, so the result does not depend on scheduling.
+// fixed order in binary64, so the result does not depend on scheduling.  Large lists read the long
+// tensors' gradients once (see the passes around seg_bracketed_kernel).
 #include <vector>
 
 #include "qa_segments.h"
+#include "qa_settle.h"
 
 namespace qa {
 
@@ -25,6 +27,9 @@ struct SegQuantArgs {
   uint32_t* part_cnt;       // [M][n_pieces]
   float* thr_ws;            // [M][n_seg]
   SegTable seg;
+  // one-read form, null without it
+  double* kept_sum;         // [M][n_pieces]; before that the samples
+  float2* band;             // [M][n_seg]
 };
 
 // The thread's 4 float4 groups f = j*256 + t of the piece's tile; elements outside [lo, hi)
@@ -32,13 +37,21 @@ struct SegQuantArgs {
 __device__ __forceinline__ void load_piece_values(const float* __restrict__ g, const Piece& pc,
                                                   float v[4][4]) {
   const int64_t base = pc.tile * kTile;
+  // streaming: the passes over the gradients read an element once each, a whole pass apart
+  typedef float floatx4 __attribute__((ext_vector_type(4)));
+  if (pc.hi - pc.lo == kTile) {                          // uniform: nothing to test per lane
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const floatx4 q = __builtin_nontemporal_load(
+          reinterpret_cast<const floatx4*>(g + base + (int64_t)(j * kThreads + (int)threadIdx.x) * 4));
+      v[j][0] = q.x; v[j][1] = q.y; v[j][2] = q.z; v[j][3] = q.w;
+    }
+    return;
+  }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int64_t i = base + (int64_t)(j * kThreads + (int)threadIdx.x) * 4;
     if (i >= pc.lo && i + 3 < pc.hi) {
-      // streaming: each of the two passes over the gradients reads an element once, a whole
-      // pass apart
-      typedef float floatx4 __attribute__((ext_vector_type(4)));
       const floatx4 q = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g + i));
       v[j][0] = q.x; v[j][1] = q.y; v[j][2] = q.z; v[j][3] = q.w;
     } else {
@@ -88,14 +101,10 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void seg_threshold_finalize_
   }
 }
 
-__global__ __launch_bounds__(kThreads) void seg_codes_partial_kernel(SegQuantArgs a) {
-  __shared__ double lds_d[kWaves];
-  __shared__ uint32_t lds_u[kWaves];
+// Codes of piece p of worker m for threshold D, and what they keep to the piece's slots.
+__device__ __forceinline__ void code_piece(const SegQuantArgs& a, const Piece& pc, int64_t p, int m, float D,
+                                           double* lds_d, uint32_t* lds_u) {
   const int t = threadIdx.x;
-  const int64_t p = blockIdx.x;
-  const int m = blockIdx.y;
-  const Piece pc = load_piece(a.seg, p, a.d);
-  const float D = a.thr_ws[(int64_t)m * a.seg.n_seg + pc.seg];
   float v[4][4];
   load_piece_values(a.g + (int64_t)m * a.g_stride, pc, v);
   double s = 0.0;
@@ -132,6 +141,13 @@ __global__ __launch_bounds__(kThreads) void seg_codes_partial_kernel(SegQuantArg
   }
 }
 
+__global__ __launch_bounds__(kThreads) void seg_codes_partial_kernel(SegQuantArgs a) {
+  __shared__ double lds_d[kWaves];
+  __shared__ uint32_t lds_u[kWaves];
+  const Piece pc = load_piece(a.seg, blockIdx.x, a.d);
+  code_piece(a, pc, blockIdx.x, blockIdx.y, a.thr_ws[(int64_t)blockIdx.y * a.seg.n_seg + pc.seg], lds_d, lds_u);
+}
+
 __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void seg_scale_finalize_kernel(SegQuantArgs a) {
   __shared__ double lds_d[kWaves];
   __shared__ double lds_c[kWaves];
@@ -149,6 +165,195 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void seg_scale_finalize_kern
     a.scales[(int64_t)m * a.scale_stride + s] = scale_from_sum(sum, (uint64_t)cnt);
 }
 
+// ---- long tensors in one read -------------------------------------------------------------------
+//
+// As for long buckets of a plain vector: every 64th piece of a tensor of at least 1024 pieces gives a
+// bracket around the tensor's threshold (five standard errors to either side, at most 8 % wide),
+// the one pass writes final codes outside the bracket, the pattern 10 inside it and the piece sums of
+// |v|, and the settling pass looks the open components up once the threshold is known.  Of tensors
+// without a bracket, or whose threshold falls outside it, it reads the gradient again.
+constexpr int kSegSampleEvery = 64;
+constexpr int64_t kSegLong = 1024;
+constexpr double kSegWidestBand = 0.08;
+
+__global__ __launch_bounds__(kThreads) void seg_sample_kernel(SegQuantArgs a) {
+  __shared__ double lds_d[kWaves];
+  const int64_t i = blockIdx.x, p = i * kSegSampleEvery + (i * 29) % kSegSampleEvery;
+  const int m = blockIdx.y;
+  double s = -1.0;                                       // not a whole tile of a long tensor
+  if (p < a.seg.n_pieces) {
+    const Piece pc = load_piece(a.seg, p, a.d);
+    int64_t p0, p1;
+    piece_range(a.seg, pc.seg, &p0, &p1);
+    if (p1 - p0 >= kSegLong && pc.hi - pc.lo == kTile) {
+      float v[4][4];
+      load_piece_values(a.g + (int64_t)m * a.g_stride, pc, v);
+      s = 0.0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s += (double)fabsf(v[j][e]);
+      s = block_sum_f64(s, lds_d);
+    }
+  }
+  if (threadIdx.x == 0) a.kept_sum[(int64_t)m * a.seg.n_pieces + i] = s;
+}
+
+__global__ __launch_bounds__(kThreads) QA_FEW_WAVES void seg_band_kernel(SegQuantArgs a) {
+  __shared__ double lds_d[kWaves];
+  const int64_t s = blockIdx.x;
+  const int m = blockIdx.y;
+  int64_t p0, p1;
+  piece_range(a.seg, s, &p0, &p1);
+  const int64_t i0 = (p0 + kSegSampleEvery - 1) / kSegSampleEvery, i1 = p1 / kSegSampleEvery;
+  const double* part = a.kept_sum + (int64_t)m * a.seg.n_pieces;
+  double sum = 0.0, diff = 0.0, n = 0.0, nd = 0.0;
+  if (p1 - p0 >= kSegLong)
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += kThreads) {
+      const double v = part[i], w = i + 1 < i1 ? part[i + 1] : -1.0;
+      if (v >= 0.0 || v != v) { sum += v; n += 1.0; }
+      if (v >= 0.0 && w >= 0.0) { diff += (w - v) * (w - v); nd += 1.0; }
+    }
+  sum = segment_sum(sum, kThreads, lds_d);
+  diff = segment_sum(diff, kThreads, lds_d);
+  n = segment_sum(n, kThreads, lds_d);
+  nd = segment_sum(nd, kThreads, lds_d);
+  if (threadIdx.x == 0) {
+    float2 band = make_float2(-1.0f, -1.0f);
+    if (n >= 12.0 && nd >= 8.0) {
+      const double mean = sum / n, rel = 5.0 * sqrt(diff / (2.0 * nd) / n) / mean + 1e-6;
+      const double mid = (double)a.thr_coef * mean / (double)kTile;
+      if (mean > 0.0 && rel < kSegWidestBand && mid < 1e38)
+        band = make_float2((float)(mid * (1.0 - rel)), (float)(mid * (1.0 + rel)));
+    }
+    a.band[(int64_t)m * a.seg.n_seg + s] = band;
+  }
+}
+
+__global__ __launch_bounds__(kThreads) void seg_bracketed_kernel(SegQuantArgs a) {
+  __shared__ double lds_s1[kWaves];
+  __shared__ double lds_s2[kWaves];
+  __shared__ uint32_t lds_c[kWaves];
+  const int t = threadIdx.x;
+  const int64_t p = blockIdx.x;
+  const int m = blockIdx.y;
+  const Piece pc = load_piece(a.seg, p, a.d);
+  const float2 band = a.band[(int64_t)m * a.seg.n_seg + pc.seg];
+  float v[4][4];
+  load_piece_values(a.g + (int64_t)m * a.g_stride, pc, v);
+  double s1[4], s2[4] = {0.0, 0.0, 0.0, 0.0};
+  uint32_t wave_cnt = 0, mine = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    s1[j] = (double)fabsf(v[j][0]);
+#pragma unroll
+    for (int e = 1; e < 4; ++e) s1[j] += (double)fabsf(v[j][e]);
+  }
+  if (band.x >= 0.0f) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      uint32_t b = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float av = fabsf(v[j][e]);
+        const bool keep = av > band.y;
+        wave_cnt += (uint32_t)__popcll(__ballot(keep));
+        s2[j] += (double)(keep ? av : 0.0f);
+        const uint32_t pat = 1u | ((__float_as_uint(v[j][e]) >> 30) & 2u);
+        b |= (keep ? pat : (av > band.x ? 2u : 0u)) << (2 * e);
+      }
+      uint32_t w = b << (8 * (t & 3));
+      w |= (uint32_t)dpp_i32<kDppQuadXor1>((int)w);
+      w |= (uint32_t)dpp_i32<kDppQuadXor2>((int)w);
+      if ((t & 3) == j) mine = w;
+    }
+    const int64_t base = pc.tile * kTile;
+    const int wlo = (int)((pc.lo - base) >> 4), whi = (int)((pc.hi - base + 15) >> 4);
+    const int wl = (t & 3) * 64 + (t >> 2);
+    if (wl >= wlo && wl < whi) a.codes[(int64_t)m * a.code_stride + pc.tile * kTileWords + wl] = mine;
+  }
+  const double S1 = wave_sum_f64((s1[0] + s1[1]) + (s1[2] + s1[3]));
+  const double S2 = wave_sum_f64((s2[0] + s2[1]) + (s2[2] + s2[3]));
+  if (t % kWave == 0) { lds_s1[t / kWave] = S1; lds_s2[t / kWave] = S2; lds_c[t / kWave] = wave_cnt; }
+  __syncthreads();
+  if (t == 0) {
+    const int64_t at = (int64_t)m * a.seg.n_pieces + p;
+    a.part_sum[at] = (lds_s1[0] + lds_s1[1]) + (lds_s1[2] + lds_s1[3]);
+    a.kept_sum[at] = (lds_s2[0] + lds_s2[1]) + (lds_s2[2] + lds_s2[3]);
+    a.part_cnt[at] = lds_c[0] + lds_c[1] + lds_c[2] + lds_c[3];
+  }
+}
+
+// Did the sample's bracket hold the threshold?  (NaN compares false.)
+__device__ __forceinline__ bool bracketed(float2 band, float D) {
+  return band.x >= 0.0f && D >= band.x && D <= band.y;
+}
+
+// Eight consecutive pieces per work-group, thread t holds word t of each piece's tile.  What a run of
+// pieces of one tensor keeps goes to the run's first slot of part_sum / part_cnt, zeros to the others.
+__global__ __launch_bounds__(kThreads) void seg_settle_kernel(SegQuantArgs a) {
+  __shared__ SettleLds lds;
+  __shared__ double lds_d[kWaves];
+  __shared__ uint32_t lds_u[kWaves];
+  const int t = threadIdx.x;
+  const int m = blockIdx.y;
+  const int64_t piece0 = (int64_t)blockIdx.x * kSettleTiles;
+  const float* g = a.g + (int64_t)m * a.g_stride;
+  uint32_t* codes = a.codes + (int64_t)m * a.code_stride;
+  const int64_t row = (int64_t)m * a.seg.n_pieces;
+  int u0 = 0;
+  while (u0 < kSettleTiles && piece0 + u0 < a.seg.n_pieces) {
+    const Piece head = load_piece(a.seg, piece0 + u0, a.d);
+    const int64_t seg = head.seg;
+    const float D = a.thr_ws[(int64_t)m * a.seg.n_seg + seg];
+    int64_t p0, p1;
+    piece_range(a.seg, seg, &p0, &p1);
+    int u1 = u0 + 1;                                     // the run of this tensor's pieces
+    const int64_t left = p1 - piece0;
+    if (left > u1) u1 = left < kSettleTiles ? (int)left : kSettleTiles;
+    if (!bracketed(a.band[(int64_t)m * a.seg.n_seg + seg], D)) {
+      for (int u = u0; u < u1; ++u) {
+        code_piece(a, load_piece(a.seg, piece0 + u, a.d), piece0 + u, m, D, lds_d, lds_u);
+        __syncthreads();                                 // LDS is free again
+      }
+      u0 = u1;
+      continue;
+    }
+    // the run's pieces lie in consecutive tiles
+    const int64_t tile0 = head.tile - u0, ntiles = (a.d + kTile - 1) / kTile;
+    const int64_t word_lo = a.seg.begin[seg] >> 4, word_hi = (a.seg.begin[seg] + a.seg.length[seg] + 15) >> 4;
+    double s = 0.0;
+    uint32_t c = 0;
+    if (t >= u0 && t < u1) { s = a.kept_sum[row + piece0 + t]; c = a.part_cnt[row + piece0 + t]; }
+    uint32_t w[kSettleTiles];
+    const auto inside = [&](int u, int64_t at) {
+      return u >= u0 && u < u1 && tile0 + u < ntiles && at >= word_lo && at < word_hi && at * 16 < a.d;
+    };
+#pragma unroll
+    for (int u = 0; u < kSettleTiles; ++u) {
+      const int64_t at = (tile0 + u) * kTileWords + t;
+      w[u] = inside(u, at) ? codes[at] : 0u;
+    }
+    if (settle_words(g, tile0, D, w, lds, s, c)) {
+#pragma unroll
+      for (int u = 0; u < kSettleTiles; ++u) {
+        const int64_t at = (tile0 + u) * kTileWords + t;
+        if (inside(u, at)) codes[at] = w[u];
+      }
+    }
+    s = wave_sum_f64(s);
+    c = wave_sum_u32(c);
+    __syncthreads();                                     // the slots have been read, LDS is free
+    if (t % kWave == 0) { lds_d[t / kWave] = s; lds_u[t / kWave] = c; }
+    __syncthreads();
+    if (t >= u0 && t < u1) {
+      a.part_sum[row + piece0 + t] = t == u0 ? (lds_d[0] + lds_d[1]) + (lds_d[2] + lds_d[3]) : 0.0;
+      a.part_cnt[row + piece0 + t] = t == u0 ? lds_u[0] + lds_u[1] + lds_u[2] + lds_u[3] : 0u;
+    }
+    u0 = u1;
+  }
+}
+
 static inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 size_t quantize_segments_workspace_bytes(const qa_segment_plan* P, int M) {
@@ -157,14 +362,19 @@ size_t quantize_segments_workspace_bytes(const qa_segment_plan* P, int M) {
          align256((size_t)M * (size_t)P->n_seg * sizeof(float));
 }
 
-int quantize_segments_launch(const qa_layout* L, const qa_segment_plan* P, const float* g,
-                             int64_t g_stride, uint32_t* codes, float* scales, float* thresholds,
-                             void* ws, size_t ws_bytes, hipStream_t stream) {
-  if (!ws || ws_bytes < quantize_segments_workspace_bytes(P, L->M)) return QA_ERR_WORKSPACE;
-  if (!aligned(ws, 256)) return QA_ERR_ALIGNMENT;
+// What the one-read form needs on top of it, 0 where it is not taken: the length of the longest tensor is
+// known on the device only, so it has to pay on large lists or cost little: from 2^27 components on.
+// 32 tensors, 58.4 M parameters, most of them in two tensors: 680 -> 500 us with 8 workers, 338 -> 250 with
+// 4; 64 tensors, 30 M parameters, 8 workers: 348 -> 346.
+constexpr int64_t kSegOneReadPieces = 32768;
+size_t segments_one_read_bytes(const qa_segment_plan* P, int M) {
+  if (P->n_pieces < kSegLong || P->n_pieces * M < kSegOneReadPieces) return 0;
+  return align256((size_t)M * (size_t)P->n_pieces * sizeof(double)) + align256((size_t)M * (size_t)P->n_seg * sizeof(float2));
+}
+
+static SegQuantArgs seg_args(const qa_layout* L, const qa_segment_plan* P, float* scales, float* thresholds, void* ws) {
   SegQuantArgs a{};
-  a.g = g; a.g_stride = g_stride; a.d = L->d;
-  a.codes = codes; a.code_stride = L->code_stride;
+  a.d = L->d;
   a.scales = scales; a.thresholds = thresholds; a.scale_stride = L->scale_stride;
   a.thr_coef = L->thr_coef;
   a.seg = seg_table_of(P);
@@ -173,8 +383,49 @@ int quantize_segments_launch(const qa_layout* L, const qa_segment_plan* P, const
   a.part_sum = reinterpret_cast<double*>(p);    p += align256((size_t)L->M * np * sizeof(double));
   a.part_cnt = reinterpret_cast<uint32_t*>(p);  p += align256((size_t)L->M * np * sizeof(uint32_t));
   a.thr_ws = reinterpret_cast<float*>(p);
+  return a;
+}
+
+// For a producer that forms the quantizer's input piece by piece and leaves its sums itself: where they
+// go, and the finalize kernels alone (which = 0: thresholds, 1: scales).
+void segments_workspace_parts(const qa_layout* L, const qa_segment_plan* P, void* ws, double** part_sum,
+                              uint32_t** part_cnt, float** thr) {
+  const SegQuantArgs a = seg_args(L, P, nullptr, nullptr, ws);
+  *part_sum = a.part_sum; *part_cnt = a.part_cnt; *thr = a.thr_ws;
+}
+void segments_finalize_launch(const qa_layout* L, const qa_segment_plan* P, int which, float* scales, void* ws,
+                              hipStream_t stream) {
+  const SegQuantArgs a = seg_args(L, P, scales, nullptr, ws);
+  const dim3 block(kThreads), grid_s((unsigned)P->n_seg, (unsigned)L->M);
+  if (which == 0) hipLaunchKernelGGL(seg_threshold_finalize_kernel, grid_s, block, 0, stream, a);
+  else hipLaunchKernelGGL(seg_scale_finalize_kernel, grid_s, block, 0, stream, a);
+}
+
+int quantize_segments_launch(const qa_layout* L, const qa_segment_plan* P, const float* g,
+                             int64_t g_stride, uint32_t* codes, float* scales, float* thresholds,
+                             void* ws, size_t ws_bytes, hipStream_t stream) {
+  if (!ws || ws_bytes < quantize_segments_workspace_bytes(P, L->M)) return QA_ERR_WORKSPACE;
+  if (!aligned(ws, 256)) return QA_ERR_ALIGNMENT;
+  SegQuantArgs a = seg_args(L, P, scales, thresholds, ws);
+  a.g = g; a.g_stride = g_stride;
+  a.codes = codes; a.code_stride = L->code_stride;
   const dim3 block(kThreads);
   const dim3 grid_p((unsigned)P->n_pieces, (unsigned)L->M), grid_s((unsigned)P->n_seg, (unsigned)L->M);
+  const size_t base = quantize_segments_workspace_bytes(P, L->M), more = segments_one_read_bytes(P, L->M);
+  if (more != 0 && ws_bytes >= base + more) {
+    char* p = static_cast<char*>(ws) + base;
+    a.kept_sum = reinterpret_cast<double*>(p);
+    a.band = reinterpret_cast<float2*>(p + align256((size_t)L->M * (size_t)P->n_pieces * sizeof(double)));
+    const dim3 samples((unsigned)((P->n_pieces + kSegSampleEvery - 1) / kSegSampleEvery), (unsigned)L->M);
+    const dim3 settle((unsigned)((P->n_pieces + kSettleTiles - 1) / kSettleTiles), (unsigned)L->M);
+    hipLaunchKernelGGL(seg_sample_kernel, samples, block, 0, stream, a);
+    hipLaunchKernelGGL(seg_band_kernel, grid_s, block, 0, stream, a);
+    hipLaunchKernelGGL(seg_bracketed_kernel, grid_p, block, 0, stream, a);
+    hipLaunchKernelGGL(seg_threshold_finalize_kernel, grid_s, block, 0, stream, a);
+    hipLaunchKernelGGL(seg_settle_kernel, settle, block, 0, stream, a);
+    hipLaunchKernelGGL(seg_scale_finalize_kernel, grid_s, block, 0, stream, a);
+    return launch_status();
+  }
   if (P->n_pieces > 0) hipLaunchKernelGGL(seg_abs_partial_kernel, grid_p, block, 0, stream, a);
   hipLaunchKernelGGL(seg_threshold_finalize_kernel, grid_s, block, 0, stream, a);
   if (P->n_pieces > 0) hipLaunchKernelGGL(seg_codes_partial_kernel, grid_p, block, 0, stream, a);

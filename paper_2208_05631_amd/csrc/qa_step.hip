@@ -690,10 +690,10 @@ __global__ __launch_bounds__(kThreads) void step_lut_kernel(StepArgs a) {
 #pragma unroll
     for (int j = 0; j < 16; ++j) s1 += (double)fabsf(q[j]);
     s1 = block_sum_f64(s1, lds_d);
-    if (t == 0) a.abs_partials[tile] = s1;
+    if (t == 0) a.abs_partials[blockIdx.x] = s1;        // tile or piece
   }
   if (MODE == kAggregate && RQ == kRqNone && a.kept_sum) {   // uniform
-    const float Delta = a.rq_thr[tile / a.rq_tiles];
+    const float Delta = a.rq_thr[a.seg.piece_tile ? k : tile / a.rq_tiles];
     double s2 = 0.0;
     uint32_t cnt = 0;
 #pragma unroll
@@ -706,8 +706,8 @@ __global__ __launch_bounds__(kThreads) void step_lut_kernel(StepArgs a) {
     if ((t % kWave) == 0) { lds_d2[t / kWave] = s2; lds_u[t / kWave] = cnt; }
     __syncthreads();
     if (t == 0) {
-      a.kept_sum[tile] = (lds_d2[0] + lds_d2[1]) + (lds_d2[2] + lds_d2[3]);
-      a.kept_cnt[tile] = (lds_u[0] + lds_u[1]) + (lds_u[2] + lds_u[3]);
+      a.kept_sum[blockIdx.x] = (lds_d2[0] + lds_d2[1]) + (lds_d2[2] + lds_d2[3]);
+      a.kept_cnt[blockIdx.x] = (lds_u[0] + lds_u[1]) + (lds_u[2] + lds_u[3]);
     }
     return;
   }
@@ -715,7 +715,7 @@ __global__ __launch_bounds__(kThreads) void step_lut_kernel(StepArgs a) {
 
   if (RQ == kRqGiven) {
     static_assert(RQ != kRqGiven || MODE != kAggregate, "the server's call writes the average out");
-    const int64_t k2 = tile / a.rq_tiles;
+    const int64_t k2 = a.seg.piece_tile ? k : tile / a.rq_tiles;
     const float Delta = a.rq_thr[k2], s = a.rq_scale[k2];
     // q = +-s comes from the whole bucket, not from this tile: the short forms of the update also
     // need s itself inside the window that was checked for the tile's own scales
@@ -1419,6 +1419,29 @@ static int step_segments_common(int mode, const qa_layout* L, const qa_segment_p
     float* th1 = reinterpret_cast<float*>(p);         p += align256((size_t)P->n_seg * 4);
     StepArgs ag = make_args(L, codes, scales);
     ag.seg = seg_table_of(P);
+    if (L->M <= kRecomputeMaxM) {
+      // few workers: every pass forms the average from the messages, none writes it out (32 tensors,
+      // 58.4 M parameters, QRDA: 356 -> 274 us at M = 1, 358 -> 288 at M = 4, 368 -> 332 at M = 8)
+      double* part_sum; uint32_t* part_cnt; float* thr;
+      segments_workspace_parts(&R, P, p, &part_sum, &part_cnt, &thr);
+      ag.abs_partials = part_sum;
+      launch_mode<kAggregate>(ag, false, false, stream);
+      segments_finalize_launch(&R, P, 0, s1, p, stream);
+      ag.abs_partials = nullptr;
+      ag.kept_sum = part_sum; ag.kept_cnt = part_cnt; ag.rq_thr = thr; ag.rq_tiles = 1;
+      launch_mode<kAggregate>(ag, false, false, stream);
+      segments_finalize_launch(&R, P, 1, s1, p, stream);
+      StepArgs a = make_args(L, codes, scales);
+      a.seg = ag.seg;
+      a.x = x; a.G = G; a.z = z;
+      a.eta = eta; a.lam_eta = lambda * eta; a.delta = delta;
+      a.t_lam = (float)t * lambda;
+      a.rq_thr = thr; a.rq_scale = s1; a.rq_tiles = 1;
+      set_fast_limits(a, mode, eta, a.lam_eta, delta);
+      if (mode == kQcmd) launch_mode_rq<kQcmd, kRqGiven>(a, track_z, stream);
+      else launch_mode_rq<kQrda, kRqGiven>(a, false, stream);
+      return launch_status();
+    }
     ag.gbar = gbar;
     launch_mode<kAggregate>(ag, false, false, stream);
     const int64_t gs = (L->d + 3) & ~int64_t(3);
@@ -1443,7 +1466,8 @@ static int step_segments_common(int mode, const qa_layout* L, const qa_segment_p
 extern "C" size_t qa_segment_workspace_bytes(const qa_segment_plan* plan, int32_t M, int op) {
   using namespace qa;
   if (!plan || plan->d < 1 || plan->n_seg < 1 || plan->n_pieces < 0 || M < 1 || M > 4096) return 0;
-  if (op == QA_OP_QUANTIZE) return quantize_segments_workspace_bytes(plan, M);
+  if (op == QA_OP_QUANTIZE)
+    return quantize_segments_workspace_bytes(plan, M) + segments_one_read_bytes(plan, M);
   if (op == QA_OP_STEP) return step_segments_workspace_bytes(plan);
   return 0;
 }

@@ -156,3 +156,60 @@ def test_segment_calls_reject_what_they_cannot_do():
     with pytest.raises(qa.QaError) as e:                                # plan of another vector
         qa.qa_step_qcmd_segments(Ld, f.plan, codes, scales, x, G, None, 0.1, 0.0, 1e-8, 0, None)
     assert e.value.code == -1
+
+
+@pytest.mark.parametrize("M", [8, 9])
+def test_long_tensors_read_once_match_oracle(M):
+    """Lists large enough for the form that reads long tensors' gradients once (2^27 components in all):
+    tensors just below and above the length that is sampled, one whose sampled pieces mislead, sparse
+    and constant ones, small ones between them; steps with the second quantization on top."""
+    lengths = [30, 1024 * 4096 - 4096, 17, 1024 * 4096 + 5, 2_000_000, 1100 * 4096, 3, 1500 * 4096 + 1, 100]
+    f = Flat.__new__(Flat)
+    f.begin, f.length, f.d = layout_of(lengths)
+    f.M, f.nseg = M, len(lengths)
+    f.L = qa.Layout.make(f.d, M, 0, 0.75, None, f.nseg)
+    f.table = torch.zeros(qa.qa_segment_plan_bytes(f.d, f.nseg), dtype=torch.uint8, device=DEV)
+    f.plan = qa.qa_segment_plan_init(f.d, f.begin, f.length, f.table)
+    f.gs = (f.d + 3) // 4 * 4
+    assert f.plan.n_pieces * M >= 32768
+    rng = np.random.default_rng(M)
+    g = rng.standard_normal((M, f.d), dtype=np.float32)
+    first = np.concatenate([[0], np.cumsum([(b + n - 1) // 4096 - b // 4096 + 1 for b, n in zip(f.begin, f.length)])])
+    b5 = int(f.begin[5])
+    for i in range(f.plan.n_pieces // 64 + 1):          # tensor 5: the sampled pieces are ten times larger
+        p = i * 64 + (i * 29) % 64
+        if first[5] < p < first[6] - 1:
+            tile = b5 // 4096 + p - first[5]
+            g[:M // 2, tile * 4096:(tile + 1) * 4096] *= 10
+    s7 = slice(int(f.begin[7]), int(f.begin[7]) + int(f.length[7]))
+    g[0, s7] *= rng.random(f.length[7]) < 0.05
+    g[1, s7] = 0.25
+    g[2, s7] = 0
+    c_ref, s_ref, th_ref = oracle.quantize_pack_segments(g, f.begin, f.length)
+    codes, scales, th = f.gpu_quantize(g)
+    c = host(codes).view(np.uint32)
+    touched = np.zeros(f.L.words, bool)
+    for b, n in zip(f.begin, f.length):
+        touched[b // 16:(b + n + 15) // 16] = True
+    # sums in another order: thresholds and scales within an ulp, codes those of the thresholds
+    assert np.allclose(host(th), th_ref, rtol=1.3e-7, atol=0)
+    assert np.allclose(host(scales), s_ref, rtol=1.3e-7, atol=0)
+    if np.array_equal(host(th), th_ref):
+        assert np.array_equal(c[:, touched], c_ref[:, touched])
+    assert (c[:, ~touched] == 0x5A5A5A5A).all()
+    x, G, z = (np.zeros(f.d, np.float32) for _ in range(3))
+    xd, Gd, zd = dev(x), dev(G), dev(z)
+    ws = workspace(qa.qa_segment_workspace_bytes(f.plan, M, qa.QA_OP_STEP))
+    oracle.step_segments(oracle.QRDA, c_ref, s_ref, f.d, f.begin, f.length, x, G, z, 1, 0.1, 1e-3, 1e-8, True)
+    qa.qa_step_qrda_segments(f.L, f.plan, dev(c_ref.view(np.int32)), dev(s_ref), xd, Gd, zd, 1, 0.1, 1e-3, 1e-8,
+                             qa.QA_REQUANT_BUCKET, ws)
+    torch.cuda.synchronize()
+    for a, r in ((xd, x), (Gd, G), (zd, z)):
+        close(host(a)[f_covered(f)], r[f_covered(f)], "state")
+
+
+def f_covered(f):
+    covered = np.zeros(f.d, bool)
+    for b, n in zip(f.begin, f.length):
+        covered[b:b + n] = True
+    return covered
