@@ -30,6 +30,7 @@ struct SelArgs {
   int seg;                     // threads per bucket inside a tile: bucket/16 for 64 <= bucket <= 4096
   int64_t nb, ntiles, tiles_per_bucket, area_words;   // buckets spanning several tiles
   uint32_t* ws_count; double* ws_s1; double* ws_s2; uint32_t* ws_c2; int64_t* ws_start; float* ws_thr;
+  int64_t samples;             // one-read quantizer: sampled tiles per bucket (at most)
 };
 
 // Granularity of a sparse message's buckets: one 4096-tile each; 64 .. 2048 coordinates, inside a
@@ -516,8 +517,8 @@ __global__ __launch_bounds__(kThreads) void select_codes_kernel(SelArgs a) {
 //     message of the Encode paragraph), span tiles: a first pass counts every tile's selected
 //     components, a scan per bucket turns the counts into each tile's first position in the
 //     bucket's stream (kept in the workspace), and the tiles then place or fetch their codes
-//     there.  Neighbouring tiles share stream words, so producers OR their part into words that
-//     a small kernel has zeroed first.
+//     there.  Neighbouring tiles share stream words, so producers OR their part into such words,
+//     which a small kernel has zeroed.
 
 // the 16 indicator bits of the thread's coordinates, without those at or beyond d
 __device__ __forceinline__ uint32_t live_mask16(const SelArgs& a, const uint32_t* ind, int64_t tile, int t) {
@@ -624,15 +625,17 @@ __global__ __launch_bounds__(kThreads) void gsel_count_ind_kernel(SelArgs a) {
 }
 
 // pass 2: per (bucket, worker), in tile order: each tile's first position in the bucket's stream,
-// the bucket's count and (with a gradient) its threshold.  One work-group per bucket; a round takes
-// 256 x 16 consecutive tiles (thread t the 16 from t*16 on) with a running offset, so the order
-// of the binary64 additions is fixed.
-constexpr int kScanRun = 16;
-template <bool HAS_G>
-__global__ __launch_bounds__(kThreads) void gsel_scan_kernel(SelArgs a) {
-  __shared__ uint32_t lds_w[kWaves];
-  __shared__ double lds_d[kWaves];
-  const int t = threadIdx.x;
+// the bucket's count and (with the tiles' sums) its threshold.  One work-group per bucket; a round
+// takes THREADS x 8 consecutive tiles (thread t the 8 from t*8 on) with a running offset, so the
+// order of the binary64 additions is fixed.  A wave for buckets of up to 512 tiles (one round), else 1024
+// threads.  Bound by the rounds' chain of a load and a barrier: 8 x 32768 tiles 13 us, with 256 threads of 16 guarded loads 35.
+constexpr int kScanRun = 8;
+template <bool HAS_G, int THREADS>
+__global__ __launch_bounds__(THREADS) void gsel_scan_kernel(SelArgs a) {
+  constexpr int kScanThreads = THREADS, kScanWaves = THREADS / kWave;
+  __shared__ uint32_t lds_w[kScanWaves];
+  __shared__ double lds_d[kScanWaves];
+  const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
   const int64_t k = blockIdx.x;
   const int m = blockIdx.y;
   const int64_t t0 = k * a.tiles_per_bucket;
@@ -642,49 +645,82 @@ __global__ __launch_bounds__(kThreads) void gsel_scan_kernel(SelArgs a) {
   int64_t* start = a.ws_start + (int64_t)m * a.ntiles;
   int64_t running = 0;
   double s1 = 0.0;
-  for (int64_t i = t0; i < t1; i += (int64_t)kThreads * kScanRun) {
+  for (int64_t i = t0; i < t1; i += (int64_t)kScanThreads * kScanRun) {
     const int64_t j0 = i + (int64_t)t * kScanRun;
     uint32_t c[kScanRun], mine = 0;
+    double v[kScanRun];
+    if (j0 + kScanRun <= t1) {                           // all loads together
 #pragma unroll
-    for (int u = 0; u < kScanRun; ++u) {
-      c[u] = j0 + u < t1 ? cnt[j0 + u] : 0u;
-      mine += c[u];
-      if (HAS_G && j0 + u < t1) s1 += s1p[j0 + u];
+      for (int u = 0; u < kScanRun; ++u) c[u] = cnt[j0 + u];
+#pragma unroll
+      for (int u = 0; u < kScanRun; ++u) v[u] = HAS_G ? s1p[j0 + u] : 0.0;
+    } else {
+#pragma unroll
+      for (int u = 0; u < kScanRun; ++u) {
+        c[u] = j0 + u < t1 ? cnt[j0 + u] : 0u;
+        v[u] = HAS_G && j0 + u < t1 ? s1p[j0 + u] : 0.0;
+      }
     }
-    uint32_t total;
-    uint32_t ex = block_exclusive_scan(mine, lds_w, &total);   // at most 256 x 16 x 4096 = 2^24
 #pragma unroll
     for (int u = 0; u < kScanRun; ++u) {
-      if (j0 + u < t1) start[j0 + u] = running + ex;
-      ex += c[u];
+      mine += c[u];
+      if (HAS_G) s1 += v[u];
+    }
+    const uint32_t incl = wave_inclusive_scan_u32(mine);
+    __syncthreads();                                     // the previous round's totals have been read
+    if (lane == kWave - 1) lds_w[wave] = incl;
+    __syncthreads();
+    uint32_t ex = incl - mine, total = 0;                // at most 1024 x 8 x 4096 = 2^25
+#pragma unroll
+    for (int w = 0; w < kScanWaves; ++w) {
+      const uint32_t x = lds_w[w];
+      if (w < wave) ex += x;
+      total += x;
+    }
+    int64_t from = running + ex;
+    if (j0 + kScanRun <= t1) {
+#pragma unroll
+      for (int u = 0; u < kScanRun; ++u) { start[j0 + u] = from; from += c[u]; }
+    } else {
+#pragma unroll
+      for (int u = 0; u < kScanRun; ++u) {
+        if (j0 + u < t1) start[j0 + u] = from;
+        from += c[u];
+      }
     }
     running += total;
   }
-  if (HAS_G) s1 = block_sum_f64(s1, lds_d);
+  if (HAS_G) {
+    s1 = wave_sum_f64(s1);
+    if (lane == 0) lds_d[wave] = s1;
+    __syncthreads();
+  }
   if (t == 0) {
     a.counts[(int64_t)m * a.scale_stride + k] = (uint32_t)running;   // a bucket holds < 2^32 here
     if (HAS_G) {
-      const float Delta = running ? threshold_from_sum(s1, a.thr_coef, running) : 0.0f;
+      double S1 = 0.0;
+      for (int w = 0; w < kScanWaves; ++w) S1 += lds_d[w];
+      const float Delta = running ? threshold_from_sum(S1, a.thr_coef, running) : 0.0f;
       a.ws_thr[(int64_t)m * a.nb + k] = Delta;
       if (a.thresholds) a.thresholds[(int64_t)m * a.scale_stride + k] = Delta;
     }
   }
 }
 
-// zero the first ceil(K/16) words of every bucket's area (a tile covers 256 of them, a work-group
-// kZeroTiles consecutive tiles)
-constexpr int kZeroTiles = 8;
+// The words of the stream that two tiles share -- those where a tile begins or ends off a word's
+// boundary -- are set to 0 for the producers to OR into; all others they store whole.  A thread per
+// tile: 9.1 us for 8 workers x 2^27 (all ceil(K/16) words of every area, before: 77).
 __global__ __launch_bounds__(kThreads) void gsel_zero_kernel(SelArgs a) {
+  const int64_t tile = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (tile >= a.ntiles) return;
   const int m = blockIdx.y;
-#pragma unroll
-  for (int u = 0; u < kZeroTiles; ++u) {
-    const int64_t tile = (int64_t)blockIdx.x * kZeroTiles + u;
-    if (tile >= a.ntiles) break;
-    const int64_t k = tile / a.tiles_per_bucket;
-    const int64_t w = (tile - k * a.tiles_per_bucket) * kTileWords + threadIdx.x;   // word of the area
-    const int64_t K = a.counts[(int64_t)m * a.scale_stride + k];
-    if (w < (K + 15) / 16) a.sel_codes[(int64_t)m * a.code_stride + k * a.area_words + w] = 0u;
-  }
+  const int64_t k = tile / a.tiles_per_bucket, at = (int64_t)m * a.ntiles + tile;
+  const uint32_t c = a.ws_count[at];
+  if (c == 0) return;
+  const int64_t from = a.ws_start[at], to = from + c;
+  uint32_t* area = a.sel_codes + (int64_t)m * a.code_stride + k * a.area_words;
+  if (from & 15) area[from >> 4] = 0u;
+  if (to & 15) area[to >> 4] = 0u;
 }
 
 // Q(S(g, I)) for buckets of 64 .. 2048 coordinates: thread t = code word t of the tile, a bucket =
@@ -743,23 +779,264 @@ __global__ __launch_bounds__(kThreads) void gsel_quantize_local_kernel(SelArgs a
   }
 }
 
-// Q(S(g, I)) for buckets that span tiles, one wave per tile and no work-group barrier on the way
-// (lane l holds code words j*64 + l of the tile, j = 0..3, as in the decoder): the threshold comes
-// from pass 2, the tile's codes go to their place in the bucket's stream (words that a
-// neighbouring tile may also touch are OR-ed into memory zeroed before), the tile's kept sum and
-// count to the workspace for gsel_scale_kernel.
+// Q(S(g, I)) of one tile for buckets that span tiles, by one wave (lane l holds code words j*64 + l
+// of the tile, j = 0..3, as in the decoder): the tile's codes, in index order, in `stream` (LDS of
+// the wave) from code position `first` on; the sums of |v| over the marked (BRACKET) and over the kept
+// components and the latter's number per lane.  BRACKET: components up to `lo` get 0, above `hi` their
+// code, those between the pattern 10.
+// Bound by the reads: 4.6 GB for 8 workers x 2^27 in 1.03 to 1.12 ms.  Half of the tile's components held
+// at a time, all of them or a quarter make no difference; slower are nontemporal loads (1.42: four lanes
+// of a 64-byte stride share every line), the gradient brought through LDS (1.20) and selecting in place of
+// the branch around an unmarked component (1.22).
+struct TileCodes {
+  double s1, s2;
+  uint32_t c2, end;                                      // end: one past the tile's last code
+};
+__device__ __forceinline__ void wave_fence() {           // order of a wave's own LDS accesses
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+template <bool BRACKET>
+__device__ __forceinline__ TileCodes code_selected_tile(const SelArgs& a, int64_t tile, int m, uint32_t first,
+                                                        float lo, float hi, uint32_t* stream) {
+  const int lane = threadIdx.x % kWave;
+  const uint32_t* ind = a.ind_in + (int64_t)m * a.ind_stride;
+  const float* g = a.g + (int64_t)m * a.g_stride;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) stream[j * 64 + lane] = 0u;
+  if (lane < 2) stream[kTileWords + lane] = 0u;
+  wave_fence();
+  TileCodes r{0.0, 0.0, 0u, first};
+#pragma unroll 1
+  for (int half = 0; half < 4; half += 2) {
+    uint32_t mask[2], incl[2];
+    float v[2][16];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int wl = (half + h) * 64 + lane;
+      const int64_t iw = tile * (kTile / 32) + wl / 2;
+      const uint32_t iv = iw < a.NW ? ind[iw] : 0u;
+      mask[h] = (iv >> (16 * (wl & 1))) & 0xFFFFu;
+      const int64_t left = a.d - (tile * kTile + (int64_t)wl * 16);
+      if (left < 16) mask[h] = left > 0 ? (mask[h] & ((1u << left) - 1u)) : 0u;
+      load16(g, a.d, tile * kTile + (int64_t)wl * 16, v[h]);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) incl[h] = wave_inclusive_scan_u32((uint32_t)__popc(mask[h]));
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t n = (uint32_t)__popc(mask[h]);
+      const uint32_t before = r.end + incl[h] - n;
+      r.end += (uint32_t)__builtin_amdgcn_readlane((int)incl[h], kWave - 1);
+      uint32_t bits = 0, filled = 0;
+#pragma unroll
+      for (int c = 0; c < 16; ++c)
+        if ((mask[h] >> c) & 1u) {
+          const float av = fabsf(v[h][c]);
+          uint32_t f;
+          if (BRACKET) {
+            r.s1 += (double)av;
+            const bool keep = av > hi;
+            if (keep) { r.s2 += (double)av; ++r.c2; }
+            f = keep ? 1u | ((__float_as_uint(v[h][c]) >> 30) & 2u) : (av > lo ? 2u : 0u);
+          } else {
+            if (av > lo) { r.s2 += (double)av; ++r.c2; }
+            f = ternary_field(v[h][c], lo);
+          }
+          bits |= f << filled;
+          filled += 2;
+        }
+      if (n) {
+        const uint32_t w0 = before / 16, sh = 2 * (before % 16);
+        atomicOr(&stream[w0], bits << sh);
+        if (sh && 2 * n + sh > 32) atomicOr(&stream[w0 + 1], bits >> (32 - sh));
+      }
+    }
+  }
+  r.s1 = wave_sum_f64(r.s1);
+  r.s2 = wave_sum_f64(r.s2);
+  r.c2 = wave_sum_u32(r.c2);
+  wave_fence();
+  return r;
+}
+
+// The assembled codes of a tile to their place in the bucket's stream (words that a neighbouring tile may
+// also touch are OR-ed into memory zeroed before), its kept sum and count to the workspace.  BRACKET:
+// the one pass of the one-read form below; else the threshold comes from pass 2.
+template <bool BRACKET>
 __global__ __launch_bounds__(kThreads) void gsel_quantize_multi_kernel(SelArgs a) {
   __shared__ uint32_t stream_all[kWaves][kTileWords + 2];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   uint32_t* stream = stream_all[wave];
-  const int64_t tile_raw = (int64_t)blockIdx.x * kWaves + wave;
-  const bool exists = tile_raw < a.ntiles;
-  const int64_t tile = exists ? tile_raw : 0;            // clamped: every wave runs the same code
+  const int64_t tile = (int64_t)blockIdx.x * kWaves + wave;
+  if (tile >= a.ntiles) return;
   const int m = blockIdx.y;
+  const int64_t at = (int64_t)m * a.ntiles + tile, k = tile / a.tiles_per_bucket;
+  const int64_t st = a.ws_start[at];
+  const uint32_t first = (uint32_t)(st & 15);
+  const float thr = a.ws_thr[(int64_t)m * a.nb + k];
+  const float lo = BRACKET ? a.scales[(int64_t)m * a.scale_stride + k] : thr;
+  if (BRACKET && !(lo >= 0.0f)) {                        // no bracket: the marked sum only
+    float v[2][16];
+    uint32_t mask[4];
+    double s1 = 0.0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) mask[j] = live_mask16(a, a.ind_in + (int64_t)m * a.ind_stride, tile, j * 64 + lane);
+#pragma unroll 1
+    for (int half = 0; half < 4; half += 2) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        load16(a.g + (int64_t)m * a.g_stride, a.d, tile * kTile + (int64_t)((half + h) * 64 + lane) * 16, v[h]);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t mk = half ? mask[2 + h] : mask[h];
+#pragma unroll
+        for (int c = 0; c < 16; ++c)
+          if ((mk >> c) & 1u) s1 += (double)fabsf(v[h][c]);
+      }
+    }
+    s1 = wave_sum_f64(s1);
+    if (lane == 0) a.ws_s1[at] = s1;
+    return;
+  }
+  const TileCodes r = code_selected_tile<BRACKET>(a, tile, m, first, lo, thr, stream);
+  const uint32_t nwords = (r.end + 15) / 16;
+  uint32_t* out = a.sel_codes + (int64_t)m * a.code_stride + k * a.area_words + (st >> 4);
+  if (r.end != first)
+    for (uint32_t w = lane; w < nwords; w += kWave) {    // at most 257 words
+      const bool shared = (w == 0 && first != 0) || (w == nwords - 1 && (r.end % 16) != 0);
+      if (shared) atomicOr(&out[w], stream[w]);
+      else out[w] = stream[w];
+    }
+  if (lane == 0) {
+    if (BRACKET) a.ws_s1[at] = r.s1;
+    a.ws_s2[at] = r.s2;
+    a.ws_c2[at] = r.c2;
+  }
+}
+
+// ---- long buckets in one read -------------------------------------------------------------------
+//
+// As for the dense quantizer: the marked components' numbers come from the indicators alone, every 64th
+// tile gives a bracket around the threshold (five standard errors to either side of the sampled ratio
+// sum / number, at most 8 % wide), the one pass writes final codes outside the bracket and the pattern
+// 10 inside it, and the settling pass looks the open components up once the threshold is known.
+// Until the scales are known, scales[] carries the bracket's lower end (-1: there is none, and the pass forms
+// the sum alone) and then whether it held the threshold (0 / 1), ws_thr its upper end and then the threshold.
+constexpr int kSelSampleEvery = 64;
+constexpr double kSelWidestBand = 0.08;
+
+__device__ __forceinline__ int64_t sampled_tile(const SelArgs& a, int64_t k, int64_t i) {
+  return k * a.tiles_per_bucket + i * kSelSampleEvery + (i * 29) % kSelSampleEvery;
+}
+__device__ __forceinline__ int64_t samples_of(const SelArgs& a, int64_t k) {
+  const int64_t all = a.ntiles - k * a.tiles_per_bucket;
+  return (all < a.tiles_per_bucket ? all : a.tiles_per_bucket) / kSelSampleEvery;
+}
+
+__global__ __launch_bounds__(kThreads) void gsel_sample_kernel(SelArgs a) {
+  __shared__ double lds_d[kWaves];
+  const int64_t k = blockIdx.x / a.samples, i = blockIdx.x % a.samples;
+  const int m = blockIdx.y;
+  if (i >= samples_of(a, k)) return;
+  const int64_t tile = sampled_tile(a, k, i);
+  const uint32_t mask = live_mask16(a, a.ind_in + (int64_t)m * a.ind_stride, tile, threadIdx.x);
+  float v[16];
+  load16(a.g + (int64_t)m * a.g_stride, a.d, tile * kTile + 16 * (int64_t)threadIdx.x, v);
+  double s = 0.0;
+#pragma unroll
+  for (int j = 0; j < 16; ++j)
+    if ((mask >> j) & 1u) s += (double)fabsf(v[j]);
+  s = block_sum_f64(s, lds_d);
+  if (threadIdx.x == 0) a.ws_s2[(int64_t)m * a.ntiles + k * a.samples + i] = s;
+}
+
+__global__ __launch_bounds__(kThreads) void gsel_band_kernel(SelArgs a) {
+  __shared__ double lds_d[kWaves];
+  const int64_t k = blockIdx.x;
+  const int m = blockIdx.y;
+  const double* part = a.ws_s2 + (int64_t)m * a.ntiles + k * a.samples;
+  const uint32_t* cnt = a.ws_count + (int64_t)m * a.ntiles;
+  const int64_t n = samples_of(a, k);
+  double sum = 0.0, num = 0.0, diff = 0.0;
+  for (int64_t i = threadIdx.x; i < n; i += kThreads) { sum += part[i]; num += (double)cnt[sampled_tile(a, k, i)]; }
+  sum = segment_sum(sum, kThreads, lds_d);
+  num = segment_sum(num, kThreads, lds_d);
+  const double ratio = num > 0.0 ? sum / num : 0.0;
+  // residuals against the ratio, neighbouring samples (trends along the vector drop out)
+  for (int64_t i = threadIdx.x; i + 1 < n; i += kThreads) {
+    const double e = (part[i + 1] - ratio * (double)cnt[sampled_tile(a, k, i + 1)]) -
+                     (part[i] - ratio * (double)cnt[sampled_tile(a, k, i)]);
+    diff += e * e;
+  }
+  diff = segment_sum(diff, kThreads, lds_d);
+  if (threadIdx.x == 0) {
+    float lo = -1.0f, hi = -1.0f;                        // no bracket
+    if (n >= 16 && ratio > 0.0) {
+      const double rel = 5.0 * sqrt(diff / (2.0 * (double)(n - 1)) * (double)n) / sum + 1e-6;
+      const double mid = (double)a.thr_coef * ratio;
+      if (rel < kSelWidestBand && mid < 1e38) { lo = (float)(mid * (1.0 - rel)); hi = (float)(mid * (1.0 + rel)); }
+    }
+    a.scales[(int64_t)m * a.scale_stride + k] = lo;
+    a.ws_thr[(int64_t)m * a.nb + k] = hi;
+  }
+}
+
+__global__ __launch_bounds__(kThreads) QA_FEW_WAVES void gsel_threshold_kernel(SelArgs a) {
+  __shared__ double lds_d[kWaves];
+  const int64_t k = blockIdx.x;
+  const int m = blockIdx.y;
+  const int64_t t0 = k * a.tiles_per_bucket;
+  const int64_t t1 = t0 + a.tiles_per_bucket < a.ntiles ? t0 + a.tiles_per_bucket : a.ntiles;
+  double s = strided_partial_sum(a.ws_s1 + (int64_t)m * a.ntiles, t0, t1);
+  s = segment_sum(s, kThreads, lds_d);
+  if (threadIdx.x == 0) {
+    const int64_t K = a.counts[(int64_t)m * a.scale_stride + k];
+    const float Delta = K ? threshold_from_sum(s, a.thr_coef, K) : 0.0f;
+    float* lo = a.scales + (int64_t)m * a.scale_stride + k;
+    float* thr = a.ws_thr + (int64_t)m * a.nb + k;
+    if (*lo >= 0.0f) *lo = Delta >= *lo && Delta <= *thr ? 1.0f : 0.0f;
+    *thr = Delta;
+    if (a.thresholds) a.thresholds[(int64_t)m * a.scale_stride + k] = Delta;
+  }
+}
+
+// A wave per tile: the time is the chain of dependent loads (8 workers x 2^27: 164 us; two tiles per wave,
+// their loads phase by phase, 190, four 336: their registers cost more waves than that saves).  With a
+// bracket that held: each lane reads its words' codes back from the stream, finds the pattern 10, and
+// exchanges it for the component's code in place.  Without a bracket the tile is coded here, and with one
+// that missed again; of a word that it shares with a neighbour then only its own bits change.
+__global__ __launch_bounds__(kThreads) void gsel_settle_kernel(SelArgs a) {
+  __shared__ uint32_t stream_all[kWaves][kTileWords + 2];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int64_t tile = (int64_t)blockIdx.x * kWaves + wave;
+  if (tile >= a.ntiles) return;
+  const int m = blockIdx.y;
+  const int64_t slot = (int64_t)m * a.ntiles + tile, k = tile / a.tiles_per_bucket;
+  const float D = a.ws_thr[(int64_t)m * a.nb + k];
+  const int64_t st = a.ws_start[slot];
+  const uint32_t first = (uint32_t)(st & 15);
+  uint32_t* out = a.sel_codes + (int64_t)m * a.code_stride + k * a.area_words + (st >> 4);
+  const float held = a.scales[(int64_t)m * a.scale_stride + k];
+  if (held != 1.0f) {
+    uint32_t* stream = stream_all[wave];
+    const TileCodes r = code_selected_tile<false>(a, tile, m, first, D, 0.0f, stream);
+    const uint32_t nwords = (r.end + 15) / 16;
+    if (r.end != first)
+      for (uint32_t w = lane; w < nwords; w += kWave) {
+        uint32_t own = 0xffffffffu;
+        if (w == 0 && first != 0) own &= 0xffffffffu << (2 * first);
+        if (w == nwords - 1 && (r.end % 16) != 0) own &= ~(0xffffffffu << (2 * (r.end % 16)));
+        if (own == 0xffffffffu) out[w] = stream[w];
+        else if (held < 0.0f) atomicOr(&out[w], stream[w]);
+        else atomicXor(&out[w], (atomicOr(&out[w], 0u) ^ stream[w]) & own);
+      }
+    if (lane == 0) { a.ws_s2[slot] = r.s2; a.ws_c2[slot] = r.c2; }
+    return;
+  }
   const uint32_t* ind = a.ind_in + (int64_t)m * a.ind_stride;
   const float* g = a.g + (int64_t)m * a.g_stride;
-  uint32_t mask[4], incl[4];
-  float v[4][16];
+  uint32_t mask[4], at[4], open[4], any = 0, start = first;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int wl = j * 64 + lane;
@@ -768,56 +1045,54 @@ __global__ __launch_bounds__(kThreads) void gsel_quantize_multi_kernel(SelArgs a
     mask[j] = (iv >> (16 * (wl & 1))) & 0xFFFFu;
     const int64_t left = a.d - (tile * kTile + (int64_t)wl * 16);
     if (left < 16) mask[j] = left > 0 ? (mask[j] & ((1u << left) - 1u)) : 0u;
-    load16(g, a.d, tile * kTile + (int64_t)wl * 16, v[j]);
-    stream[wl] = 0u;
   }
-  if (lane < 2) stream[kTileWords + lane] = 0u;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) incl[j] = wave_inclusive_scan_u32((uint32_t)__popc(mask[j]));
-  const int64_t st = a.ws_start[(int64_t)m * a.ntiles + tile];
-  const int64_t k = tile / a.tiles_per_bucket;
-  const uint32_t first = (uint32_t)(st & 15);
-  const float Delta = a.ws_thr[(int64_t)m * a.nb + k];
-  __syncthreads();                                       // the zeroed streams are in LDS
-  double s2 = 0.0;
-  uint32_t c2 = 0, start = first;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const uint32_t n = (uint32_t)__popc(mask[j]);
-    const uint32_t before = start + incl[j] - n;
-    start += (uint32_t)__builtin_amdgcn_readlane((int)incl[j], kWave - 1);
-    uint32_t bits = 0, filled = 0;
+    const uint32_t n = (uint32_t)__popc(mask[j]), incl = wave_inclusive_scan_u32(n);
+    at[j] = start + incl - n;
+    start += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+    uint32_t lo = 0u, hi = 0u;
+    const uint32_t w0 = at[j] / 16, sh = 2 * (at[j] % 16);
+    if (n) lo = out[w0];
+    if (sh && 2 * n + sh > 32) hi = out[w0 + 1];
+    uint32_t bits = (lo >> sh) | (sh ? hi << (32 - sh) : 0u);
+    if (n < 16) bits &= (1u << (2 * n)) - 1u;
+    open[j] = (bits >> 1) & ~bits & 0x55555555u;         // low bit of every code 10
+    any |= open[j];
+  }
+  if (!__any(any != 0)) return;
+  const double s_before = a.ws_s2[slot];                 // the tile's sums, to be added to
+  const uint32_t c_before = a.ws_c2[slot];
+  double s = 0.0;
+  uint32_t c = 0;
+  while (__any(any != 0)) {                              // a code of every word at a time
+    any = 0;
+    float x[4];
+    uint32_t f[4];
 #pragma unroll
-    for (int c = 0; c < 16; ++c)
-      if ((mask[j] >> c) & 1u) {
-        const float av = fabsf(v[j][c]);
-        if (av > Delta) { s2 += (double)av; ++c2; }
-        bits |= ternary_field(v[j][c], Delta) << filled;
-        filled += 2;
+    for (int j = 0; j < 4; ++j) {
+      f[j] = open[j] ? (uint32_t)(__ffs((int)open[j]) - 1) / 2 : 16u;    // the f-th marked component
+      x[j] = 0.0f;
+      if (f[j] < 16u) {
+        uint32_t left = mask[j];
+        for (uint32_t q = 0; q < f[j]; ++q) left &= left - 1u;
+        x[j] = g[tile * kTile + (int64_t)(j * 64 + lane) * 16 + (__ffs((int)left) - 1)];
       }
-    if (n) {
-      const uint32_t w0 = before / 16, sh = 2 * (before % 16);
-      atomicOr(&stream[w0], bits << sh);
-      if (sh && 2 * n + sh > 32) atomicOr(&stream[w0 + 1], bits >> (32 - sh));
     }
-  }
-  const double S2 = wave_sum_f64(s2);
-  const uint32_t C2 = wave_sum_u32(c2);
-  __syncthreads();                                       // the streams are complete
-  if (exists) {
-    const uint32_t end = start, nwords = (end + 15) / 16;  // one past the tile's last code
-    uint32_t* out = a.sel_codes + (int64_t)m * a.code_stride + k * a.area_words + (st >> 4);
-    if (end != first)
-      for (uint32_t w = lane; w < nwords; w += kWave) {    // at most 257 words
-        const bool shared = (w == 0 && first != 0) || (w == nwords - 1 && (end % 16) != 0);
-        if (shared) atomicOr(&out[w], stream[w]);
-        else out[w] = stream[w];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (f[j] < 16u) {
+        const float av = fabsf(x[j]);
+        if (av > D) { s += (double)av; ++c; }
+        const uint32_t place = at[j] + f[j];
+        atomicXor(&out[place / 16], (2u ^ ternary_field(x[j], D)) << (2 * (place % 16)));
+        open[j] &= open[j] - 1u;
+        any |= open[j];
       }
-    if (lane == 0) {
-      a.ws_s2[(int64_t)m * a.ntiles + tile] = S2;
-      a.ws_c2[(int64_t)m * a.ntiles + tile] = C2;
-    }
   }
+  s = wave_sum_f64(s);
+  c = wave_sum_u32(c);
+  if (lane == 0 && c) { a.ws_s2[slot] = s_before + s; a.ws_c2[slot] = c_before + c; }
 }
 
 // last pass of the multi-tile quantizer: scale of each (bucket, worker)
@@ -835,6 +1110,14 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void gsel_scale_kernel(SelAr
   if (threadIdx.x == 0) a.scales[(int64_t)m * a.scale_stride + k] = scale_from_sum(s, (uint64_t)c);
 }
 
+// Buckets of at least 4096 tiles (64 samples) are quantized in one read if all workers have 2^29 coordinates
+// or more.  With a bracket it is the faster form from 2^26 on; without one (marks on components of very
+// unequal sizes, one mark or none per tile) its small launches come on top of two reads, and the line lies
+// where they are repaid by the rest.  Two reads / one read with a bracket / one read without, us:
+// 8 workers x 2^27 1744 / 1310 / 1549 to 1820 (the form before, with the longer scan: 1785, 1570 to 1732),
+// 8 x 2^25 450 / 363 / 417 to 482 (462, 408 to 444), 2 x 2^25 108 / 101, 2 x 2^24 59 / 63.
+constexpr int64_t kSelOneReadBucketTiles = 4096, kSelOneReadTiles = 131072;
+
 // Which kernels serve a layout's sparse messages.
 static SelKind sel_kind(const qa_layout* L) {
   if (L->bucket == kTile || (L->bucket == 0 && L->d <= kTile)) return kSelTile;   // the tuned kernels
@@ -843,8 +1126,17 @@ static SelKind sel_kind(const qa_layout* L) {
 }
 
 static inline size_t sel_align(size_t v) { return (v + 255) & ~size_t(255); }
-static inline dim3 zero_grid(const qa_layout* L) {
-  return dim3((unsigned)((tiles_of(L->d) + kZeroTiles - 1) / kZeroTiles), (unsigned)L->M);
+// zero: a producer of streams follows
+template <bool HAS_G>
+static void scan_launch(const SelArgs& a, int M, bool zero, hipStream_t stream) {
+  const dim3 buckets((unsigned)a.nb, (unsigned)M);
+  if (a.tiles_per_bucket <= kWave * kScanRun)
+    hipLaunchKernelGGL((gsel_scan_kernel<HAS_G, kWave>), buckets, dim3(kWave), 0, stream, a);
+  else
+    hipLaunchKernelGGL((gsel_scan_kernel<HAS_G, 1024>), buckets, dim3(1024), 0, stream, a);
+  if (zero)
+    hipLaunchKernelGGL(gsel_zero_kernel, dim3((unsigned)((a.ntiles + kThreads - 1) / kThreads), (unsigned)M),
+                       dim3(kThreads), 0, stream, a);
 }
 static inline dim3 count_grid(const qa_layout* L) {
   return dim3((unsigned)((tiles_of(L->d) + kWaves * kCountTiles - 1) / (kWaves * kCountTiles)), (unsigned)L->M);
@@ -980,12 +1272,22 @@ extern "C" int qa_quantize_pack_selected(const qa_layout* layout, const float* g
     return launch_status();
   }
   const dim3 buckets((unsigned)a.nb, (unsigned)layout->M);
-  hipLaunchKernelGGL(gsel_count_kernel, tiles, block, 0, stream, a);
-  hipLaunchKernelGGL(gsel_scan_kernel<true>, buckets, block, 0, stream, a);
-  hipLaunchKernelGGL(gsel_zero_kernel, zero_grid(layout), block, 0, stream, a);
-  hipLaunchKernelGGL(gsel_quantize_multi_kernel,
-                     dim3((unsigned)((tiles_of(layout->d) + kWaves - 1) / kWaves), (unsigned)layout->M),
-                     block, 0, stream, a);
+  const dim3 waves((unsigned)((a.ntiles + kWaves - 1) / kWaves), (unsigned)layout->M);
+  a.samples = a.tiles_per_bucket / kSelSampleEvery;
+  if (a.tiles_per_bucket >= kSelOneReadBucketTiles && a.ntiles >= kSelOneReadBucketTiles &&
+      a.ntiles * layout->M >= kSelOneReadTiles && a.nb * a.samples <= 0x7fffffffLL) {
+    hipLaunchKernelGGL(gsel_count_ind_kernel, count_grid(layout), block, 0, stream, a);
+    scan_launch<false>(a, layout->M, true, stream);
+    hipLaunchKernelGGL(gsel_sample_kernel, dim3((unsigned)(a.nb * a.samples), (unsigned)layout->M), block, 0, stream, a);
+    hipLaunchKernelGGL(gsel_band_kernel, buckets, block, 0, stream, a);
+    hipLaunchKernelGGL(gsel_quantize_multi_kernel<true>, waves, block, 0, stream, a);
+    hipLaunchKernelGGL(gsel_threshold_kernel, buckets, block, 0, stream, a);
+    hipLaunchKernelGGL(gsel_settle_kernel, waves, block, 0, stream, a);
+  } else {
+    hipLaunchKernelGGL(gsel_count_kernel, tiles, block, 0, stream, a);
+    scan_launch<true>(a, layout->M, true, stream);
+    hipLaunchKernelGGL(gsel_quantize_multi_kernel<false>, waves, block, 0, stream, a);
+  }
   hipLaunchKernelGGL(gsel_scale_kernel, buckets, block, 0, stream, a);
   return launch_status();
 }
@@ -1018,7 +1320,7 @@ int decode_selected_launch(const qa_layout* layout, const uint32_t* ind, int64_t
   // the workspace (unused by a decode) take it, M*nb <= M*ntiles words
   a.counts = a.ws_c2; a.scale_stride = a.nb;
   hipLaunchKernelGGL(gsel_count_ind_kernel, count_grid(layout), block, 0, stream, a);
-  hipLaunchKernelGGL(gsel_scan_kernel<false>, dim3((unsigned)a.nb, (unsigned)layout->M), block, 0, stream, a);
+  scan_launch<false>(a, layout->M, false, stream);
   hipLaunchKernelGGL(decode_selected_kernel<kSelMulti>, wave_tiles, block, 0, stream, a);
   return launch_status();
 }
@@ -1067,8 +1369,7 @@ extern "C" int qa_select_codes(const qa_layout* layout, const uint32_t* codes, c
     return launch_status();
   }
   hipLaunchKernelGGL(gsel_count_ind_kernel, count_grid(layout), block, 0, stream, a);
-  hipLaunchKernelGGL(gsel_scan_kernel<false>, dim3((unsigned)a.nb, (unsigned)layout->M), block, 0, stream, a);
-  hipLaunchKernelGGL(gsel_zero_kernel, zero_grid(layout), block, 0, stream, a);
+  scan_launch<false>(a, layout->M, true, stream);
   hipLaunchKernelGGL(select_codes_kernel<kSelMulti>, wave_tiles, block, 0, stream, a);
   return launch_status();
 }

@@ -150,6 +150,56 @@ def test_quantize_selected_and_decode_match_oracle(d, M, bucket, p):
         assert np.array_equal(host(dense).view(np.uint32)[m, :W], oracle.decode_selected(ind[m], o_sel, d, bucket=bucket))
 
 
+def long_selection(kind, d, rng):
+    """A gradient and the marks on it, for buckets that are quantized in one read."""
+    g = (rng.standard_normal(d, dtype=np.float32) * np.float32(1e-2))
+    p = {"all": 1.0, "none": 0.0, "few": 1e-5}.get(kind, 0.2)
+    marks = rng.random(d, dtype=np.float32) < p
+    if kind == "misled":                                 # the tiles that are sampled are ten times smaller
+        tile = np.arange(d) // 4096
+        g[tile // 64 * 64 + (tile // 64 * 29) % 64 == tile] *= np.float32(0.1)
+    elif kind == "outliers":                             # no bracket
+        g[::100003] *= np.float32(1e6)
+    marks = np.concatenate([marks, np.zeros(-d % 32, bool)])
+    return g, np.packbits(marks, bitorder="little").view(np.uint32)
+
+
+@pytest.mark.parametrize("kinds,d,bucket", [(("plain", "misled", "few", "all"), (1 << 24) + 4099, 0),
+                                            (("plain", "outliers", "none"), (1 << 24) + 20001, 1 << 24)])
+def test_long_selected_buckets_read_once_match_oracle(kinds, d, bucket):
+    """2^24 coordinates and more per bucket, 2^29 in all: marked components inside the bracket of the sample
+    settled, and whole tiles coded once more where it missed or the sample gave none (a short last bucket)."""
+    rng = np.random.default_rng(len(kinds))
+    M, n = 32, len(kinds)                                # worker m's message is that of kind m % n
+    rows = [long_selection(k, d, rng) for k in kinds]
+    L = qa.Layout.make(d, M, bucket)
+    nb, NW, gs = L.n_buckets, (d + 31) // 32, (d + 3) // 4 * 4
+    g = torch.zeros((M, gs), dtype=torch.float32, device=DEV)
+    ind = torch.empty((M, NW), dtype=torch.int32, device=DEV)
+    for k, (gk, ik) in enumerate(rows):
+        g[k::n, :d] = dev(gk)
+        ind[k::n] = dev(ik.view(np.int32))
+    sel = torch.full((M, L.code_stride), 0x5A5A5A5A, dtype=torch.int32, device=DEV)
+    cnt = torch.zeros((M, nb), dtype=torch.int32, device=DEV)
+    sc, th = torch.full((2, M, nb), -1.0, dtype=torch.float32, device=DEV)
+    qa.qa_quantize_pack_selected(L, g, gs, ind, NW, sel, cnt, sc, th, workspace(qa.qa_workspace_bytes(L, qa.QA_OP_SELECT)))
+    torch.cuda.synchronize()
+    for m in range(n, M):
+        for x in (sel, cnt, sc, th):
+            assert torch.equal(x[m], x[m % n])
+    area = area_words(d, bucket)
+    for m, (gk, ik) in enumerate(rows):
+        o_sel, o_cnt, o_sc, o_th = oracle.quantize_selected(gk, ik, bucket=bucket)
+        assert np.array_equal(host(cnt)[m].view(np.uint32), o_cnt)
+        # sums of 2^24 magnitudes in binary64 (relative error 2^-29), rounded to binary32 once
+        assert np.all(np.abs(host(th)[m] - o_th) <= np.spacing(o_th)) and np.all(np.abs(host(sc)[m] - o_sc) <= np.spacing(o_sc))
+        sel_h = host(sel[m]).view(np.uint32)
+        for k in range(nb):
+            nwk, lo = (int(o_cnt[k]) + 15) // 16, k * area
+            assert np.array_equal(sel_h[lo: lo + nwk], o_sel[lo: lo + nwk]), (kinds[m], k)
+            assert np.all(sel_h[lo + nwk: min(lo + area, L.code_stride)] == 0x5A5A5A5A)
+
+
 @pytest.mark.parametrize("shared", [False, True])
 @pytest.mark.parametrize("d,M,bucket,p", [(1, 1, 0, 1.0), (1000, 2, 0, 0.3), (4096, 1, 4096, 0.5),
                                           (4097, 2, 4096, 0.02), (70001, 3, 4096, 0.2),
