@@ -1001,7 +1001,7 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void gsel_threshold_kernel(S
   }
 }
 
-// A wave per tile: the time is the chain of dependent loads (8 workers x 2^27: 164 us; two tiles per wave,
+// A wave per tile: the time is the chain of dependent loads (8 workers x 2^27: 164 to 183 us; two tiles per wave,
 // their loads phase by phase, 190, four 336: their registers cost more waves than that saves).  With a
 // bracket that held: each lane reads its words' codes back from the stream, finds the pattern 10, and
 // exchanges it for the component's code in place.  Without a bracket the tile is coded here, and with one
