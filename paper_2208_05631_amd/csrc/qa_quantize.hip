@@ -1629,6 +1629,9 @@ int quantize_launch(const qa_layout* L, const float* g, int64_t g_stride, uint32
     char* p = static_cast<char*>(ws) + need;
     a.kept_sum = reinterpret_cast<double*>(p);
     a.band = reinterpret_cast<float2*>(p + align256((size_t)L->M * a.ntiles * sizeof(double)));
+    // the tiles that the vector has: a bucket may be nominally far longer, and the settling pass leaves a
+    // sum and a count per work-group of its grid in the place of the tile sums
+    if (a.tiles_per_bucket > a.ntiles) a.tiles_per_bucket = a.ntiles;
     a.samples = a.tiles_per_bucket / kSampleEvery;
     a.settle_groups = (a.tiles_per_bucket + kSettleTiles - 1) / kSettleTiles;
     if (a.nb * a.samples <= 0x7fffffffLL && a.nb * a.settle_groups <= 0x7fffffffLL) {

@@ -764,6 +764,31 @@ def test_quantizer_of_long_buckets_matches_oracle(kinds, d, bucket):
     assert int(ulp_distance(host(scales)[:, :nb], s[:, :nb]).max()) <= 1
 
 
+@pytest.mark.parametrize("bucket", [1 << 25, 1 << 27, 1 << 30])
+def test_quantizer_of_a_bucket_far_longer_than_the_vector(bucket):
+    """A bucket size beyond the vector's length means one bucket: the same message as with one scale per vector,
+    bit for bit, and nothing written outside the workspace."""
+    d, M, guard = (1 << 24) + 4099, 2, 1 << 20
+    rng = np.random.default_rng(5)
+    gs = (d + 3) // 4 * 4
+    g = torch.zeros((M, gs), dtype=torch.float32, device=DEV)
+    g[:, :d] = dev(rng.standard_normal((M, d), dtype=np.float32))
+    messages = []
+    for b in (0, bucket):
+        L = qa.Layout.make(d, M, b)
+        assert L.n_buckets == 1
+        size = qa.qa_workspace_bytes(L, qa.QA_OP_QUANTIZE)
+        ws = torch.full((size + guard,), 0xA5, dtype=torch.uint8, device=DEV)
+        codes = torch.full((M, L.code_stride), -1, dtype=torch.int32, device=DEV)
+        sc, th = torch.zeros((2, M, 1), dtype=torch.float32, device=DEV)
+        qa.qa_quantize_pack(L, g, gs, codes, sc, th, 0, ws[:size])
+        torch.cuda.synchronize()
+        assert bool((ws[size:] == 0xA5).all())
+        messages.append((codes[:, :L.words], sc, th))
+    for a, b in zip(*messages):
+        assert torch.equal(a, b)
+
+
 # ---- exact least-squares threshold by ranking (Section 3.4) ------------------------------------
 
 @pytest.mark.parametrize("d,M,bucket", [(4096, 1, 0), (1000, 2, 0), (3, 1, 0), (4096 * 5, 3, 4096),
