@@ -350,6 +350,7 @@ __global__ __launch_bounds__(kThreads) void seg_settle_kernel(SegQuantArgs a) {
       a.part_sum[row + piece0 + t] = t == u0 ? (lds_d[0] + lds_d[1]) + (lds_d[2] + lds_d[3]) : 0.0;
       a.part_cnt[row + piece0 + t] = t == u0 ? lds_u[0] + lds_u[1] + lds_u[2] + lds_u[3] : 0u;
     }
+    __syncthreads();                                     // the waves' sums have been read: the next run may write its own
     u0 = u1;
   }
 }

@@ -208,6 +208,39 @@ def test_long_tensors_read_once_match_oracle(M):
         close(host(a)[f_covered(f)], r[f_covered(f)], "state")
 
 
+def test_long_tensors_ending_at_every_place_of_a_work_group():
+    """Long tensors (read once, settled eight pieces at a time) with one-piece tensors behind them, which the
+    same work-group codes right after it has summed what the long one keeps: the boundary at each of the
+    eight places.  Several calls give the same bits (sums in a fixed order)."""
+    lengths = []
+    for k in range(8):
+        lengths += [1024 * 4096, 100 + k]
+    # every tensor starts on a tile of its own, so that its pieces are whole tiles
+    begin = np.cumsum([0] + [-(-n // 4096) * 4096 for n in lengths])
+    f = Flat.__new__(Flat)
+    f.begin, f.length, f.d = begin[:-1].astype(np.int64), np.array(lengths, np.int64), int(begin[-1])
+    f.M, f.nseg = 4, len(lengths)
+    f.L = qa.Layout.make(f.d, f.M, 0, 0.75, None, f.nseg)
+    f.table = torch.zeros(qa.qa_segment_plan_bytes(f.d, f.nseg), dtype=torch.uint8, device=DEV)
+    f.plan = qa.qa_segment_plan_init(f.d, f.begin, f.length, f.table)
+    f.gs = f.d
+    assert f.plan.n_pieces * f.M >= 32768
+    ends = {int((b + n - 1) // 4096) % 8 for b, n in zip(f.begin, f.length) if n > 4096}
+    assert ends == set(range(8))
+    g = np.random.default_rng(3).standard_normal((f.M, f.d), dtype=np.float32)
+    c_ref, s_ref, th_ref = oracle.quantize_pack_segments(g, f.begin, f.length)
+    first = None
+    for _ in range(4):
+        codes, scales, th = f.gpu_quantize(g)
+        if first is None:
+            first = codes, scales, th
+            # sums in another order: an ulp
+            assert np.allclose(host(th), th_ref, rtol=1.3e-7, atol=0)
+            assert np.allclose(host(scales), s_ref, rtol=1.3e-7, atol=0)
+        for a, b in zip(first, (codes, scales, th)):
+            assert torch.equal(a, b)
+
+
 def f_covered(f):
     covered = np.zeros(f.d, bool)
     for b, n in zip(f.begin, f.length):
