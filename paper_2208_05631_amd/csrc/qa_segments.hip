@@ -249,7 +249,12 @@ __global__ __launch_bounds__(kThreads) void seg_bracketed_kernel(SegQuantArgs a)
 #pragma unroll
     for (int e = 1; e < 4; ++e) s1[j] += (double)fabsf(v[j][e]);
   }
-  if (band.x >= 0.0f) {
+  if (!(band.x >= 0.0f)) {                               // uniform; the settling pass codes the piece
+    const double S1 = block_sum_f64((s1[0] + s1[1]) + (s1[2] + s1[3]), lds_s1);
+    if (t == 0) a.part_sum[(int64_t)m * a.seg.n_pieces + p] = S1;
+    return;
+  }
+  {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       uint32_t b = 0;
@@ -363,13 +368,17 @@ size_t quantize_segments_workspace_bytes(const qa_segment_plan* P, int M) {
          align256((size_t)M * (size_t)P->n_seg * sizeof(float));
 }
 
-// What the one-read form needs on top of it, 0 where it is not taken: the length of the longest tensor is
-// known on the device only, so it has to pay on large lists or cost little: from 2^27 components on.
-// 32 tensors, 58.4 M parameters, most of them in two tensors: 680 -> 500 us with 8 workers, 338 -> 250 with
-// 4; 64 tensors, 30 M parameters, 8 workers: 348 -> 346.
-constexpr int64_t kSegOneReadPieces = 32768;
+// What the one-read form needs on top of it, 0 where it is not taken.  The length of the longest tensor is
+// known on the device only, so the form has to pay where there are long tensors and cost little where
+// there are none: from 2^27 components on and with 128 pieces per tensor on average.  At that limit
+// (32768 pieces in all workers together), two reads -> one, us: 1 worker x 8 tensors of 4096 pieces 193 -> 143,
+// 8 x 4 of 1024 193 -> 152; 32 tensors, 58.4 M parameters, most of them in two tensors, 3 workers 250 -> 191,
+// 8 workers 641 -> 455.  No long tensor: 1 x 64 of 1000 pieces 364 -> 372, 2 x 64 of 500 359 -> 374 (two
+// launches more, and each piece is coded in the settling pass).  Below the average, where the bracket's
+// work-group per tensor counts: 8 x 64 of 64 190 -> 203, 4 x 2000 of 5 271 -> 311, 40000 of one or two 551 -> 755.
+constexpr int64_t kSegOneReadPieces = 32768, kSegOneReadMean = 128;
 size_t segments_one_read_bytes(const qa_segment_plan* P, int M) {
-  if (P->n_pieces < kSegLong || P->n_pieces * M < kSegOneReadPieces) return 0;
+  if (P->n_pieces < kSegLong || P->n_pieces * M < kSegOneReadPieces || P->n_pieces < kSegOneReadMean * P->n_seg) return 0;
   return align256((size_t)M * (size_t)P->n_pieces * sizeof(double)) + align256((size_t)M * (size_t)P->n_seg * sizeof(float2));
 }
 

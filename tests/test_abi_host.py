@@ -158,6 +158,16 @@ def _plan_host(d, begin, length):
     return rc, npieces.value, list(table)
 
 
+@pytest.mark.parametrize("n_seg,n_pieces,M,one_read", [(32, 14279, 8, True), (32, 14279, 2, False), (8, 32768, 1, True),
+                                                       (256, 32768, 1, True), (257, 32768, 1, False),
+                                                       (2000, 10000, 4, False), (40000, 75937, 1, False)])
+def test_tensor_lists_of_short_tensors_keep_the_workspace_of_two_reads(n_seg, n_pieces, M, one_read):
+    """Lists of many short tensors do not ask for the one-read form's 8 bytes per piece and worker."""
+    need = qa.qa_segment_workspace_bytes(B.SegmentPlan(n_pieces * 4096, n_seg, n_pieces, FAKE), M, qa.QA_OP_QUANTIZE)
+    two_reads = sum((v + 255) // 256 * 256 for v in (M * n_pieces * 8, M * n_pieces * 4, M * n_seg * 4))
+    assert need - two_reads >= M * n_pieces * 8 if one_read else need == two_reads
+
+
 def test_segment_table_against_a_python_reference():
     """The piece table (built on the host, the same words that are copied to the device): every
     (4096-tile, tensor) intersection exactly once, in order, for seeded random tensor lists."""
