@@ -28,6 +28,12 @@ constexpr int kShortRow = 512;
 // work-groups) 16.6 us against 19.0; 2 x 256 rows of 30000 (236) 27.3 against 25.9.
 constexpr int kFewGroups = 192;
 
+static constexpr size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
+static constexpr size_t workspace_of(int64_t d, bool csr) {
+  return align256((size_t)kMaxBatch * sizeof(float)) + align256((size_t)kMaxBatch * sizeof(double)) +
+         (csr ? align256((size_t)d * sizeof(double)) : 0);
+}
+
 struct GradArgs {
   const float* A;            // dense matrix or CSR values
   const int64_t* indptr;
@@ -327,6 +333,11 @@ constexpr int kBinThreads = 256, kMaxRanges = 256, kMaxGroups = 64, kRowLanes = 
 constexpr int kMinLogWidth = 8, kMaxLogWidth = 14;
 constexpr uint32_t kOverflow = 0xffffffffu;
 
+// more entries than a worker's part of the workspace can hold
+constexpr int64_t max_entries() {
+  return (int64_t)(workspace_of(int64_t(kMaxRanges) << kMaxLogWidth, true) / sizeof(uint2));
+}
+
 struct BinArgs {
   uint32_t* table;           // [groups][ranges + 1], first range's entry kOverflow if the group did not fit
   uint2* entries;            // [groups][capacity]: value bits, batch row << 14 | column in range
@@ -391,6 +402,7 @@ __global__ __launch_bounds__(kBinThreads) void csr_bin_kernel(GradArgs a_all, Bi
   double s = 0.0;
   bool ok = false;
   float label = 0.0f;
+  int64_t listed = 0;                                    // entries of the team's rows, whatever their columns
   const auto row_bounds = [&](int i) {
     const int64_t r = i < last ? a.rows[i] : -1;
     ok = r >= 0 && r < a.n_rows;
@@ -423,6 +435,7 @@ __global__ __launch_bounds__(kBinThreads) void csr_bin_kernel(GradArgs a_all, Bi
   };
   if (ONE_ROW) {
     row_bounds(first + team);
+    listed = k1 - k0;
     for (int64_t k = k1 - k0 > kStep ? k0 + kStep + lane : k1; k < k1; k += kStep) {       // beyond the first chunk
       load_chunk(a, k, k1, q);
       count_chunk(false);
@@ -433,6 +446,7 @@ __global__ __launch_bounds__(kBinThreads) void csr_bin_kernel(GradArgs a_all, Bi
   } else {
     for (int i = first + team; i < last; i += kTeams) {
       row_bounds(i);
+      listed += k1 - k0;
       s = 0.0;
       for (int64_t k = k0 + lane; k < k1; k += kStep) {
         load_chunk(a, k, k1, q);
@@ -451,7 +465,11 @@ __global__ __launch_bounds__(kBinThreads) void csr_bin_kernel(GradArgs a_all, Bi
     const uint32_t o = __shfl_up(incl, off, kWave);
     if (t % kWave >= off) incl += o;
   }
-  if (t % kWave == kWave - 1) wave_total[t / kWave] = incl;
+  // The counters are 32 bits wide: they hold the group's entries as long as no team alone has more than the
+  // group's part of the workspace takes, and a group with such a team does not fit in any case.
+  static_assert(kTeams * (max_entries() + 1) < (int64_t(1) << 32), "a group that passes the test cannot wrap its counters");
+  const bool too_many = __any(listed > (int64_t)b.capacity);
+  if (t % kWave == kWave - 1) wave_total[t / kWave] = too_many ? b.capacity + 1u : incl;
   __syncthreads();
   uint32_t before = incl - mine, total = 0;
 #pragma unroll
@@ -598,12 +616,7 @@ __global__ __launch_bounds__(kThreads) void loss_finalize_kernel(GradArgs a_all)
   reduce_loss(a, lds_d);
 }
 
-static inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
-
-size_t grad_workspace_bytes(int64_t d, bool csr) {
-  return align256((size_t)kMaxBatch * sizeof(float)) + align256((size_t)kMaxBatch * sizeof(double)) +
-         (csr ? align256((size_t)d * sizeof(double)) : 0);
-}
+size_t grad_workspace_bytes(int64_t d, bool csr) { return workspace_of(d, csr); }
 
 // The two-launch form for CSR rows; false if the vector is too long for its ranges.  A worker's part of
 // the workspace holds [coefficients][losses][table][entries]: grad_workspace_bytes counts the first two

@@ -499,6 +499,30 @@ def test_local_grad_csr_across_the_column_ranges(d, n, B, M, nnz):
                 assert np.allclose(gg[m, :d], og * (keep.sum() / B), rtol=1e-5, atol=1e-6 * np.abs(og).max())
 
 
+def test_local_grad_csr_with_2_to_the_32_entries_in_sixteen_rows():
+    """Sixteen times the same row of 2^28 entries (columns repeat): as many entries as a 32-bit counter has
+    values, which must not look like none.  All values equal, so that the gradient is known."""
+    d, n, B = 300, 1 << 28, 16
+    idx = torch.arange(n, device=DEV, dtype=torch.int32).remainder_(d)
+    vals = torch.full((n,), 2.0 ** -20, dtype=torch.float32, device=DEV)
+    x = dev(np.random.default_rng(1).standard_normal(d).astype(np.float32) * 0.01)
+    L = qa.Layout.make(d, 1, 0)
+    size, guard = qa.qa_workspace_bytes(L, qa.QA_OP_GRAD_CSR), 1 << 20
+    ws = torch.full((size + guard,), 0xA5, dtype=torch.uint8, device=DEV)
+    g, loss = torch.zeros(d, dtype=torch.float32, device=DEV), torch.zeros(1, dtype=torch.float32, device=DEV)
+    qa.qa_local_grad(qa.QA_CSR, vals, dev(np.array([0, n], np.int64)), idx, 1, d, dev(np.ones(1, np.float32)),
+                     dev(np.zeros(B, np.int32)), B, x, g, loss, ws[:size])
+    torch.cuda.synchronize()
+    assert bool((ws[size:] == 0xA5).all())
+    per_column = np.bincount(np.arange(n % d), minlength=d) + n // d
+    row = per_column * 2.0 ** -20
+    p = np.float32(row @ host(x).astype(np.float64))
+    coef = np.float32(-1.0 / (1.0 + np.exp(np.float64(p))) / B)
+    # 2^32 / d additions in binary64 and the rounding of coef and g to binary32
+    assert np.allclose(host(g), B * float(coef) * row, rtol=1e-6)
+    assert host(loss)[0] == pytest.approx(np.log1p(np.exp(-np.float64(p))), rel=1e-6)
+
+
 @pytest.mark.parametrize("csr,shape", [(False, (400, 3000, 30, 48, 5)), (True, (400, 3000, 30, 48, 5)),
                                        # large batches, heavy collisions on a few columns, a ragged last row group
                                        (True, (600, 5000, 30, 301, 7)), (True, (600, 1500, 20, 256, 8))])
