@@ -8,9 +8,10 @@
 //                       accumulators;
 //              CSR   -- the batch's entries are sorted into ranges of columns while the margins are
 //                       formed, and a work-group per range adds them up in LDS and writes its part
-//                       of g; vectors of more than 2^22 columns take hardware binary64 atomic adds
-//                       into a d-long accumulator that is cleared only at the batch's columns, then
-//                       rounded into the zero-filled g.
+//                       of g; vectors of more than 2^22 columns, and batches of too many rows for
+//                       the workspace, take hardware binary64 atomic adds into a d-long accumulator
+//                       that is cleared only at the batch's columns, then rounded into the
+//                       zero-filled g.
 //   Every product coef*a is exact in binary64, so only the order of the binary64 additions can
 //   differ from a sequential evaluation.
 #include "qa_common.h"
@@ -317,9 +318,9 @@ __global__ __launch_bounds__(kThreads) void csr_scatter_kernel(GradArgs a_all) {
 //               coefficient * value into 2^LOGW binary64 accumulators in LDS and writes its part of g
 //               in one piece, zeros included.
 //
-// A group whose entries do not fit its part of the workspace (their number is known on the device
-// only; all groups of a worker together have room for some 98 000 + d entries) leaves a mark, and
-// csr_gather reads the group's rows themselves and takes what lies in its range.
+// A group whose entries do not fit its part of the workspace (all groups of a worker together have room for
+// some 98 000 + d entries) leaves a mark, and csr_gather reads the group's rows themselves and takes what
+// lies in its range.
 //
 // Ranges are as narrow as 256 of them allow (a counter per thread of csr_bin's work-group), at least 256
 // columns, at most 16384 (128 KiB of LDS): narrow ones are more work-groups on short vectors (4 x 300
@@ -332,6 +333,18 @@ __global__ __launch_bounds__(kThreads) void csr_scatter_kernel(GradArgs a_all) {
 constexpr int kBinThreads = 256, kMaxRanges = 256, kMaxGroups = 64, kRowLanes = 16;
 constexpr int kMinLogWidth = 8, kMaxLogWidth = 14;
 constexpr uint32_t kOverflow = 0xffffffffu;
+// The number of entries is known on the device only, so the line is drawn by the rows: the form is taken while
+// the groups have room for kRowEntries entries per row (or for every column).  Without that line a
+// batch that did not fit was read again by each of up to 256 ranges, in us, atomic form / no line / now:
+// 1 x 65536 rows x 100, d = 2^20 787 / 3347 / 787; 4 of them 2660 / 5186 / 2668; 1 x 65536 x 50, d = 4096
+// 627 / 4086 / 625; 8 x 4096 x 100, d = 2^17 302 / 528 / 302; 1 x 1700 x 200 there 53 / 123 / 52; and what is
+// given up: 8 x 1700 x 100 there 132 / 34 / 132.  8 x 8192 x 100, d = 2^20 is just on this side: 631 / 117 / 120.
+// Longer rows that overflow nevertheless cost up to twice the atomic form with one worker and 1.3 times with
+// eight: 1 x 256 x 2000, d = 2^17 81 -> 157, 8 workers 267 -> 325; 1 x 8192 x 200, d = 2^20 194 -> 390.
+// With room for less than kWideGather per row the gathering work-groups have 1024 threads, which reading again takes
+// less ill (1 x 4096 x 1000, d = 2^20 981 -> 620; 2003 columns, 1 x 384 x 500 58 -> 40, 8 workers 91 -> 60);
+// else 512 (16 x 256 x 100, d = 2^20 27.5 against 33.4).
+constexpr int64_t kRowEntries = 128, kWideGather = 512;
 
 // more entries than a worker's part of the workspace can hold
 constexpr int64_t max_entries() {
@@ -515,11 +528,10 @@ __global__ __launch_bounds__(kBinThreads) void csr_bin_kernel(GradArgs a_all, Bi
   }
 }
 
-template <int LOGW> constexpr int gather_threads() { return LOGW >= 14 ? 1024 : 512; }
 
-template <int LOGW>
-__global__ __launch_bounds__(gather_threads<LOGW>()) void csr_gather_kernel(GradArgs a_all, BinArgs b_all) {
-  constexpr int kWidth = 1 << LOGW, kThr = gather_threads<LOGW>(), kTeams = kThr / kRowLanes;
+template <int LOGW, int THREADS>
+__global__ __launch_bounds__(THREADS) void csr_gather_kernel(GradArgs a_all, BinArgs b_all) {
+  constexpr int kWidth = 1 << LOGW, kThr = THREADS, kTeams = kThr / kRowLanes;
   const GradArgs a = for_worker(a_all);
   const BinArgs b = for_worker(b_all);
   __shared__ double acc[kWidth];
@@ -618,7 +630,8 @@ __global__ __launch_bounds__(kThreads) void loss_finalize_kernel(GradArgs a_all)
 
 size_t grad_workspace_bytes(int64_t d, bool csr) { return workspace_of(d, csr); }
 
-// The two-launch form for CSR rows; false if the vector is too long for its ranges.  A worker's part of
+// The two-launch form for CSR rows; false if the vector is too long for its ranges or the batch has too many
+// rows for the workspace.  A worker's part of
 // the workspace holds [coefficients][losses][table][entries]: grad_workspace_bytes counts the first two
 // for the largest batch, so some 98 000 entries fit beside the d of the accumulator.
 static bool csr_launch(GradArgs a, int M, hipStream_t stream) {
@@ -641,14 +654,20 @@ static bool csr_launch(GradArgs a, int M, hipStream_t stream) {
   b.entries = reinterpret_cast<uint2*>(base + at);
   const size_t room = ((size_t)a.ws_stride_bytes - at) / sizeof(uint2) / (size_t)b.groups;
   b.capacity = room < (size_t)kOverflow ? (uint32_t)room : kOverflow - 1u;
+  const int64_t per_row = (int64_t)b.capacity / b.rows_per_group;
+  if (per_row < (a.d < kRowEntries ? a.d : kRowEntries)) return false;
+  const bool wide = log_width >= 14 || per_row < kWideGather;
   b.ws_stride_bytes = a.ws_stride_bytes;
   const dim3 grid((unsigned)b.ranges + (a.loss_out ? 1u : 0u), (unsigned)M), groups((unsigned)b.groups, (unsigned)M);
   if (b.rows_per_group == teams) hipLaunchKernelGGL(csr_bin_kernel<true>, groups, dim3(kBinThreads), 0, stream, a, b);
   else hipLaunchKernelGGL(csr_bin_kernel<false>, groups, dim3(kBinThreads), 0, stream, a, b);
   switch (log_width) {
-#define QA_GATHER(w) \
-    case w: hipLaunchKernelGGL(csr_gather_kernel<w>, grid, dim3(gather_threads<w>()), 0, stream, a, b); break
-    QA_GATHER(8); QA_GATHER(9); QA_GATHER(10); QA_GATHER(11); QA_GATHER(12); QA_GATHER(13); QA_GATHER(14);
+#define QA_GATHER(w, threads) hipLaunchKernelGGL((csr_gather_kernel<w, threads>), grid, dim3(threads), 0, stream, a, b)
+#define QA_GATHER_EITHER(w) case w: if (wide) QA_GATHER(w, 1024); else QA_GATHER(w, 512); break
+    QA_GATHER_EITHER(8); QA_GATHER_EITHER(9); QA_GATHER_EITHER(10);
+    QA_GATHER_EITHER(11); QA_GATHER_EITHER(12); QA_GATHER_EITHER(13);
+    case 14: QA_GATHER(14, 1024); break;
+#undef QA_GATHER_EITHER
 #undef QA_GATHER
     default: return false;
   }

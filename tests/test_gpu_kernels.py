@@ -448,7 +448,11 @@ def test_local_grad_csr_matches_oracle():
                                          ((1 << 21) + 1, 100, 33, 1, 50), (1 << 22, 64, 64, 1, 20),
                                          ((1 << 22) + 1, 64, 64, 1, 20),
                                          # no group, and about half of the groups, without room
-                                         (1025, 300, 400, 2, 600), (900, 200, 300, 1, 330)])
+                                         (1025, 300, 400, 2, 600), (900, 200, 300, 1, 330),
+                                         # batches just within the rows that the form takes, and just beyond them
+                                         (4099, 300, 750, 2, 100), (4099, 300, 820, 2, 100), (70000, 300, 1200, 1, 150),
+                                         (200000, 300, 2000, 1, 60), (300000, 300, 2800, 1, 60), (1 << 20, 400, 8192, 1, 40),
+                                         (1 << 21, 400, 16000, 1, 40), (1 << 21, 400, 17000, 1, 40)])
 def test_local_grad_csr_across_the_column_ranges(d, n, B, M, nnz):
     """Lengths around every width of the column ranges and the last one that takes them, batches with more
     entries than the workspace has room for (read again from the rows), rows of different lengths (also
