@@ -162,8 +162,9 @@ int qa_local_grad_batched(int format, const float* A_or_vals, const int64_t* ind
  * up to 4096 components are searched inside one wave or work-group; longer buckets, and one threshold for
  * a vector of more than 4096 components (Section 3.4's optimum over the whole gradient), are
  * found by refining histograms of the magnitudes, in 17 bytes of workspace per component
- * (d < 2^32, else QA_ERR_TOO_LARGE); the call only enqueues kernels.  A bucket with non-finite
- * components gets the threshold 0 there.  Candidates whose objectives agree to binary64 rounding
+ * (d < 2^32, else QA_ERR_TOO_LARGE); the call only enqueues kernels.  Of a bucket with
+ * infinite components these alone are kept (the objective is infinite from the first on); a NaN
+ * gives the threshold 0.  Candidates whose objectives agree to binary64 rounding
  * (likely only beyond some 1e7 components per bucket) may be resolved differently from a
  * strictly sequential summation.
  * g_stride >= d and a multiple of 4.  ws: qa_workspace_bytes(layout, QA_OP_QUANTIZE), or

@@ -26,7 +26,7 @@
 // rounding may be resolved differently from a strictly sequential summation (likely only beyond some
 // 1e7 components per bucket; both kept sets are then optimal to that resolution).  A bucket that
 // more than 2048 bins or five levels leave open (an objective constructed to be flat) is sorted by one
-// work-group behind the levels.  Non-finite members give the threshold 0.
+// work-group behind the levels.  Infinite members are kept alone, a NaN gives the threshold 0.
 //
 // Measured against a device-wide radix sort with four passes behind it (2^26 x 4 Gaussian components,
 // thresholds and codes): one threshold per vector 6660 -> 850 us (three reads of the gradient at
@@ -154,13 +154,13 @@ __device__ __forceinline__ ScanResult scan_level(LevelShape* shape, bool first, 
   for (int i = 0; i < kPerThread; ++i) {
     const int pos = kPerThread * t + i;
     low[i] = pos < nbins ? lower_end(s, lds.ranges.lo, pos) : 0u;
-    odd |= c[i] != 0 && low[i] >= kNonFinite;
+    odd |= c[i] != 0 && (low[i] > kNonFinite || (low[i] == kNonFinite && off[i] != 0));
     sum[i] = c[i] ? fma((double)off[i], ulp_of(low[i]), (double)c[i] * (double)__uint_as_float(low[i])) : 0.0;
     cnt += c[i];
     mine += sum[i];
   }
   if (t == 0) lds.threshold_bits = 0u;
-  if (__syncthreads_or(odd)) return kScanDone;           // non-finite members (all in level 0)
+  if (__syncthreads_or(odd)) return kScanDone;           // NaN members (all in level 0)
   uint32_t total_cnt;
   double total_sum;
   uint32_t k_run = scan_exclusive(cnt, lds.wave_u, &total_cnt);
@@ -225,11 +225,12 @@ __device__ __forceinline__ ScanResult scan_level(LevelShape* shape, bool first, 
       best = lds.best_obj[w]; best_k = lds.best_k[w]; best_pos = lds.best_pos[w];
     }
   const double bar = best * (1.0 - 1e-11);               // far above the rounding of the binary64 sums
+  const bool infinite = best > 1e300;                    // infinite members: they alone are kept (the smallest k)
   uint32_t survives = 0;
   int last = 0;                                          // 1 + position of this thread's last filled bin
 #pragma unroll
   for (int i = 0; i < kPerThread; ++i) {
-    if (edge[i] >= bar || inner[i] >= bar) survives |= 1u << i;
+    if (infinite ? kPerThread * t + i == best_pos : edge[i] >= bar || inner[i] >= bar) survives |= 1u << i;
     if (c[i]) last = kPerThread * t + i + 1;
   }
   lds.survives[t] = (uint8_t)survives;

@@ -975,6 +975,50 @@ def test_exact_threshold_over_several_tiles_on_hard_buckets(bucket, n, tail):
     assert int(ulp_distance(s[:, :nb], s_ref).max()) <= 1
 
 
+def non_finite_bucket(kind, n, rng):
+    v = rng.standard_normal(n).astype(np.float32)
+    if kind == "zeros and inf":
+        v[:] = 0
+    if kind != "nan":
+        v[n // 3] = -np.inf
+    if kind == "three inf":
+        v[[3, n - 1]] = np.inf
+    if kind == "largest and inf":
+        v[n // 2:] = np.finfo(np.float32).max
+    if kind in ("nan", "nan and inf"):
+        v[n // 5] = np.nan
+    return v
+
+
+NON_FINITE = ["inf", "three inf", "zeros and inf", "largest and inf", "nan", "nan and inf"]
+
+
+WIDE_EXACT = [8192, 16384, 65536, 131072]
+
+
+@pytest.mark.parametrize("bucket", WIDE_EXACT)
+def test_exact_threshold_of_non_finite_buckets(bucket):
+    """The objective is infinite as soon as an infinite component is kept, so the smallest k keeps these alone;
+    with a NaN there is no optimum and the threshold is 0.  A finite bucket follows each, and the last
+    one is incomplete."""
+    rng = np.random.default_rng(bucket)
+    parts = [p for k in NON_FINITE for p in (non_finite_bucket(k, bucket, rng), rng.standard_normal(bucket).astype(np.float32))]
+    for tail in (np.zeros(0, np.float32), non_finite_bucket("three inf", bucket // 2 + 5, rng)):
+        g = np.concatenate(parts + [tail])[None]
+        th_ref = oracle.exact_thresholds(g[0], bucket)
+        for i, k in enumerate(NON_FINITE):
+            if "nan" in k:
+                th_ref[2 * i] = 0
+        c_ref, s_ref, _ = oracle.quantize_pack(g, bucket, thresholds=th_ref[None])
+        c, s, th, L = gpu_quantize_pack(g, bucket, exact=True)
+        nb = L.n_buckets
+        assert np.array_equal(th[0, :nb].view(np.uint32), th_ref.view(np.uint32))
+        assert np.array_equal(c[:, :L.words], c_ref)
+        finite = np.isfinite(s_ref)
+        assert np.array_equal(s[:, :nb][~finite], s_ref[~finite], equal_nan=True)
+        assert int(ulp_distance(s[:, :nb][finite], s_ref[finite]).max()) <= 1
+
+
 def test_exact_threshold_of_a_long_vector_is_optimal_to_binary64_resolution():
     """Beyond some 1e7 components the objectives of neighbouring k near the optimum agree to
     binary64 rounding and the association of the sums may decide between them; what must hold
