@@ -568,7 +568,9 @@ __device__ __forceinline__ void rank_tile(const QuantArgs& a, int64_t tile, int 
     const double o = __shfl_up(incl, off, kWave);
     if ((lane & (kSegLanes - 1)) >= off) incl += o;
   }
-  double before = incl - run[15];
+  // by the neighbour and not incl - run[15], which is not a number where this thread holds an infinity
+  const double left = __shfl_up(incl, 1, kWave);
+  double before = (lane & (kSegLanes - 1)) ? left : 0.0;
   if constexpr (kSegWaves > 1) {
     if (lane == kWave - 1) lds_tot[wave] = incl;
     __syncthreads();

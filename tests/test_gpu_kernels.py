@@ -996,7 +996,7 @@ NON_FINITE = ["inf", "three inf", "zeros and inf", "largest and inf", "nan", "na
 WIDE_EXACT = [8192, 16384, 65536, 131072]
 
 
-@pytest.mark.parametrize("bucket", WIDE_EXACT)
+@pytest.mark.parametrize("bucket", [64, 128, 256, 512, 1024, 2048, 4096] + WIDE_EXACT)
 def test_exact_threshold_of_non_finite_buckets(bucket):
     """The objective is infinite as soon as an infinite component is kept, so the smallest k keeps these alone;
     with a NaN there is no optimum and the threshold is 0.  A finite bucket follows each, and the last
