@@ -149,18 +149,23 @@ __device__ __forceinline__ ScanResult scan_level(LevelShape* shape, bool first, 
   double sum[kPerThread];
   uint32_t cnt = 0;
   double mine = 0.0;
-  bool odd = false;
 #pragma unroll
   for (int i = 0; i < kPerThread; ++i) {
     const int pos = kPerThread * t + i;
     low[i] = pos < nbins ? lower_end(s, lds.ranges.lo, pos) : 0u;
-    odd |= c[i] != 0 && (low[i] > kNonFinite || (low[i] == kNonFinite && off[i] != 0));
     sum[i] = c[i] ? fma((double)off[i], ulp_of(low[i]), (double)c[i] * (double)__uint_as_float(low[i])) : 0.0;
     cnt += c[i];
     mine += sum[i];
   }
   if (t == 0) lds.threshold_bits = 0u;
-  if (__syncthreads_or(odd)) return kScanDone;           // NaN members (all in level 0)
+  if (first) {                                           // NaN members: in the top bins of level 0
+    bool odd = false;
+    if (t <= (int)((kBins - 1 - (kNonFinite >> kFirstShift)) / kPerThread))
+#pragma unroll
+      for (int i = 0; i < kPerThread; ++i)
+        odd |= c[i] != 0 && (low[i] > kNonFinite || (low[i] == kNonFinite && off[i] != 0));
+    if (__syncthreads_or(odd)) return kScanDone;
+  }
   uint32_t total_cnt;
   double total_sum;
   uint32_t k_run = scan_exclusive(cnt, lds.wave_u, &total_cnt);
@@ -230,9 +235,10 @@ __device__ __forceinline__ ScanResult scan_level(LevelShape* shape, bool first, 
   int last = 0;                                          // 1 + position of this thread's last filled bin
 #pragma unroll
   for (int i = 0; i < kPerThread; ++i) {
-    if (infinite ? kPerThread * t + i == best_pos : edge[i] >= bar || inner[i] >= bar) survives |= 1u << i;
+    if (edge[i] >= bar || inner[i] >= bar) survives |= 1u << i;
     if (c[i]) last = kPerThread * t + i + 1;
   }
+  if (infinite) survives = best_pos / kPerThread == t ? 1u << (best_pos % kPerThread) : 0u;
   lds.survives[t] = (uint8_t)survives;
   int previous = scan_exclusive_max(last, lds.wave_i);   // (barriers inside: survives[] is visible)
   if (s.shift == 0) {                                    // bins are single patterns: this is the optimum
