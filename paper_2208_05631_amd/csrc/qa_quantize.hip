@@ -1375,13 +1375,15 @@ __device__ __forceinline__ void stochastic_codes(const StochArgs& a, const float
     // lies within that margin of it (probability ~1e-6) is the correctly rounded quotient needed.
     float u[4], av[4];
     bool keep[4];
-    uint64_t sure = ~0ull;                               // lanes (masks stay in scalar registers)
+    // lanes that are certain (masks stay in scalar registers): none whose scale's reciprocal leaves the normal
+    // numbers -- it may come out infinite below 2^-126 and 0 above 2^126
+    uint64_t sure = __ballot(__float_as_uint(s) - 0x00800000u <= 0x7e000000u - 0x00800000u);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       u[e] = (float)(r[e] >> 8) * 0x1p-24f;
       av[e] = fabsf(v[j][e]);
       keep[e] = u[e] < av[e] * below;
-      sure &= __ballot(keep[e]) | __ballot(u[e] > av[e] * above);        // NaN/Inf products: unsure
+      sure &= __ballot(keep[e]) | __ballot(u[e] > av[e] * above);        // NaN products: unsure
     }
     if (sure != __ballot(true)) {
 #pragma unroll

@@ -590,6 +590,30 @@ def test_stochastic_quantizer_matches_oracle(d, M, bucket):
     assert d < 100 or not torch.equal(c2, codes)    # another step, other draws
 
 
+@pytest.mark.parametrize("bucket", [64, 256, 2048, 4096, 8192])
+def test_stochastic_quantizer_at_the_ends_of_binary32(bucket):
+    """Scales whose reciprocal is not a normal number (below 2^-126, above 2^126), around those ends, infinite."""
+    rng = np.random.default_rng(bucket)
+    ends = [2.0 ** -149, 1e-44, 1e-39, 2.0 ** -128, 2.0 ** -127, 2.0 ** -126, 1.5e-38, 1e-30, 1.0, 2.0 ** 125, 2.0 ** 126,
+            1e38, 3.4e38, np.inf]
+    parts = []
+    for e in ends:
+        v = np.exp2(rng.uniform(-12, 0, bucket)) * rng.choice([-1.0, 1.0], bucket)
+        v *= 1.0 if e == np.inf else e
+        v[bucket // 2] = e                              # the largest
+        parts.append(v.astype(np.float32))
+    g = np.stack([np.concatenate(parts), np.concatenate(parts[::-1])])
+    d, M, seed, step = g.shape[1], 2, 0x0123456789ABCDEF, 3
+    oc, osc = oracle.quantize_pack_stochastic(g, bucket=bucket, seed=seed, step=step)
+    L = qa.Layout.make(d, M, bucket)
+    codes = torch.full((M, L.code_stride), -1, dtype=torch.int32, device=DEV)
+    scales = torch.full((M, L.scale_stride), -7.0, dtype=torch.float32, device=DEV)
+    qa.qa_quantize_pack_stochastic(L, dev(g), d, codes, scales, seed, step)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(scales)[:, :L.n_buckets], osc)
+    assert np.array_equal(host(codes).view(np.uint32)[:, :L.words], oc)
+
+
 # ---- the server's call: messages in, q_t = Q(SynQ_t) out as a message ---------------------------
 
 AGGQ_CASES = [
