@@ -1181,15 +1181,14 @@ __global__ __launch_bounds__(kThreads) void quantize_bracketed_kernel(QuantArgs 
   const float2 band = a.band[(int64_t)m * a.nb + tile / a.tiles_per_bucket];
   float v[4][4];
   load_tile_stream(a.g + (int64_t)m * a.g_stride, a.d, tile, v);
-  double s1[4], s2[4] = {0.0, 0.0, 0.0, 0.0};
+  double s1 = 0.0, s2[4] = {0.0, 0.0, 0.0, 0.0};
   uint32_t wave_cnt = 0, mine = 0;
   const bool bracket = band.x >= 0.0f;
+  // in the order of quantize_abs_partial_kernel: the threshold is the same number in both forms
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    s1[j] = (double)fabsf(v[j][0]);
+  for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int e = 1; e < 4; ++e) s1[j] += (double)fabsf(v[j][e]);
-  }
+    for (int e = 0; e < 4; ++e) s1 += (double)fabsf(v[j][e]);
   if (bracket) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -1211,7 +1210,7 @@ __global__ __launch_bounds__(kThreads) void quantize_bracketed_kernel(QuantArgs 
     const int64_t widx = tile * kTileWords + (t & 3) * 64 + (t >> 2);
     if (widx < a.W) (a.codes + (int64_t)m * a.code_stride)[widx] = mine;
   }
-  const double S1 = wave_sum_f64((s1[0] + s1[1]) + (s1[2] + s1[3]));
+  const double S1 = wave_sum_f64(s1);
   const double S2 = wave_sum_f64((s2[0] + s2[1]) + (s2[2] + s2[3]));
   if (t % kWave == 0) { lds_s1[t / kWave] = S1; lds_s2[t / kWave] = S2; lds_c[t / kWave] = wave_cnt; }
   __syncthreads();

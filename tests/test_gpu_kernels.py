@@ -816,6 +816,35 @@ def test_quantizer_of_long_buckets_matches_oracle(kinds, d, bucket):
     assert int(ulp_distance(host(scales)[:, :nb], s[:, :nb]).max()) <= 1
 
 
+def order_sensitive_gradient(d):
+    """One thread's sixteen components of the first tile: a large one whose binary64 sum with each of twelve small
+    ones rounds back to it, while the small ones added up first would change it.  With coefficient 1.5 and
+    2^k components the threshold is a tie between two binary32 numbers that such a change decides."""
+    g = np.zeros(d, np.float32)
+    g[0] = (1 + 3 * 2.0 ** -23) * 2.0 ** 30
+    for j in (1024, 2048, 3072):
+        g[j:j + 4] = 2.0 ** -23
+    return g
+
+
+def test_threshold_does_not_depend_on_the_workspace():
+    """The one-read and the two-read form add the magnitudes in the same order."""
+    d, M = 1 << 24, 2
+    L = qa.Layout.make(d, M, 0, 1.5)
+    g = dev(np.stack([order_sensitive_gradient(d)] * M))
+    codes = torch.zeros((M, L.code_stride), dtype=torch.int32, device=DEV)
+    full = qa.qa_workspace_bytes(L, qa.QA_OP_QUANTIZE)
+    assert full >= M * (d // 4096) * 20
+    got = []
+    for size in (full, M * (d // 4096) * 12 + 4 * M + 768):
+        sc, th = torch.zeros((2, M, 1), dtype=torch.float32, device=DEV)
+        qa.qa_quantize_pack(L, g, d, codes, sc, th, 0, workspace(size))
+        torch.cuda.synchronize()
+        got.append(host(th))
+    assert np.array_equal(*got)
+    assert np.array_equal(got[0], oracle.quantize_pack(host(g), bucket=0, thr_coef=1.5)[2])
+
+
 @pytest.mark.parametrize("bucket", [1 << 25, 1 << 27, 1 << 30])
 def test_quantizer_of_a_bucket_far_longer_than_the_vector(bucket):
     """A bucket size beyond the vector's length means one bucket: the same message as with one scale per vector,

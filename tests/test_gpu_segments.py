@@ -208,6 +208,31 @@ def test_long_tensors_read_once_match_oracle(M):
         close(host(a)[f_covered(f)], r[f_covered(f)], "state")
 
 
+def test_threshold_of_a_long_tensor_does_not_depend_on_the_workspace():
+    """The one-read and the two-read form add the magnitudes in the same order: a gradient whose threshold, a tie
+    between two binary32 numbers, is decided by the order of a few additions."""
+    n, M = 1 << 24, 8
+    L = qa.Layout.make(n, M, 0, 1.5, None, 1)
+    table = torch.zeros(qa.qa_segment_plan_bytes(n, 1), dtype=torch.uint8, device=DEV)
+    plan = qa.qa_segment_plan_init(n, np.zeros(1, np.int64), np.array([n], np.int64), table)
+    v = np.zeros(n, np.float32)
+    v[0] = (1 + 3 * 2.0 ** -23) * 2.0 ** 30
+    for j in (1024, 2048, 3072):
+        v[j:j + 4] = 2.0 ** -23
+    g = dev(v).repeat(M, 1)
+    codes = torch.zeros((M, L.code_stride), dtype=torch.int32, device=DEV)
+    full = qa.qa_segment_workspace_bytes(plan, M, qa.QA_OP_QUANTIZE)
+    assert full >= M * plan.n_pieces * 20
+    got = []
+    for size in (full, M * plan.n_pieces * 12 + 4 * M + 768):
+        sc, th = torch.zeros((2, M, 1), dtype=torch.float32, device=DEV)
+        qa.qa_quantize_pack_segments(L, plan, g, n, codes, sc, th, workspace(size))
+        torch.cuda.synchronize()
+        got.append(host(th))
+    assert np.array_equal(*got)
+    assert np.array_equal(got[0][0], oracle.quantize_pack(v[None], bucket=0, thr_coef=1.5)[2][0])
+
+
 def test_long_tensors_ending_at_every_place_of_a_work_group():
     """Long tensors (read once, settled eight pieces at a time) with one-piece tensors behind them, which the
     same work-group codes right after it has summed what the long one keeps: the boundary at each of the
