@@ -181,8 +181,9 @@ int qa_quantize_pack(const qa_layout* layout, const float* g, int64_t g_stride, 
  * HIP graph, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, outputs and
  * results as qa_quantize_pack, bit for bit, without the workspace: the per-tile partial sums,
  * counts and thresholds that the multi-pass layouts need (one scale per vector, or buckets above
- * 4096) live in a 4 MiB array in the library's own device image instead.  The call allocates
- * nothing and frees nothing.
+ * 4096) live in a 7 MiB array in the library's own device image instead.  The call allocates
+ * nothing and frees nothing.  (Bit for bit: as qa_quantize_pack with the workspace that
+ * qa_workspace_bytes asks for.)
  *   - Limit: the partial sums fit 4 MiB (QA_STATIC_SCRATCH_BYTES), 12 bytes per worker and 4096
  *     coordinates: e.g. M * ceil(d/4096) <= 349 000.  Larger
  *     problems return QA_ERR_TOO_LARGE and launch nothing.  Layouts that need no workspace

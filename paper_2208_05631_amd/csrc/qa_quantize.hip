@@ -1696,8 +1696,13 @@ int quantize_finalize_launch(const qa_layout* L, int which, int64_t n_partials, 
 // launches.  qa_quantize_pack_static keeps them in this array instead of a caller's workspace.
 // Every GPU the library runs on holds its own copy until the process ends; its device address
 // is looked up once per device and that address (never the symbol itself) is what host code
-// hands to the kernels.
-constexpr size_t kScratchBytes = size_t(4) << 20;
+// hands to the kernels.  A call is accepted by the size of its partial sums (12 bytes per worker and
+// tile); the rest is for the one-read form, which adds 8 bytes to those 12 and 8 per worker and bucket of at
+// least 4096 tiles: the static call takes it wherever qa_quantize_pack with its full workspace does, so
+// that their sums are added in the same order.
+constexpr size_t kScratchSums = QA_STATIC_SCRATCH_BYTES, kScratchBytes = size_t(7) << 20;
+static_assert(kScratchBytes >= kScratchSums + kScratchSums / 12 * 8 + kScratchSums / 12 / kOneReadBucketTiles * 16 + 512,
+              "room for the one-read form of every accepted layout");
 static __device__ __align__(256) __attribute__((used)) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -1740,7 +1745,7 @@ extern "C" int qa_quantize_pack_static(const qa_layout* layout, const float* g, 
   if (!aligned(g, 16) || !aligned(codes, 4) || !aligned(scales, 4) || !aligned(thresholds, 4))
     return QA_ERR_ALIGNMENT;
   const size_t need = quantize_workspace_bytes(layout);
-  if (need > kScratchBytes) return QA_ERR_TOO_LARGE;
+  if (need > kScratchSums) return QA_ERR_TOO_LARGE;
   // the device-wide search has a sort's worth of scratch in reserve: not from this array
   if ((flags & QA_THRESH_EXACT) && exact_wide_workspace_bytes(layout) != 0) return QA_ERR_TOO_LARGE;
   void* ws = nullptr;

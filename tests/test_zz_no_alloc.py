@@ -59,6 +59,32 @@ def test_static_scratch_quantizer_equals_the_workspace_one_on_two_calls_in_a_row
     assert np.array_equal(c0, c1) and np.array_equal(s0.view(np.uint32), s1.view(np.uint32))
 
 
+@pytest.mark.parametrize("d", [1 << 28, 1 << 30])
+def test_static_scratch_quantizer_adds_in_the_order_of_the_workspace_one(d):
+    """Three large components and, in seven further tiles that one work-group of the one-read form shares, a small
+    one whose binary64 sum with them rounds back; added up among themselves first, as the two-read form
+    does, the small ones count.  The scale is a tie between two binary32 numbers that this decides.  At
+    2^30 components the partial sums of two reads fit the array's 4 MiB, those of one read do not."""
+    n = (1 << 23) + 2
+    L = qa.Layout.make(d, 1, 0, 1e-9)                    # everything non-zero is kept
+    g = torch.zeros((1, d), dtype=torch.float32, device=DEV)
+    g[0, :3] = torch.tensor([8 * n, 2 * n, 5], dtype=torch.float32)     # (10 n + 5) / 10
+    g[0, 4096:8 * 4096:4096] = 2.0 ** -27
+    out = []
+    for static in (False, True):
+        codes = torch.full((1, L.code_stride), -1, dtype=torch.int32, device=DEV)
+        scales, th = torch.zeros((2, 1, 1), dtype=torch.float32, device=DEV)
+        if static:
+            qa.qa_quantize_pack_static(L, g, d, codes, scales, th, 0)
+        else:
+            qa.qa_quantize_pack(L, g, d, codes, scales, th, 0, workspace(qa.qa_workspace_bytes(L, qa.QA_OP_QUANTIZE)))
+        torch.cuda.synchronize()
+        out.append((codes[:, :L.words], host(scales), host(th)))
+    assert abs(out[0][1][0, 0] - n) <= 1
+    assert torch.equal(out[0][0], out[1][0])
+    assert np.array_equal(out[0][1], out[1][1]) and np.array_equal(out[0][2], out[1][2])
+
+
 def test_static_scratch_quantizer_without_scratch_and_beyond_its_limit():
     # single-pass layouts use no scratch and have no size limit
     rng = np.random.default_rng(32)
