@@ -158,6 +158,20 @@ def test_segment_calls_reject_what_they_cannot_do():
     assert e.value.code == -1
 
 
+def check_codes(f, g, c, th, c_ref, th_ref):
+    """Every tensor's codes: the oracle's where the threshold is the oracle's, else the oracle's for the GPU's own
+    threshold.  No field holds the pattern 10, which marks a component still to be decided."""
+    for s, (b, n) in enumerate(zip(f.begin, f.length)):
+        words = slice(int(b) // 16, (int(b) + int(n) + 15) // 16)
+        assert not np.any((c[:, words] >> 1) & ~c[:, words] & 0x55555555), s
+        for m in range(f.M):
+            expected = c_ref[m, words]
+            if th[m, s] != th_ref[m, s]:
+                own = np.array([[th[m, s]]], np.float32)
+                expected = oracle.quantize_pack(g[m:m + 1, b:b + n], bucket=0, thresholds=own)[0][0]
+            assert np.array_equal(c[m, words], expected), (m, s)
+
+
 @pytest.mark.parametrize("M", [8, 9])
 def test_long_tensors_read_once_match_oracle(M):
     """Lists large enough for the form that reads long tensors' gradients once (2^27 components in all):
@@ -194,8 +208,7 @@ def test_long_tensors_read_once_match_oracle(M):
     # sums in another order: thresholds and scales within an ulp, codes those of the thresholds
     assert np.allclose(host(th), th_ref, rtol=1.3e-7, atol=0)
     assert np.allclose(host(scales), s_ref, rtol=1.3e-7, atol=0)
-    if np.array_equal(host(th), th_ref):
-        assert np.array_equal(c[:, touched], c_ref[:, touched])
+    check_codes(f, g, c, host(th), c_ref, th_ref)
     assert (c[:, ~touched] == 0x5A5A5A5A).all()
     x, G, z = (np.zeros(f.d, np.float32) for _ in range(3))
     xd, Gd, zd = dev(x), dev(G), dev(z)
@@ -262,6 +275,7 @@ def test_long_tensors_ending_at_every_place_of_a_work_group():
             # sums in another order: an ulp
             assert np.allclose(host(th), th_ref, rtol=1.3e-7, atol=0)
             assert np.allclose(host(scales), s_ref, rtol=1.3e-7, atol=0)
+            check_codes(f, g, host(codes).view(np.uint32), host(th), c_ref, th_ref)
         for a, b in zip(first, (codes, scales, th)):
             assert torch.equal(a, b)
 
