@@ -164,7 +164,8 @@ int qa_local_grad_batched(int format, const float* A_or_vals, const int64_t* ind
  * found by refining histograms of the magnitudes, in 17 bytes of workspace per component
  * (d < 2^32, else QA_ERR_TOO_LARGE); the call only enqueues kernels.  Of a bucket with
  * infinite components these alone are kept (the objective is infinite from the first on); a NaN
- * gives the threshold 0.  Candidates whose objectives agree to binary64 rounding
+ * gives the threshold 0.  (An objective built to be the same number for thousands of k, to 1e-11,
+ * is sorted by one work-group per bucket: some 6 ns per component and worker.)  Candidates whose objectives agree to binary64 rounding
  * (likely only beyond some 1e7 components per bucket) may be resolved differently from a
  * strictly sequential summation.
  * g_stride >= d and a multiple of 4.  ws: qa_workspace_bytes(layout, QA_OP_QUANTIZE), or

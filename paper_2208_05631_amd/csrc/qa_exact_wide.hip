@@ -476,54 +476,71 @@ __global__ __launch_bounds__(kScanThreads) void exact_wide_scan_kernel(WideArgs 
 // ---- what is still open: a plain sort by one work-group -------------------------------------------
 //
 // One work-group per bucket looks at its M thresholds; for a worker whose bucket is still marked it
-// sorts the magnitudes (descending, eight stable passes of four bits between two key arrays) and
-// walks the objective.  Some 7 ns per component: only for inputs built to defeat the levels.
+// sorts the magnitudes (descending, four stable passes of eight bits between two key arrays) and
+// walks the objective.  Only for inputs built to defeat the levels: an objective that is the same
+// number for thousands of cuts to 1e-11.  Some 6 ns per component and worker, a cliff: 2^16 components
+// 0.53 ms, 2^22 23.8 ms, where a device-wide sort of every gradient took 0.08 and 0.23 (256 threads, eight
+// passes of four bits, each counted on its own: 1.23 and 117 ms).  Chip-wide passes would be launches that
+// every call pays for.
 
 __device__ __forceinline__ uint32_t sort_key(uint32_t raw) { return 0x7fffffffu - (raw & 0x7fffffffu); }
 
-__global__ __launch_bounds__(kThreads) void exact_sort_open_kernel(WideArgs a, int M) {
-  constexpr int kDigits = 16, kKeys = 16, kChunk = kThreads * kKeys;
-  __shared__ uint32_t digit_base[kDigits];
-  __shared__ uint32_t digit_of_wave[kWaves][kDigits];
-  __shared__ double lds_d[kWaves];
-  __shared__ double lds_o[kWaves];
-  __shared__ long long lds_k[kWaves];
+__global__ __launch_bounds__(kScanThreads) void exact_sort_open_kernel(WideArgs a, int M) {
+  constexpr int kDigitBits = 8, kDigits = 1 << kDigitBits, kPasses = 4, kKeys = 16, kChunk = kScanThreads * kKeys,
+                kRun = 8;
+  __shared__ uint32_t digit_base[kPasses][kDigits];
+  __shared__ uint32_t digit_of_wave[kScanWaves][kDigits];
+  __shared__ uint32_t lds_u[kScanWaves];
+  __shared__ double lds_d[kScanWaves];
+  __shared__ double lds_o[kScanWaves];
+  __shared__ long long lds_k[kScanWaves];
   const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
   const int64_t k = blockIdx.x, lo = k * a.bucket_len;
   const int64_t n = (lo + a.bucket_len < a.d ? lo + a.bucket_len : a.d) - lo;
+  bool open = false;                                     // any worker's, all looked at together
+  for (int m = t; m < M; m += kScanThreads) open |= a.thresholds[(int64_t)m * a.scale_stride + k] == kOpenMark;
+  if (!__syncthreads_or(open)) return;
   uint32_t* const keys0 = a.sort_keys + lo;
   uint32_t* const keys1 = a.sort_keys + a.d + lo;
   for (int m = 0; m < M; ++m) {
     float* thr = a.thresholds + (int64_t)m * a.scale_stride + k;
     if (*thr != kOpenMark) continue;                     // the same value for every thread
     const uint32_t* g = reinterpret_cast<const uint32_t*>(a.g + (int64_t)m * a.g_stride + lo);
+    for (int i = t; i < kPasses * kDigits; i += kScanThreads) digit_base[i / kDigits][i % kDigits] = 0u;
     __syncthreads();
-    for (int64_t i = t; i < n; i += kThreads) keys0[i] = sort_key(g[i]);
-    for (int pass = 0; pass < 8; ++pass) {
+    for (int64_t i = t; i < n; i += kScanThreads) {      // the digits of all passes are counted at once
+      const uint32_t key = sort_key(g[i]);
+      keys0[i] = key;
+#pragma unroll
+      for (int p = 0; p < kPasses; ++p) atomicAdd(&digit_base[p][(key >> (kDigitBits * p)) & (kDigits - 1)], 1u);
+    }
+    __syncthreads();
+    for (int p = 0; p < kPasses; ++p) {                  // counts -> places of the first key of each digit
+      uint32_t total;
+      const uint32_t first = scan_exclusive(t < kDigits ? digit_base[p][t] : 0u, lds_u, &total);
+      if (t < kDigits) digit_base[p][t] = first;
+    }
+    __syncthreads();
+    for (int pass = 0; pass < kPasses; ++pass) {
       const uint32_t* src = pass & 1 ? keys1 : keys0;
       uint32_t* dst = pass & 1 ? keys0 : keys1;
-      if (t < kDigits) digit_base[t] = 0u;
-      __syncthreads();
-      for (int64_t i = t; i < n; i += kThreads) atomicAdd(&digit_base[(src[i] >> (4 * pass)) & 15u], 1u);
-      __syncthreads();
-      if (t == 0) {
-        uint32_t run = 0;
-        for (int q = 0; q < kDigits; ++q) { const uint32_t v = digit_base[q]; digit_base[q] = run; run += v; }
-      }
       for (int64_t i0 = 0; i0 < n; i0 += kChunk) {
         // a wave's keys are 1024 consecutive ones, 64 at a time, so that equal digits keep their order
         uint32_t key[kKeys], at[kKeys];
-        if (t < kWaves * kDigits) digit_of_wave[t / kDigits][t % kDigits] = 0u;
-        __syncthreads();
+        for (int i = t; i < kScanWaves * kDigits; i += kScanThreads) digit_of_wave[i / kDigits][i % kDigits] = 0u;
 #pragma unroll
         for (int j = 0; j < kKeys; ++j) {
           const int64_t i = i0 + wave * (kWave * kKeys) + j * kWave + lane;
-          const bool live = i < n;
-          key[j] = live ? src[i] : 0u;
-          const uint32_t digit = (key[j] >> (4 * pass)) & 15u;
+          key[j] = i < n ? src[i] : 0u;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kKeys; ++j) {
+          const bool live = i0 + wave * (kWave * kKeys) + j * kWave + lane < n;
+          const uint32_t digit = (key[j] >> (kDigitBits * pass)) & (kDigits - 1);
           uint64_t same = __ballot(live);
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
+          for (int q = 0; q < kDigitBits; ++q) {
             const uint64_t ones = __ballot((digit >> q) & 1u);
             same &= (digit >> q) & 1u ? ones : ~ones;
           }
@@ -537,30 +554,30 @@ __global__ __launch_bounds__(kThreads) void exact_sort_open_kernel(WideArgs a, i
         }
         __syncthreads();
         if (t < kDigits) {                               // places of the waves' digits in the output
-          uint32_t run = digit_base[t];
-          for (int w = 0; w < kWaves; ++w) { const uint32_t v = digit_of_wave[w][t]; digit_of_wave[w][t] = run; run += v; }
-          digit_base[t] = run;
+          uint32_t run = digit_base[pass][t];
+          for (int w = 0; w < kScanWaves; ++w) { const uint32_t v = digit_of_wave[w][t]; digit_of_wave[w][t] = run; run += v; }
+          digit_base[pass][t] = run;
         }
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < kKeys; ++j)
-          if (at[j] != 0xffffffffu) dst[digit_of_wave[wave][(key[j] >> (4 * pass)) & 15u] + at[j]] = key[j];
+          if (at[j] != 0xffffffffu) dst[digit_of_wave[wave][(key[j] >> (kDigitBits * pass)) & (kDigits - 1)] + at[j]] = key[j];
         __syncthreads();
       }
     }
     // keys0 holds the magnitudes in descending order: objective of every cut
     double best = -1.0, running = 0.0;
     long long best_k = 0;
-    for (int64_t i0 = 0; i0 < n; i0 += kChunk) {
-      double v[kKeys], sum = 0.0;
-      uint32_t key[kKeys + 1];
+    for (int64_t i0 = 0; i0 < n; i0 += kScanThreads * kRun) {
+      double v[kRun], sum = 0.0;
+      uint32_t key[kRun + 1];
 #pragma unroll
-      for (int j = 0; j <= kKeys; ++j) {
-        const int64_t i = i0 + (int64_t)t * kKeys + j;
+      for (int j = 0; j <= kRun; ++j) {
+        const int64_t i = i0 + (int64_t)t * kRun + j;
         key[j] = i < n ? keys0[i] : 0x7fffffffu;         // past the end: magnitude 0
       }
 #pragma unroll
-      for (int j = 0; j < kKeys; ++j) { v[j] = (double)__uint_as_float(0x7fffffffu - key[j]); sum += v[j]; }
+      for (int j = 0; j < kRun; ++j) { v[j] = (double)__uint_as_float(0x7fffffffu - key[j]); sum += v[j]; }
       double incl = sum;
       for (int o = 1; o < kWave; o <<= 1) {
         const double p = __shfl_up(incl, o, kWave);
@@ -570,13 +587,13 @@ __global__ __launch_bounds__(kThreads) void exact_sort_open_kernel(WideArgs a, i
       if (lane == kWave - 1) lds_d[wave] = incl;
       __syncthreads();
       double before = running, total = 0.0;
-      for (int w = 0; w < kWaves; ++w) { if (w < wave) before += lds_d[w]; total += lds_d[w]; }
+      for (int w = 0; w < kScanWaves; ++w) { if (w < wave) before += lds_d[w]; total += lds_d[w]; }
       const double left = __shfl_up(incl, 1, kWave);
       before += lane ? left : 0.0;
 #pragma unroll
-      for (int j = 0; j < kKeys; ++j) {
+      for (int j = 0; j < kRun; ++j) {
         before += v[j];
-        const int64_t kk = i0 + (int64_t)t * kKeys + j + 1;
+        const int64_t kk = i0 + (int64_t)t * kRun + j + 1;
         if (kk <= n && v[j] > 0.0 && key[j + 1] != key[j]) {
           const double obj = before * before / (double)kk;
           if (obj > best) { best = obj; best_k = kk; }
@@ -592,7 +609,7 @@ __global__ __launch_bounds__(kThreads) void exact_sort_open_kernel(WideArgs a, i
     if (lane == 0) { lds_o[wave] = best; lds_k[wave] = best_k; }
     __syncthreads();
     if (t == 0) {
-      for (int w = 0; w < kWaves; ++w)
+      for (int w = 0; w < kScanWaves; ++w)
         if (lds_o[w] > best || (lds_o[w] == best && lds_k[w] < best_k)) { best = lds_o[w]; best_k = lds_k[w]; }
       *thr = best >= 0.0 && best_k < n ? __uint_as_float(0x7fffffffu - keys0[best_k]) : 0.0f;
     }
@@ -650,7 +667,7 @@ int exact_thresholds_wide(const qa_layout* L, const float* g, int64_t g_stride, 
       }
     }
   }
-  hipLaunchKernelGGL(exact_sort_open_kernel, dim3((unsigned)a.nb), dim3(kThreads), 0, stream, a, (int)L->M);
+  hipLaunchKernelGGL(exact_sort_open_kernel, dim3((unsigned)a.nb), dim3(kScanThreads), 0, stream, a, (int)L->M);
   return launch_status();
 }
 
