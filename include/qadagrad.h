@@ -161,8 +161,9 @@ int qa_local_grad_batched(int format, const float* A_or_vals, const int64_t* ind
  * strict comparisons keep exactly the optimal set; scale and codes follow as usual.  Buckets of
  * up to 4096 components are searched inside one wave or work-group; longer buckets, and one threshold for
  * a vector of more than 4096 components (Section 3.4's optimum over the whole gradient), are
- * found by refining histograms of the magnitudes, in 17 bytes of workspace per component
- * (d < 2^32, else QA_ERR_TOO_LARGE); the call only enqueues kernels.  Of a bucket with
+ * found by refining histograms of the magnitudes (d < 2^32, else QA_ERR_TOO_LARGE).  The workspace is
+ * sized at some 17 bytes per component, of which the search's state or two arrays of sorted keys
+ * use up to 8; the call only enqueues kernels.  Of a bucket with
  * infinite components these alone are kept (the objective is infinite from the first on); a NaN
  * gives the threshold 0.  (An objective built to be the same number for thousands of k, to 1e-11,
  * is sorted by one work-group per bucket: some 6 ns per component and worker.)  Candidates whose objectives agree to binary64 rounding
@@ -171,9 +172,12 @@ int qa_local_grad_batched(int format, const float* A_or_vals, const int64_t* ind
  * g_stride >= d and a multiple of 4.  ws: qa_workspace_bytes(layout, QA_OP_QUANTIZE), or
  * qa_workspace_bytes(layout, QA_OP_QUANTIZE_EXACT) with QA_THRESH_EXACT (the two agree for
  * buckets of up to 4096 components).  Buckets of 2^24 components and more are read once instead of
- * twice if the workspace has the 8 bytes per worker and 4096 coordinates that this takes, which
- * QA_OP_QUANTIZE counts; 12 bytes per worker and 4096 coordinates plus 4 per bucket, each array rounded
- * up to 256, are enough for the call to be accepted. */
+ * twice if the vector has as many, all workers together have 2^25, and the workspace has the 8 bytes
+ * per worker and 4096 coordinates that this takes, which QA_OP_QUANTIZE counts; where a sample of the
+ * gradient does not bracket a bucket's threshold, that bucket is read again.  12 bytes per worker and
+ * 4096 coordinates plus 4 per bucket, each array rounded up to 256, are enough for the call to be
+ * accepted.  Thresholds and codes do not depend on which form runs; the kept magnitudes are added in
+ * another order, so a scale may differ in its last bit. */
 int qa_quantize_pack(const qa_layout* layout, const float* g, int64_t g_stride, uint32_t* codes,
                      float* scales, float* thresholds, uint32_t flags, void* ws, size_t ws_bytes,
                      void* stream);
@@ -242,7 +246,9 @@ int qa_step_qcmd(const qa_layout* layout, const uint32_t* codes, const float* sc
  * encoding: q_codes[w], w < ceil(d/16), and q_scales[k] (q_thresholds[k] if not NULL), with
  * k < ceil(d/bucket) buckets for QA_REQUANT_BUCKET and k = 0 for QA_REQUANT_GLOBAL (one threshold
  * and scale for the whole vector).  The result equals qa_aggregate_unpack followed by
- * qa_quantize_pack of that vector with M = 1 and the corresponding bucket; buckets of at most 4096
+ * qa_quantize_pack of that vector with M = 1 and the corresponding bucket (for buckets above 4096
+ * and longer vectors up to the order of the binary64 additions, i.e. to the last bit of a threshold
+ * or scale, and the codes of that threshold); buckets of at most 4096
  * components (and vectors of at most 4096 with one scale) are done in a single pass that never
  * writes the average.  requant must be QA_REQUANT_BUCKET or QA_REQUANT_GLOBAL.
  * ws: qa_workspace_bytes(layout, QA_OP_STEP) (may be NULL when the single pass applies).
@@ -414,7 +420,10 @@ int qa_segment_plan_host(int64_t d, int64_t n_seg, const int64_t* begin, const i
                          int64_t* table_host, size_t table_bytes, int64_t* n_pieces_out);
 
 /* Workspace of the tensor-list calls below: op = QA_OP_QUANTIZE or QA_OP_STEP (the latter only
- * needed with requant != QA_REQUANT_NONE). */
+ * needed with requant != QA_REQUANT_NONE).  For large lists QA_OP_QUANTIZE counts 8 bytes per worker
+ * and piece with which long tensors are read once; 12 bytes per worker and piece plus 4 per worker and
+ * tensor, each array rounded up to 256, are enough for qa_quantize_pack_segments to be accepted (same
+ * thresholds and codes, a scale may differ in its last bit). */
 size_t qa_segment_workspace_bytes(const qa_segment_plan* plan, int32_t M, int op);
 
 /* qa_quantize_pack per tensor: thresholds (optional output) and scales per (worker, tensor),

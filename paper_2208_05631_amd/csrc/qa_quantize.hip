@@ -209,7 +209,7 @@ __device__ __forceinline__ void bucket_sums(const double s[4], const uint32_t c[
 }
 
 // Bound by the read of the gradient; with four sums per slice, four thresholds and a division per slice
-// and barrier it was bound by vector instructions (693 per wave and tile).  2^26 x 4 Gaussian components:
+// and barrier it was bound by vector instructions (691 per wave and tile; now 398).  2^26 x 4 Gaussian components:
 // buckets of 64 269 -> 216 us, 128 256 -> 195, 256 264 -> 192, 512 262 -> 193, 1024 265 -> 190, 2048 274 -> 191
 // (4096, its own kernel: 180); 50 000 017 x 5, 256: 292 -> 217.
 template <int LOG2B>
@@ -642,7 +642,7 @@ __global__ __launch_bounds__(kThreads) void exact_threshold_kernel(QuantArgs a) 
 // -1 for a threshold and is left to the ranking network (exact_rank_marked_kernel, launched behind
 // this one).
 //
-// Bound by vector instructions (2300 per wave and bucket of 4096; the network took 78 stages for the same
+// Bound by vector instructions (2267 per wave and bucket of 4096; the network took 78 stages for the same
 // and left the codes to a second pass over the gradient).  2^26 x 4 Gaussian components, thresholds and
 // codes, ranking + quantizing before -> this: buckets of 4096 1366 -> 265 us, 2048 1300 -> 299,
 // 1024 1189 -> 385, 512 1094 -> 603.  Steps 2 to 4 cost the same for every bucket size, so halving
@@ -1099,14 +1099,14 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void quantize_scale_finalize
 //
 // The threshold of a long bucket is known only after all of it has been read, but a sample of its tiles
 // brackets it closely: [lo, hi] from the mean of every 64th tile and the spread between neighbouring
-// samples, five standard errors to either side (0.2 % for 10^8 Gaussian components).  The one pass over
+// samples, five standard errors to either side (0.3 % for 10^8 Gaussian components).  The one pass over
 // the gradient then sums |v| and writes final codes for every component outside the bracket; the few
-// inside (some 6 per 4096) get the bit pattern 10, which no message holds.  When the threshold is known
+// inside (some 10 per 4096) get the bit pattern 10, which no message holds.  When the threshold is known
 // the settling pass reads the codes, looks those components up in the gradient and replaces the
 // pattern.  Exactly the same threshold and codes as the two-read passes; the kept magnitudes are added
 // in another order.
 //
-// Where the sample says nothing (few tiles, a spread above 5 %, non-finite values) or the threshold falls
+// Where the sample says nothing (few tiles, a spread above 8 %, non-finite values) or the threshold falls
 // outside its bracket, the settling pass does the second read for that bucket after all; the cost is
 // then the two-read passes' plus the sample (1/64 of a read).
 //

@@ -168,7 +168,7 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void seg_scale_finalize_kern
 // ---- long tensors in one read -------------------------------------------------------------------
 //
 // As for long buckets of a plain vector: every 64th piece of a tensor of at least 1024 pieces gives a
-// bracket around the tensor's threshold (five standard errors to either side, at most 8 % wide),
+// bracket around the tensor's threshold (five standard errors, at most 8 % to either side),
 // the one pass writes final codes outside the bracket, the pattern 10 inside it and the piece sums of
 // |v|, and the settling pass looks the open components up once the threshold is known.  Of tensors
 // without a bracket, or whose threshold falls outside it, it reads the gradient again.

@@ -919,7 +919,7 @@ __global__ __launch_bounds__(kThreads) void gsel_quantize_multi_kernel(SelArgs a
 //
 // As for the dense quantizer: the marked components' numbers come from the indicators alone, every 64th
 // tile gives a bracket around the threshold (five standard errors to either side of the sampled ratio
-// sum / number, at most 8 % wide), the one pass writes final codes outside the bracket and the pattern
+// sum / number, at most 8 %), the one pass writes final codes outside the bracket and the pattern
 // 10 inside it, and the settling pass looks the open components up once the threshold is known.
 // Until the scales are known, scales[] carries the bracket's lower end (-1: there is none, and the pass forms
 // the sum alone) and then whether it held the threshold (0 / 1), ws_thr its upper end and then the threshold.
