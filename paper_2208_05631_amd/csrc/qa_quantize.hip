@@ -1241,25 +1241,29 @@ __global__ __launch_bounds__(kThreads) void quantize_settle_kernel(QuantArgs a) 
   uint32_t* codes = a.codes + (int64_t)m * a.code_stride;
   double s = 0.0;
   uint32_t c = 0;
-  if (band.x >= 0.0f && D >= band.x && D <= band.y) {
-    if (t < kSettleTiles && tile0 + t < tile1) {         // what the one pass has kept for certain
-      s = a.kept_sum[(int64_t)m * a.ntiles + tile0 + t];
-      c = a.part_cnt[(int64_t)m * a.ntiles + tile0 + t];
-    }
+  bool settled = band.x >= 0.0f && D >= band.x && D <= band.y;
+  if (settled) {
     uint32_t w[kSettleTiles];
 #pragma unroll
     for (int u = 0; u < kSettleTiles; ++u) {
       const int64_t widx = (tile0 + u) * kTileWords + t;
       w[u] = tile0 + u < tile1 && widx < a.W ? codes[widx] : 0u;
     }
-    if (settle_words(g, tile0, D, w, lds, s, c)) {
+    bool changed;
+    settled = settle_words(g, tile0, D, w, lds, s, c, &changed);
+    if (settled && changed) {
 #pragma unroll
       for (int u = 0; u < kSettleTiles; ++u) {
         const int64_t widx = (tile0 + u) * kTileWords + t;
         if (tile0 + u < tile1 && widx < a.W) codes[widx] = w[u];
       }
     }
-  } else {
+    if (settled && t < kSettleTiles && tile0 + t < tile1) {            // what the one pass has kept for certain
+      s += a.kept_sum[(int64_t)m * a.ntiles + tile0 + t];
+      c += a.part_cnt[(int64_t)m * a.ntiles + tile0 + t];
+    }
+  }
+  if (!settled) {                                        // the tiles are coded here
     for (int64_t tile = tile0; tile < tile1; ++tile) {
       float v[4][4];
       load_tile_stream(g, a.d, tile, v);

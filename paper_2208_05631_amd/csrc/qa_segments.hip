@@ -315,12 +315,15 @@ __global__ __launch_bounds__(kThreads) void seg_settle_kernel(SegQuantArgs a) {
     int u1 = u0 + 1;                                     // the run of this tensor's pieces
     const int64_t left = p1 - piece0;
     if (left > u1) u1 = left < kSettleTiles ? (int)left : kSettleTiles;
-    if (!bracketed(a.band[(int64_t)m * a.seg.n_seg + seg], D)) {
+    const auto code_run = [&] {
       for (int u = u0; u < u1; ++u) {
         code_piece(a, load_piece(a.seg, piece0 + u, a.d), piece0 + u, m, D, lds_d, lds_u);
         __syncthreads();                                 // LDS is free again
       }
       u0 = u1;
+    };
+    if (!bracketed(a.band[(int64_t)m * a.seg.n_seg + seg], D)) {
+      code_run();
       continue;
     }
     // the run's pieces lie in consecutive tiles
@@ -328,7 +331,6 @@ __global__ __launch_bounds__(kThreads) void seg_settle_kernel(SegQuantArgs a) {
     const int64_t word_lo = a.seg.begin[seg] >> 4, word_hi = (a.seg.begin[seg] + a.seg.length[seg] + 15) >> 4;
     double s = 0.0;
     uint32_t c = 0;
-    if (t >= u0 && t < u1) { s = a.kept_sum[row + piece0 + t]; c = a.part_cnt[row + piece0 + t]; }
     uint32_t w[kSettleTiles];
     const auto inside = [&](int u, int64_t at) {
       return u >= u0 && u < u1 && tile0 + u < ntiles && at >= word_lo && at < word_hi && at * 16 < a.d;
@@ -338,7 +340,13 @@ __global__ __launch_bounds__(kThreads) void seg_settle_kernel(SegQuantArgs a) {
       const int64_t at = (tile0 + u) * kTileWords + t;
       w[u] = inside(u, at) ? codes[at] : 0u;
     }
-    if (settle_words(g, tile0, D, w, lds, s, c)) {
+    bool changed;
+    if (!settle_words(g, tile0, D, w, lds, s, c, &changed)) {
+      code_run();
+      continue;
+    }
+    if (t >= u0 && t < u1) { s += a.kept_sum[row + piece0 + t]; c += a.part_cnt[row + piece0 + t]; }
+    if (changed) {
 #pragma unroll
       for (int u = 0; u < kSettleTiles; ++u) {
         const int64_t at = (tile0 + u) * kTileWords + t;

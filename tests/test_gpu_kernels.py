@@ -774,6 +774,8 @@ def one_read_gradient(kind, d, rng):
         delta = 0.75 * 0.67 * mean / (1 - 0.33 * 0.75)
         g[near] = (delta * (1 + 1e-3 * rng.uniform(-1, 1, int(near.sum())))).astype(np.float32)
         g *= np.where(rng.random(d) < 0.5, -1, 1).astype(np.float32)
+    elif kind == "rising":                              # all components near the threshold in a few tiles
+        g = (np.arange(1, d + 1) * np.where(rng.random(d) < 0.5, -1, 1)).astype(np.float32)
     elif kind == "zero":
         g[:] = 0
     elif kind == "nan":
@@ -785,6 +787,7 @@ def one_read_gradient(kind, d, rng):
                                             (("trend", "sample misleads"), 1 << 24, 0),
                                             (("sample empty", "crowd at the threshold"), (1 << 24) + 1, 0),
                                             (("zero", "nan", "gauss"), (1 << 24) + 4095, 0),
+                                            (("rising", "gauss", "rising", "sparse"), (1 << 24) + 70001, 0),
                                             (("gauss",), (1 << 25) + (1 << 23) + 77, 1 << 24)])
 def test_quantizer_of_long_buckets_matches_oracle(kinds, d, bucket):
     """Buckets long enough for the form that reads the gradient once (2^24 components, 2^25 in all): where the

@@ -199,6 +199,7 @@ def test_long_tensors_read_once_match_oracle(M):
     g[0, s7] *= rng.random(f.length[7]) < 0.05
     g[1, s7] = 0.25
     g[2, s7] = 0
+    g[3, s7] = np.arange(f.length[7], dtype=np.float32) * np.float32(1e-3)     # open components in a few pieces
     c_ref, s_ref, th_ref = oracle.quantize_pack_segments(g, f.begin, f.length)
     codes, scales, th = f.gpu_quantize(g)
     c = host(codes).view(np.uint32)
