@@ -510,7 +510,11 @@ __device__ __forceinline__ void rank_tile(const QuantArgs& a, int64_t tile, int 
   __shared__ double lds_obj[kWaves];
   __shared__ int lds_k[kWaves];
   __shared__ float lds_next[kWaves];
-  const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
+  // opaque: in a loop over tiles the places of the network's moves would otherwise be computed once and
+  // kept, 100 registers of them
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  const int lane = t % kWave, wave = t / kWave;
   uint32_t e[16];                 // which 16 of the tile a thread starts with does not matter
   {
     float v[4][4];
