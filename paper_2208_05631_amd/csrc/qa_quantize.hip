@@ -638,13 +638,16 @@ __global__ __launch_bounds__(kThreads) void exact_threshold_kernel(QuantArgs a) 
 //   3. the same bin by bin (a lane per bin) within the runs that reach the best edge;
 //   4. the members of the bins that still reach it, and of the next one below -- some 20 magnitudes of
 //      a smooth distribution -- are collected, ranked by counting and evaluated in binary64 exactly
-//      like the ranking network does.
+//      like the ranking network does.  More than 64 of them: if every one of these bins holds a single
+//      value (ties), the cuts between the bins are all there are, and they are compared in binary64.
 //
 // One wave per bucket, 64 to 8 components per lane: no work-group barrier.  A bucket where more than 64
-// magnitudes survive (ties, objectives flat over a long stretch), with non-finite members, with
-// subnormal ones above mean/2 or with more than 64 binades between mean/2 and max gets the mark
-// -1 for a threshold and is left to the ranking network (exact_rank_marked_kernel, launched behind
-// this one).
+// different magnitudes survive (objectives flat over a long stretch, all magnitudes within a bin), with
+// non-finite members, with subnormal ones above mean/2 or with more than 64 binades between mean/2 and
+// max gets the mark -1 for a threshold and is left to the ranking network (exact_rank_marked_kernel,
+// launched behind this one).  Such buckets pay for both: 2^24 x 4 components with |v| ~ u^(-1/2), u uniform,
+// buckets of 512 275 us by ranking all, 430 now (4096: 343, 240); ties cost less than by ranking (three
+// values, one of them 0: 512 254 -> 214, 4096 321 -> 176), but for one single value in buckets of 512 (238 -> 286).
 //
 // Bound by vector instructions (2267 per wave and bucket of 4096; the network took 78 stages for the same
 // and left the codes to a second pass over the gradient).  2^26 x 4 Gaussian components, thresholds and
@@ -783,11 +786,14 @@ void exact_histogram_kernel(QuantArgs a) {
     // (a total that overflowed makes low larger than top, a NaN larger than anything)
     bool leave = top >= 0x7f800000u || low >= top || low < 0x00800000u || (top >> 23) - (base >> 23) > 64u ||
                  shift > kMaxShift;
+    bool ties = false, look_below = false;
     uint32_t count = 0, k_above = 0;
     double s_above = 0.0;
     float env_lo = 0.0f;
     // sums are formed on magnitudes scaled by a power of two that puts max into [1, 2)
     const uint32_t rescale = ((top >> 23) - 127u) << 23;
+    // the scale in the magnitudes' own units: the power of two comes back exactly
+    const double back = __hiloint2double((int)((top >> 23) - 127u + 1023u) << 20, 0);
     if (!leave) {
       const uint32_t mask = (1u << shift) - 1u, limit = (uint32_t)kBins << shift;
       wave_lds_fence();
@@ -841,7 +847,7 @@ void exact_histogram_kernel(QuantArgs a) {
       double row_sum = row_sum0;
       uint32_t row_cnt = row_cnt0;
       uint32_t c = 0;
-      double before = 0.0;
+      double before = 0.0, row_total = 0.0;              // of this lane's bin: what lies above it, its sum
       uint32_t cnt_before = 0;
       const auto next_row = [&](int i0) {                // this lane's bin i0 + lane from the top
         const bool live = i0 + lane < n_bins;
@@ -853,6 +859,7 @@ void exact_histogram_kernel(QuantArgs a) {
         const double incl = wave_scan_f64(sum);
         const uint32_t cnt_incl = wave_scan_u32(c);
         before = row_sum + (incl - sum);
+        row_total = sum;
         cnt_before = row_cnt + (cnt_incl - c);
         row_sum += readlane_f64(incl, kWave - 1);
         row_cnt += (uint32_t)__builtin_amdgcn_readlane((int)cnt_incl, kWave - 1);
@@ -909,40 +916,92 @@ void exact_histogram_kernel(QuantArgs a) {
           }
         }
       leave = count > (uint32_t)kExactList;
+      if (leave) {                                         // does every bin of the envelope hold a single value?
+        bool several = false;
+#pragma unroll
+        for (int j = 0; j < kGroups; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t rel = magnitude_bits(v[j][e]) - base, bin = rel >> shift;
+            if (rel < limit && bin >= bin_b && bin <= bin_t) {
+              const uint64_t h = hist[bin];
+              several |= (rel & mask) * (uint32_t)(h >> 32) != (uint32_t)h;        // offset != the mean offset
+            }
+          }
+        ties = !__any(several);
+      }
+      if (ties) {                                          // the cuts between the bins are all there are
+        leave = false;
+        double best_obj = -1.0, best_sum = 0.0;
+        uint32_t best_cnt = 0, best_at = 0;
+        row_sum = row_sum0;
+        row_cnt = row_cnt0;
+#pragma unroll 1
+        for (int i0 = 0; i0 < n_bins; i0 += kWave) {
+          next_row(i0);
+          const double kept_sum = before + row_total, kept = (double)(cnt_before + c);
+          const double obj = c ? kept_sum * kept_sum / kept : -1.0;
+          if (obj > best_obj) { best_obj = obj; best_sum = kept_sum; best_cnt = cnt_before + c; best_at = (uint32_t)(i0 + lane); }
+        }
+        double top_obj = best_obj;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+          const double o = shfl_xor_f64(top_obj, off);
+          top_obj = o > top_obj ? o : top_obj;
+        }
+        // smallest k: the topmost of the bins that reach it
+        const int at = wave_reduce_i32(best_obj == top_obj ? (int)best_at : 0x7fffffff, [](int p, int q) { return p < q ? p : q; });
+        const int w = __ffsll((unsigned long long)__ballot(best_obj == top_obj && (int)best_at == at)) - 1;
+        scale = scale_from_sum(readlane_f64(best_sum, w) * back, (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)best_cnt, w));
+        // the next filled bin's value
+        look_below = true;
+#pragma unroll 1
+        for (int i0 = at + 1; i0 < n_bins && look_below; i0 += kWave) {
+          const uint64_t h = i0 + lane < n_bins ? hist[bin_top - (uint32_t)(i0 + lane)] : 0ull;
+          const uint64_t any = __ballot(h != 0ull);
+          if (any) {
+            const int l = __ffsll((unsigned long long)any) - 1;
+            const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)(h >> 32), l);
+            const uint32_t sum = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)h, l);
+            delta = __uint_as_float(base + ((bin_top - (uint32_t)(i0 + l)) << shift) + sum / cnt);
+            look_below = false;
+          }
+        }
+      }
     }
     if (leave) {                                           // the ranking network takes this bucket
       if (lane == 0) *thr_out = kRankMark;
       return;
     }
-    wave_lds_fence();
-    uint32_t key = lane < (int)count ? list[lane] : 0u;
-    uint32_t rank = 0;
-    for (int j = 0; j < (int)count; ++j) {
-      const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)key, j);
-      rank += (o > key || (o == key && j < lane)) ? 1u : 0u;
-    }
-    wave_lds_fence();
-    if (lane < (int)count) list[rank] = key;
-    wave_lds_fence();
-    key = lane < (int)count ? list[lane] : 0u;
-    const uint32_t next = lane + 1 < (int)count ? list[lane + 1] : 0u;
-    const double value = lane < (int)count ? (double)__uint_as_float(key - rescale) : 0.0;
-    const double sum = s_above + wave_scan_f64(value);
-    const double kept = (double)(k_above + (uint32_t)lane + 1u);
-    const double obj = lane < (int)count && key > next ? sum * sum / kept : -1.0;
-    double top_obj = obj;
+    if (!ties) {
+      wave_lds_fence();
+      uint32_t key = lane < (int)count ? list[lane] : 0u;
+      uint32_t rank = 0;
+      for (int j = 0; j < (int)count; ++j) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)key, j);
+        rank += (o > key || (o == key && j < lane)) ? 1u : 0u;
+      }
+      wave_lds_fence();
+      if (lane < (int)count) list[rank] = key;
+      wave_lds_fence();
+      key = lane < (int)count ? list[lane] : 0u;
+      const uint32_t next = lane + 1 < (int)count ? list[lane + 1] : 0u;
+      const double value = lane < (int)count ? (double)__uint_as_float(key - rescale) : 0.0;
+      const double sum = s_above + wave_scan_f64(value);
+      const double kept = (double)(k_above + (uint32_t)lane + 1u);
+      const double obj = lane < (int)count && key > next ? sum * sum / kept : -1.0;
+      double top_obj = obj;
 #pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-      const double o = shfl_xor_f64(top_obj, off);
-      top_obj = o > top_obj ? o : top_obj;
+      for (int off = 1; off < kWave; off <<= 1) {
+        const double o = shfl_xor_f64(top_obj, off);
+        top_obj = o > top_obj ? o : top_obj;
+      }
+      const int w = __ffsll((unsigned long long)__ballot(obj == top_obj)) - 1;       // smallest k
+      scale = scale_from_sum(readlane_f64(sum, w) * back, (uint64_t)(k_above + (uint32_t)w + 1u));
+      look_below = w + 1 >= (int)count;                    // everything collected is kept
+      if (!look_below) delta = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)key, w + 1));
     }
-    const int w = __ffsll((unsigned long long)__ballot(obj == top_obj)) - 1;       // smallest k
-    // the scale in the magnitudes' own units: the power of two comes back exactly
-    const double back = __hiloint2double((int)((top >> 23) - 127u + 1023u) << 20, 0);
-    scale = scale_from_sum(readlane_f64(sum, w) * back, (uint64_t)(k_above + (uint32_t)w + 1u));
-    if (w + 1 < (int)count) {
-      delta = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)key, w + 1));
-    } else {                                             // everything collected is kept: look below
+    if (look_below) {
       float below = 0.0f;
 #pragma unroll
       for (int j = 0; j < kGroups; ++j)

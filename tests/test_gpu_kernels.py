@@ -967,6 +967,51 @@ def test_exact_threshold_on_hard_buckets(bucket, tail):
     assert int(ulp_distance(s[:, :nb], s_ref).max()) <= 1
 
 
+def tied_bucket(kind, n, rng):
+    """Few different magnitudes, many times each."""
+    if kind == "steps":
+        v = np.round(rng.standard_normal(n) * 32) / 32
+    elif kind == "coarse steps":
+        v = np.round(rng.standard_normal(n) * 2)
+    elif kind == "one value and zeros":
+        v = np.where(rng.random(n) < 0.5, 0.01, 0.0)
+    elif kind == "close pair":                          # both kept, nothing below
+        v = np.where(rng.random(n) < 0.5, 1.0, 0.9)
+    elif kind == "close pair over many small":          # both kept, the threshold lies far below half the mean
+        v = np.where(rng.random(n) < 0.9, np.where(rng.random(n) < 0.5, 1.0, 0.9), 0.01 * rng.random(n))
+    elif kind == "beside a crowd":                      # one step's members differ in their last bits
+        v = np.round(rng.standard_normal(n) * 4) / 4
+        v = np.where(np.abs(v) == 0.5, v * (1 + rng.integers(0, 300, n) * 2.0 ** -23), v)
+    elif kind == "huge steps":
+        v = rng.integers(1, 5, n) * 8e37
+    elif kind == "steps of the smallest":
+        v = rng.integers(0, 50, n) * 2.0 ** -126
+    else:                                               # equal objectives: 1 of the first and all three of the second
+        v = np.where(np.arange(n) % 4 == 0, 3.0, 1.0)
+    return (v * np.where(rng.random(n) < 0.5, -1.0, 1.0)).astype(np.float32)
+
+
+TIED = ["steps", "coarse steps", "one value and zeros", "close pair", "close pair over many small", "beside a crowd",
+        "huge steps", "steps of the smallest", "equal objectives"]
+
+
+@pytest.mark.parametrize("bucket", [512, 1024, 2048, 4096])
+def test_exact_threshold_on_tied_magnitudes(bucket):
+    """More members around the optimum than are ranked one by one, but few values: the cuts between them are
+    compared, or the bucket is left to the ranking network where a bin holds several values."""
+    rng = np.random.default_rng(bucket)
+    for tail in (0, bucket // 2 + 3):
+        g = np.stack([np.concatenate([tied_bucket(k, bucket, rng) for k in TIED] + ([tied_bucket(k0, tail, rng)] if tail else []))
+                      for k0 in TIED])
+        th_ref = np.stack([oracle.exact_thresholds(r, bucket) for r in g])
+        c_ref, s_ref, _ = oracle.quantize_pack(g, bucket, thresholds=th_ref)
+        c, s, th, L = gpu_quantize_pack(g, bucket, exact=True)
+        nb = L.n_buckets
+        assert np.array_equal(th[:, :nb].view(np.uint32), th_ref.view(np.uint32))
+        assert np.array_equal(c[:, :L.words], c_ref)
+        assert int(ulp_distance(s[:, :nb], s_ref).max()) <= 1
+
+
 # buckets longer than one tile, and one threshold for a long vector: device-wide ranking
 @pytest.mark.parametrize("d,M,bucket", [(70001, 2, 0), (70001, 2, 8192), (4096 * 5 + 1, 3, 16384),
                                         (4097, 1, 0), (300001, 1, 0), (8192 * 3, 2, 8192),
