@@ -1419,9 +1419,12 @@ static int step_segments_common(int mode, const qa_layout* L, const qa_segment_p
     float* th1 = reinterpret_cast<float*>(p);         p += align256((size_t)P->n_seg * 4);
     StepArgs ag = make_args(L, codes, scales);
     ag.seg = seg_table_of(P);
-    if (L->M <= kRecomputeMaxM) {
+    if (L->M <= kRecomputeMaxM && (L->M <= 4 || P->n_pieces >= 3 * P->n_seg)) {
       // few workers: every pass forms the average from the messages, none writes it out (32 tensors,
-      // 58.4 M parameters, QRDA: 356 -> 274 us at M = 1, 358 -> 288 at M = 4, 368 -> 332 at M = 8)
+      // 58.4 M parameters, QRDA: 356 -> 274 us at M = 1, 358 -> 288 at M = 4, 368 -> 332 at M = 8).  Beyond
+      // four workers not where most tensors are shorter than a tile: a piece's work is then setting
+      // up (40000 tensors of 0.9 tiles: 1459 -> 1353 us at M = 4, but 1672 -> 1866 at M = 6, 1503 -> 1575 at
+      // M = 8; 10000 of 2.9 tiles at M = 8 801 -> 781)
       double* part_sum; uint32_t* part_cnt; float* thr;
       segments_workspace_parts(&R, P, p, &part_sum, &part_cnt, &thr);
       ag.abs_partials = part_sum;
