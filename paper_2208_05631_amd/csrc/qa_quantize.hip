@@ -649,7 +649,7 @@ __global__ __launch_bounds__(kThreads) void exact_threshold_kernel(QuantArgs a) 
 // buckets of 512 275 us by ranking all, 430 now (4096: 343, 240); ties cost less than by ranking (three
 // values, one of them 0: 512 254 -> 214, 4096 321 -> 176), but for one single value in buckets of 512 (238 -> 286).
 //
-// Bound by vector instructions (2267 per wave and bucket of 4096; the network took 78 stages for the same
+// Bound by vector instructions (2271 per wave and bucket of 4096; the network took 78 stages for the same
 // and left the codes to a second pass over the gradient).  2^26 x 4 Gaussian components, thresholds and
 // codes, ranking + quantizing before -> this: buckets of 4096 1366 -> 265 us, 2048 1300 -> 299,
 // 1024 1189 -> 385, 512 1094 -> 603.  Steps 2 to 4 cost the same for every bucket size, so halving
@@ -1170,8 +1170,9 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void quantize_scale_finalize
 // in another order.
 //
 // Where the sample says nothing (few tiles, a spread above 8 %, non-finite values) or the threshold falls
-// outside its bracket, the settling pass does the second read for that bucket after all; the cost is
-// then the two-read passes' plus the sample (1/64 of a read).
+// outside its bracket, the settling pass does the second read for that bucket after all.  That costs two
+// launches and the sample on top of the two-read passes (one component in 1000 non-zero, or Cauchy
+// components: 10^8 x 8 1057 -> 1122 us, 2^24 x 4 93 -> 109, 2^24 x 2 50 -> 60).
 //
 // Bound by the read of the gradient (6.2 TB/s in the one pass; the settling pass, 0.25 bytes per component and a
 // cache line per open one, takes a seventh of it).  One scale per vector, Gaussian / 10 %-dense
