@@ -1307,6 +1307,10 @@ __global__ __launch_bounds__(kThreads) void quantize_settle_kernel(QuantArgs a) 
   uint32_t c = 0;
   bool settled = band.x >= 0.0f && D >= band.x && D <= band.y;
   if (settled) {
+    if (t < kSettleTiles && tile0 + t < tile1) {         // what the one pass has kept for certain
+      s = a.kept_sum[(int64_t)m * a.ntiles + tile0 + t];
+      c = a.part_cnt[(int64_t)m * a.ntiles + tile0 + t];
+    }
     uint32_t w[kSettleTiles];
 #pragma unroll
     for (int u = 0; u < kSettleTiles; ++u) {
@@ -1322,12 +1326,10 @@ __global__ __launch_bounds__(kThreads) void quantize_settle_kernel(QuantArgs a) 
         if (tile0 + u < tile1 && widx < a.W) codes[widx] = w[u];
       }
     }
-    if (settled && t < kSettleTiles && tile0 + t < tile1) {            // what the one pass has kept for certain
-      s += a.kept_sum[(int64_t)m * a.ntiles + tile0 + t];
-      c += a.part_cnt[(int64_t)m * a.ntiles + tile0 + t];
-    }
   }
   if (!settled) {                                        // the tiles are coded here
+    s = 0.0;
+    c = 0;
     for (int64_t tile = tile0; tile < tile1; ++tile) {
       float v[4][4];
       load_tile_stream(g, a.d, tile, v);
