@@ -161,9 +161,10 @@ int qa_local_grad_batched(int format, const float* A_or_vals, const int64_t* ind
  * strict comparisons keep exactly the optimal set; scale and codes follow as usual.  Buckets of
  * up to 4096 components are searched inside one wave or work-group; longer buckets, and one threshold for
  * a vector of more than 4096 components (Section 3.4's optimum over the whole gradient), are
- * found by refining histograms of the magnitudes (d < 2^32, else QA_ERR_TOO_LARGE).  The workspace is
- * sized at some 17 bytes per component, of which the search's state or two arrays of sorted keys
- * use up to 8; the call only enqueues kernels.  Of a bucket with
+ * found by refining histograms of the magnitudes (d < 2^32, else QA_ERR_TOO_LARGE); buckets of 2^21 components
+ * and more are read once if a sample of them brackets the optimum.  The workspace is
+ * sized at some 17 bytes per component: two arrays of keys for the sort below (8), the search's state and the
+ * lists of what lies inside a bracket; the call only enqueues kernels.  Of a bucket with
  * infinite components these alone are kept (the objective is infinite from the first on); a NaN
  * gives the threshold 0.  (An objective built to be the same number for thousands of k, to 1e-11,
  * is sorted by one work-group per bucket: some 6 ns per component and worker.)  Candidates whose objectives agree to binary64 rounding

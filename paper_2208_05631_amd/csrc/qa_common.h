@@ -100,6 +100,35 @@ __device__ __forceinline__ int wave_reduce_i32(int v, F f) {
            f(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 
+// Inclusive prefix sums over the 64 lanes (shifts within rows of 16, then row broadcasts).
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t lanes_or_zero_u32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xF, false);
+}
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double lanes_or_zero_f64(double v) {
+  return __hiloint2double((int)lanes_or_zero_u32<CTRL, ROW_MASK>((uint32_t)__double2hiint(v)),
+                          (int)lanes_or_zero_u32<CTRL, ROW_MASK>((uint32_t)__double2loint(v)));
+}
+__device__ __forceinline__ double wave_scan_f64(double v) {
+  v += lanes_or_zero_f64<0x111, 0xF>(v);
+  v += lanes_or_zero_f64<0x112, 0xF>(v);
+  v += lanes_or_zero_f64<0x114, 0xF>(v);
+  v += lanes_or_zero_f64<0x118, 0xF>(v);
+  v += lanes_or_zero_f64<0x142, 0xA>(v);
+  v += lanes_or_zero_f64<0x143, 0xC>(v);
+  return v;
+}
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
+  v += lanes_or_zero_u32<0x111, 0xF>(v);
+  v += lanes_or_zero_u32<0x112, 0xF>(v);
+  v += lanes_or_zero_u32<0x114, 0xF>(v);
+  v += lanes_or_zero_u32<0x118, 0xF>(v);
+  v += lanes_or_zero_u32<0x142, 0xA>(v);
+  v += lanes_or_zero_u32<0x143, 0xC>(v);
+  return v;
+}
+
 // Sum over the whole 256-thread work-group, returned to every thread.  One barrier; `lds`
 // (kWaves doubles) must not be reused by another call before a later barrier.
 __device__ __forceinline__ double block_sum_f64(double v, double* lds) {

@@ -658,34 +658,6 @@ constexpr float kRankMark = -1.0f;
 constexpr int kExactList = 64;            // survivors that one wave ranks by counting
 constexpr float kBelowBest = 1.0f - 2e-6f;   // objectives in binary32 are good to a few 2^-24
 
-// Inclusive prefix sums over the 64 lanes (shifts within rows of 16, then row broadcasts).
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ uint32_t lanes_or_zero_u32(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xF, false);
-}
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double lanes_or_zero_f64(double v) {
-  return __hiloint2double((int)lanes_or_zero_u32<CTRL, ROW_MASK>((uint32_t)__double2hiint(v)),
-                          (int)lanes_or_zero_u32<CTRL, ROW_MASK>((uint32_t)__double2loint(v)));
-}
-__device__ __forceinline__ double wave_scan_f64(double v) {
-  v += lanes_or_zero_f64<0x111, 0xF>(v);
-  v += lanes_or_zero_f64<0x112, 0xF>(v);
-  v += lanes_or_zero_f64<0x114, 0xF>(v);
-  v += lanes_or_zero_f64<0x118, 0xF>(v);
-  v += lanes_or_zero_f64<0x142, 0xA>(v);
-  v += lanes_or_zero_f64<0x143, 0xC>(v);
-  return v;
-}
-__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
-  v += lanes_or_zero_u32<0x111, 0xF>(v);
-  v += lanes_or_zero_u32<0x112, 0xF>(v);
-  v += lanes_or_zero_u32<0x114, 0xF>(v);
-  v += lanes_or_zero_u32<0x118, 0xF>(v);
-  v += lanes_or_zero_u32<0x142, 0xA>(v);
-  v += lanes_or_zero_u32<0x143, 0xC>(v);
-  return v;
-}
 __device__ __forceinline__ float wave_sum_f32(float v) {
   v += __int_as_float(dpp_i32<kDppQuadXor1>(__float_as_int(v)));
   v += __int_as_float(dpp_i32<kDppQuadXor2>(__float_as_int(v)));
@@ -1575,8 +1547,10 @@ __global__ __launch_bounds__(kThreads) void zero_scales_kernel(float* scales, in
 static inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 size_t exact_wide_workspace_bytes(const qa_layout* L);
-int exact_thresholds_wide(const qa_layout* L, const float* g, int64_t g_stride, float* thresholds,
-                            void* ws, size_t ws_bytes, hipStream_t stream);
+int exact_thresholds_wide(const qa_layout* L, const float* g, int64_t g_stride, uint32_t* codes, float* scales,
+                          float* thresholds, double* part_sum, uint32_t* part_cnt, void* ws, size_t ws_bytes,
+                          bool* coded, hipStream_t stream);
+void quantize_workspace_parts(const qa_layout* L, void* ws, double** part_sum, uint32_t** part_cnt, float** thr);
 
 size_t quantize_workspace_bytes(const qa_layout* L) {
   if (L->bucket != 0 && L->bucket <= kTile) return 0;
@@ -1630,9 +1604,11 @@ int quantize_launch(const qa_layout* L, const float* g, int64_t g_stride, uint32
     const size_t own = quantize_workspace_bytes(L), more = exact_wide_workspace_bytes(L);
     if (!ws || ws_bytes < own + more) return QA_ERR_WORKSPACE;
     if (!aligned(ws, 256)) return QA_ERR_ALIGNMENT;
-    const int rc = exact_thresholds_wide(L, g, g_stride, thresholds, static_cast<char*>(ws) + own,
-                                           ws_bytes - own, stream);
-    if (rc != QA_OK) return rc;
+    bool coded = false;
+    quantize_workspace_parts(L, ws, &a.part_sum, &a.part_cnt, &a.thr_ws);
+    const int rc = exact_thresholds_wide(L, g, g_stride, codes, scales, thresholds, a.part_sum, a.part_cnt,
+                                         static_cast<char*>(ws) + own, ws_bytes - own, &coded, stream);
+    if (rc != QA_OK || coded) return rc;
     a.thresh_given = 1;                                  // the passes below read what it wrote
   } else if (flags & QA_THRESH_EXACT) {
     const int log2b = L->bucket ? ilog2(L->bucket) : 12;

@@ -1142,6 +1142,68 @@ def test_exact_threshold_of_a_long_vector_is_optimal_to_binary64_resolution():
     assert int(ulp_distance(s[:, :1], s_ref[:, :1]).max()) <= 1
 
 
+SAMPLED = ["gauss", "sparse laplace", "layers", "heavy", "ternary", "ramp", "outlier", "inf", "small ones", "zeros", "nan",
+           "block"]
+
+
+def sampled_vector(kind, d, rng):
+    v = rng.standard_normal(d).astype(np.float32)
+    if kind == "sparse laplace":
+        v = (rng.laplace(size=d) * (rng.random(d) < 0.05)).astype(np.float32)
+    if kind == "layers":                                 # magnitudes that differ along the vector
+        v *= np.repeat(10.0 ** -np.arange(8), -(-d // 8))[:d].astype(np.float32)
+    if kind == "heavy":                                  # an optimum of few: no bracket
+        v /= rng.standard_normal(d).astype(np.float32)
+    if kind == "ternary":                                # an optimum between two values
+        v = rng.integers(-1, 2, d).astype(np.float32)
+    if kind == "ramp":                                   # the bracket's components lie side by side: the list overflows
+        v = np.arange(d, dtype=np.float32)
+    if kind == "outlier":                                # beyond the histogram of the one pass
+        v[d // 2] = 1e30
+    if kind == "inf":
+        v[[5, d // 2]] = np.inf
+    if kind == "small ones":                             # all but a few below the histogram
+        v[rng.random(d) < 0.7] = 1e-20
+    if kind == "zeros":
+        v[:] = 0
+    if kind == "nan":
+        v[d - 3] = np.nan
+    if kind == "block":                                  # all that is kept in one place
+        v *= 1e-6
+        v[d // 3: d // 3 + d // 40] *= 1e6
+    return v
+
+
+@pytest.mark.parametrize("d,bucket", [((1 << 21) + 4099, 0), ((1 << 21) + 4099, 1 << 21), (1 << 22, 1 << 21)])
+@pytest.mark.parametrize("first", range(0, len(SAMPLED), 4))
+def test_exact_threshold_of_sampled_buckets(d, bucket, first):
+    """Buckets long enough to be sampled and read once, where the bracket holds and where it does not, next to each
+    other.  Thresholds are the oracle's unless two cuts agree to binary64 rounding (2^-52 a term over
+    2^22 terms of one sign, of which a few cancel: 1e-12 of the objective)."""
+    rng = np.random.default_rng(d + first)
+    kinds = SAMPLED[first:first + 4]
+    g = np.stack([sampled_vector(k, d, rng) for k in kinds])
+    c, s, th, L = gpu_quantize_pack(g, bucket, exact=True)
+    b = bucket or d
+    for m, kind in enumerate(kinds):
+        for k in range(L.n_buckets):
+            v = g[m, k * b:(k + 1) * b]
+            if np.isnan(v).any():
+                assert th[m, k] == 0
+                continue
+            ref = oracle.exact_thresholds(v)[0]
+            if th[m, k] != ref:
+                a = np.abs(v.astype(np.float64))
+                kept, kept_ref = a > th[m, k], a > ref
+                obj, best = a[kept].sum() ** 2 / kept.sum(), a[kept_ref].sum() ** 2 / kept_ref.sum()
+                assert (a == th[m, k]).any() and obj >= best * (1 - 1e-12), (kind, k, th[m, k], ref)
+    c_ref, s_ref, _ = oracle.quantize_pack(g, bucket, thresholds=th[:, :L.n_buckets])
+    assert np.array_equal(c[:, :L.words], c_ref)
+    finite = np.isfinite(s_ref)
+    assert np.array_equal(s[:, :L.n_buckets][~finite], s_ref[~finite])
+    assert int(ulp_distance(s[:, :L.n_buckets][finite], s_ref[finite]).max()) <= 1
+
+
 def test_exact_threshold_checks_workspace_and_missing_output():
     g = dev(np.ones((1, 8192), np.float32))
     codes = torch.zeros((1, 512), dtype=torch.int32, device=DEV)
