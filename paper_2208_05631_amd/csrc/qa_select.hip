@@ -30,6 +30,7 @@ struct SelArgs {
   int seg;                     // threads per bucket inside a tile: bucket/16 for 64 <= bucket <= 4096
   int64_t nb, ntiles, tiles_per_bucket, area_words;   // buckets spanning several tiles
   uint32_t* ws_count; double* ws_s1; double* ws_s2; uint32_t* ws_c2; int64_t* ws_start; float* ws_thr;
+  uint2* ws_open;              // one-read quantizer: kOpenSlots open components of every tile
   int64_t samples;             // one-read quantizer: sampled tiles per bucket (at most)
 };
 
@@ -392,13 +393,19 @@ constexpr DepositLut make_extract_lut() {
 }
 __device__ const DepositLut kExtractLut = make_extract_lut();
 
+// A tile's stream word w, which ends or begins inside it, to memory or to the tile's head.
+__device__ __forceinline__ void store_word(uint32_t* out, uint32_t w, uint32_t first, uint32_t bits, uint32_t* head) {
+  if (w == 0 && first != 0) *head = bits;
+  else out[w] = bits;
+}
+
 // S applied to a coded message: one wave per 4096-tile, lane l holds code words j*64 + l of the
 // tile (as in the decoder).  Each word's marked codes are packed through the extract table and
 // appended at their position in the tile's compact stream, which is assembled in LDS (one area
 // per wave) and written out in whole words.
 // kSelMulti (buckets that span tiles): the tile's codes start at code start%16 of word start/16
-// of the bucket's area (start from the scan in the workspace); words that a neighbouring tile may
-// also touch are OR-ed into memory that was zeroed before, the others stored.
+// of the bucket's area (start from the scan in the workspace); its part of a word that begins in an
+// earlier tile goes to the workspace for gsel_join_kernel, the other words are stored.
 // kSelLocal (buckets inside a tile): bucket j's stream starts at word j*seg; its first
 // ceil(K_j/16) words are written, and K_j by the bucket's first lane.
 template <int KIND>
@@ -482,12 +489,10 @@ __global__ __launch_bounds__(kThreads) void select_codes_kernel(SelArgs a) {
     const uint32_t end = start, nwords = (end + 15) / 16;  // one past the tile's last code
     uint32_t* out = a.sel_codes + (int64_t)m * a.code_stride + base;
     if (KIND == kSelMulti) {
+      uint32_t head = 0;
       if (end != first)
-        for (uint32_t w = lane; w < nwords; w += kWave) {  // at most 257 words
-          const bool shared = (w == 0 && first != 0) || (w == nwords - 1 && (end % 16) != 0);
-          if (shared) atomicOr(&out[w], stream[w]);
-          else out[w] = stream[w];
-        }
+        for (uint32_t w = lane; w < nwords; w += kWave) store_word(out, w, first, stream[w], &head);   // at most 257
+      if (lane == 0) a.ws_count[(int64_t)m * a.ntiles + tile] = head;
     } else if (KIND == kSelLocal) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -517,8 +522,8 @@ __global__ __launch_bounds__(kThreads) void select_codes_kernel(SelArgs a) {
 //     message of the Encode paragraph), span tiles: a first pass counts every tile's selected
 //     components, a scan per bucket turns the counts into each tile's first position in the
 //     bucket's stream (kept in the workspace), and the tiles then place or fetch their codes
-//     there.  Neighbouring tiles share stream words, so producers OR their part into such words,
-//     which a small kernel has zeroed.
+//     there.  Neighbouring tiles share stream words: the tile in which such a word begins stores
+//     it, and a small kernel adds what the others have left in the workspace.
 
 // the 16 indicator bits of the thread's coordinates, without those at or beyond d
 __device__ __forceinline__ uint32_t live_mask16(const SelArgs& a, const uint32_t* ind, int64_t tile, int t) {
@@ -707,22 +712,18 @@ __global__ __launch_bounds__(THREADS) void gsel_scan_kernel(SelArgs a) {
   }
 }
 
-// The words of the stream that two tiles share -- those where a tile begins or ends off a word's
-// boundary -- are set to 0 for the producers to OR into; all others they store whole.  A thread per
-// tile: 9.1 us for 8 workers x 2^27 (all ceil(K/16) words of every area, before: 77).
-__global__ __launch_bounds__(kThreads) void gsel_zero_kernel(SelArgs a) {
+// A word of the stream that several tiles share is stored by the tile it begins in; the others leave their
+// part of it, their head, in the slot of their count, and this kernel adds the heads.  A thread per tile:
+// 9 to 11 us for 8 workers x 2^27.  Two atomic ORs per tile among the stores of the coders themselves, into words zeroed
+// before, cost 0.4 ms there (the quantizer 1.11 -> 0.70 ms without them, S of a coded message 0.25 -> 0.19 as a whole).
+__global__ __launch_bounds__(kThreads) void gsel_join_kernel(SelArgs a) {
   const int64_t tile = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (tile >= a.ntiles) return;
   const int m = blockIdx.y;
   const int64_t k = tile / a.tiles_per_bucket, at = (int64_t)m * a.ntiles + tile;
-  const uint32_t c = a.ws_count[at];
-  if (c == 0) return;
-  const int64_t from = a.ws_start[at], to = from + c;
-  uint32_t* area = a.sel_codes + (int64_t)m * a.code_stride + k * a.area_words;
-  if (from & 15) area[from >> 4] = 0u;
-  if (to & 15) area[to >> 4] = 0u;
+  const uint32_t head = a.ws_count[at];
+  if (head) atomicOr(&a.sel_codes[(int64_t)m * a.code_stride + k * a.area_words + (a.ws_start[at] >> 4)], head);
 }
-
 // Q(S(g, I)) for buckets of 64 .. 2048 coordinates: thread t = code word t of the tile, a bucket =
 // a.seg consecutive threads.
 __global__ __launch_bounds__(kThreads) void gsel_quantize_local_kernel(SelArgs a) {
@@ -784,21 +785,30 @@ __global__ __launch_bounds__(kThreads) void gsel_quantize_local_kernel(SelArgs a
 // the wave) from code position `first` on; the sums of |v| over the marked (BRACKET) and over the kept
 // components and the latter's number per lane.  BRACKET: components up to `lo` get 0, above `hi` their
 // code, those between the pattern 10.
-// Bound by the reads: 4.6 GB for 8 workers x 2^27 in 1.03 to 1.12 ms.  Half of the tile's components held
-// at a time, all of them or a quarter make no difference; slower are nontemporal loads (1.42: four lanes
-// of a 64-byte stride share every line), the gradient brought through LDS (1.20) and selecting in place of
-// the branch around an unmarked component (1.22).
+// Bound by vector instructions (1500 per tile; 8 workers x 2^27: 0.77 ms without the list, 0.84 with it, which
+// the settling pass returns four times over).  Slower were nontemporal loads (four lanes of a 64-byte stride share
+// every line) and selecting in place of the branch around an unmarked component.
+// Open components are listed, value and place in the tile's codes, as long as the tile's slots last.
+constexpr uint32_t kOpenSlots = 16, kOpenUnlisted = 31;
 struct TileCodes {
   double s1, s2;
-  uint32_t c2, end;                                      // end: one past the tile's last code
+  uint32_t c2, end, open;                                // end: one past the tile's last code
 };
+__device__ __forceinline__ void list_open(uint2* list, bool open, float x, uint32_t place, uint32_t* listed) {
+  const uint64_t some = __ballot(open);
+  if (some == 0) return;                                 // uniform
+  const uint32_t slot = *listed + __builtin_amdgcn_mbcnt_hi((uint32_t)(some >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)some, 0u));
+  if (open && slot < kOpenSlots) list[slot] = make_uint2(__float_as_uint(x), place);
+  *listed += (uint32_t)__popcll(some);
+}
 __device__ __forceinline__ void wave_fence() {           // order of a wave's own LDS accesses
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
 template <bool BRACKET>
 __device__ __forceinline__ TileCodes code_selected_tile(const SelArgs& a, int64_t tile, int m, uint32_t first,
-                                                        float lo, float hi, uint32_t* stream) {
+                                                        float lo, float hi, uint32_t* stream, uint2* open_list) {
   const int lane = threadIdx.x % kWave;
   const uint32_t* ind = a.ind_in + (int64_t)m * a.ind_stride;
   const float* g = a.g + (int64_t)m * a.g_stride;
@@ -806,7 +816,7 @@ __device__ __forceinline__ TileCodes code_selected_tile(const SelArgs& a, int64_
   for (int j = 0; j < 4; ++j) stream[j * 64 + lane] = 0u;
   if (lane < 2) stream[kTileWords + lane] = 0u;
   wave_fence();
-  TileCodes r{0.0, 0.0, 0u, first};
+  TileCodes r{0.0, 0.0, 0u, first, 0u};
 #pragma unroll 1
   for (int half = 0; half < 4; half += 2) {
     uint32_t mask[2], incl[2];
@@ -830,7 +840,9 @@ __device__ __forceinline__ TileCodes code_selected_tile(const SelArgs& a, int64_
       r.end += (uint32_t)__builtin_amdgcn_readlane((int)incl[h], kWave - 1);
       uint32_t bits = 0, filled = 0;
 #pragma unroll
-      for (int c = 0; c < 16; ++c)
+      for (int c = 0; c < 16; ++c) {
+        bool open = false;
+        const uint32_t place = before - first + filled / 2;
         if ((mask[h] >> c) & 1u) {
           const float av = fabsf(v[h][c]);
           uint32_t f;
@@ -838,7 +850,8 @@ __device__ __forceinline__ TileCodes code_selected_tile(const SelArgs& a, int64_
             r.s1 += (double)av;
             const bool keep = av > hi;
             if (keep) { r.s2 += (double)av; ++r.c2; }
-            f = keep ? 1u | ((__float_as_uint(v[h][c]) >> 30) & 2u) : (av > lo ? 2u : 0u);
+            open = av > lo && !keep;
+            f = keep ? 1u | ((__float_as_uint(v[h][c]) >> 30) & 2u) : (open ? 2u : 0u);
           } else {
             if (av > lo) { r.s2 += (double)av; ++r.c2; }
             f = ternary_field(v[h][c], lo);
@@ -846,6 +859,8 @@ __device__ __forceinline__ TileCodes code_selected_tile(const SelArgs& a, int64_
           bits |= f << filled;
           filled += 2;
         }
+        if (BRACKET) list_open(open_list, open, v[h][c], place, &r.open);
+      }
       if (n) {
         const uint32_t w0 = before / 16, sh = 2 * (before % 16);
         atomicOr(&stream[w0], bits << sh);
@@ -860,19 +875,121 @@ __device__ __forceinline__ TileCodes code_selected_tile(const SelArgs& a, int64_
   return r;
 }
 
-// The assembled codes of a tile to their place in the bucket's stream (words that a neighbouring tile may
-// also touch are OR-ed into memory zeroed before), its kept sum and count to the workspace.  BRACKET:
-// the one pass of the one-read form below; else the threshold comes from pass 2.
+// The same for a tile of at most kFewMarked marked components, in two steps that leave the others out: the
+// wave reads the tile 16 bytes per lane side by side and drops the marked values into LDS at their place in
+// the stream, then takes them 64 at a time, sixteen neighbours to a code word.  Unmarked values go to a slot
+// that nobody reads: as many instructions as a branch, and the loads of LDS stay in one piece.  Bound by the
+// read of the gradient: 8 workers x 2^27, 7 % marked, 0.69 ms for 4.4 GB (the other form 0.77).  The line: LDS
+// for 1520 lets five work-groups share a CU, and two rounds of 64 cost more than the other form's words from
+// there on (30 / 45 / 97 % marked, the whole call with a line at 1520 / 2032 / 4096: 900 / 934 / 1248, 1010 /
+// 1034 / 1498 and 1068 / 1072 / 2368 us).
+constexpr uint32_t kFewMarked = 1520, kFewCodes = 1536;  // with 15 codes of a shared first word
+struct SelWaveLds {
+  uint2 words[kTile / 32];                               // indicator word, codes before it
+  union { float vals[kFewCodes + kWave]; uint32_t stream[kTileWords + 2]; };
+};
 template <bool BRACKET>
-__global__ __launch_bounds__(kThreads) void gsel_quantize_multi_kernel(SelArgs a) {
-  __shared__ uint32_t stream_all[kWaves][kTileWords + 2];
+__device__ __forceinline__ TileCodes code_few_marked(const SelArgs& a, int64_t tile, int m, uint32_t first,
+                                                     float lo, float hi, SelWaveLds& lds, uint32_t* out,
+                                                     uint2* open_list, uint32_t* head) {
+  const int lane = threadIdx.x % kWave;
+  const uint32_t* ind = a.ind_in + (int64_t)m * a.ind_stride;
+  const float* g = a.g + (int64_t)m * a.g_stride;
+  uint32_t iv[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int64_t iw = tile * (kTile / 32) + 2 * lane + h;
+    iv[h] = iw < a.NW ? ind[iw] : 0u;
+    const int64_t left = a.d - 32 * iw;
+    if (left < 32) iv[h] = left > 0 ? (iv[h] & ((1u << left) - 1u)) : 0u;
+  }
+  const uint32_t n0 = (uint32_t)__popc(iv[0]), n1 = (uint32_t)__popc(iv[1]);
+  const uint32_t incl = wave_inclusive_scan_u32(n0 + n1);
+  const uint32_t ex = first + incl - n0 - n1;
+  lds.words[2 * lane] = make_uint2(iv[0], ex);
+  lds.words[2 * lane + 1] = make_uint2(iv[1], ex + n0);
+  TileCodes r{0.0, 0.0, 0u, first + (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1), 0u};
+  wave_fence();
+  const uint32_t sh = 4 * (lane & 7), below = (1u << sh) - 1u;
+  typedef float floatx4 __attribute__((ext_vector_type(4)));
+#pragma unroll 1
+  for (int j0 = 0; j0 < 16; j0 += 8) {
+    floatx4 v[8];
+    if ((tile + 1) * kTile <= a.d) {
+      const floatx4* src = reinterpret_cast<const floatx4*>(g + tile * kTile) + j0 * kWave + lane;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = __builtin_nontemporal_load(src + j * kWave);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int64_t i = tile * kTile + ((j0 + j) * kWave + lane) * 4 + e;
+          v[j][e] = i < a.d ? g[i] : 0.0f;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const uint2 w = lds.words[8 * (j0 + j) + (lane >> 3)];
+      const uint32_t nib = w.x >> sh;
+      uint32_t pos = w.y + (uint32_t)__popc(w.x & below);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool marked = (nib & (1u << e)) != 0u;
+        lds.vals[marked ? pos : kFewCodes + lane] = v[j][e];
+        pos += marked ? 1u : 0u;
+      }
+    }
+  }
+  wave_fence();
+  uint32_t mine = 0;
+  const uint32_t nwords = r.end != first ? (r.end + 15) / 16 : 0u;
+  for (uint32_t p0 = 0, q = 0; p0 < r.end; p0 += kWave, ++q) {
+    const uint32_t p = p0 + lane;
+    const float x = p >= first && p < r.end ? lds.vals[p] : 0.0f;
+    const float av = fabsf(x);
+    uint32_t f;
+    if (BRACKET) {
+      const bool keep = av > hi, open = av > lo && !keep;
+      r.s1 += (double)av;
+      r.s2 += (double)(keep ? av : 0.0f);
+      r.c2 += (uint32_t)__popcll(__ballot(keep));
+      f = keep ? 1u | ((__float_as_uint(x) >> 30) & 2u) : (open ? 2u : 0u);
+      list_open(open_list, open, x, p - first, &r.open);
+    } else {
+      const bool keep = av > lo;
+      r.s2 += (double)(keep ? av : 0.0f);
+      r.c2 += (uint32_t)__popcll(__ballot(keep));
+      f = ternary_field(x, lo);
+    }
+    uint32_t w = f << (2 * (lane & 15));                 // the sixteen codes of a word: a row of lanes
+    w |= (uint32_t)dpp_i32<kDppQuadXor1>((int)w);
+    w |= (uint32_t)dpp_i32<kDppQuadXor2>((int)w);
+    w |= (uint32_t)dpp_i32<kDppRowHalfMirror>((int)w);
+    w |= (uint32_t)dpp_i32<kDppRowMirror>((int)w);
+    if ((uint32_t)(lane & 15) == (q & 15u)) mine = w;
+    if ((q & 15u) == 15u || p0 + kWave >= r.end) {       // 64 words, or the last ones
+      const uint32_t wl = (q >> 4) * kWave + 4 * (lane & 15) + (lane >> 4);
+      if (wl < nwords) store_word(out, wl, first, mine, head);   // word 0: lane 0
+    }
+  }
+  r.s1 = wave_sum_f64(r.s1);
+  r.s2 = wave_sum_f64(r.s2);
+  return r;
+}
+
+// The assembled codes of a tile to their place in the bucket's stream, its kept sum and count to the
+// workspace.  BRACKET: the one pass of the one-read form below; else the threshold comes from pass 2.
+template <bool BRACKET>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) void gsel_quantize_multi_kernel(SelArgs a) {
+  __shared__ SelWaveLds lds_all[kWaves];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  uint32_t* stream = stream_all[wave];
   const int64_t tile = (int64_t)blockIdx.x * kWaves + wave;
   if (tile >= a.ntiles) return;
   const int m = blockIdx.y;
   const int64_t at = (int64_t)m * a.ntiles + tile, k = tile / a.tiles_per_bucket;
   const int64_t st = a.ws_start[at];
+  const uint32_t marked = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.ws_count[at]);
   const uint32_t first = (uint32_t)(st & 15);
   const float thr = a.ws_thr[(int64_t)m * a.nb + k];
   const float lo = BRACKET ? a.scales[(int64_t)m * a.scale_stride + k] : thr;
@@ -896,22 +1013,32 @@ __global__ __launch_bounds__(kThreads) void gsel_quantize_multi_kernel(SelArgs a
       }
     }
     s1 = wave_sum_f64(s1);
-    if (lane == 0) a.ws_s1[at] = s1;
+    if (lane == 0) {                                     // the settling pass adds to zeroed shared words
+      a.ws_s1[at] = s1;
+      a.ws_count[at] = 0u;
+      uint32_t* area = a.sel_codes + (int64_t)m * a.code_stride + k * a.area_words;
+      if (marked && first) area[st >> 4] = 0u;
+      if (marked && ((st + marked) & 15)) area[(st + marked) >> 4] = 0u;
+    }
     return;
   }
-  const TileCodes r = code_selected_tile<BRACKET>(a, tile, m, first, lo, thr, stream);
-  const uint32_t nwords = (r.end + 15) / 16;
   uint32_t* out = a.sel_codes + (int64_t)m * a.code_stride + k * a.area_words + (st >> 4);
-  if (r.end != first)
-    for (uint32_t w = lane; w < nwords; w += kWave) {    // at most 257 words
-      const bool shared = (w == 0 && first != 0) || (w == nwords - 1 && (r.end % 16) != 0);
-      if (shared) atomicOr(&out[w], stream[w]);
-      else out[w] = stream[w];
-    }
+  TileCodes r;
+  uint2* open_list = BRACKET ? a.ws_open + at * kOpenSlots : nullptr;
+  uint32_t head = 0;
+  if (marked <= kFewMarked) {
+    r = code_few_marked<BRACKET>(a, tile, m, first, lo, thr, lds_all[wave], out, open_list, &head);
+  } else {
+    uint32_t* stream = lds_all[wave].stream;
+    r = code_selected_tile<BRACKET>(a, tile, m, first, lo, thr, stream, open_list);
+    const uint32_t nwords = (r.end + 15) / 16;
+    for (uint32_t w = lane; w < nwords; w += kWave) store_word(out, w, first, stream[w], &head);   // at most 257 words
+  }
   if (lane == 0) {
+    a.ws_count[at] = head;                               // lane 0 has word 0
     if (BRACKET) a.ws_s1[at] = r.s1;
     a.ws_s2[at] = r.s2;
-    a.ws_c2[at] = r.c2;
+    a.ws_c2[at] = r.c2 | ((r.open <= kOpenSlots ? r.open : kOpenUnlisted) << 16);
   }
 }
 
@@ -1001,26 +1128,19 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void gsel_threshold_kernel(S
   }
 }
 
-// A wave per tile: the time is the chain of dependent loads (8 workers x 2^27: 164 to 183 us; two tiles per wave,
-// their loads phase by phase, 190, four 336: their registers cost more waves than that saves).  With a
-// bracket that held: each lane reads its words' codes back from the stream, finds the pattern 10, and
-// exchanges it for the component's code in place.  Without a bracket the tile is coded here, and with one
-// that missed again; of a word that it shares with a neighbour then only its own bits change.
-__global__ __launch_bounds__(kThreads) void gsel_settle_kernel(SelArgs a) {
-  __shared__ uint32_t stream_all[kWaves][kTileWords + 2];
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const int64_t tile = (int64_t)blockIdx.x * kWaves + wave;
-  if (tile >= a.ntiles) return;
-  const int m = blockIdx.y;
+// A tile whose open components are not listed, by a wave.  With a bracket that held: each lane reads its
+// words' codes back from the stream, finds the pattern 10, and exchanges it for the component's code in
+// place.  Without a bracket the tile is coded here, and with one that missed again; of a word that it shares
+// with a neighbour then only its own bits change.
+__device__ __forceinline__ void settle_tile(const SelArgs& a, int64_t tile, int m, uint32_t* stream) {
+  const int lane = threadIdx.x % kWave;
   const int64_t slot = (int64_t)m * a.ntiles + tile, k = tile / a.tiles_per_bucket;
-  const float D = a.ws_thr[(int64_t)m * a.nb + k];
+  const float D = a.ws_thr[(int64_t)m * a.nb + k], held = a.scales[(int64_t)m * a.scale_stride + k];
   const int64_t st = a.ws_start[slot];
   const uint32_t first = (uint32_t)(st & 15);
   uint32_t* out = a.sel_codes + (int64_t)m * a.code_stride + k * a.area_words + (st >> 4);
-  const float held = a.scales[(int64_t)m * a.scale_stride + k];
   if (held != 1.0f) {
-    uint32_t* stream = stream_all[wave];
-    const TileCodes r = code_selected_tile<false>(a, tile, m, first, D, 0.0f, stream);
+    const TileCodes r = code_selected_tile<false>(a, tile, m, first, D, 0.0f, stream, nullptr);
     const uint32_t nwords = (r.end + 15) / 16;
     if (r.end != first)
       for (uint32_t w = lane; w < nwords; w += kWave) {
@@ -1060,9 +1180,8 @@ __global__ __launch_bounds__(kThreads) void gsel_settle_kernel(SelArgs a) {
     open[j] = (bits >> 1) & ~bits & 0x55555555u;         // low bit of every code 10
     any |= open[j];
   }
-  if (!__any(any != 0)) return;
   const double s_before = a.ws_s2[slot];                 // the tile's sums, to be added to
-  const uint32_t c_before = a.ws_c2[slot];
+  const uint32_t c_before = a.ws_c2[slot] & 0xFFFFu;
   double s = 0.0;
   uint32_t c = 0;
   while (__any(any != 0)) {                              // a code of every word at a time
@@ -1092,7 +1211,54 @@ __global__ __launch_bounds__(kThreads) void gsel_settle_kernel(SelArgs a) {
   }
   s = wave_sum_f64(s);
   c = wave_sum_u32(c);
-  if (lane == 0 && c) { a.ws_s2[slot] = s_before + s; a.ws_c2[slot] = c_before + c; }
+  if (lane == 0) { a.ws_s2[slot] = s_before + s; a.ws_c2[slot] = c_before + c; }
+}
+
+// A wave for four tiles, sixteen lanes for the listed components of each: everything that a tile needs is
+// requested at once.  Tiles without a list follow one by one.  8 workers x 2^27: 30 us; reading
+// every tile's marks and codes back took 180, a chain of dependent loads per tile.
+__global__ __launch_bounds__(kThreads) void gsel_settle_kernel(SelArgs a) {
+  __shared__ uint32_t stream_all[kWaves][kTileWords + 2];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, e = lane % (int)kOpenSlots;
+  constexpr int kTilesPerWave = kWave / (int)kOpenSlots;
+  const int64_t tile0 = ((int64_t)blockIdx.x * kWaves + wave) * kTilesPerWave, tile = tile0 + lane / (int)kOpenSlots;
+  const int m = blockIdx.y;
+  bool listed = false, unlisted = false, keep = false;
+  float av = 0.0f;
+  double s_before = 0.0;
+  uint32_t c_before = 0;
+  const int64_t slot = (int64_t)m * a.ntiles + tile;
+  if (tile < a.ntiles) {
+    const int64_t k = tile / a.tiles_per_bucket;
+    const float D = a.ws_thr[(int64_t)m * a.nb + k], held = a.scales[(int64_t)m * a.scale_stride + k];
+    const int64_t st = a.ws_start[slot];
+    const uint32_t c = a.ws_c2[slot];
+    const uint2 entry = a.ws_open[slot * kOpenSlots + e];
+    s_before = a.ws_s2[slot];
+    c_before = c & 0xFFFFu;
+    const uint32_t n = c >> 16;
+    unlisted = held != 1.0f || n > kOpenSlots;
+    listed = !unlisted && n > 0;
+    if (listed && (uint32_t)e < n) {
+      const float x = __uint_as_float(entry.x);
+      av = fabsf(x);
+      keep = av > D;
+      const int64_t place = st + entry.y;
+      uint32_t* area = a.sel_codes + (int64_t)m * a.code_stride + k * a.area_words;
+      atomicXor(&area[place >> 4], (2u ^ ternary_field(x, D)) << (2 * (uint32_t)(place & 15)));
+    }
+  }
+  double s = keep ? (double)av : 0.0;
+  uint32_t c = keep ? 1u : 0u;
+  s += dpp_f64<kDppQuadXor1>(s);       c += (uint32_t)dpp_i32<kDppQuadXor1>((int)c);
+  s += dpp_f64<kDppQuadXor2>(s);       c += (uint32_t)dpp_i32<kDppQuadXor2>((int)c);
+  s += dpp_f64<kDppRowHalfMirror>(s);  c += (uint32_t)dpp_i32<kDppRowHalfMirror>((int)c);
+  s += dpp_f64<kDppRowMirror>(s);      c += (uint32_t)dpp_i32<kDppRowMirror>((int)c);
+  if (listed && e == 0) { a.ws_s2[slot] = s_before + s; a.ws_c2[slot] = c_before + c; }
+  for (uint64_t left = __ballot(unlisted && e == 0); left; left &= left - 1) {
+    wave_fence();                                        // the stream of the tile before has been read
+    settle_tile(a, tile0 + (__ffsll((unsigned long long)left) - 1) / (int)kOpenSlots, m, stream_all[wave]);
+  }
 }
 
 // last pass of the multi-tile quantizer: scale of each (bucket, worker)
@@ -1125,30 +1291,38 @@ static SelKind sel_kind(const qa_layout* L) {
   return kSelMulti;                                                                 // buckets over several tiles
 }
 
+static bool sel_one_read(const qa_layout* L) {
+  const int64_t ntiles = tiles_of(L->d), per = L->bucket ? L->bucket / kTile : ntiles;
+  return sel_kind(L) == kSelMulti && per >= kSelOneReadBucketTiles && ntiles >= kSelOneReadBucketTiles &&
+         ntiles * L->M >= kSelOneReadTiles && buckets_of(L->d, L->bucket) * (per / kSelSampleEvery) <= 0x7fffffffLL;
+}
+
 static inline size_t sel_align(size_t v) { return (v + 255) & ~size_t(255); }
-// zero: a producer of streams follows
 template <bool HAS_G>
-static void scan_launch(const SelArgs& a, int M, bool zero, hipStream_t stream) {
+static void scan_launch(const SelArgs& a, int M, hipStream_t stream) {
   const dim3 buckets((unsigned)a.nb, (unsigned)M);
   if (a.tiles_per_bucket <= kWave * kScanRun)
     hipLaunchKernelGGL((gsel_scan_kernel<HAS_G, kWave>), buckets, dim3(kWave), 0, stream, a);
   else
     hipLaunchKernelGGL((gsel_scan_kernel<HAS_G, 1024>), buckets, dim3(1024), 0, stream, a);
-  if (zero)
-    hipLaunchKernelGGL(gsel_zero_kernel, dim3((unsigned)((a.ntiles + kThreads - 1) / kThreads), (unsigned)M),
-                       dim3(kThreads), 0, stream, a);
+}
+static void join_launch(const SelArgs& a, int M, hipStream_t stream) {
+  hipLaunchKernelGGL(gsel_join_kernel, dim3((unsigned)((a.ntiles + kThreads - 1) / kThreads), (unsigned)M),
+                     dim3(kThreads), 0, stream, a);
 }
 static inline dim3 count_grid(const qa_layout* L) {
   return dim3((unsigned)((tiles_of(L->d) + kWaves * kCountTiles - 1) / (kWaves * kCountTiles)), (unsigned)L->M);
 }
 
 // Workspace of the multi-tile path: per (worker, tile) a count, two binary64 sums, a kept count and
-// the tile's first position in its bucket's stream; per (worker, bucket) a threshold.
+// the tile's first position in its bucket's stream; per (worker, bucket) a threshold.  Quantizers that read
+// once also list open components.
 size_t select_workspace_bytes(const qa_layout* L) {
   if (sel_kind(L) != kSelMulti) return 0;
   const size_t mt = (size_t)L->M * (size_t)tiles_of(L->d);
   return sel_align(mt * 4) + 2 * sel_align(mt * 8) + sel_align(mt * 4) + sel_align(mt * 8) +
-         sel_align((size_t)L->M * (size_t)buckets_of(L->d, L->bucket) * 4);
+         sel_align((size_t)L->M * (size_t)buckets_of(L->d, L->bucket) * 4) +
+         (sel_one_read(L) ? sel_align(mt * kOpenSlots * sizeof(uint2)) : 0);
 }
 
 static int check_select_layout(const qa_layout* L) {
@@ -1179,7 +1353,8 @@ static int general_args(const qa_layout* L, SelArgs& a, void* ws, size_t ws_byte
   a.ws_s2 = reinterpret_cast<double*>(p);      p += sel_align(mt * 8);
   a.ws_c2 = reinterpret_cast<uint32_t*>(p);    p += sel_align(mt * 4);
   a.ws_start = reinterpret_cast<int64_t*>(p);  p += sel_align(mt * 8);
-  a.ws_thr = reinterpret_cast<float*>(p);
+  a.ws_thr = reinterpret_cast<float*>(p);      p += sel_align((size_t)L->M * (size_t)a.nb * 4);
+  a.ws_open = sel_one_read(L) ? reinterpret_cast<uint2*>(p) : nullptr;
   return QA_OK;
 }
 
@@ -1274,19 +1449,22 @@ extern "C" int qa_quantize_pack_selected(const qa_layout* layout, const float* g
   const dim3 buckets((unsigned)a.nb, (unsigned)layout->M);
   const dim3 waves((unsigned)((a.ntiles + kWaves - 1) / kWaves), (unsigned)layout->M);
   a.samples = a.tiles_per_bucket / kSelSampleEvery;
-  if (a.tiles_per_bucket >= kSelOneReadBucketTiles && a.ntiles >= kSelOneReadBucketTiles &&
-      a.ntiles * layout->M >= kSelOneReadTiles && a.nb * a.samples <= 0x7fffffffLL) {
+  constexpr int kSettled = kThreads / (int)kOpenSlots;   // tiles per work-group
+  const dim3 settle_grid((unsigned)((a.ntiles + kSettled - 1) / kSettled), (unsigned)layout->M);
+  if (sel_one_read(layout)) {
     hipLaunchKernelGGL(gsel_count_ind_kernel, count_grid(layout), block, 0, stream, a);
-    scan_launch<false>(a, layout->M, true, stream);
+    scan_launch<false>(a, layout->M, stream);
     hipLaunchKernelGGL(gsel_sample_kernel, dim3((unsigned)(a.nb * a.samples), (unsigned)layout->M), block, 0, stream, a);
     hipLaunchKernelGGL(gsel_band_kernel, buckets, block, 0, stream, a);
     hipLaunchKernelGGL(gsel_quantize_multi_kernel<true>, waves, block, 0, stream, a);
+    join_launch(a, layout->M, stream);
     hipLaunchKernelGGL(gsel_threshold_kernel, buckets, block, 0, stream, a);
-    hipLaunchKernelGGL(gsel_settle_kernel, waves, block, 0, stream, a);
+    hipLaunchKernelGGL(gsel_settle_kernel, settle_grid, block, 0, stream, a);
   } else {
     hipLaunchKernelGGL(gsel_count_kernel, tiles, block, 0, stream, a);
-    scan_launch<true>(a, layout->M, true, stream);
+    scan_launch<true>(a, layout->M, stream);
     hipLaunchKernelGGL(gsel_quantize_multi_kernel<false>, waves, block, 0, stream, a);
+    join_launch(a, layout->M, stream);
   }
   hipLaunchKernelGGL(gsel_scale_kernel, buckets, block, 0, stream, a);
   return launch_status();
@@ -1320,7 +1498,7 @@ int decode_selected_launch(const qa_layout* layout, const uint32_t* ind, int64_t
   // the workspace (unused by a decode) take it, M*nb <= M*ntiles words
   a.counts = a.ws_c2; a.scale_stride = a.nb;
   hipLaunchKernelGGL(gsel_count_ind_kernel, count_grid(layout), block, 0, stream, a);
-  scan_launch<false>(a, layout->M, false, stream);
+  scan_launch<false>(a, layout->M, stream);
   hipLaunchKernelGGL(decode_selected_kernel<kSelMulti>, wave_tiles, block, 0, stream, a);
   return launch_status();
 }
@@ -1369,7 +1547,8 @@ extern "C" int qa_select_codes(const qa_layout* layout, const uint32_t* codes, c
     return launch_status();
   }
   hipLaunchKernelGGL(gsel_count_ind_kernel, count_grid(layout), block, 0, stream, a);
-  scan_launch<false>(a, layout->M, true, stream);
+  scan_launch<false>(a, layout->M, stream);
   hipLaunchKernelGGL(select_codes_kernel<kSelMulti>, wave_tiles, block, 0, stream, a);
+  join_launch(a, layout->M, stream);
   return launch_status();
 }

@@ -580,3 +580,82 @@ def test_training_with_selection_matches_oracle(method, b):
     print(f"{method}: message bits with selection / dense = {bits_sparse / bits_dense:.3f}; "
           f"nnz(x) = {(ox != 0).sum()}")
     assert bits_sparse < 0.6 * bits_dense
+
+
+def marks_per_tile(counts, d, rng):
+    """Indicator words of d coordinates with counts[i % len] marks in tile i (fewer where the vector ends)."""
+    marks = np.zeros((d + 31) // 32 * 32, bool)
+    for tile, lo in enumerate(range(0, d, 4096)):
+        n = min(4096, d - lo)
+        marks[lo + rng.permutation(n)[: min(n, counts[tile % len(counts)])]] = True
+    return np.packbits(marks, bitorder="little").view(np.uint32)
+
+
+@pytest.mark.parametrize("d,bucket", [(4096 * 23 + 17, 0), (4096 * 23 + 4095, 8192), (4096 * 12, 16384)])
+def test_streams_over_tiles_of_every_marked_count_match_oracle(d, bucket):
+    """Marked counts around a word (16), a round (64), the coders' line (1520) and the full tile, behind first
+    codes at every place in a word; runs of empty tiles and of tiles that share one word."""
+    counts = [0, 1, 1, 0, 3, 15, 16, 17, 63, 64, 65, 1519, 1520, 1521, 4095, 4096, 2, 0, 0, 1023, 1024, 1025]
+    rng = np.random.default_rng(d)
+    M, NW, gs = 2, (d + 31) // 32, (d + 3) // 4 * 4
+    g = (rng.standard_normal((M, gs)) * 1e-2).astype(np.float32)
+    ind = np.stack([marks_per_tile(counts[m:] + counts[:m], d, rng) for m in range(M)])
+    L = qa.Layout.make(d, M, bucket)
+    ws = workspace(qa.qa_workspace_bytes(L, qa.QA_OP_SELECT))
+    sel, push = torch.full((2, M, L.code_stride), 0x5A5A5A5A, dtype=torch.int32, device=DEV)
+    cnt = torch.zeros((M, L.scale_stride), dtype=torch.int32, device=DEV)
+    sc, th = torch.zeros((2, M, L.scale_stride), dtype=torch.float32, device=DEV)
+    ind_d = dev(ind.view(np.int32))
+    qa.qa_quantize_pack_selected(L, dev(g), gs, ind_d, NW, sel, cnt, sc, th, ws)
+    dense = rng.integers(0, 1 << 32, (M, L.code_stride), dtype=np.uint32) & np.uint32(0x55555555)
+    qa.qa_select_codes(L, dev(dense.view(np.int32)), ind_d, NW, push, cnt, ws)
+    torch.cuda.synchronize()
+    area = area_words(d, bucket)
+    for m in range(M):
+        o_sel, o_cnt, o_sc, o_th = oracle.quantize_selected(g[m, :d], ind[m], bucket=bucket)
+        o_push, _ = oracle.select_codes(dense[m], ind[m], d, bucket=bucket)
+        assert np.array_equal(host(sc)[m, :L.n_buckets], o_sc) and np.array_equal(host(th)[m, :L.n_buckets], o_th)
+        for k in range(L.n_buckets):
+            lo, nwk = k * area, (int(o_cnt[k]) + 15) // 16
+            for got, want in ((sel, o_sel), (push, o_push)):
+                row = host(got).view(np.uint32)[m]
+                assert np.array_equal(row[lo: lo + nwk], want[lo: lo + nwk]), (m, k)
+                assert np.all(row[lo + nwk: min(lo + area, L.code_stride)] == 0x5A5A5A5A)
+
+
+@pytest.mark.parametrize("p", [0.02, 0.2, 0.5])
+def test_long_selected_buckets_with_crowded_brackets_match_oracle(p):
+    """A third of the magnitudes lie next to the threshold: some tiles list all their open components, others
+    have more of them than slots and are looked up from the stream, in both coders."""
+    rng = np.random.default_rng(int(p * 100))
+    d, M = (1 << 24) + 4099, 32
+    near = rng.random(d, dtype=np.float32) < 1 / 3
+    near &= np.arange(d) // 4096 % 5 != 0                # every fifth tile has none of them
+    g = np.where(near, 0.75 * (1 + 1e-4 * rng.standard_normal(d)), 1.125).astype(np.float32)
+    g *= np.where(rng.random(d) < 0.5, np.float32(1e-2), np.float32(-1e-2))
+    marks = np.zeros((d + 31) // 32 * 32, bool)
+    marks[:d] = rng.random(d, dtype=np.float32) < p
+    ind = np.packbits(marks, bitorder="little").view(np.uint32)
+    L = qa.Layout.make(d, M, 0)
+    NW, gs = (d + 31) // 32, (d + 3) // 4 * 4
+    gd = torch.zeros((M, gs), dtype=torch.float32, device=DEV)
+    gd[:, :d] = dev(g)
+    ind_d = dev(ind.view(np.int32)).expand(M, NW).contiguous()
+    sel = torch.full((M, L.code_stride), 0x5A5A5A5A, dtype=torch.int32, device=DEV)
+    cnt = torch.zeros((M, 1), dtype=torch.int32, device=DEV)
+    sc, th = torch.zeros((2, M, 1), dtype=torch.float32, device=DEV)
+    qa.qa_quantize_pack_selected(L, gd, gs, ind_d, NW, sel, cnt, sc, th, workspace(qa.qa_workspace_bytes(L, qa.QA_OP_SELECT)))
+    torch.cuda.synchronize()
+    o_sel, o_cnt, o_sc, o_th = oracle.quantize_selected(g, ind, bucket=0)
+    # sums of at most 2^23 magnitudes in binary64 (relative error 2^-29), rounded to binary32 once
+    assert np.all(np.abs(host(th) - o_th) <= np.spacing(o_th)) and np.all(np.abs(host(sc) - o_sc) <= np.spacing(o_sc))
+    words = (int(o_cnt[0]) + 15) // 16
+    between = np.abs(np.abs(g[marks[:d]]) - o_th[0]) <= np.spacing(o_th[0])      # may differ with the threshold's last bit
+    for m in range(M):
+        got = host(sel[m]).view(np.uint32)
+        wrong = got[:words] ^ o_sel[:words]
+        if not between.any() or np.array_equal(host(th)[m], o_th):
+            assert not wrong.any()
+        else:
+            assert np.count_nonzero(wrong) <= np.count_nonzero(between)
+        assert np.all(got[words:] == 0x5A5A5A5A)
