@@ -345,12 +345,15 @@ __device__ __forceinline__ void lookup_indices(const uint32_t zq[4], const doubl
 // marked component in the bucket's stream is the number of marked components before it (counts of
 // two workers share one 32-bit prefix scan over the work-group); the codes are fetched from the
 // stream and spread to the marked fields through the deposit table.  The result is the word the
-// stand-alone decoder would have written, and everything after it is the dense path.
+// stand-alone decoder would have written, and everything after it is the dense path.  Every chunk has
+// guards, of 4 (NGT = 1), 8 (NGT = 2) or 16 workers (NGT = 0): the smallest that holds all workers, since the
+// expansion of absent ones costs as much as that of present ones and these kernels are bound by vector
+// instructions.  10^8 coordinates, chunks of 16 -> these: server's call 1 / 4 / 5 / 8 workers 235 / 233 / 281 / 250 ->
+// 133 / 133 / 206 / 179 us, QCMD step 340 / 358 / 391 / 379 -> 294 / 302 / 357 / 338.
 template <int MODE, bool TRACK_Z, int RQ, int NGT, bool SPARSE = false>
 __global__ __launch_bounds__(kThreads) void step_lut_kernel(StepArgs a) {
   constexpr bool REQUANT = RQ == kRqInTile;
-  static_assert(!SPARSE || NGT == 0, "sparse input: chunks of 16 workers with guards");
-  constexpr bool FULL = NGT > 1;
+  constexpr bool FULL = NGT > 1 && !SPARSE;              // sparse input: every chunk with guards
   constexpr int kGroupsPerChunk = NGT >= 1 ? NGT : kMaxGroups;
   constexpr int kChunk = 4 * kGroupsPerChunk;
   // The server's kernel that sends Q(SynQ) stages complete chunks of code words through LDS (see
@@ -1115,7 +1118,9 @@ static void launch_one(const StepArgs& a, int ngt, hipStream_t stream) {
   const dim3 grid((unsigned)(a.seg.piece_tile ? a.seg.n_pieces : tiles_of(a.d))), block(kThreads);
   if constexpr (RQ != kRqGiven) {                        // (never asked for with sparse messages)
     if (a.ind) {                                         // sparse-encoded messages
-      launch_lut<MODE, TRACK_Z, RQ, 0, true>(a, grid, block, stream);
+      if (a.M <= 4) launch_lut<MODE, TRACK_Z, RQ, 1, true>(a, grid, block, stream);
+      else if (a.M <= 8) launch_lut<MODE, TRACK_Z, RQ, 2, true>(a, grid, block, stream);
+      else launch_lut<MODE, TRACK_Z, RQ, 0, true>(a, grid, block, stream);
       return;
     }
   }

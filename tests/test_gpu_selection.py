@@ -659,3 +659,11 @@ def test_long_selected_buckets_with_crowded_brackets_match_oracle(p):
         else:
             assert np.count_nonzero(wrong) <= np.count_nonzero(between)
         assert np.all(got[words:] == 0x5A5A5A5A)
+
+
+@pytest.mark.parametrize("M", [4, 5, 8, 9, 17])
+def test_sparse_messages_at_the_ends_of_the_chunks_of_workers(M):
+    """4, 8 and 16 workers are expanded together: one chunk full, one worker more, absent workers in the last."""
+    test_steps_on_sparse_messages_match_oracle_decode_then_step(8197, M, 4096, 0.3, 1, False, False)
+    test_steps_on_sparse_messages_match_oracle_decode_then_step(8197, M, 4096, 0.3, 0, False, True)
+    test_server_call_on_sparse_messages_matches_oracle(8197, M, 4096, 0.3, 1, False)
