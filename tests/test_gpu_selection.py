@@ -591,7 +591,8 @@ def marks_per_tile(counts, d, rng):
     return np.packbits(marks, bitorder="little").view(np.uint32)
 
 
-@pytest.mark.parametrize("d,bucket", [(4096 * 23 + 17, 0), (4096 * 23 + 4095, 8192), (4096 * 12, 16384)])
+@pytest.mark.parametrize("d,bucket", [(4096 * 23 + 17, 0), (4096 * 23 + 4095, 8192), (4096 * 12, 16384),
+                                      (4096 * 23 + 17, 4096), (4096 * 21 + 4095, 4096), (4096 * 22, 4096)])
 def test_streams_over_tiles_of_every_marked_count_match_oracle(d, bucket):
     """Marked counts around a word (16), a round (64), the coders' line (1520) and the full tile, behind first
     codes at every place in a word; runs of empty tiles and of tiles that share one word."""
