@@ -68,13 +68,12 @@ __device__ __forceinline__ GradArgs for_worker(GradArgs a) {
 }
 
 // Four consecutive floats at any address that is a multiple of 4: the memory system takes a 16-byte
-// load on a 4-byte boundary (rows of an odd length start on those).  Streaming (non-temporal): the
-// matrix rows of a batch are read once per pass.
+// load on a 4-byte boundary (rows of an odd length start on those).  Without the streaming hint: the column
+// sums read the margins' rows again and a later batch draws some of them again, so what the last-level
+// cache holds is worth keeping (8 x 128 rows of 100003 columns, other rows in each call 164.3 -> 162.6 us, the same
+// rows 157.3 -> 136.7; 8 x 256 rows of 30001, other rows, 104.1 -> 100.4).
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef floatx4 floatx4_any __attribute__((aligned(4)));
-__device__ __forceinline__ floatx4 stream_load4(const float* p) {
-  return __builtin_nontemporal_load(reinterpret_cast<const floatx4_any*>(p));
-}
 __device__ __forceinline__ floatx4 load4(const float* p) { return *reinterpret_cast<const floatx4_any*>(p); }
 
 // coef and loss of one sample from its binary32 margin term p = a.x
@@ -115,7 +114,7 @@ __global__ __launch_bounds__(kThreads) void dense_margin_kernel(GradArgs a_all) 
     for (; j + 4 * 3 * LANES < whole; j += 4 * 4 * LANES) {
       floatx4 v[4], w[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = stream_load4(row + j + u * 4 * LANES);
+      for (int u = 0; u < 4; ++u) v[u] = load4(row + j + u * 4 * LANES);
 #pragma unroll
       for (int u = 0; u < 4; ++u) w[u] = load4(a.x + j + u * 4 * LANES);
 #pragma unroll
@@ -127,7 +126,7 @@ __global__ __launch_bounds__(kThreads) void dense_margin_kernel(GradArgs a_all) 
       }
     }
     for (; j < whole; j += 4 * LANES) {
-      const floatx4 v = stream_load4(row + j), w = load4(a.x + j);
+      const floatx4 v = load4(row + j), w = load4(a.x + j);
       s0 = fma((double)v.x, (double)w.x, s0);
       s1 = fma((double)v.y, (double)w.y, s1);
       s2 = fma((double)v.z, (double)w.z, s2);
@@ -152,10 +151,10 @@ __global__ __launch_bounds__(kThreads) void dense_margin_kernel(GradArgs a_all) 
 // SPLIT parts of the work-group share out the rows, sixteen at a time, for 256 / SPLIT threads' columns:
 // narrow matrices would leave the chip idle with a thread walking the whole batch, where the time
 // is the number of dependent rounds of loads (8 x 256 rows of 4000 columns: 35.9 us without a split),
-// and wide ones lose nothing (8 x 128 rows of 100003 columns, both kernels: 147 us against 155; 318
-// with a column per thread, as rows that do not start on 16 bytes were read before.  Both kernels
-// are bound by the two reads of the batch, 5.6-6.4 TB/s; a second read that could come from the
-// last-level cache -- workers taken in groups of 60-220 MB -- was no faster).
+// and wide ones lose nothing (8 x 128 rows of 100003 columns, both kernels with streaming loads: 147 us against
+// 155; 318 with a column per thread, as rows that do not start on 16 bytes were read before.  Both kernels
+// are bound by the two reads of the batch, 5.6-6.4 TB/s; workers taken in groups of 60-220 MB and
+// columns in reverse, so that more of the second read comes from the last-level cache, were no faster).
 // The last work-group of a worker adds up the losses instead, if they are asked for.
 template <int SPLIT>
 __global__ __launch_bounds__(kThreads) void dense_colsum_kernel(GradArgs a_all) {
@@ -200,7 +199,7 @@ __global__ __launch_bounds__(kThreads) void dense_colsum_kernel(GradArgs a_all) 
       floatx4 v[kRows];
       if (whole) {
 #pragma unroll
-        for (int u = 0; u < kRows; ++u) v[u] = stream_load4(a.A + (int64_t)(r[u] >= 0 ? r[u] : 0) * a.d + j);
+        for (int u = 0; u < kRows; ++u) v[u] = load4(a.A + (int64_t)(r[u] >= 0 ? r[u] : 0) * a.d + j);
       } else {                                            // the last columns of a row of odd length
 #pragma unroll
         for (int u = 0; u < kRows; ++u) {
