@@ -777,7 +777,8 @@ __global__ __launch_bounds__(THREADS) void gsel_scan_kernel(SelArgs a) {
 }
 
 // A word of the stream that several tiles share is stored by the tile it begins in; the others leave their
-// part of it, their head, in the slot of their count, and this kernel adds the heads.  A thread per tile:
+// part of it, their head, in the slot of their count, and this kernel adds the heads (where their bits are 0, or hold
+// what the settling pass exchanges).  A thread per tile:
 // 9 to 11 us for 8 workers x 2^27.  Two atomic ORs per tile among the stores of the coders themselves, into words zeroed
 // before, cost 0.4 ms there (the quantizer 1.11 -> 0.70 ms without them, S of a coded message 0.25 -> 0.19 as a whole).
 __global__ __launch_bounds__(kThreads) void gsel_join_kernel(SelArgs a) {
@@ -786,7 +787,7 @@ __global__ __launch_bounds__(kThreads) void gsel_join_kernel(SelArgs a) {
   const int m = blockIdx.y;
   const int64_t k = tile / a.tiles_per_bucket, at = (int64_t)m * a.ntiles + tile;
   const uint32_t head = a.ws_count[at];
-  if (head) atomicOr(&a.sel_codes[(int64_t)m * a.code_stride + k * a.area_words + (a.ws_start[at] >> 4)], head);
+  if (head) atomicXor(&a.sel_codes[(int64_t)m * a.code_stride + k * a.area_words + (a.ws_start[at] >> 4)], head);
 }
 // Q(S(g, I)) for buckets of 64 .. 2048 coordinates: thread t = code word t of the tile, a bucket =
 // a.seg consecutive threads.
@@ -1073,13 +1074,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
       }
     }
     s1 = wave_sum_f64(s1);
-    if (lane == 0) {                                     // the settling pass adds to zeroed shared words
-      a.ws_s1[at] = s1;
-      a.ws_count[at] = 0u;
-      uint32_t* area = a.sel_codes + (int64_t)m * a.code_stride + k * a.area_words;
-      if (marked && first) area[st >> 4] = 0u;
-      if (marked && ((st + marked) & 15)) area[(st + marked) >> 4] = 0u;
-    }
+    if (lane == 0) a.ws_s1[at] = s1;
     return;
   }
   uint32_t* out = a.sel_codes + (int64_t)m * a.code_stride + k * a.area_words + (st >> 4);
@@ -1190,9 +1185,9 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void gsel_threshold_kernel(S
 
 // A tile whose open components are not listed, by a wave.  With a bracket that held: each lane reads its
 // words' codes back from the stream, finds the pattern 10, and exchanges it for the component's code in
-// place.  Without a bracket the tile is coded here, and with one that missed again; of a word that it shares
-// with a neighbour then only its own bits change.
-__device__ __forceinline__ void settle_tile(const SelArgs& a, int64_t tile, int m, uint32_t* stream) {
+// place; its head is not joined yet.  Without a bracket the tile is coded here, and with one that missed again; of a
+// word that it shares with a neighbour then only its own bits change, the head's among them.
+__device__ __forceinline__ void settle_tile(const SelArgs& a, int64_t tile, int m, SelWaveLds& lds) {
   const int lane = threadIdx.x % kWave;
   const int64_t slot = (int64_t)m * a.ntiles + tile, k = tile / a.tiles_per_bucket;
   const float D = a.ws_thr[(int64_t)m * a.nb + k], held = a.scales[(int64_t)m * a.scale_stride + k];
@@ -1200,23 +1195,30 @@ __device__ __forceinline__ void settle_tile(const SelArgs& a, int64_t tile, int 
   const uint32_t first = (uint32_t)(st & 15);
   uint32_t* out = a.sel_codes + (int64_t)m * a.code_stride + k * a.area_words + (st >> 4);
   if (held != 1.0f) {
-    const TileCodes r = code_selected_tile<false>(a, tile, m, first, D, 0.0f, stream, nullptr);
+    uint32_t head = 0;
+    TileCodes r;
+    uint32_t* stream = lds.stream;
+    // without a bracket the count of the tile's marks is still in the head's slot
+    const bool few = held < 0.0f && (uint32_t)__builtin_amdgcn_readfirstlane((int)a.ws_count[slot]) <= kFewMarked;
+    if (few) r = code_few_marked<false>(a, tile, m, first, D, 0.0f, lds, out, nullptr, &head);
+    else r = code_selected_tile<false>(a, tile, m, first, D, 0.0f, stream, nullptr);
     const uint32_t nwords = (r.end + 15) / 16;
-    if (r.end != first)
+    if (!few && r.end != first)
       for (uint32_t w = lane; w < nwords; w += kWave) {
         uint32_t own = 0xffffffffu;
         if (w == 0 && first != 0) own &= 0xffffffffu << (2 * first);
         if (w == nwords - 1 && (r.end % 16) != 0) own &= ~(0xffffffffu << (2 * (r.end % 16)));
-        if (own == 0xffffffffu) out[w] = stream[w];
-        else if (held < 0.0f) atomicOr(&out[w], stream[w]);
+        if (held < 0.0f) store_word(out, w, first, stream[w], &head);
+        else if (own == 0xffffffffu) out[w] = stream[w];
         else atomicXor(&out[w], (atomicOr(&out[w], 0u) ^ stream[w]) & own);
       }
-    if (lane == 0) { a.ws_s2[slot] = r.s2; a.ws_c2[slot] = r.c2; }
+    if (lane == 0) { a.ws_s2[slot] = r.s2; a.ws_c2[slot] = r.c2; a.ws_count[slot] = head; }
     return;
   }
   const uint32_t* ind = a.ind_in + (int64_t)m * a.ind_stride;
   const float* g = a.g + (int64_t)m * a.g_stride;
   uint32_t mask[4], at[4], open[4], any = 0, start = first;
+  const uint32_t head = a.ws_count[slot];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int wl = j * 64 + lane;
@@ -1233,7 +1235,7 @@ __device__ __forceinline__ void settle_tile(const SelArgs& a, int64_t tile, int 
     start += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
     uint32_t lo = 0u, hi = 0u;
     const uint32_t w0 = at[j] / 16, sh = 2 * (at[j] % 16);
-    if (n) lo = out[w0];
+    if (n) lo = w0 == 0 ? out[0] | head : out[w0];
     if (sh && 2 * n + sh > 32) hi = out[w0 + 1];
     uint32_t bits = (lo >> sh) | (sh ? hi << (32 - sh) : 0u);
     if (n < 16) bits &= (1u << (2 * n)) - 1u;
@@ -1278,7 +1280,7 @@ __device__ __forceinline__ void settle_tile(const SelArgs& a, int64_t tile, int 
 // requested at once.  Tiles without a list follow one by one.  8 workers x 2^27: 30 us; reading
 // every tile's marks and codes back took 180, a chain of dependent loads per tile.
 __global__ __launch_bounds__(kThreads) void gsel_settle_kernel(SelArgs a) {
-  __shared__ uint32_t stream_all[kWaves][kTileWords + 2];
+  __shared__ SelWaveLds lds_all[kWaves];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, e = lane % (int)kOpenSlots;
   constexpr int kTilesPerWave = kWave / (int)kOpenSlots;
   const int64_t tile0 = ((int64_t)blockIdx.x * kWaves + wave) * kTilesPerWave, tile = tile0 + lane / (int)kOpenSlots;
@@ -1317,7 +1319,7 @@ __global__ __launch_bounds__(kThreads) void gsel_settle_kernel(SelArgs a) {
   if (listed && e == 0) { a.ws_s2[slot] = s_before + s; a.ws_c2[slot] = c_before + c; }
   for (uint64_t left = __ballot(unlisted && e == 0); left; left &= left - 1) {
     wave_fence();                                        // the stream of the tile before has been read
-    settle_tile(a, tile0 + (__ffsll((unsigned long long)left) - 1) / (int)kOpenSlots, m, stream_all[wave]);
+    settle_tile(a, tile0 + (__ffsll((unsigned long long)left) - 1) / (int)kOpenSlots, m, lds_all[wave]);
   }
 }
 
@@ -1336,13 +1338,14 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void gsel_scale_kernel(SelAr
   if (threadIdx.x == 0) a.scales[(int64_t)m * a.scale_stride + k] = scale_from_sum(s, (uint64_t)c);
 }
 
-// Buckets of at least 4096 tiles (64 samples) are quantized in one read if all workers have 2^29 coordinates
-// or more.  With a bracket it is the faster form from 2^26 on; without one (marks on components of very
-// unequal sizes, one mark or none per tile) its small launches come on top of two reads, and the line lies
-// where they are repaid by the rest.  Two reads / one read with a bracket / one read without, us:
-// 8 workers x 2^27 1744 / 1310 / 1549 to 1820 (the form before, with the longer scan: 1785, 1570 to 1732),
-// 8 x 2^25 450 / 363 / 417 to 482 (462, 408 to 444), 2 x 2^25 108 / 101, 2 x 2^24 59 / 63.
-constexpr int64_t kSelOneReadBucketTiles = 4096, kSelOneReadTiles = 131072;
+// Buckets of at least 4096 tiles (64 samples) are quantized in one read if all workers have 2^28 coordinates
+// or more.  With a bracket it is the faster form from 2^27 on; without one (marks on components of very
+// unequal sizes, one mark or none per tile) its small launches and the second coding come on top of two reads, and
+// the line lies where that costs no more than a tenth.  Two reads / one read with a bracket / one read without, us, for
+// 7 % and for 97 % of the components marked: 8 workers x 2^27 1430 / 823 / 1518 and 1612 / 1060 / 1763,
+// 8 x 2^25 357 / 226 / 395 and 407 / 357 / 471, 4 x 2^25 183 / 127 / 210 and 215 / 208 / 255, 2 x 2^25 98 / 80 / - and 100 /
+// 119 / -.  Shorter buckets have wider brackets: 8 x 2^24 in buckets of 2^22 181 / 148 and 212 / 236.
+constexpr int64_t kSelOneReadBucketTiles = 4096, kSelOneReadTiles = 65536;
 
 // Which kernels serve a layout's sparse messages.
 static SelKind sel_kind(const qa_layout* L) {
@@ -1517,9 +1520,9 @@ extern "C" int qa_quantize_pack_selected(const qa_layout* layout, const float* g
     hipLaunchKernelGGL(gsel_sample_kernel, dim3((unsigned)(a.nb * a.samples), (unsigned)layout->M), block, 0, stream, a);
     hipLaunchKernelGGL(gsel_band_kernel, buckets, block, 0, stream, a);
     hipLaunchKernelGGL(gsel_quantize_multi_kernel<true>, waves, block, 0, stream, a);
-    join_launch(a, layout->M, stream);
     hipLaunchKernelGGL(gsel_threshold_kernel, buckets, block, 0, stream, a);
     hipLaunchKernelGGL(gsel_settle_kernel, settle_grid, block, 0, stream, a);
+    join_launch(a, layout->M, stream);
   } else {
     hipLaunchKernelGGL(gsel_count_kernel, tiles, block, 0, stream, a);
     scan_launch<true>(a, layout->M, stream);
