@@ -115,9 +115,13 @@ __device__ __forceinline__ void indicator_slab_exact(const SelArgs& a, int m, in
 // coordinates j*64 + l (j = 0..15): each ballot is 64 consecutive indicator bits.
 // Slab that lies wholly below d: no clamps or masks; the next worker's gradient is requested
 // before the current one is examined; ballot j (64 indicator bits) is kept by lane j, and lanes
-// 0..15 store the slab's 128 bytes.  The gradients are streamed (8 workers x 2^27: QCMD 992 -> 948 us, QRDA 10^8
-// 826 -> 814); x, G and z as well: no faster.
-template <int METHOD>
+// 0..15 store the slab's 128 bytes.  STREAM: gradients that the last-level cache cannot hold are streamed
+// (8 workers x 2^27: QCMD 992 -> 948 us, 8 x 10^8: QRDA 826 -> 814); x, G and z as well: no faster.  Those it
+// holds are kept for the quantizer that follows (4 x 4 M, one scale, indicator to update: 86.8 us, streamed 89.5).
+constexpr int64_t kStreamedGradients = int64_t(1) << 26;   // components of all workers: 256 MB
+template <bool STREAM>
+__device__ __forceinline__ float gradient_load(const float* p) { return STREAM ? __builtin_nontemporal_load(p) : *p; }
+template <int METHOD, bool STREAM>
 __device__ __forceinline__ void indicator_wave_full(const SelArgs& a, int64_t base, int lane) {
   const float* px = a.x + base + lane;
   const float* pG = a.G + base + lane;
@@ -133,7 +137,7 @@ __device__ __forceinline__ void indicator_wave_full(const SelArgs& a, int64_t ba
   uint32_t* out = a.ind + base / 32 + 2 * lane;
   float gn[16];
 #pragma unroll
-  for (int j = 0; j < 16; ++j) gn[j] = __builtin_nontemporal_load(pg + j * 64);
+  for (int j = 0; j < 16; ++j) gn[j] = gradient_load<STREAM>(pg + j * 64);
   for (int m = 0; m < a.M; ++m) {
     float gv[16];
 #pragma unroll
@@ -141,7 +145,7 @@ __device__ __forceinline__ void indicator_wave_full(const SelArgs& a, int64_t ba
     if (m + 1 < a.M) {                                   // the next worker's gradient, ahead of use
       const float* pn = pg + (int64_t)(m + 1) * a.g_stride;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) gn[j] = __builtin_nontemporal_load(pn + j * 64);
+      for (int j = 0; j < 16; ++j) gn[j] = gradient_load<STREAM>(pn + j * 64);
     }
     bool undecided = false;
     uint32_t lo = 0, hi = 0;
@@ -164,12 +168,12 @@ __device__ __forceinline__ void indicator_wave_full(const SelArgs& a, int64_t ba
 
 // Three waves per SIMD: measured best for this access pattern (2: 2.15 ms, 3: 1.91, 4: 1.98,
 // 6-8: 2.00 at d = 2^28, M = 8); the kernel needs only 58-77 registers and would otherwise run 6-8.
-template <int METHOD>
+template <int METHOD, bool STREAM>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 3)))
 void indicator_kernel(SelArgs a) {
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int64_t base = (int64_t)blockIdx.x * kTile + wave * 1024;
-  if (base + 1024 <= a.d) indicator_wave_full<METHOD>(a, base, lane);
+  if (base + 1024 <= a.d) indicator_wave_full<METHOD, STREAM>(a, base, lane);
   else if (base < a.d)                                   // the vector ends inside this slab: closed form
     for (int m = 0; m < a.M; ++m) indicator_slab_exact(a, m, base, lane);
 }
@@ -338,7 +342,7 @@ __device__ __forceinline__ void wave_fence() {           // order of a wave's ow
 // indicator half-word, and every fourth round each lane appends one half-word's codes to the wave's stream.
 // Bound by the read of the gradient where few are marked, by vector instructions where most are (1300 per tile;
 // with four waves per tile, 16 consecutive components per lane and a branch per component 2000).  8 workers x 10^8, 7 / 30 / 97 %
-// marked: 640 -> 570, 665 -> 592, 675 -> 640 us.
+// marked: 640 -> 570, 665 -> 592, 675 -> 640 us; of a few tiles, where one wave's chain is the time, 0.8 us slower.
 struct SelTileLds {
   uint2 words[kTile / 32];                               // indicator word, marked components before it
   uint32_t stream[kTileWords + 2];
@@ -1449,8 +1453,10 @@ extern "C" int qa_indicator(const qa_layout* layout, int method, const float* g,
   a.ind = ind_out; a.ind_stride = ind_stride;
   a.eta = eta; a.lam_eta = lambda * eta; a.delta = delta; a.t_lam = (float)t * lambda;
   const dim3 grid((unsigned)tiles_of(layout->d)), block(kThreads);
-  if (method == 0) hipLaunchKernelGGL(indicator_kernel<0>, grid, block, 0, static_cast<hipStream_t>(stream), a);
-  else hipLaunchKernelGGL(indicator_kernel<1>, grid, block, 0, static_cast<hipStream_t>(stream), a);
+  const bool streamed = layout->d * layout->M > kStreamedGradients;
+  const auto kernel = method == 0 ? (streamed ? indicator_kernel<0, true> : indicator_kernel<0, false>)
+                                  : (streamed ? indicator_kernel<1, true> : indicator_kernel<1, false>);
+  hipLaunchKernelGGL(kernel, grid, block, 0, static_cast<hipStream_t>(stream), a);
   return launch_status();
 }
 
