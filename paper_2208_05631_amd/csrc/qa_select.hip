@@ -340,7 +340,7 @@ __device__ __forceinline__ void wave_fence() {           // order of a wave's ow
 // j*64 + lane, j = 0..15) and holds it in registers for both sums.  Unmarked components become 0 and add nothing; the fields of a
 // float4 go through the extract table, the four lanes of a quad join theirs to the codes of one
 // indicator half-word, and every fourth round each lane appends one half-word's codes to the wave's stream.
-// Bound by the read of the gradient where few are marked, by vector instructions where most are (1300 per tile;
+// Bound by the read of the gradient where few are marked, by that and vector instructions where most are (1380 per tile, three quarters of the issue slots;
 // with four waves per tile, 16 consecutive components per lane and a branch per component 2000).  8 workers x 10^8, 7 / 30 / 97 %
 // marked: 640 -> 570, 665 -> 592, 675 -> 640 us; of a few tiles, where one wave's chain is the time, 0.8 us slower.
 struct SelTileLds {
