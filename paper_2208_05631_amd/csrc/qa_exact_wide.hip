@@ -37,6 +37,7 @@
 //   up to 65536 components, a work-group per bucket: 2^26 x 4 in buckets of 65536 1091 -> 972, of 8192 4583 -> 4120
 //     (bound by the scans, some 8 us per level and work-group)
 #include "qa_common.h"
+#include "qa_exact_window.h"
 
 namespace qa {
 
@@ -431,11 +432,7 @@ constexpr int kMostChunkTiles = 128, kBracketedTiles = 32;   // at most 2^19 com
 constexpr int64_t kSampledTiles = 512, kSampledInAll = 2048;
 constexpr int kUnit = 4 * kWave, kMostOften = 4, kUnitsPerWave = 4, kUnitsPerGroup = kUnitsPerWave * kScanWaves;
 constexpr int kMostUnits = kRanges / 2 * kUnitsPerWave;   // two sums of each wave in LevelRanges::sum_before
-// 32 bins per binade, 8192 to 512 around the bracket.  (Half of what a level has: the scan is bound by its
-// instructions, and with 64 per binade and 4096 bins in all it took 13 us.)
-constexpr int kFarShift = 18, kNearShift = 10, kWidestNear = 14;
 constexpr int kProofBins = 2048, kProofPerThread = kProofBins / kScanThreads;
-constexpr int kNearBins = 2 << (kFarShift - kNearShift), kMostNear = kNearBins >> (kFarShift - kWidestNear);
 constexpr int kFarAbove = 512, kFarBelow = kProofBins - kNearBins - kMostNear - kFarAbove;
 constexpr int kStage = 4096;                             // components of a chunk inside the bracket, at most
 constexpr double kMostOpen = 0.015;                      // share of the components inside the bracket
@@ -695,15 +692,10 @@ __global__ __launch_bounds__(kPassThreads) void exact_wide_probe_kernel(WideArgs
       const double open = N / 0.04 * (2.0 * half / t0) / ((double)n * (double)kUnit);
       if (half < 0.12 * t0 && fabs(step) < 0.05 * t0 && open < kMostOpen) {
         const uint32_t below = __float_as_uint((float)(t0 + step - half)), above = __float_as_uint((float)(t0 + step + half));
-        const uint32_t mid = __float_as_uint((float)(t0 + step));
-        for (int shift = kNearShift; shift <= kWidestNear; ++shift) {
-          const uint32_t near = (uint32_t)kNearBins >> (kFarShift - shift);
-          const uint32_t near0 = (mid - ((near - 1u) << (kFarShift - 1))) >> kFarShift;   // the bracket in the middle
-          if (below - (near0 << kFarShift) > (4u << shift) && above - (near0 << kFarShift) < (near << kFarShift) - (4u << shift)) {
-            st->below = below; st->above = above; st->near0 = near0; st->near_shift = (uint32_t)shift;
-            st->mode = kBracketed;
-            break;
-          }
+        const NearWindow w = near_window(below, __float_as_uint((float)(t0 + step)), above);
+        if (w.shift) {
+          st->below = below; st->above = above; st->near0 = w.near0; st->near_shift = w.shift;
+          st->mode = kBracketed;
         }
       }
     }
