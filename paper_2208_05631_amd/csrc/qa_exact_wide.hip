@@ -436,7 +436,6 @@ constexpr int kProofBins = 2048, kProofPerThread = kProofBins / kScanThreads;
 constexpr int kFarAbove = 512, kFarBelow = kProofBins - kNearBins - kMostNear - kFarAbove;
 constexpr int kStage = 4096;                             // components of a chunk inside the bracket, at most
 constexpr double kMostOpen = 0.015;                      // share of the components inside the bracket
-constexpr int64_t kManyChunks = 512;                     // two work-groups per compute unit
 constexpr int kListGroups = 64;                          // work-groups of a bucket that walk its list
 
 enum WideMode { kWholeGradient = 0, kBracketed = 1, kListed = 2 };
@@ -1009,8 +1008,12 @@ __global__ __launch_bounds__(kScanThreads) void exact_wide_prove_kernel(WideArgs
 
 // One level of a bucket: its chunk's magnitudes, or its part of the list, into the histogram, LDS first, filled
 // bins added to global memory; the last work-group scans.
-// Bound by the read of the gradient (4 bytes per component).
-__global__ __launch_bounds__(kPassThreads) __attribute__((amdgpu_waves_per_eu(8))) void exact_wide_level_kernel(WideArgs a, WideList list, int64_t chunks,
+// Bound by the read of the gradient (4 bytes per component) and, in short buckets, by the scan.  CROWDED: two
+// work-groups per compute unit, at the price of a scan with spills, where there are more work-groups than units
+// (2^26 x 4, buckets of 2^18 951 -> 857 us, ternary components 2145 -> 2098); with a unit for each the spills only
+// cost (100003 67.5 -> 64.2, 10^6 x 8 91 -> 87).
+template <bool CROWDED>
+__global__ __launch_bounds__(kPassThreads) __attribute__((amdgpu_waves_per_eu(CROWDED ? 8 : 4))) void exact_wide_level_kernel(WideArgs a, WideList list, int64_t chunks,
                                                                          int chunk_tiles, int last_level) {
   __shared__ union {
     struct { unsigned long long hist[kBins]; uint32_t lo_of[kRanges]; } pass;
@@ -1377,15 +1380,21 @@ int exact_thresholds_wide(const qa_layout* L, const float* g, int64_t g_stride, 
   if (sa.every < kMostOften) sa.every = kMostOften;
   sa.units = (int)(units / sa.every);
   sa.groups = (sa.units + kUnitsPerGroup - 1) / kUnitsPerGroup;
-  // chunks: enough for two work-groups per compute unit
-  int chunk_tiles = kPassComponents / kTile;
-  while (chunk_tiles < kMostChunkTiles && a.nb * ((tiles + chunk_tiles - 1) / chunk_tiles) * group > kManyChunks) chunk_tiles *= 2;
+  // Chunks: a work-group per compute unit, whole passes of its threads.  Two of them cost more in bins added to memory
+  // than they gain: 10^6 x 8 114 -> 87 us, 2^21 x 8 113 -> 99, 2^24 x 4 Cauchy components 267 -> 232; chunks that only double
+  // leave half the chip idle just beyond a power of two: 2^25 + 5 Cauchy components 177 -> 152.
+  constexpr int64_t kPassTiles = kPassComponents / kTile;
+  const int64_t each = a.nb * group < kComputeUnits ? kComputeUnits / (a.nb * group) : 1;
+  const int64_t per = ((tiles + each - 1) / each + kPassTiles - 1) / kPassTiles * kPassTiles;
+  const int chunk_tiles = (int)(per < kMostChunkTiles ? per : kMostChunkTiles);
   const int64_t chunks = (tiles + chunk_tiles - 1) / chunk_tiles, short_chunks = (tiles + kBracketedTiles - 1) / kBracketedTiles;
   if (a.nb * chunks > 0x7fffffffLL || a.nb * short_chunks > 0x7fffffffLL) return QA_ERR_WORKSPACE;
   for (int64_t m0 = 0; m0 < L->M; m0 += group) {
     const unsigned here = (unsigned)(L->M - m0 < group ? L->M - m0 : group);
     a.m0 = (int)m0;
     const dim3 pairs((unsigned)a.nb, here), parts((unsigned)(a.nb * chunks), here), block(kPassThreads);
+    const auto level_kernel = a.nb * chunks * here > kComputeUnits ? exact_wide_level_kernel<true>
+                                                                      : exact_wide_level_kernel<false>;
     hipLaunchKernelGGL(exact_wide_init_kernel, pairs, block, 0, stream, a);
     if (sampled) {
       const dim3 samples((unsigned)(a.nb * sa.groups), here);
@@ -1396,7 +1405,7 @@ int exact_thresholds_wide(const qa_layout* L, const float* g, int64_t g_stride, 
       hipLaunchKernelGGL(exact_wide_prove_kernel, pairs, block, 0, stream, a);
     }
     for (int level = 0; level < kLevels; ++level)
-      hipLaunchKernelGGL(exact_wide_level_kernel, parts, block, 0, stream, a, list, chunks, chunk_tiles,
+      hipLaunchKernelGGL(level_kernel, parts, block, 0, stream, a, list, chunks, chunk_tiles,
                          level == kLevels - 1 ? 1 : 0);
     hipLaunchKernelGGL(exact_sort_open_kernel, dim3((unsigned)a.nb), block, 0, stream, a, (int)here);
     hipLaunchKernelGGL(exact_wide_codes_kernel, parts, block, 0, stream, a, list, chunks, chunk_tiles);

@@ -1034,6 +1034,20 @@ def test_exact_threshold_over_several_tiles_matches_oracle(d, M, bucket, kind):
     assert int(ulp_distance(s[:, :nb], s_ref).max()) <= 1   # binary64 sums over many tiles, rounded once
 
 
+# chunks of 12 tiles with 10 and with 8 in the last, one chunk per bucket, and more work-groups than compute units
+@pytest.mark.parametrize("d,M,bucket", [(4096 * 93 + 17, 32, 0), (5 * (1 << 17) - 100, 16, 1 << 17),
+                                        (65540, 256, 0), (65540, 257, 0)])
+def test_exact_threshold_at_the_ends_of_its_chunks_matches_oracle(d, M, bucket):
+    g = make_grad("gauss", M, d, seed=d % 977 + M)
+    th_ref = np.stack([oracle.exact_thresholds(g[m], bucket) for m in range(M)])
+    c_ref, s_ref, _ = oracle.quantize_pack(g, bucket, thresholds=th_ref)
+    c, s, th, L = gpu_quantize_pack(g, bucket, exact=True)
+    nb = L.n_buckets
+    assert np.array_equal(th[:, :nb].view(np.uint32), th_ref.view(np.uint32))
+    assert np.array_equal(c[:, :L.words], c_ref)
+    assert int(ulp_distance(s[:, :nb], s_ref).max()) <= 1   # binary64 sums over many tiles, rounded once
+
+
 @pytest.mark.parametrize("bucket", [0, 8192])
 def test_exact_threshold_over_several_tiles_with_ties_zeros_and_a_ramp(bucket):
     rng = np.random.default_rng(11)

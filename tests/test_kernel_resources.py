@@ -1,6 +1,7 @@
 """Compile-time guard for the kernels whose speed hinges on occupancy: the step kernel is tuned
 for four waves per SIMD (at most 128 vector registers) and must not spill; one more register
-block costs a wave per SIMD and about 6 % of the step time on an MI355X.  hipcc cross-compiles
+block costs a wave per SIMD and about 6 % of the step time on an MI355X.  The exact threshold's and the
+selection's kernels may spill where their comments say so, and nowhere else.  hipcc cross-compiles
 for gfx950 without a GPU, so this runs with the CPU tests."""
 import os
 import re
@@ -46,3 +47,18 @@ def test_step_kernel_variants_keep_four_waves_per_simd(step_kernels):
     assert not low, low
     # four work-groups per CU must also fit the 160 KiB of LDS
     assert all(v["lds"] <= 40 * 1024 for v in step_kernels.values())
+
+
+# bytes per lane: the two forms for two work-groups per compute unit, where the work-group that scans spills, and
+# the sort of what the levels leave open
+EXACT_SPILLS = {"exact_resident_kernelILb1E": 112, "exact_wide_level_kernelILb1E": 64, "exact_sort_open_kernel": 32}
+
+
+def test_exact_threshold_kernels_spill_only_where_their_comments_say():
+    kernels = resource_usage("qa_exact_wide.hip")
+    for part in EXACT_SPILLS:
+        assert sum(part in k for k in kernels) == 1, part
+    for name, v in kernels.items():
+        assert v["scratch"] <= max([n for p, n in EXACT_SPILLS.items() if p in name], default=0), (name, v)
+        if "ILb1E" in name:
+            assert v["waves"] == 8, (name, v)
