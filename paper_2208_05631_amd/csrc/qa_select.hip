@@ -6,7 +6,7 @@
 //                               formed with wave ballots (64 consecutive coordinates per ballot).
 //   quantize_selected_kernel  : per 4096-tile, threshold/scale over the marked components only and
 //                               their 2-bit codes compacted in index order (prefix sum of the
-//                               marks, extract table, LDS bit stream).
+//                               marks, extract table, LDS bit stream); _few_ for few tiles.
 //   decode_selected_kernel    : S^{-1}: spreads the compact codes back to the dense 2-bit layout
 //                               that the fused steps read.
 //   select_codes_kernel       : S applied to a coded message (the server's push): the inverse.
@@ -342,7 +342,7 @@ __device__ __forceinline__ void wave_fence() {           // order of a wave's ow
 // indicator half-word, and every fourth round each lane appends one half-word's codes to the wave's stream.
 // Bound by the read of the gradient where few are marked, by that and vector instructions where most are (1380 per tile, three quarters of the issue slots;
 // with four waves per tile, 16 consecutive components per lane and a branch per component 2000).  8 workers x 10^8, 7 / 30 / 97 %
-// marked: 640 -> 570, 665 -> 592, 675 -> 640 us; of a few tiles, where one wave's chain is the time, 0.8 us slower.
+// marked: 640 -> 570, 665 -> 592, 675 -> 640 us.
 struct SelTileLds {
   uint2 words[kTile / 32];                               // indicator word, marked components before it
   uint32_t stream[kTileWords + 2];
@@ -458,6 +458,80 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     a.counts[at] = K;
     a.scales[at] = scale_from_sum(S2, c2);
     if (a.thresholds) a.thresholds[at] = Delta;
+  }
+}
+
+// The same with four waves per tile, 16 consecutive components per thread, for calls whose tiles the chip takes in one
+// round, where a wave's chain of instructions is the time (one tile 7.1 us as a wave, 4.0 so).  Alone / as a wave per tile, us,
+// 7 % marked, tiles of all workers: 1500 7.6 / 10.0, 2048 9.3 / 10.0, 4096 16.0 / 17.3, 5000 18.2 / 18.3, 6000 21.0 / 20.7,
+// 8000 26.7 / 25.6, 16000 49.6 / 46.0.  The magnitudes are added in another order: a threshold or scale may differ in its last bit.
+constexpr int64_t kSelFewTiles = 5120;
+__global__ __launch_bounds__(kThreads) void quantize_selected_few_kernel(SelArgs a) {
+  __shared__ uint32_t stream[kTileWords + 1];
+  __shared__ uint32_t lds_w[kWaves];
+  __shared__ double lds_s1[kWaves];
+  __shared__ double lds_s2[kWaves];
+  __shared__ uint32_t lds_c[kWaves];
+  const int t = threadIdx.x;
+  const int64_t tile = blockIdx.x;
+  const int m = blockIdx.y;
+  const float* g = a.g + (int64_t)m * a.g_stride;
+  const uint32_t mask = mask16_of(a.ind_in + (int64_t)m * a.ind_stride, a.NW, tile, t);
+  const int64_t i0 = tile * kTile + 16 * (int64_t)t;
+
+  float v[16];
+  if (i0 + 16 <= a.d) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 f = *reinterpret_cast<const float4*>(g + i0 + 4 * q);
+      v[4 * q] = f.x; v[4 * q + 1] = f.y; v[4 * q + 2] = f.z; v[4 * q + 3] = f.w;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = (i0 + j < a.d) ? g[i0 + j] : 0.0f;
+  }
+  stream[t] = 0u;
+  if (t == 0) stream[kTileWords] = 0u;
+
+  double s1 = 0.0;
+#pragma unroll
+  for (int j = 0; j < 16; ++j)
+    if ((mask >> j) & 1u) s1 += (double)fabsf(v[j]);
+  const uint32_t cnt = (uint32_t)__popc(mask);
+  uint32_t K;
+  const uint32_t before = block_exclusive_scan(cnt, lds_w, &K);
+  const double S1 = block_sum_f64(s1, lds_s1);
+  const float Delta = K ? threshold_from_sum(S1, a.thr_coef, (int64_t)K) : 0.0f;
+
+  double s2 = 0.0;
+  uint32_t c2 = 0, bits = 0, pos = 0;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    if ((mask >> j) & 1u) {
+      const float av = fabsf(v[j]);
+      if (av > Delta) { s2 += (double)av; ++c2; }
+      bits |= ternary_field(v[j], Delta) << (2 * pos);
+      ++pos;
+    }
+  }
+  // append this thread's 2*cnt bits at bit 2*before of the tile's compact stream
+  if (cnt) {
+    const uint32_t word = before / 16, sh = 2 * (before % 16);
+    atomicOr(&stream[word], bits << sh);
+    if (sh && (2 * cnt + sh > 32)) atomicOr(&stream[word + 1], bits >> (32 - sh));
+  }
+  s2 = wave_sum_f64(s2);
+  c2 = wave_sum_u32(c2);
+  if ((t % kWave) == 0) { lds_s2[t / kWave] = s2; lds_c[t / kWave] = c2; }
+  __syncthreads();
+  const uint32_t nwords = (K + 15) / 16;
+  if ((uint32_t)t < nwords) (a.sel_codes + (int64_t)m * a.code_stride)[tile * kTileWords + t] = stream[t];
+  if (t == 0) {
+    const double S2 = (lds_s2[0] + lds_s2[1]) + (lds_s2[2] + lds_s2[3]);
+    const uint32_t C = lds_c[0] + lds_c[1] + lds_c[2] + lds_c[3];
+    a.counts[(int64_t)m * a.scale_stride + tile] = K;
+    a.scales[(int64_t)m * a.scale_stride + tile] = scale_from_sum(S2, C);
+    if (a.thresholds) a.thresholds[(int64_t)m * a.scale_stride + tile] = Delta;
   }
 }
 
@@ -1507,7 +1581,10 @@ extern "C" int qa_quantize_pack_selected(const qa_layout* layout, const float* g
   const dim3 waves((unsigned)((tiles_of(layout->d) + kWaves - 1) / kWaves), (unsigned)layout->M);   // a tile per wave
   const SelKind kind = sel_kind(layout);
   if (kind == kSelTile) {
-    hipLaunchKernelGGL(quantize_selected_kernel, waves, block, 0, stream, a);
+    if (tiles_of(layout->d) * layout->M <= kSelFewTiles)
+      hipLaunchKernelGGL(quantize_selected_few_kernel, tiles, block, 0, stream, a);
+    else
+      hipLaunchKernelGGL(quantize_selected_kernel, waves, block, 0, stream, a);
     return launch_status();
   }
   rc = general_args(layout, a, ws, ws_bytes);

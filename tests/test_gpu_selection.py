@@ -624,6 +624,34 @@ def test_streams_over_tiles_of_every_marked_count_match_oracle(d, bucket):
                 assert np.all(row[lo + nwk: min(lo + area, L.code_stride)] == 0x5A5A5A5A)
 
 
+@pytest.mark.parametrize("d", [4096 * 639 + 4095, 4096 * 640 + 17])
+def test_buckets_of_4096_around_the_line_of_few_tiles_match_oracle(d):
+    """5120 tiles of all workers take four waves each, more of them one: every marked count in both."""
+    counts = [0, 1, 3, 15, 16, 17, 63, 64, 65, 1023, 1024, 1025, 4095, 4096]
+    rng = np.random.default_rng(d)
+    M, NW, gs = 8, (d + 31) // 32, (d + 3) // 4 * 4
+    g = (rng.standard_normal((M, gs), dtype=np.float32) * np.float32(1e-2))
+    ind = np.stack([marks_per_tile(counts[m:] + counts[:m], d, rng) for m in range(M)])
+    L = qa.Layout.make(d, M, 4096)
+    sel = torch.full((M, L.code_stride), 0x5A5A5A5A, dtype=torch.int32, device=DEV)
+    cnt = torch.zeros((M, L.scale_stride), dtype=torch.int32, device=DEV)
+    sc, th = torch.zeros((2, M, L.scale_stride), dtype=torch.float32, device=DEV)
+    qa.qa_quantize_pack_selected(L, dev(g), gs, dev(ind.view(np.int32)), NW, sel, cnt, sc, th, None)
+    torch.cuda.synchronize()
+    sel, cnt, sc, th = host(sel).view(np.uint32), host(cnt).view(np.uint32), host(sc), host(th)
+    for m in range(M):
+        o_sel, o_cnt, o_sc, o_th = oracle.quantize_selected(g[m, :d], ind[m], bucket=4096)
+        assert np.array_equal(cnt[m, :L.n_buckets], o_cnt)
+        # at most 4096 binary64 additions (relative error 2^-41), rounded to binary32 once
+        assert np.all(np.abs(sc[m, :L.n_buckets] - o_sc) <= np.spacing(o_sc))
+        assert np.all(np.abs(th[m, :L.n_buckets] - o_th) <= np.spacing(o_th))
+        for k in np.flatnonzero(th[m, :L.n_buckets] == o_th):
+            lo, nwk = k * 256, (int(o_cnt[k]) + 15) // 16
+            assert np.array_equal(sel[m, lo: lo + nwk], o_sel[lo: lo + nwk]), (m, k)
+            assert np.all(sel[m, lo + nwk: min(lo + 256, L.code_stride)] == 0x5A5A5A5A)
+        assert np.count_nonzero(th[m, :L.n_buckets] != o_th) <= 1
+
+
 @pytest.mark.parametrize("p", [0.02, 0.2, 0.5])
 def test_long_selected_buckets_with_crowded_brackets_match_oracle(p):
     """A third of the magnitudes lie next to the threshold: some tiles list all their open components, others
