@@ -167,7 +167,7 @@ def long_selection(kind, d, rng):
 @pytest.mark.parametrize("kinds,d,bucket", [(("plain", "misled", "few", "all"), (1 << 24) + 4099, 0),
                                             (("plain", "outliers", "none"), (1 << 24) + 20001, 1 << 24)])
 def test_long_selected_buckets_read_once_match_oracle(kinds, d, bucket):
-    """2^24 coordinates and more per bucket, 2^29 in all: marked components inside the bracket of the sample
+    """2^24 coordinates and more per bucket, 2^29 in all (one read from 2^28 on): marked components inside the bracket of the sample
     settled, and whole tiles coded once more where it missed or the sample gave none (a short last bucket)."""
     rng = np.random.default_rng(len(kinds))
     M, n = 32, len(kinds)                                # worker m's message is that of kind m % n
@@ -198,6 +198,38 @@ def test_long_selected_buckets_read_once_match_oracle(kinds, d, bucket):
             nwk, lo = (int(o_cnt[k]) + 15) // 16, k * area
             assert np.array_equal(sel_h[lo: lo + nwk], o_sel[lo: lo + nwk]), (kinds[m], k)
             assert np.all(sel_h[lo + nwk: min(lo + area, L.code_stride)] == 0x5A5A5A5A)
+
+
+@pytest.mark.parametrize("d,M", [(1 << 24, 16), (4096 * 4369, 15)])
+def test_long_selected_buckets_around_the_line_of_one_read_match_oracle(d, M):
+    """65536 tiles in all workers' vectors, the fewest that are read once, and 65535: with a bracket that holds and
+    without one."""
+    kinds = ("plain", "outliers")
+    rng = np.random.default_rng(M)
+    L = qa.Layout.make(d, M, 0)
+    per_tile = 16 * 8                                    # the lists of open components, with one read only
+    tiles, need = (d + 4095) // 4096 * M, qa.qa_workspace_bytes(L, qa.QA_OP_SELECT)
+    assert need - tiles * 32 < 2048 if tiles < 65536 else need - tiles * (32 + per_tile) < 2048
+    rows = [long_selection(k, d, rng) for k in kinds]
+    NW = d // 32
+    g, ind = torch.empty((M, d), dtype=torch.float32, device=DEV), torch.empty((M, NW), dtype=torch.int32, device=DEV)
+    for k, (gk, ik) in enumerate(rows):
+        g[k::2], ind[k::2] = dev(gk), dev(ik.view(np.int32))
+    sel = torch.full((M, L.code_stride), 0x5A5A5A5A, dtype=torch.int32, device=DEV)
+    cnt = torch.zeros((M, 1), dtype=torch.int32, device=DEV)
+    sc, th = torch.full((2, M, 1), -1.0, dtype=torch.float32, device=DEV)
+    qa.qa_quantize_pack_selected(L, g, d, ind, NW, sel, cnt, sc, th, workspace(need))
+    torch.cuda.synchronize()
+    for m in range(M):
+        if m >= 2:
+            assert all(torch.equal(x[m], x[m % 2]) for x in (sel, cnt, sc, th))
+            continue
+        o_sel, o_cnt, o_sc, o_th = oracle.quantize_selected(*rows[m], bucket=0)
+        assert host(cnt)[m].view(np.uint32) == o_cnt[0]
+        # sums of 2^24 magnitudes in binary64 (relative error 2^-29), rounded to binary32 once
+        assert abs(host(th)[m, 0] - o_th[0]) <= np.spacing(o_th[0]) and abs(host(sc)[m, 0] - o_sc[0]) <= np.spacing(o_sc[0])
+        words, got = (int(o_cnt[0]) + 15) // 16, host(sel[m]).view(np.uint32)
+        assert np.array_equal(got[:words], o_sel[:words]) and np.all(got[words:] == 0x5A5A5A5A)
 
 
 @pytest.mark.parametrize("shared", [False, True])
