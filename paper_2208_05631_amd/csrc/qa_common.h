@@ -100,7 +100,8 @@ __device__ __forceinline__ int wave_reduce_i32(int v, F f) {
            f(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 
-// Inclusive prefix sums over the 64 lanes (shifts within rows of 16, then row broadcasts).
+// Inclusive prefix sums over the 64 lanes with DPP: shifts within each row of 16 lanes, then the last lane of a row
+// is broadcast into the following rows.  A lane without a source adds 0.
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ uint32_t lanes_or_zero_u32(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xF, false);
@@ -111,12 +112,12 @@ __device__ __forceinline__ double lanes_or_zero_f64(double v) {
                           (int)lanes_or_zero_u32<CTRL, ROW_MASK>((uint32_t)__double2loint(v)));
 }
 __device__ __forceinline__ double wave_scan_f64(double v) {
-  v += lanes_or_zero_f64<0x111, 0xF>(v);
-  v += lanes_or_zero_f64<0x112, 0xF>(v);
-  v += lanes_or_zero_f64<0x114, 0xF>(v);
-  v += lanes_or_zero_f64<0x118, 0xF>(v);
-  v += lanes_or_zero_f64<0x142, 0xA>(v);
-  v += lanes_or_zero_f64<0x143, 0xC>(v);
+  v += lanes_or_zero_f64<0x111, 0xF>(v);      // row_shr:1
+  v += lanes_or_zero_f64<0x112, 0xF>(v);      // row_shr:2
+  v += lanes_or_zero_f64<0x114, 0xF>(v);      // row_shr:4
+  v += lanes_or_zero_f64<0x118, 0xF>(v);      // row_shr:8
+  v += lanes_or_zero_f64<0x142, 0xA>(v);      // row_bcast:15 into rows 1 and 3
+  v += lanes_or_zero_f64<0x143, 0xC>(v);      // row_bcast:31 into rows 2 and 3
   return v;
 }
 __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {

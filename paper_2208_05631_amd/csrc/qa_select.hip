@@ -189,7 +189,7 @@ __global__ __launch_bounds__(kThreads) void indicator_or_kernel(SelArgs a) {
 // Exclusive prefix sum of `v` over the 256 threads and the total; two barriers.
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* lds_w, uint32_t* total) {
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const uint32_t incl = wave_inclusive_scan_u32(v);
+  const uint32_t incl = wave_scan_u32(v);
   __syncthreads();
   if (lane == kWave - 1) lds_w[wave] = incl;
   __syncthreads();
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(kThreads) void decode_selected_kernel(SelArgs a) {
       // stream inside the words that exist for this tile
       const int64_t left = a.d - ((tile0 + u) * kTile + (int64_t)(j * 64 + lane) * 16);
       if (left < 16) mask[u][j] = left > 0 ? (mask[u][j] & ((1u << left) - 1u)) : 0u;
-      incl[u][j] = wave_inclusive_scan_u32((uint32_t)__popc(mask[u][j]));
+      incl[u][j] = wave_scan_u32((uint32_t)__popc(mask[u][j]));
     }
   uint32_t win_lo[kDecodeTiles][4], win_hi[kDecodeTiles][4], sh[kDecodeTiles][4];
 #pragma unroll
@@ -379,7 +379,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
       }
   }
   const uint32_t n0 = (uint32_t)__popc(iv[0]), n1 = (uint32_t)__popc(iv[1]);
-  const uint32_t incl = wave_inclusive_scan_u32(n0 + n1);
+  const uint32_t incl = wave_scan_u32(n0 + n1);
   const uint32_t K = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
   lds.words[2 * lane] = make_uint2(iv[0], incl - n0 - n1);
   lds.words[2 * lane + 1] = make_uint2(iv[1], incl - n1);
@@ -580,7 +580,7 @@ __global__ __launch_bounds__(kThreads) void select_codes_kernel(SelArgs a) {
   }
   if (lane < 2) stream[kTileWords + lane] = 0u;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) incl[j] = wave_inclusive_scan_u32((uint32_t)__popc(mask[j]));
+  for (int j = 0; j < 4; ++j) incl[j] = wave_scan_u32((uint32_t)__popc(mask[j]));
   __syncthreads();                                       // table and zeroed streams are in LDS
   int64_t base = tile * kTileWords;
   uint32_t first = 0;
@@ -813,7 +813,7 @@ __global__ __launch_bounds__(THREADS) void gsel_scan_kernel(SelArgs a) {
       mine += c[u];
       if (HAS_G) s1 += v[u];
     }
-    const uint32_t incl = wave_inclusive_scan_u32(mine);
+    const uint32_t incl = wave_scan_u32(mine);
     __syncthreads();                                     // the previous round's totals have been read
     if (lane == kWave - 1) lds_w[wave] = incl;
     __syncthreads();
@@ -971,7 +971,7 @@ __device__ __forceinline__ TileCodes code_selected_tile(const SelArgs& a, int64_
       load16(g, a.d, tile * kTile + (int64_t)wl * 16, v[h]);
     }
 #pragma unroll
-    for (int h = 0; h < 2; ++h) incl[h] = wave_inclusive_scan_u32((uint32_t)__popc(mask[h]));
+    for (int h = 0; h < 2; ++h) incl[h] = wave_scan_u32((uint32_t)__popc(mask[h]));
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const uint32_t n = (uint32_t)__popc(mask[h]);
@@ -1043,7 +1043,7 @@ __device__ __forceinline__ TileCodes code_few_marked(const SelArgs& a, int64_t t
     if (left < 32) iv[h] = left > 0 ? (iv[h] & ((1u << left) - 1u)) : 0u;
   }
   const uint32_t n0 = (uint32_t)__popc(iv[0]), n1 = (uint32_t)__popc(iv[1]);
-  const uint32_t incl = wave_inclusive_scan_u32(n0 + n1);
+  const uint32_t incl = wave_scan_u32(n0 + n1);
   const uint32_t ex = first + incl - n0 - n1;
   lds.words[2 * lane] = make_uint2(iv[0], ex);
   lds.words[2 * lane + 1] = make_uint2(iv[1], ex + n0);
@@ -1308,7 +1308,7 @@ __device__ __forceinline__ void settle_tile(const SelArgs& a, int64_t tile, int 
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const uint32_t n = (uint32_t)__popc(mask[j]), incl = wave_inclusive_scan_u32(n);
+    const uint32_t n = (uint32_t)__popc(mask[j]), incl = wave_scan_u32(n);
     at[j] = start + incl - n;
     start += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
     uint32_t lo = 0u, hi = 0u;

@@ -33,12 +33,7 @@ __device__ __forceinline__ bool settle_words(const float* __restrict__ g, int64_
     open[u] = (w[u] >> 1) & ~w[u] & 0x55555555u;         // low bit of every field 10
     mine += (uint32_t)__popc(open[u]);
   }
-  uint32_t incl = mine;
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const uint32_t o = __shfl_up(incl, off, kWave);
-    if (lane >= off) incl += o;
-  }
+  const uint32_t incl = wave_scan_u32(mine);
   if (lane == kWave - 1) lds.wave_total[wave] = incl;
 #pragma unroll
   for (int u = 0; u < kSettleTiles; ++u) lds.words[u * kTileWords + t] = w[u];

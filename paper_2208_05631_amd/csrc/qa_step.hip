@@ -531,7 +531,7 @@ __global__ __launch_bounds__(kThreads) void step_lut_kernel(StepArgs a) {
 #pragma unroll
       for (int p = 0; p < kChunk / 2; ++p) {
         const uint32_t own = (uint32_t)__popc(mk[2 * p]) | ((uint32_t)__popc(mk[2 * p + 1]) << 16);
-        const uint32_t incl = wave_inclusive_scan_u32(own);
+        const uint32_t incl = wave_scan_u32(own);
         if ((t % kWave) == kWave - 1) lds_scan[wave][p] = incl;
         ex[p] = incl - own;
       }
