@@ -1119,8 +1119,9 @@ __device__ __forceinline__ TileCodes code_few_marked(const SelArgs& a, int64_t t
 
 // The assembled codes of a tile to their place in the bucket's stream, its kept sum and count to the
 // workspace.  BRACKET: the one pass of the one-read form below; else the threshold comes from pass 2.
+// (Five waves per SIMD are what the LDS allows.)
 template <bool BRACKET>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) void gsel_quantize_multi_kernel(SelArgs a) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) void gsel_quantize_multi_kernel(SelArgs a) {
   __shared__ SelWaveLds lds_all[kWaves];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int64_t tile = (int64_t)blockIdx.x * kWaves + wave;

@@ -62,3 +62,12 @@ def test_exact_threshold_kernels_spill_only_where_their_comments_say():
         assert v["scratch"] <= max([n for p, n in EXACT_SPILLS.items() if p in name], default=0), (name, v)
         if "ILb1E" in name:
             assert v["waves"] == 8, (name, v)
+
+
+def test_selection_kernels_do_not_spill_and_reach_the_waves_they_ask_for():
+    kernels = resource_usage("qa_select.hip")
+    assert len(kernels) >= 20
+    assert not {k: v for k, v in kernels.items() if v["scratch"] != 0}
+    for part, waves in (("gsel_quantize_multi_kernel", 5), ("quantize_selected_kernel", 4), ("indicator_kernel", 3)):
+        found = [v["waves"] for k, v in kernels.items() if part in k and "indicator_or" not in k]
+        assert found and all(n == waves for n in found), (part, found)
