@@ -162,7 +162,9 @@ int qa_local_grad_batched(int format, const float* A_or_vals, const int64_t* ind
  * up to 4096 components are searched inside one wave or work-group; longer buckets, and one threshold for
  * a vector of more than 4096 components (Section 3.4's optimum over the whole gradient), are
  * found by refining histograms of the magnitudes (d < 2^32, else QA_ERR_TOO_LARGE); buckets of 2^21 components
- * and more are read once if a sample of them brackets the optimum.  The workspace is
+ * and more, 2^23 in all workers' buckets, are read once if a sample of them brackets the optimum and the call has at
+ * most some 30 workers (fewer if the last bucket is much shorter than the others; with more the lists of what lies
+ * inside the brackets do not fit the workspace, and the gradient is read several times, as in shorter buckets).  The workspace is
  * sized at some 17 bytes per component: two arrays of keys for the sort below (8), the search's state and the
  * lists of what lies inside a bracket; the call only enqueues kernels.  Of a bucket with
  * infinite components these alone are kept (the objective is infinite from the first on); a NaN

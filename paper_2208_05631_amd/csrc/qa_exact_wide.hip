@@ -31,9 +31,11 @@
 //
 // Thresholds and codes, us, levels as launches with a scan launch each and two launches for the codes -> now:
 //   one read, 2^26 x 4 Gaussian / 5 %-dense Laplace / 10 %-dense Student-t components, one scale per vector:
-//     860 803 813 -> 323 315 345 (213 of it the read at 5.4 TB/s); 2^24 x 4 265 -> 138; buckets of 2^24, 2^25 x 8 840 -> 323
-//   levels: 2^26 x 4 Cauchy components 784 -> 809 (the sample is in vain), ternary 2080 -> 2100; 10^6 x 8 151 -> 117,
-//     100003 117 -> 68; buckets of 2^18, 2^26 x 4 1011 -> 886
+//     844 797 803 -> 308 310 328 (213 of it the read at 5.4 TB/s); 2^24 x 4 264 230 235 -> 126 138 148
+//   levels, Gaussian components: 10^6 x 8 150 -> 87, 100003 119 -> 64; buckets of 2^18, 2^26 x 4 967 -> 857, 2^24 x 4 272 -> 259
+//   where the sample is in vain: Cauchy components 2^26 x 4 772 -> 756, 2^24 x 4 221 -> 232, 2^22 x 8 138 -> 169, 2^26 x 4
+//     in buckets of 2^21 778 -> 874; ternary 2^26 x 4 2036 -> 2090.  One component 10^9 times as large as the others, which the
+//     sample misses and the proof does not allow (the gradient is read once more): 2^26 x 4 775 -> 755, 2^22 x 8 138 -> 178
 //   up to 65536 components, a work-group per bucket: 2^26 x 4 in buckets of 65536 1091 -> 972, of 8192 4583 -> 4120
 //     (bound by the scans, some 8 us per level and work-group)
 #include "qa_common.h"
@@ -405,11 +407,13 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(CR
 // ---- longer buckets: the levels are launches, the histogram lies in global memory -----------------
 //
 // Work-groups of 1024 threads take a chunk each (4 to 128 tiles); the one of a bucket that finishes last scans
-// the level.  From 512 tiles on the bucket is read once in full, like the quantizer's own long buckets:
+// the level.  From 512 tiles on (2048 in all workers' buckets) and up to some 30 workers (a list of each has to fit
+// the workspace) the bucket is read once in full, like the quantizer's own long buckets:
 //
-//   sample    level 0 over some 2^20 components, spread in pieces of 256.  At the optimum the threshold is half the mean of what is
-//             kept (adding a to a sum S of k raises S^2 / k as long as a > S / 2k), so the place where
-//             S - 2 t K changes sign beside the sample's best edge is found between the bins.
+//   sample    level 0 over a quarter of the components, at most 2^20, spread in pieces of 256.  At the optimum the
+//             threshold is half the mean of what is kept (adding a to a sum S of k raises S^2 / k as long as
+//             a > S / 2k), so the place where S - 2 t K changes sign beside the sample's best edge is found
+//             between the bins.
 //   probe     the same sample against that threshold: S - 2 t K, 256 by 256.  Its slope gives a Newton step,
 //             the differences between neighbours the standard error; five of them to either side
 //             make the bracket.
@@ -427,8 +431,9 @@ constexpr int kPassThreads = kScanThreads, kPassComponents = kPassThreads * 16;
 constexpr int kMostChunkTiles = 128, kBracketedTiles = 32;   // at most 2^19 components: counts and offset sums fit a bin
 // Buckets of fewer tiles than this, or than this in all workers' buckets, are not sampled.  Levels alone / with the
 // sample, us, Gaussian, 5 %-dense Laplace and Cauchy components (the last ones' optimum keeps too few for a
-// bracket): 2^21 x 8 135 116 109 / 103 115 131; 2^22 95 82 77 / 88 98 94; 2^22 x 8 183 166 155 / 124 128 180;
-// 2^23 123 103 95 / 91 89 114; 2^26 x 4 in buckets of 2^21 805 / 509.
+// bracket): 2^22 x 2 92 75 71 / 87 98 90; 2^23 101 84 79 / 86 99 97; 2^21 x 8 113 94 91 / 91 99 107; 2^22 x 8 164 140 135 /
+// 111 116 169; 2^23 x 4 165 141 135 / 99 105 153; 2^24 x 4 259 222 216 / 126 138 232; 2^26 x 4 in buckets of 2^21 808 758
+// 740 / 508 502 874.  The second line lies where dense gradients gain; sparse ones gain from four times as many tiles on.
 constexpr int64_t kSampledTiles = 512, kSampledInAll = 2048;
 constexpr int kUnit = 4 * kWave, kMostOften = 4, kUnitsPerWave = 4, kUnitsPerGroup = kUnitsPerWave * kScanWaves;
 constexpr int kMostUnits = kRanges / 2 * kUnitsPerWave;   // two sums of each wave in LevelRanges::sum_before
@@ -517,8 +522,8 @@ __device__ __forceinline__ void take_bins(WideState* st, const int (&at)[N], uin
     if (c[i]) { st->count[at[i]] = 0u; st->offset[at[i]] = 0ull; }
 }
 
-// The sample: 256 consecutive components (a KiB) of every 64 times as many, not always the same of its group; a wave
-// takes sixteen such units.
+// The sample: units of 256 consecutive components (a KiB), one of every `every`, not always the same of its group: every
+// fourth (kMostOften), or fewer, so that a bucket has kMostUnits of them at most; a wave takes kUnitsPerWave.
 struct SampleArgs {
   int64_t every;                                         // one unit of so many
   int units, groups;                                     // of a full bucket; work-groups per bucket
@@ -1374,6 +1379,9 @@ int exact_thresholds_wide(const qa_layout* L, const float* g, int64_t g_stride, 
   const int64_t tiles = tiles_of(longest), capacity = (int64_t)((room - states) / sizeof(uint2)) / (a.nb * group);
   list.capacity = (uint32_t)(capacity < longest ? capacity : longest);
   SampleArgs sa{};
+  // A list holds a 32nd of its bucket, twice what a bracket may leave open: a quarter of a byte per component and
+  // worker, of the 9 that there are per component.  So more than some 30 workers of one long vector (fewer with a
+  // short last bucket) are not sampled.
   const bool sampled = tiles >= kSampledTiles && tiles * a.nb * L->M >= kSampledInAll && capacity >= longest / 32;
   const int64_t units = longest / kUnit;
   sa.every = (units + kMostUnits - 1) / kMostUnits;

@@ -1420,7 +1420,7 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void gsel_scale_kernel(SelAr
 // Buckets of at least 4096 tiles (64 samples) are quantized in one read if all workers have 2^28 coordinates
 // or more.  With a bracket it is the faster form from 2^27 on; without one (marks on components of very
 // unequal sizes, one mark or none per tile) its small launches and the second coding come on top of two reads, and
-// the line lies where that costs no more than a tenth.  Two reads / one read with a bracket / one read without, us, for
+// the line lies where that costs no more than a sixth and a bracket gains as much at least.  Two reads / one read with a bracket / one read without, us, for
 // 7 % and for 97 % of the components marked: 8 workers x 2^27 1430 / 823 / 1518 and 1612 / 1060 / 1763,
 // 8 x 2^25 357 / 226 / 395 and 407 / 357 / 471, 4 x 2^25 183 / 127 / 210 and 215 / 208 / 255, 2 x 2^25 98 / 80 / - and 100 /
 // 119 / -.  Shorter buckets have wider brackets: 8 x 2^24 in buckets of 2^22 181 / 148 and 212 / 236.
