@@ -68,13 +68,20 @@ __device__ __forceinline__ GradArgs for_worker(GradArgs a) {
 }
 
 // Four consecutive floats at any address that is a multiple of 4: the memory system takes a 16-byte
-// load on a 4-byte boundary (rows of an odd length start on those).  Without the streaming hint: the column
-// sums read the margins' rows again and a later batch draws some of them again, so what the last-level
-// cache holds is worth keeping (8 x 128 rows of 100003 columns, other rows in each call 164.3 -> 162.6 us, the same
-// rows 157.3 -> 136.7; 8 x 256 rows of 30001, other rows, 104.1 -> 100.4).
+// load on a 4-byte boundary (rows of an odd length start on those).
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef floatx4 floatx4_any __attribute__((aligned(4)));
 __device__ __forceinline__ floatx4 load4(const float* p) { return *reinterpret_cast<const floatx4_any*>(p); }
+// The same of a batch's rows.  The column sums read the margins' rows again and a later batch draws some of them again, so
+// rows are streamed only where the cache would not hold them anyway: batches of more than 2^27 components (512 MB, twice
+// the last-level cache).  Plain / streamed, us, other rows in each call and the same ones: 8 x 128 rows of 100003 columns 156
+// and 152 / 155 153, 8 x 256 of 30001 94 82 / 93 92, 4 x 8 of 2^20 217 156 / 224 224, 4 x 32 of 2^20 (the line) 292 288 / 285 288,
+// 4 x 64 of 2^20 427 421 / 403 402, 4 x 256 of 2^20 1525 1529 / 1445 1456, 8 x 256 of 300001 877 876 / 885 885.
+constexpr int64_t kStreamedBatch = int64_t(1) << 27;
+template <bool STREAM>
+__device__ __forceinline__ floatx4 row_load4(const float* p) {
+  return STREAM ? __builtin_nontemporal_load(reinterpret_cast<const floatx4_any*>(p)) : load4(p);
+}
 
 // coef and loss of one sample from its binary32 margin term p = a.x
 __device__ __forceinline__ void logistic_terms(float p, float y, int B, float* coef, double* loss) {
@@ -95,7 +102,7 @@ __device__ __forceinline__ void reduce_loss(const GradArgs& a, double* lds_d) {
 
 // LANES threads per batch row (the work-group, or a wave for short rows), which is read as 16-byte
 // pieces with four loads in flight per thread.
-template <int LANES>
+template <int LANES, bool STREAM>
 __global__ __launch_bounds__(kThreads) void dense_margin_kernel(GradArgs a_all) {
   static_assert(LANES == kThreads || LANES == kWave, "a work-group or a wave per row");
   const GradArgs a = for_worker(a_all);
@@ -114,7 +121,7 @@ __global__ __launch_bounds__(kThreads) void dense_margin_kernel(GradArgs a_all) 
     for (; j + 4 * 3 * LANES < whole; j += 4 * 4 * LANES) {
       floatx4 v[4], w[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = load4(row + j + u * 4 * LANES);
+      for (int u = 0; u < 4; ++u) v[u] = row_load4<STREAM>(row + j + u * 4 * LANES);
 #pragma unroll
       for (int u = 0; u < 4; ++u) w[u] = load4(a.x + j + u * 4 * LANES);
 #pragma unroll
@@ -126,7 +133,7 @@ __global__ __launch_bounds__(kThreads) void dense_margin_kernel(GradArgs a_all) 
       }
     }
     for (; j < whole; j += 4 * LANES) {
-      const floatx4 v = load4(row + j), w = load4(a.x + j);
+      const floatx4 v = row_load4<STREAM>(row + j), w = load4(a.x + j);
       s0 = fma((double)v.x, (double)w.x, s0);
       s1 = fma((double)v.y, (double)w.y, s1);
       s2 = fma((double)v.z, (double)w.z, s2);
@@ -156,7 +163,7 @@ __global__ __launch_bounds__(kThreads) void dense_margin_kernel(GradArgs a_all) 
 // are bound by the two reads of the batch, 5.6-6.4 TB/s; workers taken in groups of 60-220 MB and
 // columns in reverse, so that more of the second read comes from the last-level cache, were no faster).
 // The last work-group of a worker adds up the losses instead, if they are asked for.
-template <int SPLIT>
+template <int SPLIT, bool STREAM>
 __global__ __launch_bounds__(kThreads) void dense_colsum_kernel(GradArgs a_all) {
   constexpr int kRows = 16, kStage = 1024, kCols = kThreads / SPLIT;
   const GradArgs a = for_worker(a_all);
@@ -199,7 +206,7 @@ __global__ __launch_bounds__(kThreads) void dense_colsum_kernel(GradArgs a_all) 
       floatx4 v[kRows];
       if (whole) {
 #pragma unroll
-        for (int u = 0; u < kRows; ++u) v[u] = load4(a.A + (int64_t)(r[u] >= 0 ? r[u] : 0) * a.d + j);
+        for (int u = 0; u < kRows; ++u) v[u] = row_load4<STREAM>(a.A + (int64_t)(r[u] >= 0 ? r[u] : 0) * a.d + j);
       } else {                                            // the last columns of a row of odd length
 #pragma unroll
         for (int u = 0; u < kRows; ++u) {
@@ -706,15 +713,21 @@ static int grad_launch(int format, const float* A_or_vals, const int64_t* indptr
   if (!csr) {
     const int64_t n4 = (d + 3) / 4;
     const unsigned extra = loss_out ? 1u : 0u;            // a work-group per worker for the loss
+    const int64_t rows = n_rows < (int64_t)M * B ? n_rows : (int64_t)M * B;   // different ones, at most
+    const bool streamed = rows > kStreamedBatch / d;
     if (d <= kShortRow)
-      hipLaunchKernelGGL(dense_margin_kernel<kWave>, dim3((B + kWaves - 1) / kWaves, Mu), block, 0, stream, a);
+      hipLaunchKernelGGL((streamed ? dense_margin_kernel<kWave, true> : dense_margin_kernel<kWave, false>),
+                         dim3((B + kWaves - 1) / kWaves, Mu), block, 0, stream, a);
     else
-      hipLaunchKernelGGL(dense_margin_kernel<kThreads>, dim3(B, Mu), block, 0, stream, a);
+      hipLaunchKernelGGL((streamed ? dense_margin_kernel<kThreads, true> : dense_margin_kernel<kThreads, false>),
+                         dim3(B, Mu), block, 0, stream, a);
     const int64_t groups = (n4 + kWave - 1) / kWave;
     if (groups * M < kFewGroups && B > 64)
-      hipLaunchKernelGGL(dense_colsum_kernel<16>, dim3((unsigned)((n4 + 15) / 16) + extra, Mu), block, 0, stream, a);
+      hipLaunchKernelGGL((streamed ? dense_colsum_kernel<16, true> : dense_colsum_kernel<16, false>),
+                         dim3((unsigned)((n4 + 15) / 16) + extra, Mu), block, 0, stream, a);
     else
-      hipLaunchKernelGGL(dense_colsum_kernel<4>, dim3((unsigned)groups + extra, Mu), block, 0, stream, a);
+      hipLaunchKernelGGL((streamed ? dense_colsum_kernel<4, true> : dense_colsum_kernel<4, false>),
+                         dim3((unsigned)groups + extra, Mu), block, 0, stream, a);
     return launch_status();
   } else if (csr_launch(a, M, stream)) {
     return launch_status();

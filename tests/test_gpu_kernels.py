@@ -410,6 +410,29 @@ def test_local_grad_dense_at_any_alignment_and_batch_split(d, B, M, shift):
             assert np.allclose(host(loss), [r[1] for r in ref], rtol=1e-6)
 
 
+# just below and above 2^27 components of different rows; short rows, few and many work-groups of columns
+@pytest.mark.parametrize("d,B,M", [(300, 55925, 8), (4099, 8187, 4), (262147, 65, 8)])
+@pytest.mark.parametrize("above", [False, True])
+def test_local_grad_dense_around_the_line_of_streamed_batches(d, B, M, above):
+    rng = np.random.default_rng(d)
+    n, base = (1 << 27) // d + (1 if above else 0), 16   # the rows repeat every sixteen
+    A = rng.standard_normal((base, d)).astype(np.float32)
+    y = np.where(rng.random(base) < 0.5, -1.0, 1.0).astype(np.float32)
+    x = (rng.standard_normal(d) * 0.01).astype(np.float32)
+    rows = np.arange(M * B, dtype=np.int32).reshape(M, B) % n
+    A_d, y_d = dev(A).repeat(-(-n // base), 1)[:n], dev(y).repeat(-(-n // base))[:n]
+    gs = (d + 3) // 4 * 4
+    ws = workspace(qa.qa_workspace_bytes(qa.Layout.make(d, M, 0), qa.QA_OP_GRAD_DENSE))
+    g, loss = torch.full((M, gs), 5.0, dtype=torch.float32, device=DEV), torch.zeros(M, dtype=torch.float32, device=DEV)
+    qa.qa_local_grad_batched(qa.QA_DENSE, A_d, None, None, n, d, y_d, dev(rows), B, M, dev(x), g, gs, loss, ws)
+    torch.cuda.synchronize()
+    for m in range(M):
+        og, ol = oracle.local_grad_dense(A, y, rows[m] % base, x)
+        # binary64 sums of terms up to coef * |A| <= 6 / B each, rounded to binary32 once
+        assert np.all(np.abs(host(g)[m, :d] - og) <= np.spacing(np.abs(og)) + 6 * 2.0 ** -40)
+        assert host(loss)[m] == pytest.approx(ol, rel=1e-6)
+
+
 def _random_csr(rng, n, d, k):
     idx = np.stack([np.sort(rng.choice(d, k, replace=False)) for _ in range(n)]).astype(np.int32)
     vals = rng.standard_normal((n, k)).astype(np.float32)
