@@ -318,8 +318,9 @@ int qa_indicator_or(const qa_layout* layout, const uint32_t* ind, int64_t ind_st
  * Only the first ceil(count/16) words of an area are written (unused bits of the last one
  * are 0), the rest is left untouched: the message
  * of a bucket is 32 + b + 2*count bits.  count == 0 gives scale 0, threshold 0, no codes.
- * thresholds may be NULL.  ws: qa_workspace_bytes(layout, QA_OP_SELECT) (0 bytes, ws may be NULL,
- * unless buckets span several tiles). */
+ * thresholds may be NULL.  The order of the binary64 additions depends on the size of the call (its coordinates and
+ * workers): a threshold or scale may differ in its last bit between a worker's message alone and among others.
+ * ws: qa_workspace_bytes(layout, QA_OP_SELECT) (0 bytes, ws may be NULL, unless buckets span several tiles). */
 int qa_quantize_pack_selected(const qa_layout* layout, const float* g, int64_t g_stride,
                               const uint32_t* ind, int64_t ind_stride, uint32_t* sel_codes,
                               uint32_t* counts, float* scales, float* thresholds, void* ws,
