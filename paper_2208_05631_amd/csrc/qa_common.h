@@ -54,7 +54,9 @@ __device__ __forceinline__ double shfl_xor_f64(double v, int mask) {
 // ---- wave64 sums with DPP (no LDS traffic): every lane receives the sum of all 64 lanes ----
 template <int CTRL>
 __device__ __forceinline__ int dpp_i32(int v) {
-  return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false);   // every lane has a source
+  // every lane has a source; no former value of the target, which would be copied there first and would keep the
+  // move from being folded into the instruction that uses it
+  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
 }
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
@@ -240,9 +242,63 @@ __device__ __forceinline__ float scale_from_sum(double S2, uint64_t cnt) {
   return cnt ? (float)(S2 / (double)cnt) : 0.0f;
 }
 
+// ---- code words from compare masks ----------------------------------------------------------------
+//
+// The kernels that write codes are bound by vector instructions as much as by memory.  A field costs two: its bits
+// are shifted into the word from below, the last component first, the sign by v_alignbit and the kept bit as the
+// carry of word + word + carry.  Built from selects it was four.
+
+// word << 8 | the fields of four components, sign and kept bit; the signs of what is not kept go with clear_signs().
+// A mask that a vector compare has just written may be read as a carry two wait states later at the earliest, and
+// what the compiler puts in front of the statement is not known: hence the s_nop.
+__device__ __forceinline__ uint32_t push_codes(uint32_t word, const float (&v)[4], const uint64_t (&kept)[4]) {
+  uint64_t carry_out;
+  asm("s_nop 1\n\t"
+      "v_alignbit_b32 %0, %0, %5, 31\n\tv_addc_co_u32_e64 %0, %1, %0, %0, %9\n\t"
+      "v_alignbit_b32 %0, %0, %4, 31\n\tv_addc_co_u32_e64 %0, %1, %0, %0, %8\n\t"
+      "v_alignbit_b32 %0, %0, %3, 31\n\tv_addc_co_u32_e64 %0, %1, %0, %0, %7\n\t"
+      "v_alignbit_b32 %0, %0, %2, 31\n\tv_addc_co_u32_e64 %0, %1, %0, %0, %6"
+      : "+&v"(word), "=&s"(carry_out)
+      : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "s"(kept[0]), "s"(kept[1]), "s"(kept[2]), "s"(kept[3]));
+  return word;
+}
+__device__ __forceinline__ uint32_t clear_signs(uint32_t word) {
+  const uint32_t kept = word & 0x55555555u;
+  return word & (kept | kept << 1);
+}
+// Byte j of lane i's word (i, j in 0 .. 3 within each quad) to byte i of lane j's.
+__device__ __forceinline__ uint32_t quad_transpose(uint32_t word) {
+  const uint32_t t = threadIdx.x;
+  const uint32_t beside = (uint32_t)dpp_i32<kDppQuadXor1>((int)word);
+  const uint32_t pairs = __builtin_amdgcn_perm(beside, word, t & 1u ? 0x03070105u : 0x06020400u);
+  const uint32_t across = (uint32_t)dpp_i32<kDppQuadXor2>((int)pairs);
+  return __builtin_amdgcn_perm(across, pairs, t & 2u ? 0x03020706u : 0x05040100u);
+}
+// Code word j * 64 + thread / 4 of a tile in lane j of each quad, from v[j][e], component e of the thread's float4
+// group j * 256 + thread, and the lanes that keep it.
+__device__ __forceinline__ uint32_t code_word(const float (&v)[4][4], const uint64_t (&kept)[4][4]) {
+  uint32_t word = 0;
+#pragma unroll
+  for (int j = 3; j >= 0; --j) word = push_codes(word, v[j], kept[j]);
+  return quad_transpose(clear_signs(word));
+}
+// s += x in the lanes of `lanes` alone: one vector instruction where a selected addend takes two more.
+__device__ __forceinline__ void add_in_lanes(double& s, double x, uint64_t lanes) {
+  uint64_t all;
+  asm("s_and_saveexec_b64 %1, %3\n\tv_add_f64 %0, %0, %2\n\ts_mov_b64 exec, %1"
+      : "+v"(s), "=&s"(all) : "v"(x), "s"(lanes) : "scc");
+}
+
 // Ternary code as the 2-bit field 00 / 01 / 11; NaN compares false on both sides -> 00.
 __device__ __forceinline__ uint32_t ternary_field(float v, float Delta) {
   return v > Delta ? 1u : (v < -Delta ? 3u : 0u);
+}
+// code_word() by the two comparisons as they are defined, which differ from |v| > Delta for thresholds below 0.
+__device__ __forceinline__ uint32_t code_word_compared(const float (&v)[4][4], const float (&Delta)[4]) {
+  uint32_t word = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) word |= ternary_field(v[i / 4][i % 4], Delta[i / 4]) << (2 * i);
+  return quad_transpose(word);
 }
 
 #endif  // __HIPCC__

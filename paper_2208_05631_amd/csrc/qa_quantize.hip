@@ -10,6 +10,7 @@
 //                    tile partial (count, sum) -> finalize scale; the gradient is read twice, or,
 //                    for long buckets, once: a sample brackets the threshold beforehand.
 #include <mutex>
+#include <type_traits>
 
 #include "qa_common.h"
 #include "qa_settle.h"
@@ -78,37 +79,29 @@ __device__ __forceinline__ void load_tile_stream(const float* __restrict__ g, in
   }
 }
 
-// Ternary fields of the thread's 16 elements -> the four code words of its quad (group j of
-// lanes 4q..4q+3 is code word j*64 + t/4 of the tile); lane (t & 3) == j stores word j.
-__device__ __forceinline__ void pack_and_store(const float v[4][4], const float Delta[4],
-                                               uint32_t* __restrict__ codes_m, int64_t tile,
-                                               int64_t W) {
+// The thread's word of the tile (word j*64 + t/4 for j = t & 3).
+__device__ __forceinline__ void store_code_word(uint32_t* __restrict__ codes_m, int64_t tile, int64_t W, uint32_t word) {
   const int t = threadIdx.x;
-  uint32_t mine = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    uint32_t b = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) b |= ternary_field(v[j][e], Delta[j]) << (2 * e);
-    uint32_t w = b << (8 * (t & 3));
-    w |= (uint32_t)dpp_i32<kDppQuadXor1>((int)w);
-    w |= (uint32_t)dpp_i32<kDppQuadXor2>((int)w);
-    if ((t & 3) == j) mine = w;
-  }
   const int64_t widx = tile * kTileWords + (t & 3) * 64 + (t >> 2);
-  if (widx < W) codes_m[widx] = mine;
+  if (widx < W) codes_m[widx] = word;
 }
 
-__device__ __forceinline__ void kept_sums(const float v[4], float Delta, double* s_out,
-                                          uint32_t* c_out) {
-  double s = 0.0;
-  uint32_t c = 0;
+// What threshold D keeps of the thread's elements, added to s, and of the wave's, added to wave_cnt; the code word.
+__device__ __forceinline__ uint32_t code_tile(const float (&v)[4][4], float D, double& s, uint32_t& wave_cnt) {
+  uint64_t keep[4][4];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const float av = fabsf(v[e]);
-    if (av > Delta) { s += (double)av; ++c; }
+  for (int j = 0; j < 4; ++j) {
+    double sj = 0.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      keep[j][e] = __ballot(fabsf(v[j][e]) > D);
+      wave_cnt += (uint32_t)__popcll(keep[j][e]);
+      add_in_lanes(sj, (double)fabsf(v[j][e]), keep[j][e]);
+    }
+    s += sj;
   }
-  *s_out = s; *c_out = c;
+  const float Delta[4] = {D, D, D, D};
+  return D < 0.0f ? code_word_compared(v, Delta) : code_word(v, keep);
 }
 
 // ---- 64 <= bucket < 4096 : single pass, several buckets per tile --------------------------------
@@ -158,12 +151,9 @@ __device__ __forceinline__ double slices_sum_f64(const double s[4]) {
   if (LANES >= 64) v = add_rows_f64<32>(v);
   return v;
 }
+// the same for counts that a quad's lane l holds for slice l & 3 already
 template <int LANES>
-__device__ __forceinline__ uint32_t slices_sum_u32(const uint32_t c[4]) {
-  const bool odd = threadIdx.x & 1, high = threadIdx.x & 2;
-  const uint32_t a = (odd ? c[1] : c[0]) + (uint32_t)dpp_i32<kDppQuadXor1>((int)(odd ? c[0] : c[1]));
-  const uint32_t b = (odd ? c[3] : c[2]) + (uint32_t)dpp_i32<kDppQuadXor1>((int)(odd ? c[2] : c[3]));
-  uint32_t v = (high ? b : a) + (uint32_t)dpp_i32<kDppQuadXor2>((int)(high ? a : b));
+__device__ __forceinline__ uint32_t quads_sum_u32(uint32_t v) {
   v += lanes_xor4_u32(v);
   v += (uint32_t)dpp_i32<kDppRowRor8>((int)v);
   if (LANES >= 32) v = add_rows_u32<16>(v);
@@ -174,12 +164,12 @@ __device__ __forceinline__ uint32_t slices_sum_u32(const uint32_t c[4]) {
 // The sums over the buckets that hold this thread's part of slice l & 3.  lds_*: 16 entries each that
 // nobody else uses; the work-group's threads all take part (barriers for buckets above 256).
 template <int LOG2B, bool WITH_COUNT>
-__device__ __forceinline__ void bucket_sums(const double s[4], const uint32_t c[4], double* lds_s, uint32_t* lds_c,
+__device__ __forceinline__ void bucket_sums(const double s[4], uint32_t quad_count, double* lds_s, uint32_t* lds_c,
                                             double* sum, uint32_t* count) {
   constexpr int SEG = LOG2B >= 10 ? 256 : (1 << LOG2B) / 4;     // threads per bucket within a slice
   constexpr int LANES = SEG < 64 ? SEG : 64;
   *sum = slices_sum_f64<LANES>(s);
-  if (WITH_COUNT) *count = slices_sum_u32<LANES>(c);
+  if (WITH_COUNT) *count = quads_sum_u32<LANES>(quad_count);
   if constexpr (SEG > 64) {
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, j = lane & 3;
     __syncthreads();                                     // earlier readers of lds are done
@@ -208,11 +198,11 @@ __device__ __forceinline__ void bucket_sums(const double s[4], const uint32_t c[
   }
 }
 
-// Bound by the read of the gradient; with four sums per slice, four thresholds and a division per slice
-// and barrier it was bound by vector instructions (691 per wave and tile; now 398).  2^26 x 4 Gaussian components:
-// buckets of 64 269 -> 216 us, 128 256 -> 195, 256 264 -> 192, 512 262 -> 193, 1024 265 -> 190, 2048 274 -> 191
-// (4096, its own kernel: 180); 50 000 017 x 5, 256: 292 -> 217.
-template <int LOG2B>
+// Bound by the read of the gradient; where the last-level cache holds that, by vector instructions (about 240 per wave
+// and tile: magnitudes stay converted from the first sum to the second, which adds them under a lane mask, and fields
+// are shifted in; 398 with selects).  3 000 001 x 8 Gaussian components, buckets of 256 17.3 -> 16.0 us, 1024
+// 17.6 -> 16.3; 2^26 x 4, 512 and 1024 179 -> 177, 256 176 either way.
+template <int LOG2B, bool GIVEN>                         // a.thresh_given
 __device__ __forceinline__ void quantize_buckets_of_tile(const QuantArgs& a, int64_t tile, int m) {
   __shared__ double lds_s[4 * kWaves];
   __shared__ uint32_t lds_c[4 * kWaves];
@@ -227,9 +217,8 @@ __device__ __forceinline__ void quantize_buckets_of_tile(const QuantArgs& a, int
   const int kb = (((t & 3) * kThreads + t) * 4) >> LOG2B;
   const int64_t k = tile * (kTile >> LOG2B) + kb;
   float mine_delta;                                      // of that bucket
-  if (!a.thresh_given) {
+  if constexpr (!GIVEN) {
     double S1[4], sum;
-    const uint32_t none[4] = {0u, 0u, 0u, 0u};
     uint32_t unused;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -237,7 +226,7 @@ __device__ __forceinline__ void quantize_buckets_of_tile(const QuantArgs& a, int
 #pragma unroll
       for (int e = 1; e < 4; ++e) S1[j] += (double)fabsf(v[j][e]);
     }
-    bucket_sums<LOG2B, false>(S1, none, lds_s, lds_c, &sum, &unused);
+    bucket_sums<LOG2B, false>(S1, 0u, lds_s, lds_c, &sum, &unused);
     // Every bucket of the tile is complete unless the vector ends inside the tile; dividing by
     // the power of two b is then an exact scaling, the same value as the division.
     if (whole) {
@@ -256,83 +245,41 @@ __device__ __forceinline__ void quantize_buckets_of_tile(const QuantArgs& a, int
   Delta[2] = __int_as_float(dpp_i32<0xAA>(__float_as_int(mine_delta)));
   Delta[3] = __int_as_float(dpp_i32<0xFF>(__float_as_int(mine_delta)));
 
-  // kept sums, counts and 2-bit fields; for Delta >= 0 the field of a kept element is
-  // 01 | sign << 1, a negative (given) threshold takes the two plain comparisons
-  const bool plain = __any(mine_delta < 0.0f);
-  double S2[4];
-  uint32_t C[4];
-  uint32_t mine = 0;
+  // kept sums and 2-bit fields; a negative (given) threshold takes the two plain comparisons
+  double S2[4] = {0.0, 0.0, 0.0, 0.0};
+  uint64_t keep[4][4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    double s2 = 0.0;
-    uint32_t c = 0, bits = 0;
+  for (int j = 0; j < 4; ++j)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float av = fabsf(v[j][e]);
-      const bool keep = av > Delta[j];
-      s2 += (double)(keep ? av : 0.0f);
-      c += keep ? 1u : 0u;
-      const uint32_t pat = 1u | ((__float_as_uint(v[j][e]) >> 30) & 2u);
-      bits |= (keep ? pat : 0u) << (2 * e);
+      keep[j][e] = __ballot(fabsf(v[j][e]) > Delta[j]);
+      add_in_lanes(S2[j], (double)fabsf(v[j][e]), keep[j][e]);
     }
-    if (plain) {
-      bits = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) bits |= ternary_field(v[j][e], Delta[j]) << (2 * e);
-    }
-    S2[j] = s2; C[j] = c;
-    uint32_t w = bits << (8 * (t & 3));
-    w |= (uint32_t)dpp_i32<kDppQuadXor1>((int)w);
-    w |= (uint32_t)dpp_i32<kDppQuadXor2>((int)w);
-    if ((t & 3) == j) mine = w;
-  }
-  {
-    const int64_t widx = tile * kTileWords + (t & 3) * 64 + (t >> 2);
-    if (widx < a.W) (a.codes + (int64_t)m * a.code_stride)[widx] = mine;
-  }
+  const uint32_t mine = GIVEN && __any(mine_delta < 0.0f) ? code_word_compared(v, Delta) : code_word(v, keep);
+  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, mine);
   double sum;
   uint32_t count;
-  bucket_sums<LOG2B, true>(S2, C, lds_s, lds_c, &sum, &count);
+  // a lane's word holds the quad's components of slice l & 3; what is kept has a field other than 0
+  bucket_sums<LOG2B, true>(S2, (uint32_t)__popc(mine & 0x55555555u), lds_s, lds_c, &sum, &count);
   // the quad with the bucket's first element writes (of a bucket of two slices, the first one's lane)
   constexpr int SEG = LOG2B >= 10 ? 256 : b / 4;
   const bool writes = (t & (SEG - 1)) < 4 && (LOG2B < 11 || (t & 1) == 0);
   if (writes && k < a.nb) {
     a.scales[(int64_t)m * a.scale_stride + k] = scale_from_sum(sum, count);
-    if (a.thresholds && !a.thresh_given) a.thresholds[(int64_t)m * a.scale_stride + k] = mine_delta;
+    if (!GIVEN && a.thresholds) a.thresholds[(int64_t)m * a.scale_stride + k] = mine_delta;
   }
 }
 
-template <int LOG2B>
+template <int LOG2B, bool GIVEN>
 __global__ __launch_bounds__(kThreads) void quantize_bucket_kernel(QuantArgs a) {
-  quantize_buckets_of_tile<LOG2B>(a, blockIdx.x, blockIdx.y);
+  quantize_buckets_of_tile<LOG2B, GIVEN>(a, blockIdx.x, blockIdx.y);
 }
 
 // ---- bucket == 4096 == the tile : single pass, two work-group reductions ---------------------
 
-// Kept-magnitude sum, kept count (wave-wide, from the compare masks on the scalar unit) and the
-// 2-bit fields of one float4 group.  For Delta >= 0 (always, unless a caller hands in a negative
-// threshold)  v > Delta or v < -Delta  <=>  |v| > Delta, and the field is 01 | sign << 1.
-__device__ __forceinline__ uint32_t quantize4(const float v[4], float Delta, bool plain_compare,
-                                              double& s2, uint32_t& wave_cnt) {
-  uint32_t b = 0;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const float av = fabsf(v[e]);
-    const bool keep = av > Delta;
-    wave_cnt += (uint32_t)__popcll(__ballot(keep));
-    s2 += (double)(keep ? av : 0.0f);
-    uint32_t f;
-    if (plain_compare) {
-      f = ternary_field(v[e], Delta);
-    } else {
-      const uint32_t pat = 1u | ((__float_as_uint(v[e]) >> 30) & 2u);
-      f = keep ? pat : 0u;
-    }
-    b |= f << (2 * e);
-  }
-  return b;
-}
-
+// Bound by the read of the gradient; where the last-level cache holds that, by vector instructions (about 220 per
+// wave, 323 with selects): 2^20 x 16 components 12.2 -> 11.1 us, 3 000 001 x 8 19.1 -> 17.0.
+template <bool GIVEN>                                    // a.thresh_given
 __device__ __forceinline__ void quantize_tile(const QuantArgs& a, int64_t tile, int m) {
   __shared__ double lds_s1[kWaves];
   __shared__ double lds_s2[kWaves];
@@ -340,8 +287,9 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, int64_t tile, 
   const int t = threadIdx.x;
   const int64_t lo = tile * kTile;
   const float* g = a.g + (int64_t)m * a.g_stride;
+  const bool whole = lo + kTile <= a.d;
   float v[4][4];
-  if (lo + kTile <= a.d) {
+  if (whole) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       // the gradient is read exactly once: nontemporal
@@ -355,7 +303,7 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, int64_t tile, 
   }
 
   float Delta;
-  if (!a.thresh_given) {
+  if constexpr (!GIVEN) {
     double sj[4];                                        // four independent chains
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -364,26 +312,27 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, int64_t tile, 
       for (int e = 1; e < 4; ++e) sj[j] += (double)fabsf(v[j][e]);
     }
     const double S1 = block_sum_f64((sj[0] + sj[1]) + (sj[2] + sj[3]), lds_s1);
-    const int64_t n = (a.d - lo) < (int64_t)kTile ? (a.d - lo) : (int64_t)kTile;
-    Delta = threshold_from_sum(S1, a.thr_coef, n);
+    // dividing by 4096 is an exact scaling
+    Delta = whole ? (float)(((double)a.thr_coef * S1) * (1.0 / (double)kTile))
+                  : threshold_from_sum(S1, a.thr_coef, a.d - lo);
   } else {
     Delta = a.thresholds[(int64_t)m * a.scale_stride + tile];
   }
-  const bool plain_compare = Delta < 0.0f;               // uniform; only with a given threshold
-
   double s2j[4] = {0.0, 0.0, 0.0, 0.0};
+  uint64_t keep[4][4];
   uint32_t wave_cnt = 0;
-  uint32_t mine = 0;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const uint32_t b = quantize4(v[j], Delta, plain_compare, s2j[j], wave_cnt);
-    uint32_t w = b << (8 * (t & 3));
-    w |= (uint32_t)dpp_i32<kDppQuadXor1>((int)w);
-    w |= (uint32_t)dpp_i32<kDppQuadXor2>((int)w);
-    if ((t & 3) == j) mine = w;
-  }
-  const int64_t widx = tile * kTileWords + (t & 3) * 64 + (t >> 2);
-  if (widx < a.W) (a.codes + (int64_t)m * a.code_stride)[widx] = mine;
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      keep[j][e] = __ballot(fabsf(v[j][e]) > Delta);
+      wave_cnt += (uint32_t)__popcll(keep[j][e]);
+      add_in_lanes(s2j[j], (double)fabsf(v[j][e]), keep[j][e]);
+    }
+  // v > Delta or v < -Delta  <=>  |v| > Delta, unless a caller hands in a threshold below 0 (uniform)
+  const float Delta4[4] = {Delta, Delta, Delta, Delta};
+  const uint32_t mine = GIVEN && Delta < 0.0f ? code_word_compared(v, Delta4) : code_word(v, keep);
+  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, mine);
 
   const double s2 = wave_sum_f64((s2j[0] + s2j[1]) + (s2j[2] + s2j[3]));
   if ((t % kWave) == 0) { lds_s2[t / kWave] = s2; lds_c[t / kWave] = wave_cnt; }
@@ -392,12 +341,13 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, int64_t tile, 
     const double S2 = (lds_s2[0] + lds_s2[1]) + (lds_s2[2] + lds_s2[3]);
     const uint32_t C = lds_c[0] + lds_c[1] + lds_c[2] + lds_c[3];
     a.scales[(int64_t)m * a.scale_stride + tile] = scale_from_sum(S2, C);
-    if (a.thresholds && !a.thresh_given) a.thresholds[(int64_t)m * a.scale_stride + tile] = Delta;
+    if (!GIVEN && a.thresholds) a.thresholds[(int64_t)m * a.scale_stride + tile] = Delta;
   }
 }
 
+template <bool GIVEN>
 __global__ __launch_bounds__(kThreads) void quantize_tile_kernel(QuantArgs a) {
-  quantize_tile(a, blockIdx.x, blockIdx.y);
+  quantize_tile<GIVEN>(a, blockIdx.x, blockIdx.y);
 }
 
 // ---- exact optimal threshold by ranking (Section 3.4: the magnitudes are sorted and each one
@@ -1039,8 +989,8 @@ __global__ __launch_bounds__(kThreads) void exact_rank_marked_kernel(QuantArgs a
     marks &= ~(((1ull << kPerTile) - 1ull) << ((tile - tile0) * kPerTile));
     rank_tile<LOG2B>(a, tile, m);
     __syncthreads();                                     // its thresholds are read next
-    if constexpr (LOG2B == 12) quantize_tile(a, tile, m);
-    else quantize_buckets_of_tile<LOG2B>(a, tile, m);
+    if constexpr (LOG2B == 12) quantize_tile<true>(a, tile, m);
+    else quantize_buckets_of_tile<LOG2B, true>(a, tile, m);
     __syncthreads();                                     // LDS is free for the next tile
   }
 }
@@ -1095,17 +1045,9 @@ __global__ __launch_bounds__(kThreads) void quantize_codes_partial_kernel(QuantA
   load_tile_stream(a.g + (int64_t)m * a.g_stride, a.d, tile, v);
   double s = 0.0;
   uint32_t c = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    double sj; uint32_t cj;
-    kept_sums(v[j], D, &sj, &cj);
-    s += sj; c += cj;
-  }
+  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, code_tile(v, D, s, c));
   s = wave_sum_f64(s);
-  c = wave_sum_u32(c);
   if ((threadIdx.x % kWave) == 0) { lds_d[threadIdx.x / kWave] = s; lds_u[threadIdx.x / kWave] = c; }
-  const float Delta[4] = {D, D, D, D};
-  pack_and_store(v, Delta, a.codes + (int64_t)m * a.code_stride, tile, a.W);
   __syncthreads();
   if (threadIdx.x == 0) {
     a.part_sum[(int64_t)m * a.ntiles + tile] = (lds_d[0] + lds_d[1]) + (lds_d[2] + lds_d[3]);
@@ -1243,13 +1185,15 @@ __global__ __launch_bounds__(kThreads) void quantize_bracketed_kernel(QuantArgs 
       w |= (uint32_t)dpp_i32<kDppQuadXor2>((int)w);
       if ((t & 3) == j) mine = w;
     }
-    const int64_t widx = tile * kTileWords + (t & 3) * 64 + (t >> 2);
-    if (widx < a.W) (a.codes + (int64_t)m * a.code_stride)[widx] = mine;
   }
   const double S1 = wave_sum_f64(s1);
   const double S2 = wave_sum_f64((s2[0] + s2[1]) + (s2[2] + s2[3]));
   if (t % kWave == 0) { lds_s1[t / kWave] = S1; lds_s2[t / kWave] = S2; lds_c[t / kWave] = wave_cnt; }
-  __syncthreads();
+  __syncthreads();                                       // (before the store, which it would wait for)
+  if (bracket) {
+    const int64_t widx = tile * kTileWords + (t & 3) * 64 + (t >> 2);
+    if (widx < a.W) (a.codes + (int64_t)m * a.code_stride)[widx] = mine;
+  }
   if (t == 0) {
     const int64_t at = (int64_t)m * a.ntiles + tile;
     a.part_sum[at] = (lds_s1[0] + lds_s1[1]) + (lds_s1[2] + lds_s1[3]);
@@ -1301,19 +1245,13 @@ __global__ __launch_bounds__(kThreads) void quantize_settle_kernel(QuantArgs a) 
   }
   if (!settled) {                                        // the tiles are coded here
     s = 0.0;
-    c = 0;
+    uint32_t kept = 0;
     for (int64_t tile = tile0; tile < tile1; ++tile) {
       float v[4][4];
       load_tile_stream(g, a.d, tile, v);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        double sj; uint32_t cj;
-        kept_sums(v[j], D, &sj, &cj);
-        s += sj; c += cj;
-      }
-      const float Delta[4] = {D, D, D, D};
-      pack_and_store(v, Delta, codes, tile, a.W);
+      store_code_word(codes, tile, a.W, code_tile(v, D, s, kept));
     }
+    c = t % kWave == 0 ? kept : 0u;
   }
   s = wave_sum_f64(s);
   c = wave_sum_u32(c);
@@ -1438,8 +1376,7 @@ __device__ __forceinline__ void stochastic_codes(const StochArgs& a, const float
     w |= (uint32_t)dpp_i32<kDppQuadXor2>((int)w);
     if ((t & 3) == j) mine = w;
   }
-  const int64_t widx = tile * kTileWords + (t & 3) * 64 + (t >> 2);
-  if (widx < a.q.W) (a.q.codes + (int64_t)m * a.q.code_stride)[widx] = mine;
+  store_code_word(a.q.codes + (int64_t)m * a.q.code_stride, tile, a.q.W, mine);
 }
 
 // bucket == tile (4096, or one scale per vector with d <= 4096): one pass
@@ -1643,24 +1580,32 @@ int quantize_launch(const qa_layout* L, const float* g, int64_t g_stride, uint32
     a.thresh_given = 1;                                  // the passes below read what it wrote
   }
 
+  const auto launch_buckets = [&](auto log2b) {
+    if (a.thresh_given) hipLaunchKernelGGL((quantize_bucket_kernel<log2b(), true>), grid_tiles, block, 0, stream, a);
+    else hipLaunchKernelGGL((quantize_bucket_kernel<log2b(), false>), grid_tiles, block, 0, stream, a);
+  };
+  const auto launch_tile = [&] {
+    if (a.thresh_given) hipLaunchKernelGGL(quantize_tile_kernel<true>, grid_tiles, block, 0, stream, a);
+    else hipLaunchKernelGGL(quantize_tile_kernel<false>, grid_tiles, block, 0, stream, a);
+  };
   if (L->bucket != 0 && L->bucket <= kTile) {
     a.log2b = ilog2(L->bucket);
     a.bucket_len = L->bucket;
     switch (a.log2b) {
-      case 6: hipLaunchKernelGGL(quantize_bucket_kernel<6>, grid_tiles, block, 0, stream, a); break;
-      case 7: hipLaunchKernelGGL(quantize_bucket_kernel<7>, grid_tiles, block, 0, stream, a); break;
-      case 8: hipLaunchKernelGGL(quantize_bucket_kernel<8>, grid_tiles, block, 0, stream, a); break;
-      case 9: hipLaunchKernelGGL(quantize_bucket_kernel<9>, grid_tiles, block, 0, stream, a); break;
-      case 10: hipLaunchKernelGGL(quantize_bucket_kernel<10>, grid_tiles, block, 0, stream, a); break;
-      case 11: hipLaunchKernelGGL(quantize_bucket_kernel<11>, grid_tiles, block, 0, stream, a); break;
-      default: hipLaunchKernelGGL(quantize_tile_kernel, grid_tiles, block, 0, stream, a); break;
+      case 6: launch_buckets(std::integral_constant<int, 6>()); break;
+      case 7: launch_buckets(std::integral_constant<int, 7>()); break;
+      case 8: launch_buckets(std::integral_constant<int, 8>()); break;
+      case 9: launch_buckets(std::integral_constant<int, 9>()); break;
+      case 10: launch_buckets(std::integral_constant<int, 10>()); break;
+      case 11: launch_buckets(std::integral_constant<int, 11>()); break;
+      default: launch_tile(); break;
     }
     return launch_status();
   }
   if (L->bucket == 0 && a.ntiles == 1) {                 // the whole vector is one tile: one pass
     a.log2b = ilog2(kTile);
     a.bucket_len = kTile;
-    hipLaunchKernelGGL(quantize_tile_kernel, grid_tiles, block, 0, stream, a);
+    launch_tile();
     return launch_status();
   }
 

@@ -125,16 +125,16 @@ __device__ __forceinline__ void code_piece(const SegQuantArgs& a, const Piece& p
     w |= (uint32_t)dpp_i32<kDppQuadXor2>((int)w);
     if ((t & 3) == j) mine = w;
   }
+  s = wave_sum_f64(s);
+  c = wave_sum_u32(c);
+  if ((t % kWave) == 0) { lds_d[t / kWave] = s; lds_u[t / kWave] = c; }
+  __syncthreads();
   // words of the tile that hold coordinates of this piece
   const int64_t base = pc.tile * kTile;
   const int wlo = (int)((pc.lo - base) >> 4), whi = (int)((pc.hi - base + 15) >> 4);
   const int wl = (t & 3) * 64 + (t >> 2);
   if (wl >= wlo && wl < whi)
     a.codes[(int64_t)m * a.code_stride + pc.tile * kTileWords + wl] = mine;
-  s = wave_sum_f64(s);
-  c = wave_sum_u32(c);
-  if ((t % kWave) == 0) { lds_d[t / kWave] = s; lds_u[t / kWave] = c; }
-  __syncthreads();
   if (t == 0) {
     a.part_sum[(int64_t)m * a.seg.n_pieces + p] = (lds_d[0] + lds_d[1]) + (lds_d[2] + lds_d[3]);
     a.part_cnt[(int64_t)m * a.seg.n_pieces + p] = lds_u[0] + lds_u[1] + lds_u[2] + lds_u[3];
@@ -271,15 +271,15 @@ __global__ __launch_bounds__(kThreads) void seg_bracketed_kernel(SegQuantArgs a)
       w |= (uint32_t)dpp_i32<kDppQuadXor2>((int)w);
       if ((t & 3) == j) mine = w;
     }
-    const int64_t base = pc.tile * kTile;
-    const int wlo = (int)((pc.lo - base) >> 4), whi = (int)((pc.hi - base + 15) >> 4);
-    const int wl = (t & 3) * 64 + (t >> 2);
-    if (wl >= wlo && wl < whi) a.codes[(int64_t)m * a.code_stride + pc.tile * kTileWords + wl] = mine;
   }
   const double S1 = wave_sum_f64(s1);
   const double S2 = wave_sum_f64((s2[0] + s2[1]) + (s2[2] + s2[3]));
   if (t % kWave == 0) { lds_s1[t / kWave] = S1; lds_s2[t / kWave] = S2; lds_c[t / kWave] = wave_cnt; }
-  __syncthreads();
+  __syncthreads();                                       // (before the store, which it would wait for)
+  const int64_t base = pc.tile * kTile;
+  const int wlo = (int)((pc.lo - base) >> 4), whi = (int)((pc.hi - base + 15) >> 4);
+  const int wl = (t & 3) * 64 + (t >> 2);
+  if (wl >= wlo && wl < whi) a.codes[(int64_t)m * a.code_stride + pc.tile * kTileWords + wl] = mine;
   if (t == 0) {
     const int64_t at = (int64_t)m * a.seg.n_pieces + p;
     a.part_sum[at] = (lds_s1[0] + lds_s1[1]) + (lds_s1[2] + lds_s1[3]);
