@@ -282,6 +282,15 @@ __device__ __forceinline__ uint32_t code_word(const float (&v)[4][4], const uint
   for (int j = 3; j >= 0; --j) word = push_codes(word, v[j], kept[j]);
   return quad_transpose(clear_signs(word));
 }
+// A store that goes through the second-level cache at once instead of leaving its line there until it is evicted.
+// For words written beside a stream of reads many times as long, which late evictions disturb (2^30 components read
+// and 1/16 of that written by a kernel that does nothing else: 713 us, with this 677, without any writes 597).  Not
+// where a barrier follows in a loop (it waits for memory then), and not for read-modify-write streams, which
+// write as much as they read (the fused step's accesses 813 -> 838 us at 2^28 coordinates, 8 workers).  The indicator's
+// words lose by it too (8 x 10^8: 823 -> 847 us), the exact threshold's one pass does not change.
+__device__ __forceinline__ void store_through(uint32_t* p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 // s += x in the lanes of `lanes` alone: one vector instruction where a selected addend takes two more.
 __device__ __forceinline__ void add_in_lanes(double& s, double x, uint64_t lanes) {
   uint64_t all;

@@ -83,7 +83,7 @@ __device__ __forceinline__ void load_tile_stream(const float* __restrict__ g, in
 __device__ __forceinline__ void store_code_word(uint32_t* __restrict__ codes_m, int64_t tile, int64_t W, uint32_t word) {
   const int t = threadIdx.x;
   const int64_t widx = tile * kTileWords + (t & 3) * 64 + (t >> 2);
-  if (widx < W) codes_m[widx] = word;
+  if (widx < W) store_through(codes_m + widx, word);
 }
 
 // What threshold D keeps of the thread's elements, added to s, and of the wave's, added to wave_cnt; the code word.
@@ -201,7 +201,7 @@ __device__ __forceinline__ void bucket_sums(const double s[4], uint32_t quad_cou
 // Bound by the read of the gradient; where the last-level cache holds that, by vector instructions (about 240 per wave
 // and tile: magnitudes stay converted from the first sum to the second, which adds them under a lane mask, and fields
 // are shifted in; 398 with selects).  3 000 001 x 8 Gaussian components, buckets of 256 17.3 -> 16.0 us, 1024
-// 17.6 -> 16.3; 2^26 x 4, 512 and 1024 179 -> 177, 256 176 either way.
+// 17.6 -> 16.3.  With the words stored through the cache 2^26 x 4, 512 and 1024 178 -> 171, 256 177 -> 171.
 template <int LOG2B, bool GIVEN>                         // a.thresh_given
 __device__ __forceinline__ void quantize_buckets_of_tile(const QuantArgs& a, int64_t tile, int m) {
   __shared__ double lds_s[4 * kWaves];
@@ -279,6 +279,7 @@ __global__ __launch_bounds__(kThreads) void quantize_bucket_kernel(QuantArgs a) 
 
 // Bound by the read of the gradient; where the last-level cache holds that, by vector instructions (about 220 per
 // wave, 323 with selects): 2^20 x 16 components 12.2 -> 11.1 us, 3 000 001 x 8 19.1 -> 17.0.
+// With the words stored through the cache 2^28 x 4 721 -> 691 (6.6 TB/s).
 template <bool GIVEN>                                    // a.thresh_given
 __device__ __forceinline__ void quantize_tile(const QuantArgs& a, int64_t tile, int m) {
   __shared__ double lds_s1[kWaves];
@@ -962,7 +963,7 @@ void exact_histogram_kernel(QuantArgs a) {
       if ((lane & 3) == j) mine = w;
     }
     const int64_t widx = w0 + (j4 + (lane & 3)) * 16 + (lane >> 2);
-    if ((lane & 3) < kQuads && widx < a.W) codes[widx] = mine;
+    if ((lane & 3) < kQuads && widx < a.W) store_through(codes + widx, mine);
   }
 }
 
@@ -1192,7 +1193,7 @@ __global__ __launch_bounds__(kThreads) void quantize_bracketed_kernel(QuantArgs 
   __syncthreads();                                       // (before the store, which it would wait for)
   if (bracket) {
     const int64_t widx = tile * kTileWords + (t & 3) * 64 + (t >> 2);
-    if (widx < a.W) (a.codes + (int64_t)m * a.code_stride)[widx] = mine;
+    if (widx < a.W) store_through(a.codes + (int64_t)m * a.code_stride + widx, mine);
   }
   if (t == 0) {
     const int64_t at = (int64_t)m * a.ntiles + tile;

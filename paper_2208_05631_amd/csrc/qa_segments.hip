@@ -279,7 +279,7 @@ __global__ __launch_bounds__(kThreads) void seg_bracketed_kernel(SegQuantArgs a)
   const int64_t base = pc.tile * kTile;
   const int wlo = (int)((pc.lo - base) >> 4), whi = (int)((pc.hi - base + 15) >> 4);
   const int wl = (t & 3) * 64 + (t >> 2);
-  if (wl >= wlo && wl < whi) a.codes[(int64_t)m * a.code_stride + pc.tile * kTileWords + wl] = mine;
+  if (wl >= wlo && wl < whi) store_through(a.codes + (int64_t)m * a.code_stride + pc.tile * kTileWords + wl, mine);
   if (t == 0) {
     const int64_t at = (int64_t)m * a.seg.n_pieces + p;
     a.part_sum[at] = (lds_s1[0] + lds_s1[1]) + (lds_s1[2] + lds_s1[3]);

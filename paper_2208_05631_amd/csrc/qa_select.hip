@@ -342,7 +342,7 @@ __device__ __forceinline__ void wave_fence() {           // order of a wave's ow
 // indicator half-word, and every fourth round each lane appends one half-word's codes to the wave's stream.
 // Bound by the read of the gradient where few are marked, by that and vector instructions where most are (1380 per tile, three quarters of the issue slots;
 // with four waves per tile, 16 consecutive components per lane and a branch per component 2000).  8 workers x 10^8, 7 / 30 / 97 %
-// marked: 640 -> 570, 665 -> 592, 675 -> 640 us.
+// marked: 640 -> 570, 665 -> 592, 675 -> 640 us; with the words stored through the cache, 97 %, another 3 %.
 struct SelTileLds {
   uint2 words[kTile / 32];                               // indicator word, marked components before it
   uint32_t stream[kTileWords + 2];
@@ -452,7 +452,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   const uint32_t nwords = (K + 15) / 16;
 #pragma unroll
   for (int j = 0; j < 4; ++j)
-    if ((uint32_t)(j * kWave + lane) < nwords) out[j * kWave + lane] = lds.stream[j * kWave + lane];
+    if ((uint32_t)(j * kWave + lane) < nwords) store_through(out + j * kWave + lane, lds.stream[j * kWave + lane]);
   if (lane == 0) {
     const int64_t at = (int64_t)m * a.scale_stride + tile;
     a.counts[at] = K;
@@ -538,7 +538,7 @@ __global__ __launch_bounds__(kThreads) void quantize_selected_few_kernel(SelArgs
 // A tile's stream word w, which ends or begins inside it, to memory or to the tile's head.
 __device__ __forceinline__ void store_word(uint32_t* out, uint32_t w, uint32_t first, uint32_t bits, uint32_t* head) {
   if (w == 0 && first != 0) *head = bits;
-  else out[w] = bits;
+  else store_through(out + w, bits);
 }
 
 // S applied to a coded message: one wave per 4096-tile, lane l holds code words j*64 + l of the
