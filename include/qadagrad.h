@@ -176,10 +176,12 @@ int qa_local_grad_batched(int format, const float* A_or_vals, const int64_t* ind
  * qa_workspace_bytes(layout, QA_OP_QUANTIZE_EXACT) with QA_THRESH_EXACT (the two agree for
  * buckets of up to 4096 components).  Buckets of 2^24 components and more are read once instead of
  * twice if the vector has as many, all workers together have 2^25, and the workspace has the 8 bytes
- * per worker and 4096 coordinates that this takes, which QA_OP_QUANTIZE counts; where a sample of the
+ * per worker and 4096 coordinates that this takes; with another 128, for lists of the components inside the bracket
+ * below, it is faster.  QA_OP_QUANTIZE counts both.  Where a sample of the
  * gradient does not bracket a bucket's threshold, that bucket is read again.  12 bytes per worker and
  * 4096 coordinates plus 4 per bucket, each array rounded up to 256, are enough for the call to be
- * accepted.  Thresholds and codes do not depend on which form runs; the kept magnitudes are added in
+ * accepted.  Thresholds and codes do not depend on which form runs; one read with and without lists agree in the scales
+ * as well; with two the kept magnitudes are added in
  * another order, so a scale may differ in its last bit. */
 int qa_quantize_pack(const qa_layout* layout, const float* g, int64_t g_stride, uint32_t* codes,
                      float* scales, float* thresholds, uint32_t flags, void* ws, size_t ws_bytes,
@@ -424,7 +426,7 @@ int qa_segment_plan_host(int64_t d, int64_t n_seg, const int64_t* begin, const i
                          int64_t* table_host, size_t table_bytes, int64_t* n_pieces_out);
 
 /* Workspace of the tensor-list calls below: op = QA_OP_QUANTIZE or QA_OP_STEP (the latter only
- * needed with requant != QA_REQUANT_NONE).  For large lists QA_OP_QUANTIZE counts 8 bytes per worker
+ * needed with requant != QA_REQUANT_NONE).  For large lists QA_OP_QUANTIZE counts 136 bytes per worker
  * and piece with which long tensors are read once; 12 bytes per worker and piece plus 4 per worker and
  * tensor, each array rounded up to 256, are enough for qa_quantize_pack_segments to be accepted (same
  * thresholds and codes, a scale may differ in its last bit). */

@@ -42,7 +42,9 @@ struct QuantArgs {
   double* kept_sum;          // [M][ntiles]; before that the samples' sums
   float2* band;              // [M][nb]
   int64_t samples;           // sampled tiles per bucket (at most)
-  int64_t settle_groups;     // work-groups per bucket of the settling pass
+  int sample_every;          // one tile of so many
+  int64_t settle_groups;     // partial sums per bucket that the settling pass leaves
+  uint16_t* open;            // [M][ntiles][kWaves][kOpenSlots], null where there is no room for it
 };
 
 // Load the thread's 4 float4 groups of tile `tile`; elements at or beyond d read as +0.
@@ -1076,26 +1078,26 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void quantize_scale_finalize
 // ---- long buckets in one read -------------------------------------------------------------------
 //
 // The threshold of a long bucket is known only after all of it has been read, but a sample of its tiles
-// brackets it closely: [lo, hi] from the mean of every 64th tile and the spread between neighbouring
-// samples, five standard errors to either side (0.3 % for 10^8 Gaussian components).  The one pass over
-// the gradient then sums |v| and writes final codes for every component outside the bracket; the few
-// inside (some 10 per 4096) get the bit pattern 10, which no message holds.  When the threshold is known
-// the settling pass reads the codes, looks those components up in the gradient and replaces the
-// pattern.  Exactly the same threshold and codes as the two-read passes; the kept magnitudes are added
-// in another order.
+// brackets it closely: [lo, hi] from the mean of every 64th tile (every 32nd of buckets below 16384 tiles) and the
+// spread between neighbouring samples, four standard errors to either side (0.25 % for 10^8 Gaussian components; one
+// bracket in 15000 misses).  The one pass over the gradient then sums |v| and writes final codes for every component
+// outside the bracket; of the few inside (some 9 per 4096) it lists the float4 groups.  When the threshold is known
+// the settling pass looks those up in the gradient and joins their codes to the words.  Exactly the same threshold and
+// codes as the two-read passes; the kept magnitudes are added in another order.  A caller whose workspace
+// has no room for the lists gets the pattern 10, which no message holds, for an open component, and a settling pass that
+// reads the codes: the same sums in the same order.
 //
 // Where the sample says nothing (few tiles, a spread above 8 %, non-finite values) or the threshold falls
 // outside its bracket, the settling pass does the second read for that bucket after all.  That costs two
-// launches and the sample on top of the two-read passes (one component in 1000 non-zero, or Cauchy
-// components: 10^8 x 8 1057 -> 1122 us, 2^24 x 4 93 -> 109, 2^24 x 2 50 -> 60).
+// launches and the sample on top of the two-read passes.
 //
-// Bound by the read of the gradient (6.2 TB/s in the one pass; the settling pass, 0.25 bytes per component and a
-// cache line per open one, takes a seventh of it).  One scale per vector, Gaussian / 10 %-dense
-// Student-t / 5 %-dense Laplace components, two reads -> one: 10^8 x 8 1039 -> 708 / 649 / 635 us;
-// 10^8 x 1 150 -> 111 / 103 / 101; 2^24 x 4 91 -> 76 / 68 / 66; 2^24 x 2 47.5 -> 47.5 / 42 / 41.
-// Below that the two further launches cost more than the second read (2^24 x 1 27.4 -> 31), and buckets
+// Bound by the read of the gradient (6.4 TB/s in the one pass).  What an open component costs is a cache line read and,
+// if it is kept, one changed: hence the four standard errors (five: 2^24 x 4 Gaussian components 97 us for 78, with lists
+// that overflow here and there) and the denser sample where the bucket gives few (78 for 86; 10^8 x 8 Student-t with
+// it 605 for 595).
+// Below 2^25 components the two further launches cost more than the second read (2^24 x 1 27.4 -> 31), and buckets
 // of fewer than 4096 tiles give too few samples (2^22: 343 -> 376 at 2^26 x 4 sparse components).
-constexpr int kSampleEvery = 64;
+constexpr int64_t kManyTiles = 16384;
 constexpr float kWidestBand = 0.08f;
 
 // Full tiles of bucket k.
@@ -1108,9 +1110,9 @@ __global__ __launch_bounds__(kThreads) void quantize_sample_kernel(QuantArgs a) 
   __shared__ double lds_d[kWaves];
   const int64_t k = blockIdx.x / a.samples, i = blockIdx.x % a.samples;
   const int m = blockIdx.y;
-  if (i >= whole_tiles(a, k) / kSampleEvery) return;
-  // one tile of every 64, not always the same one of them
-  const int64_t tile = k * a.tiles_per_bucket + i * kSampleEvery + (i * 29) % kSampleEvery;
+  if (i >= whole_tiles(a, k) / a.sample_every) return;
+  // one tile of every 64 or 32, not always the same one of them
+  const int64_t tile = k * a.tiles_per_bucket + i * a.sample_every + (i * 29) % a.sample_every;
   float v[4][4];
   load_tile(a.g + (int64_t)m * a.g_stride, a.d, tile, v);
   double s = 0.0;
@@ -1127,7 +1129,7 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void quantize_band_kernel(Qu
   const int64_t k = blockIdx.x;
   const int m = blockIdx.y;
   const double* part = a.kept_sum + ((int64_t)m * a.nb + k) * a.samples;
-  const int64_t n = whole_tiles(a, k) / kSampleEvery;
+  const int64_t n = whole_tiles(a, k) / a.sample_every;
   double sum = 0.0, diff = 0.0;
   for (int64_t i = threadIdx.x; i < n; i += kThreads) {
     const double v = part[i], w = i + 1 < n ? part[i + 1] : v;
@@ -1140,7 +1142,7 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void quantize_band_kernel(Qu
     float2 band = make_float2(-1.0f, -1.0f);               // no bracket
     if (n >= 16) {
       // neighbouring samples differ by two independent deviations; trends along the vector drop out
-      const double mean = sum / (double)n, rel = 5.0 * sqrt(diff / (2.0 * (double)(n - 1)) / (double)n) / mean + 1e-6;
+      const double mean = sum / (double)n, rel = 4.0 * sqrt(diff / (2.0 * (double)(n - 1)) / (double)n) / mean + 1e-6;
       const double mid = (double)a.thr_coef * mean / (double)kTile;
       if (mean > 0.0 && rel < (double)kWidestBand && mid < 1e38)
         band = make_float2((float)(mid * (1.0 - rel)), (float)(mid * (1.0 + rel)));
@@ -1149,7 +1151,9 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void quantize_band_kernel(Qu
   }
 }
 
-// The one pass: tile sums of |v|; with a bracket also codes, sums and counts of what is certainly kept.
+// The one pass: tile sums of |v|; with a bracket also codes, sums and counts of what is certainly kept, and the open
+// components, LISTED or marked.
+template <bool LISTED>
 __global__ __launch_bounds__(kThreads) void quantize_bracketed_kernel(QuantArgs a) {
   __shared__ double lds_s1[kWaves];
   __shared__ double lds_s2[kWaves];
@@ -1157,77 +1161,145 @@ __global__ __launch_bounds__(kThreads) void quantize_bracketed_kernel(QuantArgs 
   const int64_t tile = blockIdx.x;
   const int m = blockIdx.y;
   const int t = threadIdx.x;
+  const int64_t at = (int64_t)m * a.ntiles + tile;
   const float2 band = a.band[(int64_t)m * a.nb + tile / a.tiles_per_bucket];
   float v[4][4];
   load_tile_stream(a.g + (int64_t)m * a.g_stride, a.d, tile, v);
-  double s1 = 0.0, s2[4] = {0.0, 0.0, 0.0, 0.0};
-  uint32_t wave_cnt = 0, mine = 0;
-  const bool bracket = band.x >= 0.0f;
-  // in the order of quantize_abs_partial_kernel: the threshold is the same number in both forms
+  double s1 = 0.0, s2 = 0.0;
+  if (!(band.x >= 0.0f)) {                               // uniform; the settling pass codes the tile
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) s1 += (double)fabsf(v[j][e]);
-  if (bracket) {
+      for (int e = 0; e < 4; ++e) s1 += (double)fabsf(v[j][e]);
+    const double S1 = block_sum_f64(s1, lds_s1);
+    if (t == 0) a.part_sum[at] = S1;
+    return;
+  }
+  uint32_t wave_cnt = 0;
+  uint64_t open[4][4];
+  uint32_t word = code_outside(v, band, s1, s2, wave_cnt, open);
+  if (!LISTED) {
+    uint32_t marks = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      uint32_t b = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float av = fabsf(v[j][e]);
-        const bool keep = av > band.y;
-        wave_cnt += (uint32_t)__popcll(__ballot(keep));
-        s2[j] += (double)(keep ? av : 0.0f);
-        const uint32_t pat = 1u | ((__float_as_uint(v[j][e]) >> 30) & 2u);
-        b |= (keep ? pat : (av > band.x ? 2u : 0u)) << (2 * e);
-      }
-      uint32_t w = b << (8 * (t & 3));
-      w |= (uint32_t)dpp_i32<kDppQuadXor1>((int)w);
-      w |= (uint32_t)dpp_i32<kDppQuadXor2>((int)w);
-      if ((t & 3) == j) mine = w;
+    for (int i = 0; i < 16; ++i) {
+      const float av = fabsf(v[i / 4][i % 4]);
+      marks |= av > band.x && !(av > band.y) ? 2u << (2 * i) : 0u;
     }
+    word |= quad_transpose(marks);
   }
-  const double S1 = wave_sum_f64(s1);
-  const double S2 = wave_sum_f64((s2[0] + s2[1]) + (s2[2] + s2[3]));
+  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, word);
+  if (LISTED) wave_cnt |= list_open(open, a.open + (at * kWaves + t / kWave) * kOpenSlots) << 16;
+  const double S1 = wave_sum_f64(s1), S2 = wave_sum_f64(s2);
   if (t % kWave == 0) { lds_s1[t / kWave] = S1; lds_s2[t / kWave] = S2; lds_c[t / kWave] = wave_cnt; }
-  __syncthreads();                                       // (before the store, which it would wait for)
-  if (bracket) {
-    const int64_t widx = tile * kTileWords + (t & 3) * 64 + (t >> 2);
-    if (widx < a.W) store_through(a.codes + (int64_t)m * a.code_stride + widx, mine);
-  }
+  __syncthreads();
   if (t == 0) {
-    const int64_t at = (int64_t)m * a.ntiles + tile;
     a.part_sum[at] = (lds_s1[0] + lds_s1[1]) + (lds_s1[2] + lds_s1[3]);
     a.kept_sum[at] = (lds_s2[0] + lds_s2[1]) + (lds_s2[2] + lds_s2[3]);
-    a.part_cnt[at] = lds_c[0] + lds_c[1] + lds_c[2] + lds_c[3];
+    a.part_cnt[at] = tile_counts(lds_c);
   }
 }
 
-// The settling pass: eight tiles per work-group, thread t holds word t of each.  Its sums and counts of all
-// that these tiles keep take the place of the tile sums of |v|, which the threshold has been made of: [M][nb * settle_groups]
-// sums, then as many counts.
-__global__ __launch_bounds__(kThreads) void quantize_settle_kernel(QuantArgs a) {
+// A tile read again: its codes for threshold D, and what they keep per wave.
+__device__ __forceinline__ void code_again(const QuantArgs& a, int m, int64_t tile, float D, double* wave_sum,
+                                           uint32_t* wave_cnt) {
+  float v[4][4];
+  load_tile_stream(a.g + (int64_t)m * a.g_stride, a.d, tile, v);
+  double s = 0.0;
+  uint32_t c = 0;
+  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, code_tile(v, D, s, c));
+  s = wave_sum_f64(s);
+  if (threadIdx.x % kWave == 0) { wave_sum[threadIdx.x / kWave] = s; wave_cnt[threadIdx.x / kWave] = c; }
+}
+// The settling pass leaves a sum and a count of all that eight tiles keep, in the place of the tile sums of |v|, which
+// the threshold has been made of: [M][nb * settle_groups] sums, then as many counts.  Called by the first wave, lane l with
+// tile l of the group's eights and its four waves' sums and counts, or all of it in the first ones' place; `live`: it has such an eight.
+struct TileKept {
+  double sum[kWaves];
+  uint32_t cnt[kWaves];
+};
+__device__ __forceinline__ void settled_parts(const QuantArgs& a, int m, int64_t part, bool live, bool again, const TileKept& k) {
+  double s = again ? (k.sum[0] + k.sum[1]) + (k.sum[2] + k.sum[3]) : k.sum[0];
+  uint32_t c = again ? k.cnt[0] + k.cnt[1] + k.cnt[2] + k.cnt[3] : k.cnt[0];
+  s += dpp_f64<kDppQuadXor1>(s);        c += (uint32_t)dpp_i32<kDppQuadXor1>((int)c);
+  s += dpp_f64<kDppQuadXor2>(s);        c += (uint32_t)dpp_i32<kDppQuadXor2>((int)c);
+  s += dpp_f64<kDppRowHalfMirror>(s);   c += (uint32_t)dpp_i32<kDppRowHalfMirror>((int)c);
+  if (live && threadIdx.x % 8 == 0) {
+    const int64_t groups = a.nb * a.settle_groups, at = (int64_t)m * groups + part;
+    a.part_sum[at] = s;
+    reinterpret_cast<uint32_t*>(a.part_sum + gridDim.y * groups)[at] = c;
+  }
+}
+
+// With lists: a wave per eight tiles, eight lanes per tile, no look at the codes.  Tiles that have to be coded again are
+// left to the whole work-group.  Bound by latency where few components are open (10^8 x 8 10 %-dense Student-t 76 us
+// with marks, 26 with lists), by the lines that they touch where many are.
+__global__ __launch_bounds__(kThreads) void quantize_settle_listed_kernel(QuantArgs a) {
+  __shared__ TileKept kept[kWaves * kSettleTiles];
+  __shared__ uint32_t lds_again[kWaves];
+  const int t = threadIdx.x, lane = t % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int64_t per_bucket = (a.settle_groups + kWaves - 1) / kWaves;
+  const int64_t k = blockIdx.x / per_bucket, part0 = (blockIdx.x % per_bucket) * kWaves;
+  const int m = blockIdx.y;
+  const int64_t tile0 = k * a.tiles_per_bucket + part0 * kSettleTiles;
+  const int64_t bucket1 = (k + 1) * a.tiles_per_bucket < a.ntiles ? (k + 1) * a.tiles_per_bucket : a.ntiles;
+  const int own = wave * kSettleTiles + lane / 8;        // of the 32 tiles
+  const int64_t tile = tile0 + own, at = (int64_t)m * a.ntiles + tile;
+  const bool live = tile < bucket1;
+  const float D = a.thr_ws[(int64_t)m * a.nb + k];
+  const float2 band = a.band[(int64_t)m * a.nb + k];
+  const uint32_t counts = live ? a.part_cnt[at] : 0u;
+  const double certain = live ? a.kept_sum[at] : 0.0;
+  const bool again = live && (!bracket_held(band, D) || too_many_open(counts));
+  double s = 0.0;
+  uint32_t c = 0;
+  if (live && !again) {
+    const uint32_t list = (lane & 7) >> 1, n = (counts >> (16 + 4 * list)) & 15u;
+    settle_listed<4>(a.open + (at * kWaves + list) * kOpenSlots, (uint32_t)lane & 1u, 2u, n,
+                     a.g + (int64_t)m * a.g_stride + tile * kTile, a.d - tile * kTile, band, D,
+                     a.codes + (int64_t)m * a.code_stride + tile * kTileWords, s, c);
+  }
+  s += dpp_f64<kDppQuadXor1>(s);        c += (uint32_t)dpp_i32<kDppQuadXor1>((int)c);
+  s += dpp_f64<kDppQuadXor2>(s);        c += (uint32_t)dpp_i32<kDppQuadXor2>((int)c);
+  s += dpp_f64<kDppRowHalfMirror>(s);   c += (uint32_t)dpp_i32<kDppRowHalfMirror>((int)c);
+  const uint64_t again_lanes = __ballot(again);          // eight equal bits per tile
+  if ((lane & 7) == 0 && !again) {
+    kept[own].sum[0] = live ? certain + s : 0.0;
+    kept[own].cnt[0] = live ? c + (counts & 0xFFFFu) : 0u;
+  }
+  if (lane == 0) {
+    uint32_t tiles = 0;
+#pragma unroll
+    for (int u = 0; u < kSettleTiles; ++u) tiles |= (uint32_t)(again_lanes >> (8 * u) & 1ull) << u;
+    lds_again[wave] = tiles << (wave * kSettleTiles);
+  }
+  __syncthreads();
+  const uint32_t repeat = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds_again[0] | lds_again[1] | lds_again[2] | lds_again[3]));
+  for (uint32_t left = repeat; left; left &= left - 1u) {  // uniform
+    const int u = __ffs((int)left) - 1;
+    code_again(a, m, tile0 + u, D, kept[u].sum, kept[u].cnt);
+  }
+  if (repeat) __syncthreads();
+  if (wave == 0)
+    settled_parts(a, m, k * a.settle_groups + part0 + lane / 8, lane < kWaves * kSettleTiles && part0 + lane / 8 < a.settle_groups,
+                  lane < kWaves * kSettleTiles && (repeat >> (lane & 31) & 1u), kept[lane & 31]);
+}
+
+// With marks: eight tiles per work-group, thread t holds word t of each.  The same sums in the same order.
+__global__ __launch_bounds__(kThreads) void quantize_settle_marked_kernel(QuantArgs a) {
   __shared__ SettleLds lds;
-  __shared__ double lds_d[kWaves];
-  __shared__ uint32_t lds_u[kWaves];
+  __shared__ TileKept kept[kSettleTiles];
   const int64_t k = blockIdx.x / a.settle_groups, part = blockIdx.x % a.settle_groups;
   const int m = blockIdx.y;
   const int t = threadIdx.x;
   const int64_t tile0 = k * a.tiles_per_bucket + part * kSettleTiles;
   const int64_t bucket_end = (k + 1) * a.tiles_per_bucket < a.ntiles ? (k + 1) * a.tiles_per_bucket : a.ntiles;
   const int64_t tile1 = tile0 + kSettleTiles < bucket_end ? tile0 + kSettleTiles : bucket_end;
+  const uint32_t here = tile1 > tile0 ? (1u << (tile1 - tile0)) - 1u : 0u;   // (the last bucket may be shorter)
   const float D = a.thr_ws[(int64_t)m * a.nb + k];
-  const float2 band = a.band[(int64_t)m * a.nb + k];
-  const float* g = a.g + (int64_t)m * a.g_stride;
   uint32_t* codes = a.codes + (int64_t)m * a.code_stride;
-  double s = 0.0;
-  uint32_t c = 0;
-  bool settled = band.x >= 0.0f && D >= band.x && D <= band.y;
-  if (settled) {
-    if (t < kSettleTiles && tile0 + t < tile1) {         // what the one pass has kept for certain
-      s = a.kept_sum[(int64_t)m * a.ntiles + tile0 + t];
-      c = a.part_cnt[(int64_t)m * a.ntiles + tile0 + t];
-    }
+  uint32_t repeat = here;
+  if (bracket_held(a.band[(int64_t)m * a.nb + k], D)) {
     uint32_t w[kSettleTiles];
 #pragma unroll
     for (int u = 0; u < kSettleTiles; ++u) {
@@ -1235,34 +1307,32 @@ __global__ __launch_bounds__(kThreads) void quantize_settle_kernel(QuantArgs a) 
       w[u] = tile0 + u < tile1 && widx < a.W ? codes[widx] : 0u;
     }
     bool changed;
-    settled = settle_words(g, tile0, D, w, lds, s, c, &changed);
-    if (settled && changed) {
+    repeat = (uint32_t)__builtin_amdgcn_readfirstlane(
+        (int)settle_words(a.g + (int64_t)m * a.g_stride, tile0, D, w, lds, &changed));
+    if (changed) {
 #pragma unroll
       for (int u = 0; u < kSettleTiles; ++u) {
         const int64_t widx = (tile0 + u) * kTileWords + t;
         if (tile0 + u < tile1 && widx < a.W) codes[widx] = w[u];
       }
     }
-  }
-  if (!settled) {                                        // the tiles are coded here
-    s = 0.0;
-    uint32_t kept = 0;
-    for (int64_t tile = tile0; tile < tile1; ++tile) {
-      float v[4][4];
-      load_tile_stream(g, a.d, tile, v);
-      store_code_word(codes, tile, a.W, code_tile(v, D, s, kept));
+    if (t < kSettleTiles && !(repeat >> t & 1u)) {
+      const bool live = tile0 + t < tile1;
+      const int64_t at = (int64_t)m * a.ntiles + tile0 + t;
+      kept[t].sum[0] = live ? a.kept_sum[at] + lds.sum[t] : 0.0;
+      kept[t].cnt[0] = live ? (a.part_cnt[at] & 0xFFFFu) + lds.count[t] : 0u;
     }
-    c = t % kWave == 0 ? kept : 0u;
+  } else if (t < kSettleTiles && !(here >> t & 1u)) {
+    kept[t].sum[0] = 0.0;
+    kept[t].cnt[0] = 0u;
   }
-  s = wave_sum_f64(s);
-  c = wave_sum_u32(c);
-  if (t % kWave == 0) { lds_d[t / kWave] = s; lds_u[t / kWave] = c; }
+  if (repeat) __syncthreads();                           // (a word of a tile that is coded again may have been rewritten)
+  for (uint32_t left = repeat; left; left &= left - 1u) {
+    const int u = __ffs((int)left) - 1;
+    code_again(a, m, tile0 + u, D, kept[u].sum, kept[u].cnt);
+  }
   __syncthreads();
-  if (t == 0) {
-    const int64_t groups = a.nb * a.settle_groups, at = (int64_t)m * groups + blockIdx.x;
-    a.part_sum[at] = (lds_d[0] + lds_d[1]) + (lds_d[2] + lds_d[3]);
-    reinterpret_cast<uint32_t*>(a.part_sum + gridDim.y * groups)[at] = lds_u[0] + lds_u[1] + lds_u[2] + lds_u[3];
-  }
+  if (t < kWave) settled_parts(a, m, blockIdx.x, t < kSettleTiles, repeat >> (t & 7) & 1u, kept[t & 7]);
 }
 
 __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void quantize_settled_scale_kernel(QuantArgs a) {
@@ -1501,11 +1571,18 @@ size_t quantize_workspace_bytes(const qa_layout* L) {
 // What the one-read form needs on top of it, 0 where it is not taken: buckets of fewer than 4096 tiles
 // (64 samples), or less than 2^25 components in all.
 constexpr int64_t kOneReadBucketTiles = 4096, kOneReadTiles = 8192;
-size_t one_read_bytes(const qa_layout* L) {
+static size_t one_read_sums_bytes(const qa_layout* L) {
   const int64_t nt = tiles_of(L->d), nb = buckets_of(L->d, L->bucket);
   const int64_t per = L->bucket ? L->bucket / kTile : nt;
   if (per < kOneReadBucketTiles || nt < kOneReadBucketTiles || nt * L->M < kOneReadTiles) return 0;
   return align256((size_t)L->M * nt * sizeof(double)) + align256((size_t)L->M * nb * sizeof(float2));
+}
+static size_t open_lists_bytes(const qa_layout* L) {
+  return (size_t)L->M * tiles_of(L->d) * kWaves * kOpenSlots * sizeof(uint16_t);
+}
+size_t one_read_bytes(const qa_layout* L) {
+  const size_t sums = one_read_sums_bytes(L);
+  return sums ? sums + open_lists_bytes(L) : 0;
 }
 
 // Where the multi-pass quantizer keeps its per-tile sums, counts and per-bucket thresholds inside
@@ -1619,24 +1696,29 @@ int quantize_launch(const qa_layout* L, const float* g, int64_t g_stride, uint32
   a.log2b = L->bucket ? ilog2(L->bucket) : 0;
   const dim3 grid_buckets((unsigned)a.nb, (unsigned)L->M);
 
-  if (!a.thresh_given && !(flags & kQuantAbsPartialsGiven) && one_read_bytes(L) != 0 &&
-      ws_bytes >= need + one_read_bytes(L)) {
+  const size_t one_read_sums = one_read_sums_bytes(L);
+  if (!a.thresh_given && !(flags & kQuantAbsPartialsGiven) && one_read_sums != 0 && ws_bytes >= need + one_read_sums) {
     char* p = static_cast<char*>(ws) + need;
     a.kept_sum = reinterpret_cast<double*>(p);
     a.band = reinterpret_cast<float2*>(p + align256((size_t)L->M * a.ntiles * sizeof(double)));
-    // the tiles that the vector has: a bucket may be nominally far longer, and the settling pass leaves a
-    // sum and a count per work-group of its grid in the place of the tile sums
+    if (ws_bytes >= need + one_read_sums + open_lists_bytes(L)) a.open = reinterpret_cast<uint16_t*>(p + one_read_sums);
+    // the tiles that the vector has: a bucket may be nominally far longer, and the settling pass leaves its
+    // sums and counts in the place of the tile sums
     if (a.tiles_per_bucket > a.ntiles) a.tiles_per_bucket = a.ntiles;
-    a.samples = a.tiles_per_bucket / kSampleEvery;
+    a.sample_every = a.tiles_per_bucket >= kManyTiles ? 64 : 32;
+    a.samples = a.tiles_per_bucket / a.sample_every;
     a.settle_groups = (a.tiles_per_bucket + kSettleTiles - 1) / kSettleTiles;
     if (a.nb * a.samples <= 0x7fffffffLL && a.nb * a.settle_groups <= 0x7fffffffLL) {
       const dim3 grid_samples((unsigned)(a.nb * a.samples), (unsigned)L->M);
-      const dim3 grid_settle((unsigned)(a.nb * a.settle_groups), (unsigned)L->M);
+      const dim3 grid_settle((unsigned)(a.nb * (a.open ? (a.settle_groups + kWaves - 1) / kWaves : a.settle_groups)),
+                             (unsigned)L->M);
       hipLaunchKernelGGL(quantize_sample_kernel, grid_samples, block, 0, stream, a);
       hipLaunchKernelGGL(quantize_band_kernel, grid_buckets, block, 0, stream, a);
-      hipLaunchKernelGGL(quantize_bracketed_kernel, grid_tiles, block, 0, stream, a);
+      if (a.open) hipLaunchKernelGGL(quantize_bracketed_kernel<true>, grid_tiles, block, 0, stream, a);
+      else hipLaunchKernelGGL(quantize_bracketed_kernel<false>, grid_tiles, block, 0, stream, a);
       hipLaunchKernelGGL(quantize_threshold_finalize_kernel, grid_buckets, block, 0, stream, a);
-      hipLaunchKernelGGL(quantize_settle_kernel, grid_settle, block, 0, stream, a);
+      if (a.open) hipLaunchKernelGGL(quantize_settle_listed_kernel, grid_settle, block, 0, stream, a);
+      else hipLaunchKernelGGL(quantize_settle_marked_kernel, grid_settle, block, 0, stream, a);
       hipLaunchKernelGGL(quantize_settled_scale_kernel, grid_buckets, block, 0, stream, a);
       return launch_status();
     }

@@ -30,6 +30,7 @@ struct SegQuantArgs {
   // one-read form, null without it
   double* kept_sum;         // [M][n_pieces]; before that the samples
   float2* band;             // [M][n_seg]
+  uint16_t* open;           // [M][n_pieces][kWaves][kOpenSlots]
 };
 
 // The thread's 4 float4 groups f = j*256 + t of the piece's tile; elements outside [lo, hi)
@@ -167,12 +168,12 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void seg_scale_finalize_kern
 
 // ---- long tensors in one read -------------------------------------------------------------------
 //
-// As for long buckets of a plain vector: every 64th piece of a tensor of at least 1024 pieces gives a
-// bracket around the tensor's threshold (five standard errors, at most 8 % to either side),
-// the one pass writes final codes outside the bracket, the pattern 10 inside it and the piece sums of
-// |v|, and the settling pass looks the open components up once the threshold is known.  Of tensors
+// As for long buckets of a plain vector: every 32nd piece of a tensor of at least 1024 pieces gives a
+// bracket around the tensor's threshold (four standard errors, at most 8 % to either side),
+// the one pass writes final codes outside the bracket and the piece sums of |v| and lists the open float4 groups,
+// and the settling pass looks these up once the threshold is known.  Of tensors
 // without a bracket, or whose threshold falls outside it, it reads the gradient again.
-constexpr int kSegSampleEvery = 64;
+constexpr int kSegSampleEvery = 32;
 constexpr int64_t kSegLong = 1024;
 constexpr double kSegWidestBand = 0.08;
 
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void seg_band_kernel(SegQuan
   if (threadIdx.x == 0) {
     float2 band = make_float2(-1.0f, -1.0f);
     if (n >= 12.0 && nd >= 8.0) {
-      const double mean = sum / n, rel = 5.0 * sqrt(diff / (2.0 * nd) / n) / mean + 1e-6;
+      const double mean = sum / n, rel = 4.0 * sqrt(diff / (2.0 * nd) / n) / mean + 1e-6;
       const double mid = (double)a.thr_coef * mean / (double)kTile;
       if (mean > 0.0 && rel < kSegWidestBand && mid < 1e38)
         band = make_float2((float)(mid * (1.0 - rel)), (float)(mid * (1.0 + rel)));
@@ -237,133 +238,84 @@ __global__ __launch_bounds__(kThreads) void seg_bracketed_kernel(SegQuantArgs a)
   const int t = threadIdx.x;
   const int64_t p = blockIdx.x;
   const int m = blockIdx.y;
+  const int64_t at = (int64_t)m * a.seg.n_pieces + p;
   const Piece pc = load_piece(a.seg, p, a.d);
   const float2 band = a.band[(int64_t)m * a.seg.n_seg + pc.seg];
   float v[4][4];
   load_piece_values(a.g + (int64_t)m * a.g_stride, pc, v);
-  double s1 = 0.0, s2[4] = {0.0, 0.0, 0.0, 0.0};
-  uint32_t wave_cnt = 0, mine = 0;
-  // in the order of seg_abs_partial_kernel: the threshold is the same number in both forms
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) s1 += (double)fabsf(v[j][e]);
+  double s1 = 0.0, s2 = 0.0;
   if (!(band.x >= 0.0f)) {                               // uniform; the settling pass codes the piece
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s1 += (double)fabsf(v[j][e]);
     const double S1 = block_sum_f64(s1, lds_s1);
-    if (t == 0) a.part_sum[(int64_t)m * a.seg.n_pieces + p] = S1;
+    if (t == 0) a.part_sum[at] = S1;
     return;
   }
-  {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      uint32_t b = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float av = fabsf(v[j][e]);
-        const bool keep = av > band.y;
-        wave_cnt += (uint32_t)__popcll(__ballot(keep));
-        s2[j] += (double)(keep ? av : 0.0f);
-        const uint32_t pat = 1u | ((__float_as_uint(v[j][e]) >> 30) & 2u);
-        b |= (keep ? pat : (av > band.x ? 2u : 0u)) << (2 * e);
-      }
-      uint32_t w = b << (8 * (t & 3));
-      w |= (uint32_t)dpp_i32<kDppQuadXor1>((int)w);
-      w |= (uint32_t)dpp_i32<kDppQuadXor2>((int)w);
-      if ((t & 3) == j) mine = w;
-    }
-  }
-  const double S1 = wave_sum_f64(s1);
-  const double S2 = wave_sum_f64((s2[0] + s2[1]) + (s2[2] + s2[3]));
-  if (t % kWave == 0) { lds_s1[t / kWave] = S1; lds_s2[t / kWave] = S2; lds_c[t / kWave] = wave_cnt; }
-  __syncthreads();                                       // (before the store, which it would wait for)
+  // in the order of seg_abs_partial_kernel: the threshold is the same number in both forms
+  uint32_t wave_cnt = 0;
+  uint64_t open[4][4];
+  const uint32_t word = code_outside(v, band, s1, s2, wave_cnt, open);
   const int64_t base = pc.tile * kTile;
   const int wlo = (int)((pc.lo - base) >> 4), whi = (int)((pc.hi - base + 15) >> 4);
   const int wl = (t & 3) * 64 + (t >> 2);
-  if (wl >= wlo && wl < whi) store_through(a.codes + (int64_t)m * a.code_stride + pc.tile * kTileWords + wl, mine);
+  if (wl >= wlo && wl < whi) store_through(a.codes + (int64_t)m * a.code_stride + pc.tile * kTileWords + wl, word);
+  wave_cnt |= list_open(open, a.open + (at * kWaves + t / kWave) * kOpenSlots) << 16;
+  const double S1 = wave_sum_f64(s1), S2 = wave_sum_f64(s2);
+  if (t % kWave == 0) { lds_s1[t / kWave] = S1; lds_s2[t / kWave] = S2; lds_c[t / kWave] = wave_cnt; }
+  __syncthreads();
   if (t == 0) {
-    const int64_t at = (int64_t)m * a.seg.n_pieces + p;
     a.part_sum[at] = (lds_s1[0] + lds_s1[1]) + (lds_s1[2] + lds_s1[3]);
     a.kept_sum[at] = (lds_s2[0] + lds_s2[1]) + (lds_s2[2] + lds_s2[3]);
-    a.part_cnt[at] = lds_c[0] + lds_c[1] + lds_c[2] + lds_c[3];
+    a.part_cnt[at] = tile_counts(lds_c);
   }
 }
 
-// Did the sample's bracket hold the threshold?  (NaN compares false.)
-__device__ __forceinline__ bool bracketed(float2 band, float D) {
-  return band.x >= 0.0f && D >= band.x && D <= band.y;
-}
-
-// Eight consecutive pieces per work-group, thread t holds word t of each piece's tile.  What a run of
-// pieces of one tensor keeps goes to the run's first slot of part_sum / part_cnt, zeros to the others.
+// Eight consecutive pieces per work-group, 32 lanes per listed piece; the others are coded one by one.  What a piece
+// keeps goes to its slots of part_sum / part_cnt.
 __global__ __launch_bounds__(kThreads) void seg_settle_kernel(SegQuantArgs a) {
-  __shared__ SettleLds lds;
   __shared__ double lds_d[kWaves];
   __shared__ uint32_t lds_u[kWaves];
-  const int t = threadIdx.x;
+  __shared__ uint32_t lds_again[kSettleTiles];
+  const int t = threadIdx.x, lane = t & 31;
   const int m = blockIdx.y;
   const int64_t piece0 = (int64_t)blockIdx.x * kSettleTiles;
-  const float* g = a.g + (int64_t)m * a.g_stride;
-  uint32_t* codes = a.codes + (int64_t)m * a.code_stride;
-  const int64_t row = (int64_t)m * a.seg.n_pieces;
-  int u0 = 0;
-  while (u0 < kSettleTiles && piece0 + u0 < a.seg.n_pieces) {
-    const Piece head = load_piece(a.seg, piece0 + u0, a.d);
-    const int64_t seg = head.seg;
-    const float D = a.thr_ws[(int64_t)m * a.seg.n_seg + seg];
-    int64_t p0, p1;
-    piece_range(a.seg, seg, &p0, &p1);
-    int u1 = u0 + 1;                                     // the run of this tensor's pieces
-    const int64_t left = p1 - piece0;
-    if (left > u1) u1 = left < kSettleTiles ? (int)left : kSettleTiles;
-    const auto code_run = [&] {
-      for (int u = u0; u < u1; ++u) {
-        code_piece(a, load_piece(a.seg, piece0 + u, a.d), piece0 + u, m, D, lds_d, lds_u);
-        __syncthreads();                                 // LDS is free again
-      }
-      u0 = u1;
-    };
-    if (!bracketed(a.band[(int64_t)m * a.seg.n_seg + seg], D)) {
-      code_run();
-      continue;
+  const int64_t p = piece0 + t / 32, row = (int64_t)m * a.seg.n_pieces, at = row + p;
+  bool again = false, listed = false;
+  double s = 0.0, kept = 0.0;
+  uint32_t c = 0;
+  if (p < a.seg.n_pieces) {
+    const Piece pc = load_piece(a.seg, p, a.d);
+    const float D = a.thr_ws[(int64_t)m * a.seg.n_seg + pc.seg];
+    const float2 band = a.band[(int64_t)m * a.seg.n_seg + pc.seg];
+    const uint32_t counts = a.part_cnt[at];
+    kept = a.kept_sum[at];
+    again = !bracket_held(band, D) || too_many_open(counts);   // (without a bracket the piece has no counts)
+    listed = !again;
+    if (listed) {
+      const uint32_t list = lane >> 3, n = (counts >> (16 + 4 * list)) & 15u;
+      settle_listed<2>(a.open + (at * kWaves + list) * kOpenSlots, (uint32_t)lane & 7u, 8u, n,
+                       a.g + (int64_t)m * a.g_stride + pc.tile * kTile, pc.hi - pc.tile * kTile, band, D,
+                       a.codes + (int64_t)m * a.code_stride + pc.tile * kTileWords, s, c);
+      if (lane == 0) c += counts & 0xFFFFu;
     }
-    // the run's pieces lie in consecutive tiles
-    const int64_t tile0 = head.tile - u0, ntiles = (a.d + kTile - 1) / kTile;
-    const int64_t word_lo = a.seg.begin[seg] >> 4, word_hi = (a.seg.begin[seg] + a.seg.length[seg] + 15) >> 4;
-    double s = 0.0;
-    uint32_t c = 0;
-    uint32_t w[kSettleTiles];
-    const auto inside = [&](int u, int64_t at) {
-      return u >= u0 && u < u1 && tile0 + u < ntiles && at >= word_lo && at < word_hi && at * 16 < a.d;
-    };
-#pragma unroll
-    for (int u = 0; u < kSettleTiles; ++u) {
-      const int64_t at = (tile0 + u) * kTileWords + t;
-      w[u] = inside(u, at) ? codes[at] : 0u;
-    }
-    bool changed;
-    if (!settle_words(g, tile0, D, w, lds, s, c, &changed)) {
-      code_run();
-      continue;
-    }
-    if (t >= u0 && t < u1) { s += a.kept_sum[row + piece0 + t]; c += a.part_cnt[row + piece0 + t]; }
-    if (changed) {
-#pragma unroll
-      for (int u = 0; u < kSettleTiles; ++u) {
-        const int64_t at = (tile0 + u) * kTileWords + t;
-        if (inside(u, at)) codes[at] = w[u];
-      }
-    }
-    s = wave_sum_f64(s);
-    c = wave_sum_u32(c);
-    __syncthreads();                                     // the slots have been read, LDS is free
-    if (t % kWave == 0) { lds_d[t / kWave] = s; lds_u[t / kWave] = c; }
-    __syncthreads();
-    if (t >= u0 && t < u1) {
-      a.part_sum[row + piece0 + t] = t == u0 ? (lds_d[0] + lds_d[1]) + (lds_d[2] + lds_d[3]) : 0.0;
-      a.part_cnt[row + piece0 + t] = t == u0 ? lds_u[0] + lds_u[1] + lds_u[2] + lds_u[3] : 0u;
-    }
-    __syncthreads();                                     // the waves' sums have been read: the next run may write its own
-    u0 = u1;
+  }
+  s += dpp_f64<kDppQuadXor1>(s);          c += (uint32_t)dpp_i32<kDppQuadXor1>((int)c);
+  s += dpp_f64<kDppQuadXor2>(s);          c += (uint32_t)dpp_i32<kDppQuadXor2>((int)c);
+  s += dpp_f64<kDppRowHalfMirror>(s);     c += (uint32_t)dpp_i32<kDppRowHalfMirror>((int)c);
+  s += dpp_f64<kDppRowMirror>(s);         c += (uint32_t)dpp_i32<kDppRowMirror>((int)c);
+  s += __shfl_xor(s, 16, kWave);          c += (uint32_t)__shfl_xor((int)c, 16, kWave);
+  if (lane == 0) {
+    lds_again[t / 32] = again ? 1u : 0u;
+    if (listed) { a.part_sum[at] = s + kept; a.part_cnt[at] = c; }
+  }
+  __syncthreads();
+  for (int u = 0; u < kSettleTiles; ++u) {
+    if (lds_again[u] == 0u) continue;                    // uniform
+    const Piece pc = load_piece(a.seg, piece0 + u, a.d);
+    code_piece(a, pc, piece0 + u, m, a.thr_ws[(int64_t)m * a.seg.n_seg + pc.seg], lds_d, lds_u);
+    __syncthreads();                                     // LDS is free again
   }
 }
 
@@ -380,13 +332,14 @@ size_t quantize_segments_workspace_bytes(const qa_segment_plan* P, int M) {
 // there are none: from 2^27 components on and with 128 pieces per tensor on average.  At that limit
 // (32768 pieces in all workers together), two reads -> one, us: 1 worker x 8 tensors of 4096 pieces 193 -> 143,
 // 8 x 4 of 1024 193 -> 152; 32 tensors, 58.4 M parameters, most of them in two tensors, 3 workers 250 -> 191,
-// 8 workers 641 -> 455.  No long tensor: 1 x 64 of 1000 pieces 364 -> 372, 2 x 64 of 500 359 -> 374 (two
+// 8 workers 641 -> 420.  No long tensor: 1 x 64 of 1000 pieces 364 -> 372, 2 x 64 of 500 359 -> 374 (two
 // launches more, and each piece is coded in the settling pass).  Below the average, where the bracket's
 // work-group per tensor counts: 8 x 64 of 64 190 -> 203, 4 x 2000 of 5 271 -> 311, 40000 of one or two 551 -> 755.
 constexpr int64_t kSegOneReadPieces = 32768, kSegOneReadMean = 128;
 size_t segments_one_read_bytes(const qa_segment_plan* P, int M) {
   if (P->n_pieces < kSegLong || P->n_pieces * M < kSegOneReadPieces || P->n_pieces < kSegOneReadMean * P->n_seg) return 0;
-  return align256((size_t)M * (size_t)P->n_pieces * sizeof(double)) + align256((size_t)M * (size_t)P->n_seg * sizeof(float2));
+  return align256((size_t)M * (size_t)P->n_pieces * sizeof(double)) + align256((size_t)M * (size_t)P->n_seg * sizeof(float2)) +
+         (size_t)M * (size_t)P->n_pieces * kWaves * kOpenSlots * sizeof(uint16_t);
 }
 
 static SegQuantArgs seg_args(const qa_layout* L, const qa_segment_plan* P, float* scales, float* thresholds, void* ws) {
@@ -432,7 +385,9 @@ int quantize_segments_launch(const qa_layout* L, const qa_segment_plan* P, const
   if (more != 0 && ws_bytes >= base + more) {
     char* p = static_cast<char*>(ws) + base;
     a.kept_sum = reinterpret_cast<double*>(p);
-    a.band = reinterpret_cast<float2*>(p + align256((size_t)L->M * (size_t)P->n_pieces * sizeof(double)));
+    p += align256((size_t)L->M * (size_t)P->n_pieces * sizeof(double));
+    a.band = reinterpret_cast<float2*>(p);
+    a.open = reinterpret_cast<uint16_t*>(p + align256((size_t)L->M * (size_t)P->n_seg * sizeof(float2)));
     const dim3 samples((unsigned)((P->n_pieces + kSegSampleEvery - 1) / kSegSampleEvery), (unsigned)L->M);
     const dim3 settle((unsigned)((P->n_pieces + kSettleTiles - 1) / kSettleTiles), (unsigned)L->M);
     hipLaunchKernelGGL(seg_sample_kernel, samples, block, 0, stream, a);

@@ -1265,3 +1265,52 @@ def test_exact_threshold_checks_workspace_and_missing_output():
         qa.qa_quantize_pack(L, g, 8192, codes, scales, th,
                             qa.QA_THRESH_EXACT | qa.QA_THRESH_GIVEN, None)
     assert e.value.code == -1
+
+
+def crowded(g, tile, groups):
+    """Components near the threshold of g in `groups` float4 groups of one wave's quarter of a tile, the rest of it far
+    below."""
+    delta = np.float32(0.75) * np.abs(g).mean(dtype=np.float64)
+    part = g[tile * 4096:(tile + 1) * 4096].reshape(4, 4, 64, 4)          # group index j, wave, lane, component
+    part[:, 1] = np.float32(1e-3) * delta
+    at = part[:, 1].reshape(-1, 4).copy()
+    at[:groups] = np.float32(delta) * np.where(np.arange(4) % 2, np.float32(1.0003), np.float32(-0.9997))
+    part[:, 1] = at.reshape(4, 64, 4)
+
+
+@pytest.mark.parametrize("d", [1 << 24, (1 << 24) + 4099, (1 << 26) + 1])   # one tile of 32 sampled, and one of 64
+def test_long_quantizer_lists_what_is_open(d):
+    """Lists of 14 float4 groups (the longest), of 15 (the tiles are coded again) and of a whole wave; open components in the
+    last, incomplete tile, behind which the row holds other values; a sample that misleads.  Same codes as with two
+    reads, same message bit for bit from the call that has no room for lists."""
+    rng = np.random.default_rng(11)
+    M, gs = 2, (d + 3) // 4 * 4 + 8
+    g = (rng.standard_normal((M, d)) * 1e-2).astype(np.float32)
+    for tile, groups in ((5, 14), (13, 15), (21, 256), (22, 1), ((d >> 12) - 1, 14)):
+        crowded(g[0], tile, groups)
+    delta = np.float32(0.75) * np.abs(g[0]).mean(dtype=np.float64)
+    g[0, -1] = delta * np.float32(1.0002)
+    every = 64 if d >= 1 << 26 else 32
+    tile = np.arange(d) >> 12
+    g[1][tile // every * every + (tile // every * 29) % every == tile] *= np.float32(0.5)
+    gp = np.full((M, gs), delta, np.float32)              # padding inside the bracket belongs to nobody
+    gp[:, :d] = g
+    L = qa.Layout.make(d, M, 0)
+    gd, out = dev(gp), []
+    full = qa.qa_workspace_bytes(L, qa.QA_OP_QUANTIZE)
+    for how in ("listed", "two reads", "static"):
+        codes = torch.full((M, L.code_stride), -1, dtype=torch.int32, device=DEV)
+        sc, th = torch.zeros((2, M, 1), dtype=torch.float32, device=DEV)
+        if how == "static":
+            qa.qa_quantize_pack_static(L, gd, gs, codes, sc, th, 0)
+        else:
+            qa.qa_quantize_pack(L, gd, gs, codes, sc, th, 0, workspace(full if how == "listed" else M * ((d >> 12) + 1) * 12 + 4 * M + 768))
+        torch.cuda.synchronize()
+        out.append((codes[:, :L.words], sc, th))
+    for a, b in zip(out[0], out[2]):
+        assert torch.equal(a, b)
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][2], out[1][2])
+    assert int(ulp_distance(host(out[0][1]), host(out[1][1])).max()) <= 1
+    c_ref, _, t_ref = oracle.quantize_pack(g, bucket=0)
+    if np.array_equal(host(out[0][2]), t_ref):
+        assert np.array_equal(host(out[0][0]).view(np.uint32), c_ref)
