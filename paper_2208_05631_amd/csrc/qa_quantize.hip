@@ -1381,14 +1381,28 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
   out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
 
-__device__ __forceinline__ float tile_abs_max(const float v[4][4]) {
-  float s = 0.0f;
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { const float a = fabsf(v[j][e]); s = a > s ? a : s; }   // NaN never wins
-  return s;
+// The largest magnitude among the thread's values, NaNs left out.  As whole numbers the negative values' patterns grow
+// with the magnitude above all others, the others' below: two three-way maxima for two values.
+__device__ __forceinline__ float abs_max(const float* v, int n) {
+  uint32_t neg = 0;
+  int pos = 0;
+  for (int i = 0; i < n; ++i) {
+    const uint32_t b = __float_as_uint(v[i]);
+    neg = b > neg ? b : neg;
+    pos = (int)b > pos ? (int)b : pos;
+  }
+  uint32_t top = neg & 0x80000000u ? neg & 0x7fffffffu : 0u;
+  top = (uint32_t)pos > top ? (uint32_t)pos : top;
+  if (__any(top > 0x7f800000u)) {                        // rare: a NaN among the wave's values
+    top = 0;
+    for (int i = 0; i < n; ++i) {
+      const uint32_t b = __float_as_uint(v[i]) & 0x7fffffffu;
+      top = b <= 0x7f800000u && b > top ? b : top;
+    }
+  }
+  return __uint_as_float(top);
 }
+__device__ __forceinline__ float tile_abs_max(const float v[4][4]) { return abs_max(v[0], 16); }
 
 __device__ __forceinline__ float wave_max_f32(float s) {
   float o;
@@ -1405,49 +1419,52 @@ __device__ __forceinline__ float wave_max_f32(float s) {
   return r;
 }
 
+// Hardware conversion: 0 for NaN and below 0, the largest number above the range.
+__device__ __forceinline__ uint32_t to_u32_saturated(float x) {
+  uint32_t r;
+  asm("v_cvt_u32_f32 %0, %1" : "=v"(r) : "v"(x));
+  return r;
+}
+
 // codes of the tile, float4 group j of every thread with scale sj[j]; element (j, e) of thread t
 // is vector index base + 4*(j*256+t)+e
-// Bound by instruction issue, much of it Philox's 80 wide multiplies per thread.  Three-input exclusive or, the margins
-// in the reciprocal and the lanes' certainty as masks: 2^30 components, bucket 4096, 0.90 -> 0.81 ms.
+//
+// Keep iff u < fl(|v| / s), u = (r >> 8) * 2^-24.  Compared as whole numbers: the reciprocal's product (good to 2.5e-7)
+// less a part in 10^6, in units of 2^-32, lies below the quotient, and 8192 units further on (5841 would do: 2.3e-6 of
+// the largest quotient, 1, one unit and the 255 that r is above u) above it.  Only when r lies between the two
+// (probability 2e-6) is the correctly rounded quotient needed, and where the scale leaves the range in which none of the factors
+// overflows or loses bits.
+// Bound by instruction issue, half of it Philox's, and memory.  2^28 x 4 components, bucket 4096, with margins in binary32
+// and fields from selects 800 us, now 713; 2^20 x 16 14.6 -> 12.7, buckets of 256, 2^26 x 4 285 -> 264.
 __device__ __forceinline__ void stochastic_codes(const StochArgs& a, const float v[4][4],
                                                  const float sj[4], int64_t tile, int m) {
   const int t = threadIdx.x;
-  uint32_t mine = 0;
+  float vv[4][4];
+  uint64_t kept[4][4];
+  const uint64_t grp0 = (uint64_t)tile * (kTile / 4);      // a multiple of 1024: no carry from the thread's part
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const float s = sj[j];
-    const float rs = __builtin_amdgcn_rcpf(s);
-    const float below = rs * 0.999999f, above = rs * 1.000001f;
-    const uint64_t grp = (uint64_t)tile * (kTile / 4) + (uint64_t)(j * kThreads + t);
+    const float below = __builtin_amdgcn_rcpf(s) * (0.999999f * 0x1p32f);
     uint32_t r[4];
-    philox4x32_10((uint32_t)grp, (uint32_t)(grp >> 32), (uint32_t)m, a.step, a.seed_lo, a.seed_hi, r);
-    // keep iff u < fl(|v| / s).  The hardware reciprocal gives |v|/s to a few ulp; only when u
-    // lies within that margin of it (probability ~1e-6) is the correctly rounded quotient needed.
-    float u[4], av[4];
-    bool keep[4];
-    // lanes that are certain (masks stay in scalar registers): none whose scale's reciprocal leaves the normal
-    // numbers -- it may come out infinite below 2^-126 and 0 above 2^126
-    uint64_t sure = __ballot(__float_as_uint(s) - 0x00800000u <= 0x7e000000u - 0x00800000u);
+    philox4x32_10((uint32_t)grp0 | (uint32_t)(j * kThreads + t), (uint32_t)(grp0 >> 32), (uint32_t)m, a.step, a.seed_lo,
+                  a.seed_hi, r);
+    // 2^-90 .. 2^125
+    bool unsure = __float_as_uint(s) - 0x12800000u > 0x7e000000u - 0x12800000u;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      u[e] = (float)(r[e] >> 8) * 0x1p-24f;
-      av[e] = fabsf(v[j][e]);
-      keep[e] = u[e] < av[e] * below;
-      sure &= __ballot(keep[e]) | __ballot(u[e] > av[e] * above);        // NaN products: unsure
+      vv[j][e] = v[j][e];
+      const uint32_t low = to_u32_saturated(fabsf(v[j][e]) * below);
+      uint32_t above;                                    // r - low; the borrow says r < low
+      asm("v_sub_co_u32_e64 %0, %1, %2, %3" : "=v"(above), "=s"(kept[j][e]) : "v"(r[e]), "v"(low));
+      unsure |= above < 8192u;
     }
-    if (sure != __ballot(true)) {
+    if (__any(unsure)) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) keep[e] = u[e] < av[e] / s;
+      for (int e = 0; e < 4; ++e) kept[j][e] = __ballot((float)(r[e] >> 8) * 0x1p-24f < fabsf(v[j][e]) / s);
     }
-    uint32_t b = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) b |= (keep[e] ? (v[j][e] < 0.0f ? 3u : 1u) : 0u) << (2 * e);
-    uint32_t w = b << (8 * (t & 3));
-    w |= (uint32_t)dpp_i32<kDppQuadXor1>((int)w);
-    w |= (uint32_t)dpp_i32<kDppQuadXor2>((int)w);
-    if ((t & 3) == j) mine = w;
   }
-  store_code_word(a.q.codes + (int64_t)m * a.q.code_stride, tile, a.q.W, mine);
+  store_code_word(a.q.codes + (int64_t)m * a.q.code_stride, tile, a.q.W, code_word(vv, kept));
 }
 
 // bucket == tile (4096, or one scale per vector with d <= 4096): one pass
@@ -1503,10 +1520,7 @@ __global__ __launch_bounds__(kThreads) void quantize_stochastic_bucket_kernel(St
   float sj[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    float s = 0.0f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { const float av = fabsf(v[j][e]); s = av > s ? av : s; }
-    sj[j] = segment_max_f32(s, seg, lds_m);
+    sj[j] = segment_max_f32(abs_max(v[j], 4), seg, lds_m);
   }
   if (groups > kThreads) {                               // 2048: j = 0,1 and j = 2,3 share a bucket
     const float lo = sj[0] > sj[1] ? sj[0] : sj[1], hi = sj[2] > sj[3] ? sj[2] : sj[3];
