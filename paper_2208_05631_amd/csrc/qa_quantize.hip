@@ -602,10 +602,11 @@ __global__ __launch_bounds__(kThreads) void exact_threshold_kernel(QuantArgs a) 
 // buckets of 512 275 us by ranking all, 430 now (4096: 343, 240); ties cost less than by ranking (three
 // values, one of them 0: 512 254 -> 214, 4096 321 -> 176), but for one single value in buckets of 512 (238 -> 286).
 //
-// Bound by vector instructions (2271 per wave and bucket of 4096; the network took 78 stages for the same
+// Bound by vector instructions (some 1900 per wave and bucket of 4096; the network took 78 stages for the same
 // and left the codes to a second pass over the gradient).  2^26 x 4 Gaussian components, thresholds and
-// codes, ranking + quantizing before -> this: buckets of 4096 1366 -> 265 us, 2048 1300 -> 299,
-// 1024 1189 -> 385, 512 1094 -> 603.  Steps 2 to 4 cost the same for every bucket size, so halving
+// codes, ranking + quantizing -> this: buckets of 4096 1366 -> 235 us, 2048 1300 -> 273,
+// 1024 1189 -> 347, 512 1094 -> 587.  (2^28 x 4, 4096: 992 -> 940 with one comparison and one bit field per component for
+// the histogram, where it was a mask, a difference, a comparison and a shift, and with fields shifted in.)  Steps 2 to 4 cost the same for every bucket size, so halving
 // the bucket nearly doubles the time: at 256 the network (889 us) stays ahead.
 constexpr float kRankMark = -1.0f;
 constexpr int kExactList = 64;            // survivors that one wave ranks by counting
@@ -688,15 +689,22 @@ void exact_histogram_kernel(QuantArgs a) {
 #pragma unroll
   for (int r = 0; r < kPer; ++r) hist[r * kWave + lane] = 0;
 
-  float s32[4] = {0.0f, 0.0f, 0.0f, 0.0f}, top_f = 0.0f;
+  // the largest magnitude by whole numbers: among negative values the largest pattern, among the others the largest
+  // signed one, three at a time (a NaN shows in the total)
+  float s32[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  uint32_t neg = 0;
+  int pos = 0;
 #pragma unroll
   for (int j = 0; j < kGroups; ++j)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       s32[e] += fabsf(v[j][e]);
-      top_f = fmaxf(top_f, fabsf(v[j][e]));
+      const uint32_t bits = __float_as_uint(v[j][e]);
+      neg = bits > neg ? bits : neg;
+      pos = (int)bits > pos ? (int)bits : pos;
     }
-  const uint32_t top = __float_as_uint(wave_max_positive(top_f));
+  neg = neg & 0x80000000u ? neg & 0x7fffffffu : 0u;
+  const uint32_t top = (uint32_t)wave_reduce_i32((uint32_t)pos > neg ? pos : (int)neg, [](int p, int q) { return p > q ? p : q; });
   const float total = wave_sum_f32((s32[0] + s32[1]) + (s32[2] + s32[3]));       // NaN if any member is
 
   float* thr_out = a.thresholds + (int64_t)m * a.scale_stride + k;
@@ -720,17 +728,21 @@ void exact_histogram_kernel(QuantArgs a) {
     // the scale in the magnitudes' own units: the power of two comes back exactly
     const double back = __hiloint2double((int)((top >> 23) - 127u + 1023u) << 20, 0);
     if (!leave) {
+      // no member lies above the last bin, so one comparison tells which are counted; `base` is a multiple of a bin
       const uint32_t mask = (1u << shift) - 1u, limit = (uint32_t)kBins << shift;
+      const uint32_t bin_base = base >> shift;
+      const float first_counted = __uint_as_float(base);
       wave_lds_fence();
 #pragma unroll
       for (int j = 0; j < kGroups; ++j)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const uint32_t rel = magnitude_bits(v[j][e]) - base;
-          if (rel < limit)
-            atomicAdd(reinterpret_cast<unsigned long long*>(hist + (rel >> shift)),
-                      (1ull << 32) | (unsigned long long)(rel & mask));
-        }
+        for (int e = 0; e < 4; ++e)
+          if (fabsf(v[j][e]) >= first_counted) {
+            const uint32_t bits = __float_as_uint(v[j][e]);
+            const uint32_t bin = __builtin_amdgcn_ubfe(bits, (uint32_t)shift, 31u - (uint32_t)shift) - bin_base;
+            atomicAdd(reinterpret_cast<unsigned long long*>(hist + bin),
+                      (1ull << 32) | (unsigned long long)(bits & mask));
+          }
       wave_lds_fence();
       // sum of a bin's members in binary64: count * lower end + offsets in units of the last place
       const auto scaled_end = [&](uint32_t bin) { return base + (bin << shift) - rescale; };
@@ -831,12 +843,11 @@ void exact_histogram_kernel(QuantArgs a) {
       for (int j = 0; j < kGroups; ++j)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float x = __uint_as_float(magnitude_bits(v[j][e]));
-          const uint64_t who = __ballot(x >= env_lo && x < env_hi);
+          const uint64_t who = __ballot(fabsf(v[j][e]) >= env_lo) & __ballot(fabsf(v[j][e]) < env_hi);
           if (who) {
             const uint32_t at = count + __builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32),
                                             __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u));
-            if (((who >> lane) & 1ull) && at < (uint32_t)kExactList) list[at] = __float_as_uint(x);
+            if (((who >> lane) & 1ull) && at < (uint32_t)kExactList) list[at] = __float_as_uint(fabsf(v[j][e]));
             count += (uint32_t)__popcll(who);
           }
         }
@@ -949,21 +960,16 @@ void exact_histogram_kernel(QuantArgs a) {
 #pragma unroll
   for (int j4 = 0; j4 < kGroups; j4 += 4) {
     constexpr int kQuads = kGroups < 4 ? kGroups : 4;
-    uint32_t mine = 0;
+    float x[4][4] = {};
+    uint64_t kept[4][4] = {};
 #pragma unroll
-    for (int j = 0; j < kQuads; ++j) {
-      uint32_t bits = 0;
+    for (int j = 0; j < kQuads; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float x = v[j4 + j][e];
-        const uint32_t pat = 1u | ((__float_as_uint(x) >> 30) & 2u);
-        bits |= (fabsf(x) > delta ? pat : 0u) << (2 * e);
+        x[j][e] = v[j4 + j][e];
+        kept[j][e] = __ballot(fabsf(x[j][e]) > delta);
       }
-      uint32_t w = bits << (8 * (lane & 3));
-      w |= (uint32_t)dpp_i32<kDppQuadXor1>((int)w);
-      w |= (uint32_t)dpp_i32<kDppQuadXor2>((int)w);
-      if ((lane & 3) == j) mine = w;
-    }
+    const uint32_t mine = code_word(x, kept);
     const int64_t widx = w0 + (j4 + (lane & 3)) * 16 + (lane >> 2);
     if ((lane & 3) < kQuads && widx < a.W) store_through(codes + widx, mine);
   }
