@@ -850,6 +850,209 @@ __global__ __launch_bounds__(kThreads) void step_lut_kernel(StepArgs a) {
   if (MODE == kQrda || TRACK_Z) store_state(a.z, tile_base, lo, hi, full_tile, sz);
 }
 
+// ---- the same for few tiles ---------------------------------------------------------------------
+//
+// A call of few tiles leaves the kernel above one wave per SIMD or less, and its time is that wave's chain of some
+// 1900 instructions (one tile, 4 workers: 8.0 us, of which 3 are the launch).  Here a tile is a work-group of 1024
+// threads with four coordinates each, float4 group t of the tile: a quarter of the chain, no tables and no
+// hand-over through LDS, codes read as bytes, workers added in the order in which the sum is written, full forms of square root and
+// division.  Everything is requested at once, and with ordinary loads: what a small call touches is in the caches and is
+// wanted there again.
+constexpr int kFewThreads = kTile / 4, kFewWaves = kFewThreads / kWave;
+
+// Sum of v over aligned segments of `seg` consecutive threads (a power of two, 16 .. 1024) for every thread of them.  lds: one
+// entry per wave.  Barriers if seg > 64.
+template <typename T>
+__device__ __forceinline__ T few_segment_sum(T v, int seg, T* lds) {
+  const int lim = seg < kWave ? seg : kWave;
+  for (int off = 1; off < lim; off <<= 1) v += __shfl_xor(v, off, kWave);
+  if (seg > kWave) {
+    const int wave = threadIdx.x / kWave, per = seg / kWave, w0 = wave & ~(per - 1);
+    if (threadIdx.x % kWave == 0) lds[wave] = v;
+    __syncthreads();
+    v = lds[w0];
+    for (int w = 1; w < per; ++w) v += lds[w0 + w];
+  }
+  return v;
+}
+__device__ __forceinline__ double few_sum_f64(double v, double* lds) {
+  v = wave_sum_f64(v);
+  if (threadIdx.x % kWave == 0) lds[threadIdx.x / kWave] = v;
+  __syncthreads();
+  double s = lds[0];
+#pragma unroll
+  for (int w = 1; w < kFewWaves; ++w) s += lds[w];
+  return s;
+}
+__device__ __forceinline__ uint32_t few_sum_u32(uint32_t v, uint32_t* lds) {
+  v = wave_sum_u32(v);
+  if (threadIdx.x % kWave == 0) lds[threadIdx.x / kWave] = v;
+  __syncthreads();
+  uint32_t s = lds[0];
+#pragma unroll
+  for (int w = 1; w < kFewWaves; ++w) s += lds[w];
+  return s;
+}
+// coordinates i .. i + 3, of which those in [lo, hi) exist (lo is a multiple of 16)
+__device__ __forceinline__ void few_load(const float* __restrict__ p, int64_t i, int64_t lo, int64_t hi, float (&v)[4]) {
+  if (i >= lo && i + 3 < hi) {
+    const float4 q = *reinterpret_cast<const float4*>(p + i);
+    v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = i >= lo && i + e < hi ? p[i + e] : 0.0f;
+  }
+}
+__device__ __forceinline__ void few_store(float* __restrict__ p, int64_t i, int64_t lo, int64_t hi, const float (&v)[4]) {
+  if (i >= lo && i + 3 < hi) {
+    *reinterpret_cast<float4*>(p + i) = make_float4(v[0], v[1], v[2], v[3]);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (i >= lo && i + e < hi) p[i + e] = v[e];
+  }
+}
+
+template <int MODE, bool TRACK_Z, int RQ>
+__global__ __launch_bounds__(kFewThreads) void step_few_kernel(StepArgs a) {
+  constexpr bool kUsesZ = MODE == kQrda || TRACK_Z;
+  __shared__ double lds_s1[kFewWaves], lds_s2[kFewWaves];
+  __shared__ uint32_t lds_c[kFewWaves];
+  const int t = threadIdx.x;
+  int64_t tile, lo, hi, k;
+  if (a.seg.piece_tile) {
+    const Piece pc = load_piece(a.seg, blockIdx.x, a.d);
+    tile = pc.tile; lo = pc.lo; hi = pc.hi; k = pc.seg;
+  } else {
+    tile = blockIdx.x;
+    lo = tile * kTile;
+    hi = lo + kTile < a.d ? lo + kTile : a.d;
+    k = a.log2b >= 0 ? (lo >> a.log2b) : 0;
+  }
+  const int64_t i = tile * kTile + 4 * (int64_t)t;
+  const bool own_scales = !a.tile_uniform;               // uniform over the launch
+  const int64_t last = a.d - 1, here = i < last ? i : last;   // (threads beyond the vector read a scale that exists)
+  const float* sc = a.scales + (own_scales ? here >> a.log2b : k);
+  const int64_t words_here = a.W - tile * kTileWords;
+  const int row_bytes = 4 * (int)(words_here >= kTileWords ? kTileWords : words_here);
+  const uint32_t* ctile = a.codes + tile * kTileWords;
+
+  float G[4], x[4], z[4];
+  if (MODE != kAggregate) few_load(a.G, i, lo, hi, G);
+  if (MODE == kQcmd) few_load(a.x, i, lo, hi, x);
+  if (MODE != kAggregate && kUsesZ) few_load(a.z, i, lo, hi, z);
+
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  constexpr int kAhead = 8;
+  for (int m0 = 0; m0 < a.M; m0 += kAhead) {
+    uint32_t byte[kAhead];
+    float sm[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int m = m0 + u < a.M ? m0 + u : a.M - 1;
+      const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<uint32_t*>(ctile + (int64_t)m * a.code_stride), 0, row_bytes, 0x00020000);
+      byte[u] = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(r, t, 0, 0);   // 0 at and beyond the row's end
+      sm[u] = sc[(int64_t)m * a.scale_stride];
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      if (m0 + u >= a.M) break;                          // uniform
+      const uint32_t b = sanitize(byte[u]);
+      const double s = (double)sm[u];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int c = ((int)(b << (30 - 2 * e))) >> 30;
+        acc[e] = fma((double)c, s, acc[e]);
+      }
+    }
+  }
+  float q[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    q[e] = a.M_pow2 ? (float)(acc[e] * a.inv_M) : (float)(acc[e] / (double)a.M);
+    if (i < lo || i + e >= hi) q[e] = 0.0f;
+  }
+
+  if (MODE == kAggregate && a.abs_partials) {             // uniform
+    double s1 = 0.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s1 += (double)fabsf(q[e]);
+    s1 = few_sum_f64(s1, lds_s1);
+    if (t == 0) a.abs_partials[blockIdx.x] = s1;          // tile or piece
+  }
+  if (MODE == kAggregate && RQ == kRqNone && a.kept_sum) {   // uniform
+    const float Delta = a.rq_thr[a.seg.piece_tile ? k : tile / a.rq_tiles];
+    double s2 = 0.0;
+    uint32_t cnt = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float av = fabsf(q[e]);
+      if (av > Delta) { s2 += (double)av; ++cnt; }
+    }
+    s2 = few_sum_f64(s2, lds_s2);
+    cnt = few_sum_u32(cnt, lds_c);
+    if (t == 0) { a.kept_sum[blockIdx.x] = s2; a.kept_cnt[blockIdx.x] = cnt; }
+    return;
+  }
+  if (MODE == kAggregate && RQ == kRqNone) {
+    if (a.gbar) few_store(a.gbar, i, lo, hi, q);          // uniform
+    return;
+  }
+  if (RQ == kRqGiven) {
+    const int64_t k2 = a.seg.piece_tile ? k : tile / a.rq_tiles;
+    const float Delta = a.rq_thr[k2], s = a.rq_scale[k2];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) q[e] = q[e] > Delta ? s : (q[e] < -Delta ? -s : 0.0f);
+  }
+  if (RQ == kRqInTile) {
+    const int seg = own_scales ? (1 << a.log2b) / 4 : kFewThreads;
+    int64_t n = hi - lo;
+    if (own_scales) {
+      const int64_t b = (int64_t)1 << a.log2b, blo = (i >> a.log2b) << a.log2b;
+      n = (a.d - blo) < b ? (a.d - blo) : b;              // true length of the thread's bucket
+    }
+    double s1 = 0.0, s2 = 0.0;
+    uint32_t cnt = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s1 += (double)fabsf(q[e]);
+    s1 = own_scales ? few_segment_sum(s1, seg, lds_s1) : few_sum_f64(s1, lds_s1);
+    const float Delta = n > 0 ? threshold_from_sum(s1, a.thr_coef, n) : 0.0f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float av = fabsf(q[e]);
+      if (av > Delta) { s2 += (double)av; ++cnt; }
+    }
+    s2 = own_scales ? few_segment_sum(s2, seg, lds_s2) : few_sum_f64(s2, lds_s2);
+    cnt = own_scales ? few_segment_sum(cnt, seg, lds_c) : few_sum_u32(cnt, lds_c);
+    const float s = scale_from_sum(s2, cnt);
+    if (MODE == kAggregate) {
+      uint32_t word = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) word |= ternary_field(q[e], Delta) << (2 * e);
+      word <<= 8 * (t & 3);
+      word |= (uint32_t)dpp_i32<kDppQuadXor1>((int)word);
+      word |= (uint32_t)dpp_i32<kDppQuadXor2>((int)word);
+      if ((t & 3) == 0 && (int64_t)(t >> 2) < words_here) a.q_codes[tile * kTileWords + (t >> 2)] = word;
+      if ((t & (seg - 1)) == 0 && n > 0) {
+        const int64_t kq = own_scales ? i >> a.log2b : k;
+        a.q_scales[kq] = s;
+        if (a.q_thresholds) a.q_thresholds[kq] = Delta;
+      }
+      return;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) q[e] = q[e] > Delta ? s : (q[e] < -Delta ? -s : 0.0f);
+  }
+  if constexpr (MODE != kAggregate) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) update_coordinate<MODE, TRACK_Z>(a, q[e], x[e], G[e], z[e]);
+    few_store(a.G, i, lo, hi, G);
+    few_store(a.x, i, lo, hi, x);
+    if (kUsesZ) few_store(a.z, i, lo, hi, z);
+  }
+}
+
 // ---- the two sums behind Q(SynQ) with one scale, from messages with one scale each -------------
 //
 // One scale per message (the paper's message) and at most 8 workers: the tables of partial sums
@@ -1113,6 +1316,13 @@ static void launch_lut(const StepArgs& a, dim3 grid, dim3 block, hipStream_t str
 }
 
 // ngt: the NGT of the kernel variant
+// step_few_kernel up to so many tiles (or pieces), workers, and tiles times workers.  QCMD step with one scale per 4096 /
+// QRDA step with buckets of 256 quantized again, us, the kernel of tables -> this: 1 worker 1 tile 6.6 -> 5.9 / 8.3 -> 5.4,
+// 512 tiles 8.4 -> 7.0 / 11.9 -> 10.1; 4 workers 256 tiles 6.9 -> 5.6 / 9.6 -> 7.8, 512 8.3 -> 8.0 / 11.8 -> 11.3;
+// 8 workers 25 tiles 6.5 -> 5.4 / 8.3 -> 7.1, 256 7.2 -> 6.5 / 9.6 -> 8.7, 512 8.6 -> 9.2 / 11.7 -> 12.6; 16 workers
+// 100 tiles 7.7 -> 7.7 / 9.8 -> 9.4, 256 8.2 -> 8.4 / 10.8 -> 10.5; 64 workers 1 tile 11.6 -> 17.9.
+constexpr unsigned kFewTiles = 512;
+constexpr int kFewWorkers = 16, kFewRows = 2048;
 template <int MODE, bool TRACK_Z, int RQ>
 static void launch_one(const StepArgs& a, int ngt, hipStream_t stream) {
   const dim3 grid((unsigned)(a.seg.piece_tile ? a.seg.n_pieces : tiles_of(a.d))), block(kThreads);
@@ -1123,6 +1333,10 @@ static void launch_one(const StepArgs& a, int ngt, hipStream_t stream) {
       else launch_lut<MODE, TRACK_Z, RQ, 0, true>(a, grid, block, stream);
       return;
     }
+  }
+  if (grid.x <= kFewTiles && a.M <= kFewWorkers && (int)grid.x * a.M <= kFewRows) {
+    hipLaunchKernelGGL((step_few_kernel<MODE, TRACK_Z, RQ>), grid, dim3(kFewThreads), 0, stream, a);
+    return;
   }
   switch (ngt) {
     case 4: launch_lut<MODE, TRACK_Z, RQ, 4>(a, grid, block, stream); break;

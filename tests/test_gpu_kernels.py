@@ -1314,3 +1314,43 @@ def test_long_quantizer_lists_what_is_open(d):
     c_ref, _, t_ref = oracle.quantize_pack(g, bucket=0)
     if np.array_equal(host(out[0][2]), t_ref):
         assert np.array_equal(host(out[0][0]).view(np.uint32), c_ref)
+
+
+# both kernels of the steps: up to 512 tiles, 16 workers and 2048 tiles times workers a work-group of 1024 threads takes a
+# tile, beyond them the one with tables
+@pytest.mark.parametrize("tiles,M,bucket,requant", [
+    (512, 1, 0, 0), (513, 1, 4096, 1), (512, 4, 64, 1), (513, 4, 256, 1), (256, 8, 2048, 1), (257, 8, 1024, 0),
+    (128, 16, 65536, 1), (129, 16, 0, 2), (3, 17, 512, 1), (1, 17, 0, 2), (5, 24, 4096, 0), (5, 32, 4096, 1),
+    (5, 20, 8192, 0), (2, 64, 128, 1)])
+@pytest.mark.parametrize("method", ["qcmd", "qcmd_z", "qrda"])
+def test_steps_on_either_side_of_the_line_of_few_tiles(method, tiles, M, bucket, requant):
+    """State with values at the ends of the exponent range next to ordinary ones, an incomplete last tile, garbage in
+    the code fields behind it: the oracle's bits from both kernels."""
+    d = tiles * 4096 - 4089 + 4 * (M % 5)
+    rng = np.random.default_rng(tiles + 31 * M)
+    g = make_grad("laplace_sparse", M, d, seed=M)
+    oc, osc, _ = oracle.quantize_pack(g, bucket=bucket)
+    if d % 16:
+        oc[:, -1] |= np.uint32((0xFFFFFFFF << (2 * (d % 16))) & 0xFFFFFFFF)
+    L = qa.Layout.make(d, M, bucket)
+    pool = np.array([0.0, -0.0, 1e-45, 1e-40, 1e-35, 1.2e-29, 1.3e-29, 1e-20, 1.0, 1e20, 9e37, 3e38, np.inf, np.nan], np.float32)
+    x0 = (rng.standard_normal(d) * 1e-2 * (rng.random(d) < 0.5)).astype(np.float32)
+    G0 = (rng.random(d) * 1e-5).astype(np.float32)
+    z0 = (rng.standard_normal(d) * 1e-3).astype(np.float32)
+    for a, signed in ((x0, True), (G0, False), (z0, True)):
+        where = rng.random(d) < 0.01
+        v = rng.choice(pool, int(where.sum()))
+        a[where] = v * rng.choice([-1, 1], v.size) if signed else np.abs(v)
+    ox, oG, oz = x0.copy(), G0.copy(), z0.copy()
+    st = GpuState(L, oc, osc, x0, G0, z0)
+    with np.errstate(all="ignore"):
+        if method == "qrda":
+            oracle.step_qrda(oc, osc, d, bucket, ox, oG, oz, 3, 0.1, 2e-4, 1e-8, requant)
+            st.qrda(3, 0.1, 2e-4, 1e-8, requant)
+        else:
+            tz = method == "qcmd_z"
+            oracle.step_qcmd(oc, osc, d, bucket, ox, oG, oz if tz else None, 0.1, 2e-4, 1e-8, requant)
+            st.qcmd(0.1, 2e-4, 1e-8, requant, track_z=tz)
+    for name, a, o in zip("xGz", st.get(), (ox, oG, oz)):
+        same = (a.view(np.uint32) == o.view(np.uint32)) | (np.isnan(a) & np.isnan(o))
+        assert same.all(), (name, int((~same).sum()), a[~same][:4], o[~same][:4])
