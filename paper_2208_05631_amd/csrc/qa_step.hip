@@ -1185,6 +1185,144 @@ __global__ __launch_bounds__(kThreads) void requant_sums_kernel(SumArgs a) {
   }
 }
 
+// ---- the same from a count of the workers' code combinations ------------------------------------
+//
+// With one scale per message a coordinate's average depends on nothing but the combination of its M codes, of which
+// there are 3^M (6561 for 8 workers).  Counted once, they give both sums: the threshold from count times value of every
+// combination, then what it keeps.  One pass over the messages instead of two with a binary64 addition, a division
+// and two conversions per coordinate in each; a value is formed in the workers' order, whatever the scales, and count times value is
+// exact.  A combination's number is the sum of two table entries in the steps' index bytes (base 3, in bytes of
+// the histogram); all workers' zero, the most frequent one, is left out and is what remains of d.
+// Bound by vector instructions (22 per coordinate; with the numbers from a table in LDS by that: 66 us for 63 at
+// 10^8 x 8).  Step with one scale, the two sum passes and two finalizing launches -> these three launches, us: 10^8
+// coordinates, 6 workers 470 -> 353, 8 dense 412 -> 361, 8 sparse 399 -> 354; 2^24, 5 workers 98 -> 73, 8 88 -> 80; 2^22 (1024 tiles,
+// the line) 40 -> 31 and 32.4 -> 31.4.  For 5 to 8 workers: with fewer the lanes of a wave meet in few bins.
+constexpr int kComboThreads = 1024, kComboGroups = 512, kMaxCombos = 6561;
+struct ComboArgs {
+  SumArgs m;
+  int combos;                           // 3^M
+  int tiles_per_group;
+  uint32_t* counts;                     // [groups][combos]
+  double* total;                        // [combos]
+  float* value;                         // [combos] |average|
+  float* thr_out; float* scale_out; float* threshold_user;
+  float thr_coef;
+  int groups;
+};
+
+// Four index bytes (four workers' non-zero bits, then their negative bits) to the numbers 0 .. 80 of their combinations:
+// digit = non-zero + negative, a pair of bits at a time through a four-entry table that a byte permutation looks up.
+__device__ __forceinline__ uint32_t combo_numbers(uint32_t z) {
+  z &= z << 4 | 0x0F0F0F0Fu;                             // negative only with non-zero: the pattern 10 reads as 0
+  const uint32_t low = 0x04030100u, high = 0x241B0900u;  // 0, 1, 3, 4 and nine times that
+  return (__builtin_amdgcn_perm(0u, low, z & 0x03030303u) + __builtin_amdgcn_perm(0u, high, (z >> 2) & 0x03030303u)) +
+         (__builtin_amdgcn_perm(0u, low, (z >> 4) & 0x03030303u) + __builtin_amdgcn_perm(0u, high, (z >> 6) & 0x03030303u));
+}
+
+__global__ __launch_bounds__(kComboThreads) void combo_count_kernel(ComboArgs c) {
+  __shared__ uint32_t hist[kMaxCombos];
+  const SumArgs& a = c.m;
+  const int t = threadIdx.x;
+  for (int i = t; i < c.combos; i += kComboThreads) hist[i] = 0u;
+  __syncthreads();
+  const int64_t word0 = (int64_t)blockIdx.x * c.tiles_per_group * kTileWords;
+  const int64_t past = word0 + (int64_t)c.tiles_per_group * kTileWords;
+  const int64_t word1 = past < a.W ? past : a.W;
+  for (int64_t base = word0; base < word1; base += kComboThreads) {
+    const int64_t left = word1 - base;
+    const uint32_t row_bytes = 4u * (uint32_t)(left < kComboThreads ? left : kComboThreads);
+    uint32_t w[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m)                           // words beyond the row read as 0
+      w[m] = m < a.M ? stream_load(a.codes + base + (int64_t)m * a.code_stride, 4u * (uint32_t)t, row_bytes) : 0u;
+    const int64_t live = a.d - 16 * (base + t);            // fields at or beyond d are no components
+    if (live < 16) {
+      const uint32_t mask = live > 0 ? (1u << (2 * (uint32_t)live)) - 1u : 0u;
+#pragma unroll
+      for (int m = 0; m < 8; ++m) w[m] &= mask;
+    }
+    uint32_t zq[8];
+    gather_group(w[0], w[1], w[2], w[3], zq);
+    gather_group(w[4], w[5], w[6], w[7], zq + 4);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t lo = combo_numbers(zq[j]), hi = combo_numbers(zq[4 + j]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const uint32_t at = ((hi >> (8 * r)) & 0xFFu) * 81u + ((lo >> (8 * r)) & 0xFFu);
+        if (at) atomicAdd(&hist[at], 1u);
+      }
+    }
+  }
+  __syncthreads();
+  for (int i = t; i < c.combos; i += kComboThreads) c.counts[(int64_t)blockIdx.x * c.combos + i] = hist[i];
+}
+
+// 64 combinations per work-group, sixteen slices of the groups' counts; the combinations' magnitudes.
+__global__ __launch_bounds__(kComboThreads) void combo_total_kernel(ComboArgs c) {
+  __shared__ double part[kComboThreads];
+  const SumArgs& a = c.m;
+  const int t = threadIdx.x, i = (int)blockIdx.x * kWave + t % kWave;
+  constexpr int kSlices = kComboThreads / kWave;
+  double s = 0.0;
+  if (i < c.combos) {
+#pragma unroll 8
+    for (int g = t / kWave; g < c.groups; g += kSlices) s += (double)c.counts[(int64_t)g * c.combos + i];
+  }
+  part[t] = s;
+  __syncthreads();
+  if (t < kWave && i < c.combos) {
+#pragma unroll
+    for (int w = 1; w < kSlices; ++w) s += part[w * kWave + t];
+    c.total[i] = s;
+    double acc = 0.0;
+    uint32_t rest = (uint32_t)i;
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+      if (m < a.M) {                                     // worker 0, 1, ...
+        const uint32_t digit = rest % 3u;
+        rest /= 3u;
+        acc = fma(digit == 2u ? -1.0 : (double)digit, (double)a.scales[(int64_t)m * a.scale_stride], acc);
+      }
+    c.value[i] = fabsf(a.M_pow2 ? (float)(acc * a.inv_M) : (float)(acc / (double)a.M));
+  }
+}
+
+// Threshold and scale from the combinations' numbers, one work-group.
+__global__ __launch_bounds__(kComboThreads) void combo_scale_kernel(ComboArgs c) {
+  constexpr int kPer = (kMaxCombos + kComboThreads - 1) / kComboThreads;
+  __shared__ double lds[kFewWaves], lds2[kFewWaves], lds3[kFewWaves], lds4[kFewWaves];
+  const SumArgs& a = c.m;
+  const int t = threadIdx.x;
+  double n[kPer], others = 0.0;
+  float av[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int i = t + u * kComboThreads;
+    n[u] = i > 0 && i < c.combos ? c.total[i] : 0.0;
+    av[u] = i < c.combos ? c.value[i] : 0.0f;
+    others += n[u];
+  }
+  others = few_sum_f64(others, lds);
+  if (t == 0) n[0] = (double)a.d - others;               // all zero (not a number where a scale is none)
+  double s1 = 0.0, s2 = 0.0, kept = 0.0;
+#pragma unroll
+  for (int u = 0; u < kPer; ++u)
+    if (n[u] > 0.0) s1 += n[u] * (double)av[u];
+  s1 = few_sum_f64(s1, lds2);
+  const float Delta = threshold_from_sum(s1, c.thr_coef, a.d);
+#pragma unroll
+  for (int u = 0; u < kPer; ++u)
+    if (n[u] > 0.0 && av[u] > Delta) { s2 += n[u] * (double)av[u]; kept += n[u]; }
+  s2 = few_sum_f64(s2, lds3);
+  kept = few_sum_f64(kept, lds4);
+  if (t == 0) {
+    *c.thr_out = Delta;
+    if (c.threshold_user) *c.threshold_user = Delta;
+    *c.scale_out = scale_from_sum(s2, (uint64_t)kept);
+  }
+}
+
 // ---- host side -------------------------------------------------------------------------------
 
 static inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
@@ -1389,13 +1527,39 @@ static SumArgs sum_args(const StepArgs& messages) {
   return sa;
 }
 
+constexpr int kComboMinM = 5;              // see combo_count_kernel
+constexpr int64_t kComboTiles = 1024;
+// scratch: what is left of the workspace behind the quantizer's part (256-byte aligned).
 static int requant_sums_from_messages(const StepArgs& messages, const qa_layout* R, float* scales,
-                                      float* thresholds, void* qws, size_t qws_bytes,
+                                      float* thresholds, void* qws, size_t qws_bytes, size_t scratch_bytes,
                                       const float** thr_out, hipStream_t stream) {
   if (!qws || qws_bytes == 0 || qws_bytes < quantize_workspace_bytes(R)) return QA_ERR_WORKSPACE;
   double* part_sum; uint32_t* part_cnt; float* thr;
   quantize_workspace_parts(R, qws, &part_sum, &part_cnt, &thr);
   *thr_out = thr;
+  if (one_scale_everywhere(messages, R) && messages.M >= kComboMinM && tiles_of(messages.d) >= kComboTiles) {
+    ComboArgs c{};
+    c.m = sum_args(messages);
+    c.combos = 1;
+    for (int m = 0; m < messages.M; ++m) c.combos *= 3;
+    c.tiles_per_group = (int)((c.m.ntiles + kComboGroups - 1) / kComboGroups);
+    c.tiles_per_group = (c.tiles_per_group + 3) & ~3;    // whole rounds of a work-group
+    c.groups = (int)((c.m.ntiles + c.tiles_per_group - 1) / c.tiles_per_group);
+    const size_t counts = align256((size_t)c.groups * c.combos * sizeof(uint32_t));
+    if (scratch_bytes >= counts + (size_t)c.combos * (sizeof(double) + sizeof(float))) {
+      char* p = static_cast<char*>(qws) + qws_bytes;
+      c.counts = reinterpret_cast<uint32_t*>(p);
+      c.total = reinterpret_cast<double*>(p + counts);
+      c.value = reinterpret_cast<float*>(c.total + c.combos);
+      c.thr_out = thr; c.scale_out = scales; c.threshold_user = thresholds;
+      c.thr_coef = messages.thr_coef;
+      const dim3 block(kComboThreads);
+      hipLaunchKernelGGL(combo_count_kernel, dim3((unsigned)c.groups), block, 0, stream, c);
+      hipLaunchKernelGGL(combo_total_kernel, dim3((unsigned)((c.combos + kWave - 1) / kWave)), block, 0, stream, c);
+      hipLaunchKernelGGL(combo_scale_kernel, dim3(1), block, 0, stream, c);
+      return launch_status();
+    }
+  }
   if (one_scale_everywhere(messages, R)) {
     // one scale per message and one for Q(SynQ): the lean kernel, one partial per work-group
     SumArgs sa = sum_args(messages);
@@ -1477,8 +1641,8 @@ static int step_common(int mode, const qa_layout* L, const uint32_t* codes, cons
       char* p = static_cast<char*>(ws);
       float* s1 = reinterpret_cast<float*>(p);            p += align256((size_t)R.scale_stride * 4);
       const size_t qws = quantize_workspace_bytes(&R);
-      rc = requant_sums_from_messages(make_args(L, codes, scales), &R, s1, nullptr, p, qws, &given_thr,
-                                      stream);
+      rc = requant_sums_from_messages(make_args(L, codes, scales), &R, s1, nullptr, p, qws,
+                                      static_cast<char*>(ws) + ws_bytes - (p + qws), &given_thr, stream);
       if (rc != QA_OK) return rc;
       given_scale = s1;
     } else {
@@ -1578,7 +1742,7 @@ static int aggregate_quantize_common(const qa_layout* L, const uint32_t* codes, 
     // three passes over the messages (sums, kept sums, codes) instead of writing the average out
     // (long vectors only: five launches against four, d = 2^24 and M = 8: 0.044 against 0.039 ms)
     const float* thr = nullptr;
-    rc = requant_sums_from_messages(ag, &R, q_scales, q_thresholds, p, qws, &thr, stream);
+    rc = requant_sums_from_messages(ag, &R, q_scales, q_thresholds, p, qws, ws_bytes - qws, &thr, stream);
     if (rc != QA_OK) return rc;
     SumArgs sa = sum_args(ag);
     sa.thr = thr; sa.q_codes = q_codes;

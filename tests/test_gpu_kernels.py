@@ -1354,3 +1354,42 @@ def test_steps_on_either_side_of_the_line_of_few_tiles(method, tiles, M, bucket,
     for name, a, o in zip("xGz", st.get(), (ox, oG, oz)):
         same = (a.view(np.uint32) == o.view(np.uint32)) | (np.isnan(a) & np.isnan(o))
         assert same.all(), (name, int((~same).sum()), a[~same][:4], o[~same][:4])
+
+
+@pytest.mark.parametrize("scales", ["close", "wide", "inf"])
+@pytest.mark.parametrize("M", [4, 5, 6, 7, 8])
+def test_sums_from_counted_combinations_match_oracle(M, scales):
+    """5 to 8 workers of at least 1024 tiles, one scale per message: the two sums behind Q(SynQ) from the number of
+    coordinates with each combination of codes; an odd number of tiles, a last word that ends inside."""
+    test_steps_with_one_scale_everywhere_match_oracle(4096 * 1025 + 4 * M + 1, M, scales)
+
+
+@pytest.mark.parametrize("tiles,M", [(1024, 7), (16385, 5), (16384, 8)])
+def test_counted_combinations_with_crowded_bins_and_reserved_codes(tiles, M):
+    """All workers of one mind over most of the vector (one bin takes nearly everything), the pattern 10 among the codes
+    (read as 0); step and, from 16384 tiles on, the server's call."""
+    d = 4096 * tiles - 5
+    rng = np.random.default_rng(tiles + M)
+    words = (d + 15) // 16
+    oc = np.full((M, words), 0x55555555, np.uint32)
+    oc[:, ::3] = rng.integers(0, 1 << 32, (M, (words + 2) // 3), dtype=np.uint32)
+    osc = (1e-2 * rng.uniform(0.5, 1.5, (M, 1))).astype(np.float32)
+    L = qa.Layout.make(d, M, 0)
+    x0 = (rng.standard_normal(d) * 1e-2).astype(np.float32)
+    G0 = (rng.random(d) * 1e-4).astype(np.float32)
+    ox, oG = x0.copy(), G0.copy()
+    oracle.step_qcmd(oc, osc, d, 0, ox, oG, None, 0.1, 1e-4, 1e-8, 2)
+    st = GpuState(L, oc, osc, x0, G0, np.zeros(1, np.float32))
+    st.qcmd(0.1, 1e-4, 1e-8, 2, track_z=False)
+    x, G, _ = st.get()
+    assert np.array_equal(x, ox) and np.array_equal(G, oG)
+    if tiles >= 16384:
+        avg = oracle.aggregate(oc, osc, d, 0)
+        c_ref, s_ref, t_ref = oracle.quantize_pack(avg[None], bucket=0)
+        q = torch.zeros((1, words), dtype=torch.int32, device=DEV)
+        qs, qt = torch.zeros((2, 1, 1), dtype=torch.float32, device=DEV)
+        qa.qa_aggregate_quantize(L, dev(oc.view(np.int32)), dev(osc), 2, q, qs, qt,
+                                 workspace(qa.qa_workspace_bytes(L, qa.QA_OP_STEP)))
+        torch.cuda.synchronize()
+        assert np.array_equal(host(qs), s_ref) and np.array_equal(host(qt), t_ref)
+        assert np.array_equal(host(q).view(np.uint32), c_ref)
