@@ -415,10 +415,13 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(CR
 //             a > S / 2k), so the place where S - 2 t K changes sign beside the sample's best edge is found
 //             between the bins.
 //   probe     the same sample against that threshold: S - 2 t K, 256 by 256.  Its slope gives a Newton step,
-//             the differences between neighbours the standard error; five of them to either side
+//             the differences between neighbours the standard error; four of them to either side
 //             make the bracket.
-//   pass      all components, once: those above the bracket are coded as kept, those below as 0, those inside
-//             get the pattern 10 and are listed with their places.  Its histogram is finest around the bracket.
+//   pass      all components, once: those above the bracket are coded as kept, all others as 0, and those inside
+//             are listed with their places.  Its histogram is finest around the bracket.  (With four standard errors
+//             to a side the list holds a fifth less than with five, and since what is listed is coded 0 until it is
+//             settled, only its kept components, some half, are atomics then: 27.7 to 11.9 us for 2^26 Gaussian
+//             components, the whole call 316 to 303 us; the wider bracket 307.)
 //   prove     the scan's bounds show that no cut outside the bracket can be the optimum, or the levels go on over the
 //             whole gradient from the bins that survive.
 //   level     as above, over the list instead of the gradient; some 250 000 of 2^26 Gaussian components.
@@ -692,7 +695,7 @@ __global__ __launch_bounds__(kPassThreads) void exact_wide_probe_kernel(WideArgs
     const double slope = 2.0 * K - N / 0.04;
     if (pairs >= 64 && K >= 256.0 && N >= 64.0 && slope > 0.2 * K) {
       const double step = excess / slope;
-      const double half = 5.0 * sqrt((double)n * diff / (2.0 * (double)pairs)) / slope + 0.02 * fabs(step) + 1e-4 * t0;
+      const double half = 4.0 * sqrt((double)n * diff / (2.0 * (double)pairs)) / slope + 0.02 * fabs(step) + 1e-4 * t0;
       const double open = N / 0.04 * (2.0 * half / t0) / ((double)n * (double)kUnit);
       if (half < 0.12 * t0 && fabs(step) < 0.05 * t0 && open < kMostOpen) {
         const uint32_t below = __float_as_uint((float)(t0 + step - half)), above = __float_as_uint((float)(t0 + step + half));
@@ -962,7 +965,7 @@ __global__ __launch_bounds__(kPassThreads) void exact_wide_bracketed_kernel(Wide
       add_code_byte(j, byte, &mine);
     });
     const int64_t word = i0 / 16 + (t & 3) * (kPassThreads / 4) + (t >> 2);
-    if (16 * word < hi) codes[word] = mine;
+    if (16 * word < hi) codes[word] = mine & (mine << 1 | 0x55555555u);   // 10 -> 00
     for (uint32_t left = (fields >> 1) & ~fields & 0x55555555u; left; left &= left - 1u) {
       const int f = __builtin_ctz(left) >> 1;            // component f % 4 of group f / 4
       uint32_t by[4];
@@ -1124,7 +1127,7 @@ __global__ __launch_bounds__(kPassThreads) void exact_wide_codes_kernel(WideArgs
     for (uint32_t i = (uint32_t)chunk * kPassThreads + t; i < listed; i += (uint32_t)chunks * kPassThreads) {
       const uint2 e = entries[i];
       const uint32_t code = ternary_field(__uint_as_float(e.y), D);
-      atomicXor(&codes[e.x >> 4], (2u ^ code) << (2 * (e.x & 15u)));
+      if (code) atomicOr(&codes[e.x >> 4], code << (2 * (e.x & 15u)));   // the pass has left 0
     }
     return;
   }
