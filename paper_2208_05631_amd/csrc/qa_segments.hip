@@ -168,36 +168,63 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void seg_scale_finalize_kern
 
 // ---- long tensors in one read -------------------------------------------------------------------
 //
-// As for long buckets of a plain vector: every 32nd piece of a tensor of at least 1024 pieces gives a
+// As for long buckets of a plain vector: 32 samples or more of a tensor of at least 128 pieces give a
 // bracket around the tensor's threshold (four standard errors, at most 8 % to either side),
 // the one pass writes final codes outside the bracket and the piece sums of |v| and lists the open float4 groups,
 // and the settling pass looks these up once the threshold is known.  Of tensors
-// without a bracket, or whose threshold falls outside it, it reads the gradient again.
+// without a bracket, or whose threshold falls outside it, it reads the gradient again.  32 samples hold the bracket of a
+// Gaussian tensor to 0.8 %, of whose components the lists have room for all but a few in a hundred pieces; with 16 a
+// fifth of the pieces would be read again, so shorter tensors keep both reads.
 constexpr int kSegSampleEvery = 32;
+constexpr int64_t kSegShortest = 128;
 constexpr int64_t kSegLong = 1024;
 constexpr double kSegWidestBand = 0.08;
 
+// Every how many pieces (a power of two) a tensor of n pieces is sampled: 32 samples, of a long tensor more; 0: none.
+__device__ __forceinline__ int64_t seg_sample_stride(int64_t n) {
+  return n >= kSegLong ? 32 : n >= 512 ? 16 : n >= 256 ? 8 : n >= kSegShortest ? 4 : 0;
+}
+
+// A work-group looks through 32 pieces, a wave reads a sampled one; sample k of a tensor goes to slot k of the tensor's
+// slots, as -1 if the piece is not a whole tile.
 __global__ __launch_bounds__(kThreads) void seg_sample_kernel(SegQuantArgs a) {
-  __shared__ double lds_d[kWaves];
-  const int64_t i = blockIdx.x, p = i * kSegSampleEvery + (i * 29) % kSegSampleEvery;
-  const int m = blockIdx.y;
-  double s = -1.0;                                       // not a whole tile of a long tensor
-  if (p < a.seg.n_pieces) {
-    const Piece pc = load_piece(a.seg, p, a.d);
+  const int m = blockIdx.y, lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  const int64_t own = (int64_t)blockIdx.x * kSegSampleEvery + lane % kSegSampleEvery;
+  bool sampled = false;
+  int64_t slot = 0, tile = 0;
+  if (own < a.seg.n_pieces) {
+    const Piece pc = load_piece(a.seg, own, a.d);
     int64_t p0, p1;
     piece_range(a.seg, pc.seg, &p0, &p1);
-    if (p1 - p0 >= kSegLong && pc.hi - pc.lo == kTile) {
-      float v[4][4];
-      load_piece_values(a.g + (int64_t)m * a.g_stride, pc, v);
-      s = 0.0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s += (double)fabsf(v[j][e]);
-      s = block_sum_f64(s, lds_d);
+    const int64_t stride = seg_sample_stride(p1 - p0);
+    if (stride != 0 && own >= p0) {
+      const int64_t k = (own - p0) / stride;
+      sampled = (own - p0) % stride == k * 29 % stride && (k + 1) * stride <= p1 - p0;
+      slot = (int64_t)m * a.seg.n_pieces + p0 + k;
+      tile = pc.hi - pc.lo == kTile ? pc.tile : -1;
     }
   }
-  if (threadIdx.x == 0) a.kept_sum[(int64_t)m * a.seg.n_pieces + i] = s;
+  int rank = 0;
+  for (uint32_t left = (uint32_t)__ballot(sampled); left; left &= left - 1u, ++rank) {   // the same in every wave
+    if (rank % kWaves != wave) continue;
+    const int u = __ffs((int)left) - 1;
+    const int64_t whole = __shfl(tile, u, kWave);
+    double s = -1.0;
+    if (whole >= 0) {
+      typedef float floatx4 __attribute__((ext_vector_type(4)));
+      const floatx4* g = reinterpret_cast<const floatx4*>(a.g + (int64_t)m * a.g_stride + whole * kTile) + lane;
+      floatx4 q[kTile / 4 / kWave];
+#pragma unroll
+      for (int i = 0; i < kTile / 4 / kWave; ++i) q[i] = __builtin_nontemporal_load(g + i * kWave);
+      s = 0.0;
+#pragma unroll
+      for (int i = 0; i < kTile / 4 / kWave; ++i)
+        s += ((double)fabsf(q[i].x) + (double)fabsf(q[i].y)) + ((double)fabsf(q[i].z) + (double)fabsf(q[i].w));
+      s = wave_sum_f64(s);
+    }
+    if (lane == u) a.kept_sum[slot] = s;
+  }
 }
 
 __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void seg_band_kernel(SegQuantArgs a) {
@@ -206,15 +233,14 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void seg_band_kernel(SegQuan
   const int m = blockIdx.y;
   int64_t p0, p1;
   piece_range(a.seg, s, &p0, &p1);
-  const int64_t i0 = (p0 + kSegSampleEvery - 1) / kSegSampleEvery, i1 = p1 / kSegSampleEvery;
-  const double* part = a.kept_sum + (int64_t)m * a.seg.n_pieces;
+  const int64_t stride = seg_sample_stride(p1 - p0), samples = stride != 0 ? (p1 - p0) / stride : 0;
+  const double* part = a.kept_sum + (int64_t)m * a.seg.n_pieces + p0;
   double sum = 0.0, diff = 0.0, n = 0.0, nd = 0.0;
-  if (p1 - p0 >= kSegLong)
-    for (int64_t i = i0 + threadIdx.x; i < i1; i += kThreads) {
-      const double v = part[i], w = i + 1 < i1 ? part[i + 1] : -1.0;
-      if (v >= 0.0 || v != v) { sum += v; n += 1.0; }
-      if (v >= 0.0 && w >= 0.0) { diff += (w - v) * (w - v); nd += 1.0; }
-    }
+  for (int64_t i = threadIdx.x; i < samples; i += kThreads) {
+    const double v = part[i], w = i + 1 < samples ? part[i + 1] : -1.0;
+    if (v >= 0.0 || v != v) { sum += v; n += 1.0; }
+    if (v >= 0.0 && w >= 0.0) { diff += (w - v) * (w - v); nd += 1.0; }
+  }
   sum = segment_sum(sum, kThreads, lds_d);
   diff = segment_sum(diff, kThreads, lds_d);
   n = segment_sum(n, kThreads, lds_d);
@@ -332,9 +358,10 @@ size_t quantize_segments_workspace_bytes(const qa_segment_plan* P, int M) {
 // there are none: from 2^27 components on and with 128 pieces per tensor on average.  At that limit
 // (32768 pieces in all workers together), two reads -> one, us: 1 worker x 8 tensors of 4096 pieces 193 -> 143,
 // 8 x 4 of 1024 193 -> 152; 32 tensors, 58.4 M parameters, most of them in two tensors, 3 workers 250 -> 191,
-// 8 workers 641 -> 420.  No long tensor: 1 x 64 of 1000 pieces 364 -> 372, 2 x 64 of 500 359 -> 374 (two
-// launches more, and each piece is coded in the settling pass).  Below the average, where the bracket's
-// work-group per tensor counts: 8 x 64 of 64 190 -> 203, 4 x 2000 of 5 271 -> 311, 40000 of one or two 551 -> 755.
+// 8 workers 641 -> 420.  With the step, one read for tensors of 1024 pieces on -> of 128 on: 2 x 64 of 500 832 -> 690,
+// 1 x 64 of 1000 1279 -> 1128, 8 x 60 of 130 510 -> 398, 4 x 100 of 300 1145 -> 928.  Below the average, where the
+// bracket's work-group per tensor counts (quantizer): 8 x 64 of 64 190 -> 203, 4 x 2000 of 5 271 -> 311, 40000 of one or
+// two 551 -> 755.
 constexpr int64_t kSegOneReadPieces = 32768, kSegOneReadMean = 128;
 size_t segments_one_read_bytes(const qa_segment_plan* P, int M) {
   if (P->n_pieces < kSegLong || P->n_pieces * M < kSegOneReadPieces || P->n_pieces < kSegOneReadMean * P->n_seg) return 0;

@@ -222,6 +222,39 @@ def test_long_tensors_read_once_match_oracle(M):
         close(host(a)[f_covered(f)], r[f_covered(f)], "state")
 
 
+@pytest.mark.parametrize("kind", ["gauss", "misled", "sparse"])
+def test_tensors_on_either_side_of_the_sampled_lengths_match_oracle(kind):
+    """Lists read once: tensors around 128, 256 and 512 pieces (sampled every 4th, 8th, 16th piece, shorter ones not at
+    all), whole tiles and not; with the sampled pieces larger than the others the threshold leaves its bracket."""
+    lengths = [5, 127 * 4096, 128 * 4096, 130 * 4096 - 9, 255 * 4096 + 7, 256 * 4096, 511 * 4096 - 80, 512 * 4096 + 1, 150 * 4096]
+    f = Flat.__new__(Flat)
+    f.begin, f.length, f.d = layout_of(lengths)
+    f.M, f.nseg = 16, len(lengths)
+    f.L = qa.Layout.make(f.d, f.M, 0, 0.75, None, f.nseg)
+    f.table = torch.zeros(qa.qa_segment_plan_bytes(f.d, f.nseg), dtype=torch.uint8, device=DEV)
+    f.plan = qa.qa_segment_plan_init(f.d, f.begin, f.length, f.table)
+    f.gs = (f.d + 3) // 4 * 4
+    assert f.plan.n_pieces * f.M >= 32768 and f.plan.n_pieces >= 128 * f.nseg
+    rng = np.random.default_rng(len(kind))
+    g = rng.standard_normal((f.M, f.d), dtype=np.float32)
+    if kind == "sparse":
+        g *= rng.random((f.M, f.d), dtype=np.float32) < 0.05
+    if kind == "misled":
+        for b, n in zip(f.begin, f.length):
+            t0, pieces = b // 4096, (b + n - 1) // 4096 - b // 4096 + 1
+            stride = 16 if pieces >= 512 else 8 if pieces >= 256 else 4
+            for k in range(pieces // stride):
+                p = k * stride + k * 29 % stride
+                if 0 < p < pieces - 1:
+                    g[::2, (t0 + p) * 4096:(t0 + p + 1) * 4096] *= 1.5
+    c_ref, s_ref, th_ref = oracle.quantize_pack_segments(g, f.begin, f.length)
+    codes, scales, th = f.gpu_quantize(g)
+    # sums in another order: thresholds and scales within an ulp, codes those of the thresholds
+    assert np.allclose(host(th), th_ref, rtol=1.3e-7, atol=0)
+    assert np.allclose(host(scales), s_ref, rtol=1.3e-7, atol=0)
+    check_codes(f, g, host(codes).view(np.uint32), host(th), c_ref, th_ref)
+
+
 def test_threshold_of_a_long_tensor_does_not_depend_on_the_workspace():
     """The one-read and the two-read form add the magnitudes in the same order: a gradient whose threshold, a tie
     between two binary32 numbers, is decided by the order of a few additions."""
