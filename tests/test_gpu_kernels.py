@@ -1316,6 +1316,26 @@ def test_long_quantizer_lists_what_is_open(d):
         assert np.array_equal(host(out[0][0]).view(np.uint32), c_ref)
 
 
+# buckets of 2 .. 16 tiles are held in registers; 65537 components under one scale are the first that are not
+@pytest.mark.parametrize("bucket,d", [(8192, 8193), (8192, 5 * 8192 - 7), (16384, 3 * 16384), (16384, 16384 + 4097), (32768, 2 * 32768 + 4096),
+                                      (32768, 20481), (65536, 3 * 65536 - 4095), (65536, 65536 + 1), (65536, 40000),
+                                      (0, 4097), (0, 8192), (0, 12291), (0, 32769), (0, 65535), (0, 65536), (0, 65537)])
+def test_buckets_held_in_registers_match_oracle_and_the_two_passes(bucket, d):
+    """Incomplete last tiles and buckets, buckets longer than the vector; with the thresholds handed in, the passes over
+    the gradient give the same message bit for bit (sums added in the same order), also of infinities and NaN."""
+    rng = np.random.default_rng(d)
+    M = 3
+    g = (rng.standard_normal((M, d)) * 10.0 ** rng.integers(-3, 3, (M, d))).astype(np.float32)
+    codes, scales, th, L = gpu_quantize_pack(g, bucket)
+    quantizer_parity(g, bucket, codes, scales, th, (bucket, d))
+    assert (codes[:, L.words:] == 0xFFFFFFFF).all() and (scales[:, L.n_buckets:] == -7).all()
+    g[0, 7], g[1, d - 1], g[2, :] = np.inf, np.nan, 0
+    codes, scales, th, L = gpu_quantize_pack(g, bucket)
+    other = gpu_quantize_pack(g, bucket, thresholds=th[:, :L.n_buckets])
+    assert np.array_equal(codes, other[0])
+    assert np.array_equal(scales.view(np.uint32), other[1].view(np.uint32))
+
+
 # both kernels of the steps: up to 512 tiles, 16 workers and 2048 tiles times workers a work-group of 1024 threads takes a
 # tile, beyond them the one with tables
 @pytest.mark.parametrize("tiles,M,bucket,requant", [
