@@ -81,9 +81,9 @@ __device__ __forceinline__ void load_tile_stream(const float* __restrict__ g, in
   }
 }
 
-// The thread's word of the tile (word j*64 + t/4 for j = t & 3).
-__device__ __forceinline__ void store_code_word(uint32_t* __restrict__ codes_m, int64_t tile, int64_t W, uint32_t word) {
-  const int t = threadIdx.x;
+// The word of the tile's thread t (word j*64 + t/4 for j = t & 3).
+__device__ __forceinline__ void store_code_word(uint32_t* __restrict__ codes_m, int64_t tile, int64_t W, uint32_t word,
+                                                int t) {
   const int64_t widx = tile * kTileWords + (t & 3) * 64 + (t >> 2);
   if (widx < W) store_through(codes_m + widx, word);
 }
@@ -258,7 +258,7 @@ __device__ __forceinline__ void quantize_buckets_of_tile(const QuantArgs& a, int
       add_in_lanes(S2[j], (double)fabsf(v[j][e]), keep[j][e]);
     }
   const uint32_t mine = GIVEN && __any(mine_delta < 0.0f) ? code_word_compared(v, Delta) : code_word(v, keep);
-  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, mine);
+  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, mine, threadIdx.x);
   double sum;
   uint32_t count;
   // a lane's word holds the quad's components of slice l & 3; what is kept has a field other than 0
@@ -335,7 +335,7 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, int64_t tile, 
   // v > Delta or v < -Delta  <=>  |v| > Delta, unless a caller hands in a threshold below 0 (uniform)
   const float Delta4[4] = {Delta, Delta, Delta, Delta};
   const uint32_t mine = GIVEN && Delta < 0.0f ? code_word_compared(v, Delta4) : code_word(v, keep);
-  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, mine);
+  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, mine, threadIdx.x);
 
   const double s2 = wave_sum_f64((s2j[0] + s2j[1]) + (s2j[2] + s2j[3]));
   if ((t % kWave) == 0) { lds_s2[t / kWave] = s2; lds_c[t / kWave] = wave_cnt; }
@@ -1054,7 +1054,7 @@ __global__ __launch_bounds__(kThreads) void quantize_codes_partial_kernel(QuantA
   load_tile_stream(a.g + (int64_t)m * a.g_stride, a.d, tile, v);
   double s = 0.0;
   uint32_t c = 0;
-  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, code_tile(v, D, s, c));
+  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, code_tile(v, D, s, c), threadIdx.x);
   s = wave_sum_f64(s);
   if ((threadIdx.x % kWave) == 0) { lds_d[threadIdx.x / kWave] = s; lds_u[threadIdx.x / kWave] = c; }
   __syncthreads();
@@ -1090,22 +1090,14 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void quantize_scale_finalize
 // one bucket only, and nothing is read while it is coded.  Two passes -> held, us, at 2^26 x 4 components: buckets of
 // 8192 495 -> 178, 16384 415 -> 186, 32768 372 -> 169, 65536 351 -> 229; 3 000 001 x 8: 48 -> 18, 40 -> 19, 37 -> 19,
 // 35 -> 27; one scale for 5000 .. 65 000 components, 1 or 16 workers: 16 -> 5 .. 10.
+template <int TILES> constexpr int kHeldSide = TILES < 4 ? TILES : 4;   // tiles side by side
+// Element e of float4 group j of thread t of tile tile0 + u * side by side + side; beyond d +0.
 template <int TILES>
-__global__ __launch_bounds__((TILES < 4 ? TILES : 4) * kThreads, TILES < 16 ? 8 : 4) void quantize_held_kernel(QuantArgs a) {
-  constexpr int kSide = TILES < 4 ? TILES : 4, kEach = TILES / kSide;
-  __shared__ double lds_s1[TILES][kWaves], lds_s2[TILES][kWaves];
-  __shared__ uint32_t lds_c[TILES][kWaves];
-  const int t = threadIdx.x % kThreads, lane = threadIdx.x % kWave;
-  const int side = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kThreads);
-  const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
-  const int64_t k = blockIdx.x, tile0 = k * a.tiles_per_bucket;
-  const int m = blockIdx.y;
-  const float* __restrict__ g = a.g + (int64_t)m * a.g_stride;
-  const int64_t left = a.ntiles - tile0;
-  const int tiles = (int)(left < a.tiles_per_bucket ? left : a.tiles_per_bucket);   // TILES at most
+__device__ __forceinline__ void load_held(const float* __restrict__ g, int64_t d, int64_t tile0, int side, int t,
+                                          float (&v)[TILES / kHeldSide<TILES>][4][4]) {
+  constexpr int kSide = kHeldSide<TILES>, kEach = TILES / kSide;
   typedef float floatx4 __attribute__((ext_vector_type(4)));
-  float v[kEach][4][4];
-  if ((tile0 + TILES) * kTile <= a.d) {                  // uniform
+  if ((tile0 + TILES) * kTile <= d) {                  // uniform
 #pragma unroll
     for (int u = 0; u < kEach; ++u)
 #pragma unroll
@@ -1120,15 +1112,32 @@ __global__ __launch_bounds__((TILES < 4 ? TILES : 4) * kThreads, TILES < 16 ? 8 
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int64_t i = (tile0 + u * kSide + side) * kTile + 4 * (int64_t)(j * kThreads + t);
-        if (i + 3 < a.d) {
+        if (i + 3 < d) {
           const floatx4 q = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g + i));
           v[u][j][0] = q.x; v[u][j][1] = q.y; v[u][j][2] = q.z; v[u][j][3] = q.w;
         } else {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[u][j][e] = i + e < a.d ? g[i + e] : 0.0f;
+          for (int e = 0; e < 4; ++e) v[u][j][e] = i + e < d ? g[i + e] : 0.0f;
         }
       }
   }
+}
+
+template <int TILES>
+__global__ __launch_bounds__(kHeldSide<TILES> * kThreads, TILES < 16 ? 8 : 4) void quantize_held_kernel(QuantArgs a) {
+  constexpr int kSide = kHeldSide<TILES>, kEach = TILES / kSide;
+  __shared__ double lds_s1[TILES][kWaves], lds_s2[TILES][kWaves];
+  __shared__ uint32_t lds_c[TILES][kWaves];
+  const int t = threadIdx.x % kThreads, lane = threadIdx.x % kWave;
+  const int side = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kThreads);
+  const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int64_t k = blockIdx.x, tile0 = k * a.tiles_per_bucket;
+  const int m = blockIdx.y;
+  const float* __restrict__ g = a.g + (int64_t)m * a.g_stride;
+  const int64_t left = a.ntiles - tile0;
+  const int tiles = (int)(left < a.tiles_per_bucket ? left : a.tiles_per_bucket);   // TILES at most
+  float v[kEach][4][4];
+  load_held<TILES>(g, a.d, tile0, side, t, v);
 #pragma unroll
   for (int u = 0; u < kEach; ++u) {
     double s = 0.0;
@@ -1159,9 +1168,7 @@ __global__ __launch_bounds__((TILES < 4 ? TILES : 4) * kThreads, TILES < 16 ? 8 
     uint32_t c = 0;
     const int of = u * kSide + side;
     if (of < tiles) {                                    // uniform in the wave
-      const uint32_t word = code_tile(v[u], Delta, s, c);
-      const int64_t at = (tile0 + of) * kTileWords + (t & 3) * 64 + (t >> 2);
-      if (at < a.W) store_through(codes + at, word);
+      store_code_word(codes, tile0 + of, a.W, code_tile(v[u], Delta, s, c), t);
       s = wave_sum_f64(s);
     }
     if (lane == 0) { lds_s2[of][wave] = s; lds_c[of][wave] = c; }
@@ -1289,7 +1296,7 @@ __global__ __launch_bounds__(kThreads) void quantize_bracketed_kernel(QuantArgs 
     }
     word |= quad_transpose(marks);
   }
-  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, word);
+  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, word, threadIdx.x);
   if (LISTED) wave_cnt |= list_open(open, a.open + (at * kWaves + t / kWave) * kOpenSlots) << 16;
   const double S1 = wave_sum_f64(s1), S2 = wave_sum_f64(s2);
   if (t % kWave == 0) { lds_s1[t / kWave] = S1; lds_s2[t / kWave] = S2; lds_c[t / kWave] = wave_cnt; }
@@ -1308,7 +1315,7 @@ __device__ __forceinline__ void code_again(const QuantArgs& a, int m, int64_t ti
   load_tile_stream(a.g + (int64_t)m * a.g_stride, a.d, tile, v);
   double s = 0.0;
   uint32_t c = 0;
-  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, code_tile(v, D, s, c));
+  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, code_tile(v, D, s, c), threadIdx.x);
   s = wave_sum_f64(s);
   if (threadIdx.x % kWave == 0) { wave_sum[threadIdx.x / kWave] = s; wave_cnt[threadIdx.x / kWave] = c; }
 }
@@ -1539,8 +1546,7 @@ __device__ __forceinline__ uint32_t to_u32_saturated(float x) {
 // Bound by instruction issue, half of it Philox's, and memory.  2^28 x 4 components, bucket 4096, with margins in binary32
 // and fields from selects 800 us, now 713; 2^20 x 16 14.6 -> 12.7, buckets of 256, 2^26 x 4 285 -> 264.
 __device__ __forceinline__ void stochastic_codes(const StochArgs& a, const float v[4][4],
-                                                 const float sj[4], int64_t tile, int m) {
-  const int t = threadIdx.x;
+                                                 const float sj[4], int64_t tile, int m, int t) {
   float vv[4][4];
   uint64_t kept[4][4];
   const uint64_t grp0 = (uint64_t)tile * (kTile / 4);      // a multiple of 1024: no carry from the thread's part
@@ -1566,7 +1572,7 @@ __device__ __forceinline__ void stochastic_codes(const StochArgs& a, const float
       for (int e = 0; e < 4; ++e) kept[j][e] = __ballot((float)(r[e] >> 8) * 0x1p-24f < fabsf(v[j][e]) / s);
     }
   }
-  store_code_word(a.q.codes + (int64_t)m * a.q.code_stride, tile, a.q.W, code_word(vv, kept));
+  store_code_word(a.q.codes + (int64_t)m * a.q.code_stride, tile, a.q.W, code_word(vv, kept), t);
 }
 
 // bucket == tile (4096, or one scale per vector with d <= 4096): one pass
@@ -1583,7 +1589,7 @@ __global__ __launch_bounds__(kThreads) void quantize_stochastic_tile_kernel(Stoc
   for (int w = 0; w < kWaves; ++w) s = lds_m[w] > s ? lds_m[w] : s;
   if (threadIdx.x == 0) a.q.scales[(int64_t)m * a.q.scale_stride + tile] = s;
   const float sj[4] = {s, s, s, s};
-  stochastic_codes(a, v, sj, tile, m);
+  stochastic_codes(a, v, sj, tile, m, threadIdx.x);
 }
 
 // Maximum over aligned segments of `seg` consecutive threads (a power of two, 16 <= seg <= 256);
@@ -1638,14 +1644,43 @@ __global__ __launch_bounds__(kThreads) void quantize_stochastic_bucket_kernel(St
       }
     }
   }
-  stochastic_codes(a, v, sj, tile, m);
+  stochastic_codes(a, v, sj, tile, m, threadIdx.x);
 }
 
-// bucket > 4096 or one scale per large vector: the maxima fold into scales[] (which an earlier launch zeroed) with
+// buckets of 2 .. 16 tiles: held as by quantize_held_kernel, the scale is the largest magnitude.  Three launches and two
+// reads -> one, us, at 2^26 x 4 components: buckets of 8192 328 -> 196, 16384 329 -> 221, 32768 331 -> 198, 65536 331 -> 247
+// (one work-group's bucket fills the registers of a compute unit); 3 000 001 x 8: 34 -> 20, 34 -> 24, 36 -> 24, 36 -> 32;
+// one scale for 5000 .. 30 000 components 14 -> 5 .. 7, for 65 000 12 on either way.
+template <int TILES>
+__global__ __launch_bounds__(kHeldSide<TILES> * kThreads, TILES < 16 ? 8 : 4) void quantize_stochastic_held_kernel(StochArgs a) {
+  constexpr int kSide = kHeldSide<TILES>, kEach = TILES / kSide;
+  __shared__ float lds_m[kSide * kWaves];
+  const int t = threadIdx.x % kThreads;
+  const int side = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kThreads);
+  const int64_t k = blockIdx.x, tile0 = k * a.q.tiles_per_bucket;
+  const int m = blockIdx.y;
+  float v[kEach][4][4];
+  load_held<TILES>(a.q.g + (int64_t)m * a.q.g_stride, a.q.d, tile0, side, t, v);
+  float s = wave_max_f32(abs_max(v[0][0], kEach * 16));
+  if (threadIdx.x % kWave == 0) lds_m[threadIdx.x / kWave] = s;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kSide * kWaves; ++w) s = lds_m[w] > s ? lds_m[w] : s;
+  s = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(s)));
+  if (threadIdx.x == 0) a.q.scales[(int64_t)m * a.q.scale_stride + k] = s;
+  const float sj[4] = {s, s, s, s};
+#pragma unroll
+  for (int u = 0; u < kEach; ++u) {
+    const int of = u * kSide + side;
+    if (of < a.q.tiles_per_bucket && tile0 + of < a.q.ntiles) stochastic_codes(a, v[u], sj, tile0 + of, m, t);
+  }
+}
+
+// longer buckets or one scale per large vector: the maxima fold into scales[] (which an earlier launch zeroed) with
 // integer atomic max on the bit pattern of the non-negative float; then the codes, with the finished scale.
 // A work-group takes `span` consecutive tiles of a bucket and its maximum goes to the scale once: additions to one address
 // follow each other at 42 ns, which was nearly all of the time with one per wave and tile (one scale per vector,
-// 2^26 x 4 components 3166 us, now 350; 3 000 001 x 8 288 -> 43; buckets of 65536, 2^26 x 4 373 -> 330).
+// 2^26 x 4 components 3166 us, now 350; 3 000 001 x 8 288 -> 43).
 __global__ __launch_bounds__(kThreads) void quantize_stochastic_max_kernel(StochArgs a) {
   __shared__ float lds_m[kWaves];
   const int64_t per_bucket = (a.q.tiles_per_bucket + a.span - 1) / a.span;
@@ -1679,7 +1714,7 @@ __global__ __launch_bounds__(kThreads) void quantize_stochastic_codes_kernel(Sto
   load_tile_stream(a.q.g + (int64_t)m * a.q.g_stride, a.q.d, tile, v);
   const float s = a.q.scales[(int64_t)m * a.q.scale_stride + tile / a.q.tiles_per_bucket];
   const float sj[4] = {s, s, s, s};
-  stochastic_codes(a, v, sj, tile, m);
+  stochastic_codes(a, v, sj, tile, m, threadIdx.x);
 }
 
 __global__ __launch_bounds__(kThreads) void zero_scales_kernel(float* scales, int64_t stride, int64_t nb) {
@@ -2028,6 +2063,14 @@ extern "C" int qa_quantize_pack_stochastic(const qa_layout* layout, const float*
   }
   a.q.tiles_per_bucket = layout->bucket ? layout->bucket / kTile : a.q.ntiles;
   if (a.q.tiles_per_bucket > a.q.ntiles) a.q.tiles_per_bucket = a.q.ntiles;
+  if (a.q.tiles_per_bucket <= 16) {
+    const dim3 buckets((unsigned)a.q.nb, (unsigned)layout->M), block_of_4(4 * kThreads);
+    if (a.q.tiles_per_bucket <= 2) hipLaunchKernelGGL(quantize_stochastic_held_kernel<2>, buckets, dim3(2 * kThreads), 0, stream, a);
+    else if (a.q.tiles_per_bucket <= 4) hipLaunchKernelGGL(quantize_stochastic_held_kernel<4>, buckets, block_of_4, 0, stream, a);
+    else if (a.q.tiles_per_bucket <= 8) hipLaunchKernelGGL(quantize_stochastic_held_kernel<8>, buckets, block_of_4, 0, stream, a);
+    else hipLaunchKernelGGL(quantize_stochastic_held_kernel<16>, buckets, block_of_4, 0, stream, a);
+    return launch_status();
+  }
   hipLaunchKernelGGL(zero_scales_kernel, dim3((unsigned)((a.q.nb + kThreads - 1) / kThreads),
                                               (unsigned)layout->M), block, 0, stream, scales,
                      layout->scale_stride, a.q.nb);

@@ -613,6 +613,29 @@ def test_stochastic_quantizer_matches_oracle(d, M, bucket):
     assert d < 100 or not torch.equal(c2, codes)    # another step, other draws
 
 
+# buckets of 2 .. 16 tiles are held in registers; 65537 components under one scale are the first that are not
+@pytest.mark.parametrize("bucket,d", [(8192, 5 * 8192 - 7), (16384, 16384 + 4097), (32768, 2 * 32768 + 4096), (32768, 20481),
+                                      (65536, 3 * 65536 - 4095), (65536, 40000), (0, 4097), (0, 12291), (0, 32769),
+                                      (0, 65536), (0, 65537)])
+def test_stochastic_quantizer_of_buckets_held_in_registers_matches_oracle(bucket, d):
+    """Incomplete last tiles and buckets, buckets longer than the vector, a bucket of zeros, NaN."""
+    rng = np.random.default_rng(d)
+    M, seed, step = 3, 0xFEDCBA9876543210, 5
+    g = rng.standard_normal((M, d)).astype(np.float32)
+    g[0, :4096], g[1, d - 1], g[2, :65536] = 0, np.nan, 0
+    oc, osc = oracle.quantize_pack_stochastic(g, bucket=bucket, seed=seed, step=step)
+    L, gs = qa.Layout.make(d, M, bucket), (d + 3) // 4 * 4 + 4
+    gp = np.full((M, gs), 9, np.float32)                  # padding belongs to nobody
+    gp[:, :d] = g
+    codes = torch.full((M, L.code_stride), -1, dtype=torch.int32, device=DEV)
+    scales = torch.full((M, L.scale_stride), -7.0, dtype=torch.float32, device=DEV)
+    qa.qa_quantize_pack_stochastic(L, dev(gp), gs, codes, scales, seed, step)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(scales)[:, :L.n_buckets], osc)
+    assert np.array_equal(host(codes).view(np.uint32)[:, :L.words], oc)
+    assert (host(codes)[:, L.words:] == -1).all() and (host(scales)[:, L.n_buckets:] == -7).all()
+
+
 @pytest.mark.parametrize("bucket", [64, 256, 2048, 4096, 8192])
 def test_stochastic_quantizer_at_the_ends_of_binary32(bucket):
     """Scales whose reciprocal is not a normal number (below 2^-126, above 2^126), around those ends, infinite."""
