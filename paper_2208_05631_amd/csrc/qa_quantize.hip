@@ -2075,8 +2075,8 @@ extern "C" int qa_quantize_pack_stochastic(const qa_layout* layout, const float*
                                               (unsigned)layout->M), block, 0, stream, scales,
                      layout->scale_stride, a.q.nb);
   constexpr int64_t kMaxGroups = 1024;                   // some work-groups per compute unit, up to 16 tiles each
-  const int64_t tiles = a.q.ntiles * layout->M, longest = a.q.tiles_per_bucket < 16 ? a.q.tiles_per_bucket : 16;
-  a.span = (int)(tiles / kMaxGroups < 1 ? 1 : (tiles / kMaxGroups < longest ? tiles / kMaxGroups : longest));
+  const int64_t tiles = a.q.ntiles * layout->M;
+  a.span = (int)(tiles / kMaxGroups < 1 ? 1 : (tiles / kMaxGroups < 16 ? tiles / kMaxGroups : 16));
   const int64_t groups = a.q.nb * ((a.q.tiles_per_bucket + a.span - 1) / a.span);
   hipLaunchKernelGGL(quantize_stochastic_max_kernel, dim3((unsigned)groups, (unsigned)layout->M), block, 0, stream, a);
   hipLaunchKernelGGL(quantize_stochastic_codes_kernel, grid, block, 0, stream, a);
