@@ -6,7 +6,8 @@
 //
 //   bucket <= 4096 : one kernel; sums, threshold, scale and codes of a tile's buckets are
 //                    formed in registers/LDS; the gradient is read once (4 B/elem + 0.25 B out).
-//   bucket  > 4096 or 0 (whole vector): tile partial sums -> finalize threshold -> codes and
+//   up to 65536    : the same with a larger work-group per bucket.
+//   longer buckets or 0 (whole vector): tile partial sums -> finalize threshold -> codes and
 //                    tile partial (count, sum) -> finalize scale; the gradient is read twice, or,
 //                    for long buckets, once: a sample brackets the threshold beforehand.
 #include <mutex>
