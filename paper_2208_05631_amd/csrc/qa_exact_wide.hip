@@ -420,7 +420,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(CR
 //   pass      all components, once: those above the bracket are coded as kept, all others as 0, and those inside
 //             are listed with their places.  Its histogram is finest around the bracket.  (With four standard errors
 //             to a side the list holds a fifth less than with five, and since what is listed is coded 0 until it is
-//             settled, only its kept components, some half, are atomics then: 27.7 to 11.9 us for 2^26 Gaussian
+//             settled, only its kept components, some half, are atomics then: 27.7 to 11.9 us for 2^26 x 4 Gaussian
 //             components, the whole call 316 to 303 us; the wider bracket 307.)
 //   prove     the scan's bounds show that no cut outside the bracket can be the optimum, or the levels go on over the
 //             whole gradient from the bins that survive.
