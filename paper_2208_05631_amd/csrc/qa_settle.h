@@ -3,6 +3,7 @@
 // Internal to libqadagrad.
 #pragma once
 #include "qa_common.h"
+#include "qa_open_group.h"
 
 namespace qa {
 
@@ -69,12 +70,13 @@ __device__ __forceinline__ uint32_t list_open(const uint64_t (&open)[4][4], uint
 
 // Looks the open components of groups list[first], list[first + stride], .. (n in all) up: what threshold D keeps of them
 // is added to s and c, its codes join the tile's words, where the one pass has left 00.  (Magnitudes inside a bracket
-// share their units of the last place: their binary64 sum is exact, in any order.)  live: components of the tile from
-// here on, those beyond belong to nobody.  AHEAD groups are requested together.
+// share their units of the last place: their binary64 sum is exact, in any order.)  live: components of the row from
+// the tile's first on, those beyond belong to nobody and are not read.  AHEAD groups are requested together.
 template <int AHEAD>
 __device__ __forceinline__ void settle_listed(const uint16_t* __restrict__ list, uint32_t first, uint32_t stride,
                                               uint32_t n, const float* __restrict__ g, int64_t live, float2 band, float D,
                                               uint32_t* words, double& s, uint32_t& c) {
+  const uint32_t here = live < kTile ? (uint32_t)live : (uint32_t)kTile;
   for (uint32_t i0 = first; i0 < n; i0 += AHEAD * stride) {
     uint32_t group[AHEAD];
     float4 q[AHEAD];
@@ -82,7 +84,7 @@ __device__ __forceinline__ void settle_listed(const uint16_t* __restrict__ list,
     for (int k = 0; k < AHEAD; ++k) group[k] = i0 + k * stride < n ? list[i0 + k * stride] : 0u;
 #pragma unroll
     for (int k = 0; k < AHEAD; ++k)
-      q[k] = i0 + k * stride < n ? *reinterpret_cast<const float4*>(g + 4 * group[k]) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      q[k] = i0 + k * stride < n ? load_group<float4>(g, group[k], here) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
     for (int k = 0; k < AHEAD; ++k) {
       const float x[4] = {q[k].x, q[k].y, q[k].z, q[k].w};
@@ -90,7 +92,7 @@ __device__ __forceinline__ void settle_listed(const uint16_t* __restrict__ list,
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float av = fabsf(x[e]);
-        if (av > D && !(av > band.y) && 4 * group[k] + e < live) {   // D >= band.x
+        if (av > D && !(av > band.y)) {                  // D >= band.x >= 0
           s += (double)av;
           ++c;
           byte |= ternary_field(x[e], D) << (2 * e);
