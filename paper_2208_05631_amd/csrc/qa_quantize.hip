@@ -31,6 +31,7 @@ struct QuantArgs {
   int log2b;               // log2(bucket); unused when bucket == 0
   float thr_coef;
   int thresh_given;
+  int through;             // code words go through the cache at once: words_go_through()
   // two-pass path
   double* part_sum;        // [M][ntiles]
   uint32_t* part_cnt;      // [M][ntiles]
@@ -82,13 +83,29 @@ __device__ __forceinline__ void load_tile_stream(const float* __restrict__ g, in
   }
 }
 
+// The kernels that code a tile per work-group (quantize_tile, quantize_buckets_of_tile, quantize_codes_partial_kernel,
+// quantize_bracketed_kernel) store 64 bytes of words side by side.  Through the cache if these are whole: every worker's
+// row of words begins on a multiple of 64 bytes; of other rows from 2^27 components in all (512 MB) on.  There each store
+// leaves two partial pieces, which cost more than late evictions as long as the last-level cache takes part.  Other
+// gradients in each call, 7 workers, us, stores left in the cache / through it, rows on 64 bytes: quantizer, 4096: 128 MB
+// 23.6 / 23.8, 256 45.8 / 44.6, 512 91.2 / 87.2; with the step: 4096, 96 MB 33.2 / 33.9, 256 79.5 / 77.9, 512 152 / 147;
+// one scale, 96 MB 55.8 / 56.3, 256 130 / 128, 512 (read once) 182 / 178.  Other rows: quantizer, 4096: 96 MB 18.1 / 19.5,
+// 192 34.2 / 35.6, 384 68.6 / 68.3, 512 91.6 / 89.9, 1024 184 / 178; 256: 128 MB 24.0 / 24.9, 1024 187 / 181; with the
+// step: 4096, 96 MB 33.4 / 35.1, 256 81.0 / 82.4, 512 154 / 155; one scale, 128 MB 72.9 / 74.6, 320 160 / 161, 512
+// 185 / 185.  Kernels whose work-groups hold more tiles or that issue more per word are not slower with such stores at any
+// size (buckets of 8192 on, the stochastic rule, the exact one).
+constexpr int64_t kThroughFrom = int64_t(1) << 27;
+static bool words_go_through(const qa_layout* L, const uint32_t* codes) {
+  const int64_t between = L->M > 1 ? 4 * L->code_stride : 0;
+  return ((reinterpret_cast<uintptr_t>(codes) | (uintptr_t)between) & 63u) == 0 || L->d > kThroughFrom / L->M;
+}
+
 // The word of the tile's thread t (word j*64 + t/4 for j = t & 3).
-template <bool THROUGH = true>
 __device__ __forceinline__ void store_code_word(uint32_t* __restrict__ codes_m, int64_t tile, int64_t W, uint32_t word,
-                                                int t) {
+                                                int t, bool through = true) {
   const int64_t widx = tile * kTileWords + (t & 3) * 64 + (t >> 2);
   if (widx >= W) return;
-  if (THROUGH) store_through(codes_m + widx, word);
+  if (through) store_through(codes_m + widx, word);      // uniform
   else codes_m[widx] = word;
 }
 
@@ -264,7 +281,7 @@ __device__ __forceinline__ void quantize_buckets_of_tile(const QuantArgs& a, int
   const uint32_t mine = GIVEN && __any(mine_delta < 0.0f) ? code_word_compared(v, Delta) : code_word(v, keep);
   // after the ranking kernel, part of the gradient comes from the last-level cache, and stores through the caches cost
   // more than they save (exact threshold, 5e7 x 2, buckets of 64 / 256: 273.8 / 331.3 us, without 272.0 / 329.2)
-  store_code_word<!GIVEN>(a.codes + (int64_t)m * a.code_stride, tile, a.W, mine, threadIdx.x);
+  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, mine, threadIdx.x, !GIVEN && a.through);
   double sum;
   uint32_t count;
   // a lane's word holds the quad's components of slice l & 3; what is kept has a field other than 0
@@ -341,7 +358,7 @@ __device__ __forceinline__ void quantize_tile(const QuantArgs& a, int64_t tile, 
   // v > Delta or v < -Delta  <=>  |v| > Delta, unless a caller hands in a threshold below 0 (uniform)
   const float Delta4[4] = {Delta, Delta, Delta, Delta};
   const uint32_t mine = GIVEN && Delta < 0.0f ? code_word_compared(v, Delta4) : code_word(v, keep);
-  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, mine, threadIdx.x);
+  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, mine, threadIdx.x, a.through);
 
   const double s2 = wave_sum_f64((s2j[0] + s2j[1]) + (s2j[2] + s2j[3]));
   if ((t % kWave) == 0) { lds_s2[t / kWave] = s2; lds_c[t / kWave] = wave_cnt; }
@@ -1060,7 +1077,7 @@ __global__ __launch_bounds__(kThreads) void quantize_codes_partial_kernel(QuantA
   load_tile_stream(a.g + (int64_t)m * a.g_stride, a.d, tile, v);
   double s = 0.0;
   uint32_t c = 0;
-  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, code_tile(v, D, s, c), threadIdx.x);
+  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, code_tile(v, D, s, c), threadIdx.x, a.through);
   s = wave_sum_f64(s);
   if ((threadIdx.x % kWave) == 0) { lds_d[threadIdx.x / kWave] = s; lds_u[threadIdx.x / kWave] = c; }
   __syncthreads();
@@ -1302,7 +1319,7 @@ __global__ __launch_bounds__(kThreads) void quantize_bracketed_kernel(QuantArgs 
     }
     word |= quad_transpose(marks);
   }
-  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, word, threadIdx.x);
+  store_code_word(a.codes + (int64_t)m * a.code_stride, tile, a.W, word, threadIdx.x, a.through);
   if (LISTED) wave_cnt |= list_open(open, a.open + (at * kWaves + t / kWave) * kOpenSlots) << 16;
   const double S1 = wave_sum_f64(s1), S2 = wave_sum_f64(s2);
   if (t % kWave == 0) { lds_s1[t / kWave] = S1; lds_s2[t / kWave] = S2; lds_c[t / kWave] = wave_cnt; }
@@ -1785,6 +1802,7 @@ int quantize_launch(const qa_layout* L, const float* g, int64_t g_stride, uint32
   a.scales = scales; a.thresholds = thresholds; a.scale_stride = L->scale_stride;
   a.thr_coef = L->thr_coef;
   a.thresh_given = (flags & QA_THRESH_GIVEN) ? 1 : 0;
+  a.through = words_go_through(L, codes) ? 1 : 0;
   a.ntiles = tiles_of(L->d);
   a.nb = buckets_of(L->d, L->bucket);
   const dim3 block(kThreads);

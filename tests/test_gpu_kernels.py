@@ -1436,3 +1436,27 @@ def test_counted_combinations_with_crowded_bins_and_reserved_codes(tiles, M):
         torch.cuda.synchronize()
         assert np.array_equal(host(qs), s_ref) and np.array_equal(host(qt), t_ref)
         assert np.array_equal(host(q).view(np.uint32), c_ref)
+
+
+# rows of code words that begin on 64 bytes are stored through the cache, others (below 2^27 components) not
+@pytest.mark.parametrize("d", [4096 * 65 - 9, 4096 * 33 + 4])
+@pytest.mark.parametrize("bucket", [0, 256, 4096])
+@pytest.mark.parametrize("first,between", [(0, 0), (0, 3), (16, 0), (1, 0), (5, 8)])
+def test_code_words_of_rows_that_begin_anywhere(d, bucket, first, between):
+    """The message does not depend on where the rows begin, and the words around a row stay as they were; two reads with
+    one scale."""
+    M = 5
+    g = make_grad("gauss", M, d, seed=d % 97)
+    L = qa.Layout.make(d, M, bucket, code_stride=(d + 15) // 256 * 16 + 16 + between)
+    gs = (d + 3) // 4 * 4
+    gp = np.zeros((M, gs), np.float32)
+    gp[:, :d] = g
+    buf = torch.full((first + M * L.code_stride + 64,), -1, dtype=torch.int32, device=DEV)
+    scales, th = torch.zeros((2, M, L.scale_stride), dtype=torch.float32, device=DEV)
+    qa.qa_quantize_pack(L, dev(gp), gs, buf[first:], scales, th, 0, workspace(qa.qa_workspace_bytes(L, qa.QA_OP_QUANTIZE)))
+    torch.cuda.synchronize()
+    buf = host(buf).view(np.uint32)
+    rows = buf[first:first + M * L.code_stride].reshape(M, -1)
+    quantizer_parity(g, bucket, rows, host(scales), host(th), (bucket, d, first, between))
+    assert (buf[:first] == 0xFFFFFFFF).all() and (buf[first + M * L.code_stride:] == 0xFFFFFFFF).all()
+    assert (rows[:, L.words:] == 0xFFFFFFFF).all()
