@@ -1453,14 +1453,42 @@ static void launch_lut(const StepArgs& a, dim3 grid, dim3 block, hipStream_t str
   hipLaunchKernelGGL((step_lut_kernel<MODE, TRACK_Z, RQ, NGT, SPARSE>), grid, block, 0, stream, a);
 }
 
+// Whether step_few_kernel takes a launch of so many tiles (or pieces).  Captured calls with other messages and state in
+// each, us, the kernel of tables -> this.  (On messages and state that the caches still hold from the call before, the lines
+// would lie at more tiles.)
+// QCMD step with one scale per 4096 / QRDA step with buckets of 256 quantized again: 1 worker 1 tile 6.1 -> 3.3 / 8.3 ->
+// 5.1, 256 tiles 7.4 -> 5.5 / 9.5 -> 7.7, 400 8.4 -> 7.7 / 11.2 -> 10.8; 2 workers 400 tiles 8.5 -> 8.1 / 11.2 -> 11.1, 512
+// 8.9 -> 9.1 / 11.5 -> 12.0; 4 workers 256 tiles (a work-group per compute unit) 7.6 -> 6.5 / 9.6 -> 8.7, 350 8.4 -> 8.5 /
+// 11.2 -> 11.8; 8 workers 200 tiles 8.5 -> 7.3 / 9.5 -> 9.5, 256 8.7 -> 7.8 / 9.8 -> 10.2; 10 workers 170 tiles 8.7 -> 8.2 /
+// 11.1 -> 10.4; 12 workers 100 tiles 8.4 -> 8.3 / 10.7 -> 10.3, 128 8.5 -> 8.6 / 10.8 -> 10.6; 16 workers 25 tiles 7.6 ->
+// 7.1 / 9.5 -> 8.8, 50 7.6 -> 7.8 / 9.7 -> 10.0, 100 8.3 -> 9.5 / 10.5 -> 11.5.
+// QCMD that keeps z, buckets of 1024 quantized again: 8 workers 100 tiles 10.2 -> 10.2, 170 10.5 -> 10.7, 256 10.8 -> 11.7;
+// 12 workers 50 tiles 10.9 -> 10.6, 100 11.8 -> 12.2; 16 workers 25 tiles 10.3 -> 10.3, 50 10.6 -> 12.1.
+// QCMD, buckets of 4096 quantized again (both sums over the work-group): old / new 4 workers 200 tiles 1.03, 256 0.99, 7
+// workers 64 tiles 1.09, 128 0.96, 8 workers 50 tiles 1.00, 64 0.95, 12 workers 25 tiles 1.00, 64 0.90, 14 workers 5 tiles 0.99.
+// The average written out, 1 / 3 / 7 workers: 100 tiles 3.7 -> 2.7 / 4.0 -> 3.6 / 5.0 -> 4.7, 256 3.9 -> 3.2 / 4.3 -> 4.0 /
+// 5.2 -> 5.5; 4 and 8 workers fill the tables: 100 tiles 3.7 -> 3.7 and 4.0 -> 4.6.  Quantized again per 256: 2 workers
+// 256 tiles 5.1 -> 5.0, 4 workers 5 tiles 5.0 -> 5.2; one scale for one tile 1 worker 3.9 -> 4.0, 4 workers 3.9 -> 4.7.  The
+// sums and codes of one scale for more: 2 workers 128 tiles 11.0 -> 10.5, 256 11.6 -> 12.0, 7 workers 100 tiles 12.1 -> 11.9,
+// 200 12.8 -> 14.0, 8 workers 50 tiles 11.2 -> 11.7; the step behind such sums, 8 workers: 50 tiles 18.7 -> 17.2 in all, 128
+// 19.3 -> 20.3.
+template <int MODE, bool TRACK_Z, int RQ>
+static bool few_tiles(const StepArgs& a, int64_t tiles) {
+  const int M = a.M;
+  const int64_t rows = tiles * M;
+  if (MODE == kAggregate) {
+    if (RQ == kRqInTile) return M <= 2 && !a.tile_uniform && tiles <= 256;
+    if (a.gbar && !a.abs_partials) return M <= 7 && tiles <= (M != 4 ? 200 : 128);
+    return M <= 7 && tiles <= (M != 4 ? 128 : 100) && rows <= 700;
+  }
+  if (M > 16 || tiles > (M <= 2 ? 400 : 256)) return false;
+  if (RQ == kRqInTile && a.tile_uniform) return tiles <= 256 && rows <= (M <= 4 ? 800 : M <= 10 ? 400 : M <= 12 ? 300 : 0);
+  if (RQ == kRqInTile && TRACK_Z) return rows <= (M <= 10 ? 800 : 400);
+  if (RQ == kRqGiven && M % 8 == 0) return rows <= 400;
+  return rows <= (M <= 8 && RQ != kRqInTile ? 2048 : M <= 10 ? 1600 : M <= 13 ? 1200 : 640);
+}
+
 // ngt: the NGT of the kernel variant
-// step_few_kernel up to so many tiles (or pieces), workers, and tiles times workers.  QCMD step with one scale per 4096 /
-// QRDA step with buckets of 256 quantized again, us, the kernel of tables -> this: 1 worker 1 tile 6.6 -> 5.9 / 8.3 -> 5.4,
-// 512 tiles 8.4 -> 7.0 / 11.9 -> 10.1; 4 workers 256 tiles 6.9 -> 5.6 / 9.6 -> 7.8, 512 8.3 -> 8.0 / 11.8 -> 11.3;
-// 8 workers 25 tiles 6.5 -> 5.4 / 8.3 -> 7.1, 256 7.2 -> 6.5 / 9.6 -> 8.7, 512 8.6 -> 9.2 / 11.7 -> 12.6; 16 workers
-// 100 tiles 7.7 -> 7.7 / 9.8 -> 9.4, 256 8.2 -> 8.4 / 10.8 -> 10.5; 64 workers 1 tile 11.6 -> 17.9.
-constexpr unsigned kFewTiles = 512;
-constexpr int kFewWorkers = 16, kFewRows = 2048;
 template <int MODE, bool TRACK_Z, int RQ>
 static void launch_one(const StepArgs& a, int ngt, hipStream_t stream) {
   const dim3 grid((unsigned)(a.seg.piece_tile ? a.seg.n_pieces : tiles_of(a.d))), block(kThreads);
@@ -1472,7 +1500,7 @@ static void launch_one(const StepArgs& a, int ngt, hipStream_t stream) {
       return;
     }
   }
-  if (grid.x <= kFewTiles && a.M <= kFewWorkers && (int)grid.x * a.M <= kFewRows) {
+  if (few_tiles<MODE, TRACK_Z, RQ>(a, grid.x)) {
     hipLaunchKernelGGL((step_few_kernel<MODE, TRACK_Z, RQ>), grid, dim3(kFewThreads), 0, stream, a);
     return;
   }

@@ -1359,12 +1359,14 @@ def test_buckets_held_in_registers_match_oracle_and_the_two_passes(bucket, d):
     assert np.array_equal(scales.view(np.uint32), other[1].view(np.uint32))
 
 
-# both kernels of the steps: up to 512 tiles, 16 workers and 2048 tiles times workers a work-group of 1024 threads takes a
-# tile, beyond them the one with tables
+# both kernels of the steps: up to 400 tiles of two workers, 256 of more, and 400 to 2048 tiles times workers a work-group
+# of 1024 threads takes a tile, beyond them the one with tables
 @pytest.mark.parametrize("tiles,M,bucket,requant", [
     (512, 1, 0, 0), (513, 1, 4096, 1), (512, 4, 64, 1), (513, 4, 256, 1), (256, 8, 2048, 1), (257, 8, 1024, 0),
     (128, 16, 65536, 1), (129, 16, 0, 2), (3, 17, 512, 1), (1, 17, 0, 2), (5, 24, 4096, 0), (5, 32, 4096, 1),
-    (5, 20, 8192, 0), (2, 64, 128, 1)])
+    (5, 20, 8192, 0), (2, 64, 128, 1), (400, 2, 256, 1), (401, 2, 4096, 0), (257, 3, 1024, 1), (200, 8, 128, 1), (201, 8, 128, 1),
+    (100, 12, 4096, 0), (101, 12, 2048, 1), (40, 16, 256, 1), (41, 16, 256, 1), (100, 8, 1024, 1), (101, 8, 1024, 1),
+    (25, 16, 512, 1), (26, 16, 512, 1)])
 @pytest.mark.parametrize("method", ["qcmd", "qcmd_z", "qrda"])
 def test_steps_on_either_side_of_the_line_of_few_tiles(method, tiles, M, bucket, requant):
     """State with values at the ends of the exponent range next to ordinary ones, an incomplete last tile, garbage in
@@ -1460,3 +1462,31 @@ def test_code_words_of_rows_that_begin_anywhere(d, bucket, first, between):
     quantizer_parity(g, bucket, rows, host(scales), host(th), (bucket, d, first, between))
     assert (buf[:first] == 0xFFFFFFFF).all() and (buf[first + M * L.code_stride:] == 0xFFFFFFFF).all()
     assert (rows[:, L.words:] == 0xFFFFFFFF).all()
+
+
+# the average and its second quantization: few tiles and few workers, one more of either
+@pytest.mark.parametrize("tiles,M,bucket", [(128, 7, 4096), (129, 7, 4096), (128, 4, 0), (129, 4, 256), (200, 3, 4096), (201, 3, 0),
+                                            (256, 2, 256), (257, 2, 128), (5, 8, 1024), (1, 2, 64), (1, 1, 0)])
+def test_server_on_either_side_of_the_line_of_few_tiles(tiles, M, bucket):
+    """qa_aggregate_unpack, and qa_aggregate_quantize with a scale per bucket and with one: the oracle's bits (one scale for
+    several tiles: its sums in another order)."""
+    d = tiles * 4096 - 4089 + 4 * M
+    rng = np.random.default_rng(tiles + M)
+    g = make_grad("student", M, d, seed=M)
+    oc, osc, _ = oracle.quantize_pack(g, bucket=bucket)
+    avg = oracle.aggregate(oc, osc, d, bucket)
+    L = qa.Layout.make(d, M, bucket)
+    codes, scales = dev(oc.view(np.int32)), dev(osc)
+    out = torch.full(((d + 3) // 4 * 4 + 4,), 7.0, dtype=torch.float32, device=DEV)
+    qa.qa_aggregate_unpack(L, codes, scales, out)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(out)[:d].view(np.uint32), avg.view(np.uint32)) and (host(out)[d:] == 7).all()
+    for requant, b in ((qa.QA_REQUANT_BUCKET, bucket), (qa.QA_REQUANT_GLOBAL, 0)):
+        if requant == qa.QA_REQUANT_BUCKET and bucket == 0:
+            continue
+        q = torch.full((1, L.words + 4), -1, dtype=torch.int32, device=DEV)
+        qs, qt = torch.full((2, 1, oracle.n_buckets(d, b) + 4), -7.0, dtype=torch.float32, device=DEV)
+        qa.qa_aggregate_quantize(L, codes, scales, requant, q, qs, qt, workspace(qa.qa_workspace_bytes(L, qa.QA_OP_STEP)))
+        torch.cuda.synchronize()
+        quantizer_parity(avg[None], b, host(q).view(np.uint32), host(qs), host(qt), (tiles, M, b))
+        assert (host(q)[:, L.words:] == -1).all() and (host(qs)[:, oracle.n_buckets(d, b):] == -7).all()
