@@ -85,16 +85,17 @@ __device__ __forceinline__ void load_tile_stream(const float* __restrict__ g, in
 
 // The kernels that code a tile per work-group (quantize_tile, quantize_buckets_of_tile, quantize_codes_partial_kernel,
 // quantize_bracketed_kernel) store 64 bytes of words side by side.  Through the cache if these are whole: every worker's
-// row of words begins on a multiple of 64 bytes; of other rows from 2^27 components in all (512 MB) on.  There each store
+// row of words begins on a multiple of 64 bytes; of other rows from 7 * 2^24 components in all (448 MB) on.  There each store
 // leaves two partial pieces, which cost more than late evictions as long as the last-level cache takes part.  Other
 // gradients in each call, 7 workers, us, stores left in the cache / through it, rows on 64 bytes: quantizer, 4096: 128 MB
 // 23.6 / 23.8, 256 45.8 / 44.6, 512 91.2 / 87.2; with the step: 4096, 96 MB 33.2 / 33.9, 256 79.5 / 77.9, 512 152 / 147;
 // one scale, 96 MB 55.8 / 56.3, 256 130 / 128, 512 (read once) 182 / 178.  Other rows: quantizer, 4096: 96 MB 18.1 / 19.5,
-// 192 34.2 / 35.6, 384 68.6 / 68.3, 512 91.6 / 89.9, 1024 184 / 178; 256: 128 MB 24.0 / 24.9, 1024 187 / 181; with the
-// step: 4096, 96 MB 33.4 / 35.1, 256 81.0 / 82.4, 512 154 / 155; one scale, 128 MB 72.9 / 74.6, 320 160 / 161, 512
+// 192 34.2 / 35.6, 384 68.6 / 68.3, 512 91.6 / 89.9, 1024 184 / 178; 256: 128 MB 24.0 / 24.9, 256 47.6 / 47.0, 384
+// 71.2 / 69.3, 1024 187 / 181; 64, 5 workers, 502 MB 92.5 / 89.9; with the step: 4096, 96 MB 33.4 / 35.1, 256 81.0 / 82.4,
+// 416 137 / 139, 512 154 / 155; 256: 256 MB 82.1 / 83.7, 448 150 / 152; one scale, 128 MB 72.9 / 74.6, 320 160 / 161, 512
 // 185 / 185.  Kernels whose work-groups hold more tiles or that issue more per word are not slower with such stores at any
 // size (buckets of 8192 on, the stochastic rule, the exact one).
-constexpr int64_t kThroughFrom = int64_t(1) << 27;
+constexpr int64_t kThroughFrom = int64_t(7) << 24;
 static bool words_go_through(const qa_layout* L, const uint32_t* codes) {
   const int64_t between = L->M > 1 ? 4 * L->code_stride : 0;
   return ((reinterpret_cast<uintptr_t>(codes) | (uintptr_t)between) & 63u) == 0 || L->d > kThroughFrom / L->M;

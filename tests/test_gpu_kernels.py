@@ -1440,7 +1440,7 @@ def test_counted_combinations_with_crowded_bins_and_reserved_codes(tiles, M):
         assert np.array_equal(host(q).view(np.uint32), c_ref)
 
 
-# rows of code words that begin on 64 bytes are stored through the cache, others (below 2^27 components) not
+# rows of code words that begin on 64 bytes are stored through the cache, others (up to 7 * 2^24 components) not
 @pytest.mark.parametrize("d", [4096 * 65 - 9, 4096 * 33 + 4])
 @pytest.mark.parametrize("bucket", [0, 256, 4096])
 @pytest.mark.parametrize("first,between", [(0, 0), (0, 3), (16, 0), (1, 0), (5, 8)])
