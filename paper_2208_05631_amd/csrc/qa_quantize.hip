@@ -6,8 +6,9 @@
 //
 //   bucket <= 4096 : one kernel; sums, threshold, scale and codes of a tile's buckets are
 //                    formed in registers/LDS; the gradient is read once (4 B/elem + 0.25 B out).
-//   up to 65536    : the same with a larger work-group per bucket.
-//   longer buckets or 0 (whole vector): tile partial sums -> finalize threshold -> codes and
+//   up to 65536, and whole vectors (0) that short: the same with a larger work-group per bucket, beyond 45056
+//                    components if there are enough of them.
+//   otherwise      : tile partial sums -> finalize threshold -> codes and
 //                    tile partial (count, sum) -> finalize scale; the gradient is read twice, or,
 //                    for long buckets, once: a sample brackets the threshold beforehand.
 #include <mutex>
@@ -1113,7 +1114,14 @@ __global__ __launch_bounds__(kThreads) QA_FEW_WAVES void quantize_scale_finalize
 // codes and scales are the same numbers.  Bound by HBM up to 8 tiles; of 16 tiles the registers of a compute unit hold
 // one bucket only, and nothing is read while it is coded.  Two passes -> held, us, at 2^26 x 4 components: buckets of
 // 8192 495 -> 178, 16384 415 -> 186, 32768 372 -> 169, 65536 351 -> 229; 3 000 001 x 8: 48 -> 18, 40 -> 19, 37 -> 19,
-// 35 -> 27; one scale for 5000 .. 65 000 components, 1 or 16 workers: 16 -> 5 .. 10.
+// 35 -> 27; one scale for 5000 .. 40 000 components, 1 or 16 workers: 9 .. 10 -> 3 .. 9.5 (captured).
+// A work-group takes its time for a long bucket, and two passes have one per tile.  Captured calls with other gradients in
+// each, two passes -> held, us: 8 tiles, 1 work-group 8.9 -> 6.7, 24 10.2 -> 8.4; 11 tiles 1 9.1 -> 8.8, 3 9.5 -> 9.5, 24
+// 10.8 -> 10.0; 12 tiles 4 9.3 -> 10.3, 24 11.0 -> 10.9; 14 tiles 32 0.96 times as fast, 48 1.06; 16 tiles 1 9.1 -> 9.6, 4 9.4 ->
+// 12.8, 48 13.4 -> 14.2, 64 14.7 -> 14.8, 96 17.2 -> 15.1.
+static bool bucket_is_held(int64_t tiles, int64_t groups) {
+  return tiles <= 11 || (tiles <= 16 && groups >= 12 * (tiles - 10));
+}
 template <int TILES> constexpr int kHeldSide = TILES < 4 ? TILES : 4;   // tiles side by side
 // Element e of float4 group j of thread t of tile tile0 + u * side by side + side; beyond d +0.
 template <int TILES>
@@ -1893,9 +1901,8 @@ int quantize_launch(const qa_layout* L, const float* g, int64_t g_stride, uint32
   a.log2b = L->bucket ? ilog2(L->bucket) : 0;
   const dim3 grid_buckets((unsigned)a.nb, (unsigned)L->M);
 
-  // as long as the registers of a work-group hold the bucket: faster from a single bucket on (quantize_held_kernel)
   const int64_t held = a.tiles_per_bucket < a.ntiles ? a.tiles_per_bucket : a.ntiles;
-  if (!a.thresh_given && !(flags & kQuantAbsPartialsGiven) && held <= 16) {
+  if (!a.thresh_given && !(flags & kQuantAbsPartialsGiven) && bucket_is_held(held, a.nb * L->M)) {
     const dim3 block_of_4(4 * kThreads);
     if (held <= 2) hipLaunchKernelGGL(quantize_held_kernel<2>, grid_buckets, dim3(2 * kThreads), 0, stream, a);
     else if (held <= 4) hipLaunchKernelGGL(quantize_held_kernel<4>, grid_buckets, block_of_4, 0, stream, a);

@@ -1490,3 +1490,17 @@ def test_server_on_either_side_of_the_line_of_few_tiles(tiles, M, bucket):
         torch.cuda.synchronize()
         quantizer_parity(avg[None], b, host(q).view(np.uint32), host(qs), host(qt), (tiles, M, b))
         assert (host(q)[:, L.words:] == -1).all() and (host(qs)[:, oracle.n_buckets(d, b):] == -7).all()
+
+
+# 12 tiles are held from 24 work-groups on, 13 from 36, 16 from 72
+@pytest.mark.parametrize("bucket,d,M", [(0, 45057, 23), (0, 45057, 24), (0, 49157, 35), (0, 49157, 36), (65536, 3 * 65536 - 5, 23),
+                                        (65536, 3 * 65536 - 5, 24), (65536, 61441, 59), (65536, 61441, 72)])
+def test_long_buckets_on_either_side_of_the_line_of_held_ones(bucket, d, M):
+    """The oracle's message, and with the thresholds handed in (two passes on either side) the same one bit for bit."""
+    rng = np.random.default_rng(M)
+    g = (rng.standard_normal((M, d)) * 10.0 ** rng.integers(-3, 3, (M, 1))).astype(np.float32)
+    codes, scales, th, L = gpu_quantize_pack(g, bucket)
+    quantizer_parity(g, bucket, codes, scales, th, (bucket, d, M))
+    other = gpu_quantize_pack(g, bucket, thresholds=th[:, :L.n_buckets])
+    assert np.array_equal(codes, other[0])
+    assert np.array_equal(scales.view(np.uint32), other[1].view(np.uint32))
