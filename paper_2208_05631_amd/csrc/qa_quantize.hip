@@ -1682,7 +1682,13 @@ __global__ __launch_bounds__(kThreads) void quantize_stochastic_bucket_kernel(St
 // buckets of 2 .. 16 tiles: held as by quantize_held_kernel, the scale is the largest magnitude.  Three launches and two
 // reads -> one, us, at 2^26 x 4 components: buckets of 8192 328 -> 196, 16384 329 -> 221, 32768 331 -> 198, 65536 331 -> 247
 // (one work-group's bucket fills the registers of a compute unit); 3 000 001 x 8: 34 -> 20, 34 -> 24, 36 -> 24, 36 -> 32;
-// one scale for 5000 .. 30 000 components 14 -> 5 .. 7, for 65 000 12 on either way.
+// one scale for 5000 .. 24 000 components 7 -> 3.5 .. 6.5 (captured).  A work-group takes its time here too: three launches ->
+// held, captured, us: 6 tiles 1 work-group 6.9 -> 6.3, 8 7.5 -> 7.9, 48 9.4 -> 8.4; 7 tiles 4 7.2 -> 7.7, 32 8.4 -> 8.7, 48 9.8 ->
+// 9.0; 8 tiles 1 6.9 -> 7.8, 4 7.1 -> 9.0, 48 9.7 -> 10.1, 64 10.4 -> 10.3; 16 tiles 1 6.8 -> 11.8, 16 9.9 -> 15.6, 64 15.1 ->
+// 16.8, 96 17.4 -> 17.3.
+static bool bucket_is_held_stochastic(int64_t tiles, int64_t groups) {
+  return tiles <= 6 || (tiles <= 16 && groups >= 6 * tiles);
+}
 template <int TILES>
 __global__ __launch_bounds__(kHeldSide<TILES> * kThreads, TILES < 16 ? 8 : 4) void quantize_stochastic_held_kernel(StochArgs a) {
   constexpr int kSide = kHeldSide<TILES>, kEach = TILES / kSide;
@@ -2095,7 +2101,7 @@ extern "C" int qa_quantize_pack_stochastic(const qa_layout* layout, const float*
   }
   a.q.tiles_per_bucket = layout->bucket ? layout->bucket / kTile : a.q.ntiles;
   if (a.q.tiles_per_bucket > a.q.ntiles) a.q.tiles_per_bucket = a.q.ntiles;
-  if (a.q.tiles_per_bucket <= 16) {
+  if (bucket_is_held_stochastic(a.q.tiles_per_bucket, a.q.nb * layout->M)) {
     const dim3 buckets((unsigned)a.q.nb, (unsigned)layout->M), block_of_4(4 * kThreads);
     if (a.q.tiles_per_bucket <= 2) hipLaunchKernelGGL(quantize_stochastic_held_kernel<2>, buckets, dim3(2 * kThreads), 0, stream, a);
     else if (a.q.tiles_per_bucket <= 4) hipLaunchKernelGGL(quantize_stochastic_held_kernel<4>, buckets, block_of_4, 0, stream, a);

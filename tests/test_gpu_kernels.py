@@ -1504,3 +1504,23 @@ def test_long_buckets_on_either_side_of_the_line_of_held_ones(bucket, d, M):
     other = gpu_quantize_pack(g, bucket, thresholds=th[:, :L.n_buckets])
     assert np.array_equal(codes, other[0])
     assert np.array_equal(scales.view(np.uint32), other[1].view(np.uint32))
+
+
+# 6 tiles are always held, 7 from 42 work-groups on, 16 from 96; otherwise the maxima come from a pass of their own
+@pytest.mark.parametrize("bucket,d,M", [(0, 24577, 41), (0, 24577, 42), (0, 24576, 1), (32768, 5 * 32768 - 9, 9), (32768, 5 * 32768 - 9, 10),
+                                        (65536, 3 * 65536 - 5, 31), (65536, 3 * 65536 - 5, 32), (65536, 61441, 2)])
+def test_stochastic_quantizer_on_either_side_of_the_line_of_held_buckets(bucket, d, M):
+    """The oracle's message: scales from whole buckets and the incomplete last one, a bucket of zeros, NaN."""
+    rng = np.random.default_rng(d + M)
+    g = rng.standard_normal((M, d), dtype=np.float32)
+    g[0, :bucket or d], g[M - 1, d - 1], g[M - 1, 7] = 0, np.nan, -9
+    oc, osc = oracle.quantize_pack_stochastic(g, bucket=bucket, seed=3, step=7)
+    L, gs = qa.Layout.make(d, M, bucket), (d + 3) // 4 * 4
+    gp = np.full((M, gs), 99, np.float32)                 # padding belongs to nobody
+    gp[:, :d] = g
+    codes = torch.full((M, L.code_stride), -1, dtype=torch.int32, device=DEV)
+    scales = torch.full((M, L.scale_stride), -7.0, dtype=torch.float32, device=DEV)
+    qa.qa_quantize_pack_stochastic(L, dev(gp), gs, codes, scales, 3, 7)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(scales), osc)
+    assert np.array_equal(host(codes).view(np.uint32), oc)
