@@ -631,7 +631,9 @@ __global__ __launch_bounds__(kThreads) void exact_threshold_kernel(QuantArgs a) 
 // and left the codes to a second pass over the gradient).  2^26 x 4 Gaussian components, thresholds and
 // codes, ranking + quantizing -> this: buckets of 4096 1366 -> 235 us, 2048 1300 -> 273,
 // 1024 1189 -> 347, 512 1094 -> 587.  (2^28 x 4, 4096: 992 -> 940 with one comparison and one bit field per component for
-// the histogram, where it was a mask, a difference, a comparison and a shift, and with fields shifted in.)  Steps 2 to 4 cost the same for every bucket size, so halving
+// the histogram, where it was a mask, a difference, a comparison and a shift, and with fields shifted in; 2^26 x 8 485 -> 473
+// without a jump round the addition of each component: 100003 x 4, 10 %-dense Student-t, 13.8 -> 12.7, but where one
+// component in 1000 is not 0, 5e7 x 2, 92 -> 97.)  Steps 2 to 4 cost the same for every bucket size, so halving
 // the bucket nearly doubles the time: at 256 the network (889 us) stays ahead.
 constexpr float kRankMark = -1.0f;
 constexpr int kExactList = 64;            // survivors that one wave ranks by counting
@@ -762,7 +764,7 @@ void exact_histogram_kernel(QuantArgs a) {
       for (int j = 0; j < kGroups; ++j)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (fabsf(v[j][e]) >= first_counted) {
+          if (__builtin_expect(fabsf(v[j][e]) >= first_counted, 1)) {   // no branch round it
             const uint32_t bits = __float_as_uint(v[j][e]);
             const uint32_t bin = __builtin_amdgcn_ubfe(bits, (uint32_t)shift, 31u - (uint32_t)shift) - bin_base;
             atomicAdd(reinterpret_cast<unsigned long long*>(hist + bin),
