@@ -1241,6 +1241,7 @@ __global__ __launch_bounds__(kHeldSide<TILES> * kThreads, TILES < 16 ? 8 : 4) vo
 // Below 2^25 components the two further launches cost more than the second read (2^24 x 1 27.4 -> 31), and buckets
 // of fewer than 4096 tiles give too few samples (2^22: 343 -> 376 at 2^26 x 4 sparse components).
 constexpr int64_t kManyTiles = 16384;
+constexpr int64_t kSpreadBelow = 512;                    // work-groups, see quantize_settle_listed_kernel
 constexpr float kWidestBand = 0.08f;
 
 // Full tiles of bucket k.
@@ -1376,6 +1377,10 @@ __device__ __forceinline__ void settled_parts(const QuantArgs& a, int m, int64_t
 // With lists: a wave per eight tiles, eight lanes per tile, no look at the codes.  Tiles that have to be coded again are
 // left to the whole work-group.  Bound by latency where few components are open (10^8 x 8 10 %-dense Student-t 76 us
 // with marks, 26 with lists), by the lines that they touch where many are.
+// A bucket without a bracket (or whose threshold lies outside) is coded again as a whole, and 32 tiles one after the other
+// leave the chip idle where there are few groups: then the grid has four layers (kSpreadBelow), each of which codes one of
+// the four eights of such a bucket, and the first one alone settles the others (2^24 x 2 components, one in 1000 not 0, the
+// whole call 74 -> 58 us; 512 groups, 2^24 x 4, keep the chip busy: 108 with eights as groups and with four of them).
 __global__ __launch_bounds__(kThreads) void quantize_settle_listed_kernel(QuantArgs a) {
   __shared__ TileKept kept[kWaves * kSettleTiles];
   __shared__ uint32_t lds_again[kWaves];
@@ -1388,9 +1393,12 @@ __global__ __launch_bounds__(kThreads) void quantize_settle_listed_kernel(QuantA
   const int64_t bucket1 = (k + 1) * a.tiles_per_bucket < a.ntiles ? (k + 1) * a.tiles_per_bucket : a.ntiles;
   const int own = wave * kSettleTiles + lane / 8;        // of the 32 tiles
   const int64_t tile = tile0 + own, at = (int64_t)m * a.ntiles + tile;
-  const bool live = tile < bucket1;
   const float D = a.thr_ws[(int64_t)m * a.nb + k];
   const float2 band = a.band[(int64_t)m * a.nb + k];
+  const bool all = gridDim.z == 1 || bracket_held(band, D);
+  const int eight = (int)blockIdx.z;
+  if (all && eight != 0) return;                         // uniform
+  const bool live = tile < bucket1 && (all || wave == eight);
   const uint32_t counts = live ? a.part_cnt[at] : 0u;
   const double certain = live ? a.kept_sum[at] : 0.0;
   const bool again = live && (!bracket_held(band, D) || too_many_open(counts));
@@ -1424,7 +1432,8 @@ __global__ __launch_bounds__(kThreads) void quantize_settle_listed_kernel(QuantA
   }
   if (repeat) __syncthreads();
   if (wave == 0)
-    settled_parts(a, m, k * a.settle_groups + part0 + lane / 8, lane < kWaves * kSettleTiles && part0 + lane / 8 < a.settle_groups,
+    settled_parts(a, m, k * a.settle_groups + part0 + lane / 8,
+                  lane < kWaves * kSettleTiles && part0 + lane / 8 < a.settle_groups && (all || lane / 8 == eight),
                   lane < kWaves * kSettleTiles && (repeat >> (lane & 31) & 1u), kept[lane & 31]);
 }
 
@@ -1933,8 +1942,8 @@ int quantize_launch(const qa_layout* L, const float* g, int64_t g_stride, uint32
     a.settle_groups = (a.tiles_per_bucket + kSettleTiles - 1) / kSettleTiles;
     if (a.nb * a.samples <= 0x7fffffffLL && a.nb * a.settle_groups <= 0x7fffffffLL) {
       const dim3 grid_samples((unsigned)(a.nb * a.samples), (unsigned)L->M);
-      const dim3 grid_settle((unsigned)(a.nb * (a.open ? (a.settle_groups + kWaves - 1) / kWaves : a.settle_groups)),
-                             (unsigned)L->M);
+      const int64_t settle = a.nb * (a.open ? (a.settle_groups + kWaves - 1) / kWaves : a.settle_groups);
+      const dim3 grid_settle((unsigned)settle, (unsigned)L->M, a.open && settle * L->M < kSpreadBelow ? kWaves : 1);
       hipLaunchKernelGGL(quantize_sample_kernel, grid_samples, block, 0, stream, a);
       hipLaunchKernelGGL(quantize_band_kernel, grid_buckets, block, 0, stream, a);
       if (a.open) hipLaunchKernelGGL(quantize_bracketed_kernel<true>, grid_tiles, block, 0, stream, a);
