@@ -104,3 +104,17 @@ def quantizer_parity(g, bucket, codes, scales, thresholds, what="", thr_coef=0.7
     assert np.array_equal(codes[:, :W], oc2[:, :W]), f"codes differ for the same thresholds {what}"
     assert int(ulp_distance(gs, osc2[:, :nb]).max()) <= 1, f"scale off by more than 1 ulp {what}"
     return int((~same).sum())
+
+
+def sampled_tiles(d):
+    """The tiles of one bucket of d components that the form with one read samples (whole tiles only)."""
+    every = 64 if (d + 4095) // 4096 >= 16384 else 32
+    i = np.arange(d // 4096 // every)
+    return i * every + i * 29 % every
+
+
+def sampled_pieces(pieces):
+    """The same for a tensor of so many pieces of a list, counted from its first one."""
+    every = 32 if pieces >= 1024 else 16 if pieces >= 512 else 8 if pieces >= 256 else 4
+    i = np.arange(pieces // every if pieces >= 128 else 0)
+    return i * every + i * 29 % every

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
     import paper_2208_05631_amd as qa
-    from gpu_util import DEV, GpuState, dev, gpu_quantize_pack, host, quantizer_parity, ulp_distance, workspace
+    from gpu_util import DEV, GpuState, dev, gpu_quantize_pack, host, quantizer_parity, sampled_tiles, ulp_distance, workspace
 
 RTOL = 1e-5
 
@@ -809,10 +809,9 @@ def one_read_gradient(kind, d, rng):
     elif kind == "trend":                               # magnitudes grow along the vector
         g *= (1.0 + 3.0 * np.arange(d, dtype=np.float32) / d)
     elif kind == "sample misleads":                     # the tiles that are sampled are ten times smaller
-        at = (tile // 64 * 64 + (tile // 64 * 29) % 64 == tile)
-        g[at] *= np.float32(0.1)
+        g[np.isin(tile, sampled_tiles(d))] *= np.float32(0.1)
     elif kind == "sample empty":
-        g[(tile // 64 * 64 + (tile // 64 * 29) % 64 == tile)] = 0
+        g[np.isin(tile, sampled_tiles(d))] = 0
     elif kind == "crowd at the threshold":              # a third of the components within 1e-3 of it
         near = rng.random(d) < 0.33
         mean = np.abs(g[~near]).mean(dtype=np.float64)
@@ -1301,11 +1300,21 @@ def crowded(g, tile, groups):
     part[:, 1] = at.reshape(4, 64, 4)
 
 
-@pytest.mark.parametrize("d", [1 << 24, (1 << 24) + 4099, (1 << 26) + 1])   # one tile of 32 sampled, and one of 64
-def test_long_quantizer_lists_what_is_open(d):
+def one_read_without_lists_bytes(L):
+    """A workspace for the form with one read that marks what is open in the code words: sums, counts and thresholds of the
+    two reads, sums and brackets of the one."""
+    def arrays(*sizes):
+        return sum((n + 255) // 256 * 256 for n in sizes)
+    tiles, nb = (L.d + 4095) // 4096, L.n_buckets
+    return arrays(L.M * tiles * 8, L.M * tiles * 4, L.M * nb * 4) + arrays(L.M * tiles * 8, L.M * nb * 8)
+
+
+@pytest.mark.parametrize("d,bucket", [(1 << 24, 0), ((1 << 24) + 4099, 0), ((1 << 26) + 1, 0),   # one tile of 32 sampled, one of 64
+                                      ((1 << 25) + (1 << 24) - 7 * 4096 - 30, 1 << 24)])         # the last bucket shorter
+def test_long_quantizer_lists_what_is_open(d, bucket):
     """Lists of 14 float4 groups (the longest), of 15 (the tiles are coded again) and of a whole wave; open components in the
     last, incomplete tile, behind which the row holds other values; a sample that misleads.  Same codes as with two
-    reads, same message bit for bit from the call that has no room for lists."""
+    reads, same message bit for bit from a call that has no room for lists and marks what is open in its words."""
     rng = np.random.default_rng(11)
     M, gs = 2, (d + 3) // 4 * 4 + 8
     g = (rng.standard_normal((M, d)) * 1e-2).astype(np.float32)
@@ -1313,30 +1322,33 @@ def test_long_quantizer_lists_what_is_open(d):
         crowded(g[0], tile, groups)
     delta = np.float32(0.75) * np.abs(g[0]).mean(dtype=np.float64)
     g[0, -1] = delta * np.float32(1.0002)
-    every = 64 if d >= 1 << 26 else 32
-    tile = np.arange(d) >> 12
-    g[1][tile // every * every + (tile // every * 29) % every == tile] *= np.float32(0.5)
+    b = bucket or d
+    for lo in range(0, d, b):
+        n = min(b, d - lo)
+        g[1, lo:lo + n][np.isin(np.arange(n) >> 12, sampled_tiles(b)[sampled_tiles(b) < n >> 12])] *= np.float32(0.5)
     gp = np.full((M, gs), delta, np.float32)              # padding inside the bracket belongs to nobody
     gp[:, :d] = g
-    L = qa.Layout.make(d, M, 0)
+    L = qa.Layout.make(d, M, bucket)
+    nb, tiles = L.n_buckets, (d + 4095) >> 12
     gd, out = dev(gp), []
     full = qa.qa_workspace_bytes(L, qa.QA_OP_QUANTIZE)
-    for how in ("listed", "two reads", "static"):
+    sizes = {"listed": full, "two reads": M * tiles * 12 + 4 * M * nb + 768, "marked": one_read_without_lists_bytes(L)}
+    assert sizes["two reads"] < sizes["marked"] and sizes["marked"] + M * tiles * 128 == full
+    for how in ("listed", "two reads", "marked", "static"):
         codes = torch.full((M, L.code_stride), -1, dtype=torch.int32, device=DEV)
-        sc, th = torch.zeros((2, M, 1), dtype=torch.float32, device=DEV)
+        sc, th = torch.zeros((2, M, nb), dtype=torch.float32, device=DEV)
         if how == "static":
             qa.qa_quantize_pack_static(L, gd, gs, codes, sc, th, 0)
         else:
-            qa.qa_quantize_pack(L, gd, gs, codes, sc, th, 0, workspace(full if how == "listed" else M * ((d >> 12) + 1) * 12 + 4 * M + 768))
+            qa.qa_quantize_pack(L, gd, gs, codes, sc, th, 0, workspace(sizes[how]))
         torch.cuda.synchronize()
         out.append((codes[:, :L.words], sc, th))
-    for a, b in zip(out[0], out[2]):
-        assert torch.equal(a, b)
+    for other in out[2:]:
+        for one, two in zip(out[0], other):
+            assert torch.equal(one, two)
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][2], out[1][2])
     assert int(ulp_distance(host(out[0][1]), host(out[1][1])).max()) <= 1
-    c_ref, _, t_ref = oracle.quantize_pack(g, bucket=0)
-    if np.array_equal(host(out[0][2]), t_ref):
-        assert np.array_equal(host(out[0][0]).view(np.uint32), c_ref)
+    quantizer_parity(g, bucket, host(out[0][0]).view(np.uint32), host(out[0][1]), host(out[0][2]), (d, bucket))
 
 
 # buckets of 2 .. 16 tiles are held in registers; 65537 components under one scale are the first that are not

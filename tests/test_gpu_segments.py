@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
     import paper_2208_05631_amd as qa
-    from gpu_util import DEV, dev, host, workspace
+    from gpu_util import DEV, dev, host, sampled_pieces, workspace
 
 RTOL = 1e-5
 
@@ -188,13 +188,10 @@ def test_long_tensors_read_once_match_oracle(M):
     assert f.plan.n_pieces * M >= 32768
     rng = np.random.default_rng(M)
     g = rng.standard_normal((M, f.d), dtype=np.float32)
-    first = np.concatenate([[0], np.cumsum([(b + n - 1) // 4096 - b // 4096 + 1 for b, n in zip(f.begin, f.length)])])
-    b5 = int(f.begin[5])
-    for i in range(f.plan.n_pieces // 64 + 1):          # tensor 5: the sampled pieces are ten times larger
-        p = i * 64 + (i * 29) % 64
-        if first[5] < p < first[6] - 1:
-            tile = b5 // 4096 + p - first[5]
-            g[:M // 2, tile * 4096:(tile + 1) * 4096] *= 10
+    t5, pieces = f.begin[5] // 4096, (f.begin[5] + f.length[5] - 1) // 4096 - f.begin[5] // 4096 + 1
+    for p in sampled_pieces(pieces):                     # tensor 5: the sampled pieces are ten times larger
+        if 0 < p < pieces - 1:
+            g[:M // 2, (t5 + p) * 4096:(t5 + p + 1) * 4096] *= 10
     s7 = slice(int(f.begin[7]), int(f.begin[7]) + int(f.length[7]))
     g[0, s7] *= rng.random(f.length[7]) < 0.05
     g[1, s7] = 0.25
@@ -242,9 +239,7 @@ def test_tensors_on_either_side_of_the_sampled_lengths_match_oracle(kind):
     if kind == "misled":
         for b, n in zip(f.begin, f.length):
             t0, pieces = b // 4096, (b + n - 1) // 4096 - b // 4096 + 1
-            stride = 16 if pieces >= 512 else 8 if pieces >= 256 else 4
-            for k in range(pieces // stride):
-                p = k * stride + k * 29 % stride
+            for p in sampled_pieces(pieces):
                 if 0 < p < pieces - 1:
                     g[::2, (t0 + p) * 4096:(t0 + p + 1) * 4096] *= 1.5
     c_ref, s_ref, th_ref = oracle.quantize_pack_segments(g, f.begin, f.length)
