@@ -1,7 +1,7 @@
 """Compile-time guard for the kernels whose speed hinges on occupancy: the step kernel is tuned
 for four waves per SIMD (at most 128 vector registers) and must not spill; one more register
 block costs a wave per SIMD and about 6 % of the step time on an MI355X.  The exact threshold's and the
-selection's kernels may spill where their comments say so, and nowhere else.  hipcc cross-compiles
+selection's kernels may spill where their comments say so, and nowhere else, the quantizers' not at all.  hipcc cross-compiles
 for gfx950 without a GPU, so this runs with the CPU tests."""
 import os
 import re
@@ -32,8 +32,13 @@ def resource_usage(source):
 
 
 @pytest.fixture(scope="module")
-def step_kernels():
-    return {k: v for k, v in resource_usage("qa_step.hip").items() if "step_lut_kernel" in k}
+def step_resources():
+    return resource_usage("qa_step.hip")
+
+
+@pytest.fixture(scope="module")
+def step_kernels(step_resources):
+    return {k: v for k, v in step_resources.items() if "step_lut_kernel" in k}
 
 
 def test_no_step_kernel_variant_spills(step_kernels):
@@ -71,3 +76,22 @@ def test_selection_kernels_do_not_spill_and_reach_the_waves_they_ask_for():
     for part, waves in (("gsel_quantize_multi_kernel", 5), ("quantize_selected_kernel", 4), ("indicator_kernel", 3)):
         found = [v["waves"] for k, v in kernels.items() if part in k and "indicator_or" not in k]
         assert found and all(n == waves for n in found), (part, found)
+
+
+def test_quantizer_kernels_do_not_spill_and_keep_their_waves():
+    """The kernels that hold a bucket use every register that their work-groups' waves leave them."""
+    kernels = resource_usage("qa_quantize.hip")
+    assert not {k: v for k, v in kernels.items() if v["scratch"] != 0}
+    for part, waves in (("quantize_held_kernelILi2E", 8), ("quantize_held_kernelILi4E", 8), ("quantize_held_kernelILi8E", 8),
+                        ("quantize_held_kernelILi16E", 4), ("stochastic_held_kernelILi16E", 4), ("quantize_tile_kernelILb0E", 8),
+                        ("quantize_bucket_kernelILi8ELb0E", 8), ("quantize_bucket_kernelILi9ELb0E", 7),
+                        ("quantize_bucket_kernelILi11ELb0E", 6), ("quantize_bracketed_kernel", 8), ("settle_listed_kernel", 5)):
+        found = [v["waves"] for k, v in kernels.items() if part in k]
+        assert found and all(n >= waves for n in found), (part, found)
+
+
+def test_kernels_of_few_tiles_do_not_spill_and_fit_a_compute_unit(step_resources):
+    """A work-group is 16 waves: four per SIMD."""
+    kernels = {k: v for k, v in step_resources.items() if "step_few_kernel" in k}
+    assert len(kernels) >= 9
+    assert not {k: v for k, v in kernels.items() if v["scratch"] != 0 or v["waves"] < 4}
