@@ -1469,16 +1469,18 @@ static void launch_lut(const StepArgs& a, dim3 grid, dim3 block, hipStream_t str
 // The average written out, 1 / 3 / 7 workers: 100 tiles 3.7 -> 2.7 / 4.0 -> 3.6 / 5.0 -> 4.7, 256 3.9 -> 3.2 / 4.3 -> 4.0 /
 // 5.2 -> 5.5; 4 and 8 workers fill the tables: 100 tiles 3.7 -> 3.7 and 4.0 -> 4.6.  Quantized again per 256: 2 workers
 // 256 tiles 5.1 -> 5.0, 4 workers 5 tiles 5.0 -> 5.2; one scale for one tile 1 worker 3.9 -> 4.0, 4 workers 3.9 -> 4.7.  The
-// sums and codes of one scale for more: 2 workers 128 tiles 11.0 -> 10.5, 256 11.6 -> 12.0, 7 workers 100 tiles 12.1 -> 11.9,
-// 200 12.8 -> 14.0, 8 workers 50 tiles 11.2 -> 11.7; the step behind such sums, 8 workers: 50 tiles 18.7 -> 17.2 in all, 128
-// 19.3 -> 20.3.
+// average with its sums, for one scale, and codes: 2 workers 128 tiles 11.0 -> 10.5, 256 11.6 -> 12.0, 7 workers 100 tiles
+// 12.1 -> 11.9, 200 12.8 -> 14.0, 8 workers 50 tiles 11.2 -> 11.7.  A step's sums alone, old / new of the whole step with this
+// kernel behind them: 5 workers 200 tiles 1.09, with the tables 1.04, 7 workers 256 1.00 and 0.99, 4 workers 128 1.01 and
+// 1.02, 200 1.00 and 1.03; the step behind such sums, 8 workers: 50 tiles 18.7 -> 17.2 in all, 128 19.3 -> 20.3.
 template <int MODE, bool TRACK_Z, int RQ>
 static bool few_tiles(const StepArgs& a, int64_t tiles) {
   const int M = a.M;
   const int64_t rows = tiles * M;
   if (MODE == kAggregate) {
     if (RQ == kRqInTile) return M <= 2 && !a.tile_uniform && tiles <= 256;
-    if (a.gbar && !a.abs_partials) return M <= 7 && tiles <= (M != 4 ? 200 : 128);
+    if (!a.gbar) return M <= 7 && tiles <= (M != 4 ? 256 : 100);
+    if (!a.abs_partials) return M <= 7 && tiles <= (M != 4 ? 200 : 128);
     return M <= 7 && tiles <= (M != 4 ? 128 : 100) && rows <= 700;
   }
   if (M > 16 || tiles > (M <= 2 ? 400 : 256)) return false;

@@ -1377,6 +1377,7 @@ def test_buckets_held_in_registers_match_oracle_and_the_two_passes(bucket, d):
     (512, 1, 0, 0), (513, 1, 4096, 1), (512, 4, 64, 1), (513, 4, 256, 1), (256, 8, 2048, 1), (257, 8, 1024, 0),
     (128, 16, 65536, 1), (129, 16, 0, 2), (3, 17, 512, 1), (1, 17, 0, 2), (5, 24, 4096, 0), (5, 32, 4096, 1),
     (5, 20, 8192, 0), (2, 64, 128, 1), (400, 2, 256, 1), (401, 2, 4096, 0), (257, 3, 1024, 1), (200, 8, 128, 1), (201, 8, 128, 1),
+    (256, 7, 4096, 2), (257, 7, 256, 2), (100, 4, 4096, 2), (101, 4, 1024, 2), (50, 8, 256, 2), (51, 8, 4096, 2),
     (100, 12, 4096, 0), (101, 12, 2048, 1), (40, 16, 256, 1), (41, 16, 256, 1), (100, 8, 1024, 1), (101, 8, 1024, 1),
     (25, 16, 512, 1), (26, 16, 512, 1)])
 @pytest.mark.parametrize("method", ["qcmd", "qcmd_z", "qrda"])
