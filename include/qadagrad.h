@@ -239,7 +239,9 @@ int qa_aggregate_unpack(const qa_layout* layout, const uint32_t* codes, const fl
  * ws: qa_workspace_bytes(layout, QA_OP_STEP); only used when the second quantization cannot
  * be done in one pass (QA_REQUANT_GLOBAL, or QA_REQUANT_BUCKET with bucket > 4096); may be
  * NULL with ws_bytes 0 otherwise.  In that case the call enqueues several kernels (the two sums
- * behind the threshold and the scale of q, each followed by a small finalize kernel, then the
+ * behind the threshold and the scale of q, each followed by a small finalize kernel, or, with one
+ * scale per message and for q, 5 to 8 workers and 1024 tiles of 4096 coordinates or more, a count
+ * of the combinations of their codes and two small kernels that form both sums from it; then the
  * update); otherwise exactly one.  Nothing is copied or waited for: the call can be recorded
  * into a HIP graph. */
 int qa_step_qcmd(const qa_layout* layout, const uint32_t* codes, const float* scales, float* x,

@@ -1582,8 +1582,9 @@ __device__ __forceinline__ uint32_t to_u32_saturated(float x) {
 // is vector index base + 4*(j*256+t)+e
 //
 // Keep iff u < fl(|v| / s), u = (r >> 8) * 2^-24.  Compared as whole numbers: the reciprocal's product (good to 2.5e-7)
-// less a part in 10^6, in units of 2^-32, lies below the quotient, and 8192 units further on (5841 would do: 2.3e-6 of
-// the largest quotient, 1, one unit and the 255 that r is above u) above it.  Only when r lies between the two
+// less a part in 10^6, in units of 2^-32, lies below the quotient, and 8192 units further on above it (5810 would do: of
+// the largest quotient, 1, the 1.013e-6 that 0.999999f leaves off, the product's 2.5e-7 and the quotient's own rounding, 3e-8,
+// 1.3e-6 in all; one unit; the 255 that r is above u).  Only when r lies between the two
 // (probability 2e-6) is the correctly rounded quotient needed, and where the scale leaves the range in which none of the factors
 // overflows or loses bits.
 // Bound by instruction issue, half of it Philox's, and memory.  2^28 x 4 components, bucket 4096, with margins in binary32
@@ -1790,7 +1791,7 @@ size_t quantize_workspace_bytes(const qa_layout* L) {
 }
 
 // What the one-read form needs on top of it, 0 where it is not taken: buckets of fewer than 4096 tiles
-// (64 samples), or less than 2^25 components in all.
+// (128 samples), or less than 2^25 components in all.
 constexpr int64_t kOneReadBucketTiles = 4096, kOneReadTiles = 8192;
 static size_t one_read_sums_bytes(const qa_layout* L) {
   const int64_t nt = tiles_of(L->d), nb = buckets_of(L->d, L->bucket);
@@ -2005,7 +2006,9 @@ int quantize_finalize_launch(const qa_layout* L, int which, int64_t n_partials, 
 // hands to the kernels.  A call is accepted by the size of its partial sums (12 bytes per worker and
 // tile); the rest is for the one-read form, which adds 8 bytes to those 12 and 8 per worker and bucket of at
 // least 4096 tiles: the static call takes it wherever qa_quantize_pack with its full workspace does, so
-// that their sums are added in the same order.
+// that their sums are added in the same order.  Up to some 49 600 tiles of all workers (2 * 10^8 components) the array
+// has room for the lists of open groups as well, another 128 bytes each; beyond, what is open is marked in the
+// code words, with the same result.
 constexpr size_t kScratchSums = QA_STATIC_SCRATCH_BYTES, kScratchBytes = size_t(7) << 20;
 static_assert(kScratchBytes >= kScratchSums + kScratchSums / 12 * 8 + kScratchSums / 12 / kOneReadBucketTiles * 16 + 512,
               "room for the one-read form of every accepted layout");

@@ -1191,12 +1191,15 @@ __global__ __launch_bounds__(kThreads) void requant_sums_kernel(SumArgs a) {
 // there are 3^M (6561 for 8 workers).  Counted once, they give both sums: the threshold from count times value of every
 // combination, then what it keeps.  One pass over the messages instead of two with a binary64 addition, a division
 // and two conversions per coordinate in each; a value is formed in the workers' order, whatever the scales, and count times value is
-// exact.  A combination's number is the sum of two table entries in the steps' index bytes (base 3, in bytes of
-// the histogram); all workers' zero, the most frequent one, is left out and is what remains of d.
+// exact for counts up to 2^29 (24 bits and 53), beyond that rounded once, 2^-53 of it.  A combination's number is the sum
+// of two table entries in the steps' index bytes (base 3, in bytes of the histogram); all workers' zero, the most frequent one, is left out and is what remains of d.
 // Bound by vector instructions (22 per coordinate; with the numbers from a table in LDS by that: 66 us for 63 at
 // 10^8 x 8).  Step with one scale, the two sum passes and two finalizing launches -> these three launches, us: 10^8
 // coordinates, 6 workers 470 -> 353, 8 dense 412 -> 361, 8 sparse 399 -> 354; 2^24, 5 workers 98 -> 73, 8 88 -> 80; 2^22 (1024 tiles,
-// the line) 40 -> 31 and 32.4 -> 31.4.  For 5 to 8 workers: with fewer the lanes of a wave meet in few bins.
+// the line) 40 -> 31 and 32.4 -> 31.4.  For 5 to 8 workers: with fewer the lanes of a wave meet in few bins.  They do so too
+// where the workers agree, but for 0, which is not counted.  Worst case, all of one sign everywhere, the sum passes -> these,
+// captured: 5 workers 2^22 36 -> 40, 10^8 460 -> 624, 8 workers 32 -> 42 and 399 -> 629; over half of the coordinates: 5 workers
+// 36 -> 33 and 460 -> 460, 8 workers 33 -> 35 and 405 -> 469.
 constexpr int kComboThreads = 1024, kComboGroups = 512, kMaxCombos = 6561;
 struct ComboArgs {
   SumArgs m;
@@ -1559,7 +1562,8 @@ static SumArgs sum_args(const StepArgs& messages) {
 
 constexpr int kComboMinM = 5;              // see combo_count_kernel
 constexpr int64_t kComboTiles = 1024;
-// scratch: what is left of the workspace behind the quantizer's part (256-byte aligned).
+// scratch: what is left of the workspace behind the quantizer's part (256-byte aligned), where other layouts have the
+// average: 4 bytes per coordinate, of which the counts take 13.4 MB at most from 1024 tiles (16.7 MB) on.
 static int requant_sums_from_messages(const StepArgs& messages, const qa_layout* R, float* scales,
                                       float* thresholds, void* qws, size_t qws_bytes, size_t scratch_bytes,
                                       const float** thr_out, hipStream_t stream) {
@@ -1576,19 +1580,18 @@ static int requant_sums_from_messages(const StepArgs& messages, const qa_layout*
     c.tiles_per_group = (c.tiles_per_group + 3) & ~3;    // whole rounds of a work-group
     c.groups = (int)((c.m.ntiles + c.tiles_per_group - 1) / c.tiles_per_group);
     const size_t counts = align256((size_t)c.groups * c.combos * sizeof(uint32_t));
-    if (scratch_bytes >= counts + (size_t)c.combos * (sizeof(double) + sizeof(float))) {
-      char* p = static_cast<char*>(qws) + qws_bytes;
-      c.counts = reinterpret_cast<uint32_t*>(p);
-      c.total = reinterpret_cast<double*>(p + counts);
-      c.value = reinterpret_cast<float*>(c.total + c.combos);
-      c.thr_out = thr; c.scale_out = scales; c.threshold_user = thresholds;
-      c.thr_coef = messages.thr_coef;
-      const dim3 block(kComboThreads);
-      hipLaunchKernelGGL(combo_count_kernel, dim3((unsigned)c.groups), block, 0, stream, c);
-      hipLaunchKernelGGL(combo_total_kernel, dim3((unsigned)((c.combos + kWave - 1) / kWave)), block, 0, stream, c);
-      hipLaunchKernelGGL(combo_scale_kernel, dim3(1), block, 0, stream, c);
-      return launch_status();
-    }
+    if (scratch_bytes < counts + (size_t)c.combos * (sizeof(double) + sizeof(float))) return QA_ERR_WORKSPACE;
+    char* p = static_cast<char*>(qws) + qws_bytes;
+    c.counts = reinterpret_cast<uint32_t*>(p);
+    c.total = reinterpret_cast<double*>(p + counts);
+    c.value = reinterpret_cast<float*>(c.total + c.combos);
+    c.thr_out = thr; c.scale_out = scales; c.threshold_user = thresholds;
+    c.thr_coef = messages.thr_coef;
+    const dim3 block(kComboThreads);
+    hipLaunchKernelGGL(combo_count_kernel, dim3((unsigned)c.groups), block, 0, stream, c);
+    hipLaunchKernelGGL(combo_total_kernel, dim3((unsigned)((c.combos + kWave - 1) / kWave)), block, 0, stream, c);
+    hipLaunchKernelGGL(combo_scale_kernel, dim3(1), block, 0, stream, c);
+    return launch_status();
   }
   if (one_scale_everywhere(messages, R)) {
     // one scale per message and one for Q(SynQ): the lean kernel, one partial per work-group
